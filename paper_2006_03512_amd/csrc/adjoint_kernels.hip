@@ -339,7 +339,7 @@ static void launch_adj_shape_t(const mrf_ctx* c, const AdjSrc& a, float* lambar,
     if constexpr (G != 0) {
         constexpr int CAP = kRayCap[Q];
         const int64_t n = c->ray_cnt[Q];
-        const uint32_t* list = (const uint32_t*)c->b_ray_list[Q].p;
+        const uint32_t* list = (const uint32_t*)c->b_ray_list.p + c->ray_off[Q];
         if constexpr (ray_class_lds(Q)) {
             constexpr int RPW = kAdjShapes[Q][I].rpw;
             hipLaunchKernelGGL((ray_adj_lds_k<G, CAP / G, RPW, KF>), dim3((unsigned)n), dim3(kTile * G / RPW), 0, s,

@@ -56,10 +56,8 @@ std::vector<uint64_t> graph_key(const mrf_ctx* c, int K, int keep)
                                  &c->b_ckpt,   &c->b_tsum,  &c->b_tbar,  &c->b_tiles, &c->b_counts, &c->b_theta2,
                                  &c->b_kfw,    &c->b_pair_m, &c->b_pair_x, &c->b_kfx, &c->b_kfxb, &c->b_kf_vox};
     for (const mrf::DevBuf* b : bufs) k.push_back((uint64_t)(uintptr_t)b->p);
-    for (const auto& b : c->b_ray_list) k.push_back((uint64_t)(uintptr_t)b.p);
-    for (const auto& b : c->b_vox_list) k.push_back((uint64_t)(uintptr_t)b.p);
-    for (const auto& b : c->b_vox_desc) k.push_back((uint64_t)(uintptr_t)b.p);
-    for (const auto& b : c->b_pair_desc) k.push_back((uint64_t)(uintptr_t)b.p);
+    for (const mrf::DevBuf* b : {&c->b_ray_list, &c->b_vox_desc, &c->b_pair_desc})
+        k.push_back((uint64_t)(uintptr_t)b->p);
     for (int i = 0; i < mrf::kVoxClasses; ++i) k.push_back((uint64_t)c->pair_cnt[i]);
     k.push_back((uint64_t)c->n_kf_vox);
     k.push_back((uint64_t)c->cell_px);
@@ -266,16 +264,12 @@ void mrf_destroy(mrf_ctx* c)
                      &c->b_bin, &c->b_tin, &c->b_tout, &c->b_g, &c->b_lam, &c->b_ell, &c->b_vedge,
                      &c->b_vptr, &c->b_theta, &c->b_theta2, &c->b_L, &c->b_thetabar, &c->b_sigma, &c->b_bias,
                      &c->b_ckpt, &c->b_tsum, &c->b_tbar, &c->b_metric, &c->b_bricks,
-                     &c->b_ellbar, &c->b_lambar, &c->b_gsum, &c->b_tmp64, &c->b_cls, &c->b_sigpart,
-                     &c->b_misc, &c->b_frame_list, &c->b_tiles, &c->b_tbase, &c->b_export,
+                     &c->b_ellbar, &c->b_lambar, &c->b_gsum, &c->b_tmp64, &c->b_part, &c->b_sigpart,
+                     &c->b_misc, &c->b_ray_list, &c->b_vox_desc, &c->b_pair_desc, &c->b_tiles, &c->b_tbase, &c->b_export,
                      &c->b_kfw, &c->b_kflen, &c->b_pair_m, &c->b_pair_x, &c->b_kfx, &c->b_kfxb, &c->b_kf_vox,
                      &c->b_kfxr, &c->b_kfy, &c->b_kfws};
     for (DevBuf* b : all) free_buf(*b);
     for (auto& b : c->b_host_in) free_buf(b);
-    for (auto& b : c->b_pair_desc) free_buf(b);
-    for (auto& b : c->b_ray_list) free_buf(b);
-    for (auto& b : c->b_vox_list) free_buf(b);
-    for (auto& b : c->b_vox_desc) free_buf(b);
     if (c->ev_in) hipEventDestroy(c->ev_in);
     if (c->ev_out) hipEventDestroy(c->ev_out);
     if (c->aux) hipStreamDestroy(c->aux);
@@ -388,7 +382,7 @@ static int build_impl(mrf_ctx* c, const mrf_scene* scenes, int32_t n_scenes, con
     c->scenes_h.clear();
     c->frames_h.clear();
     // copies of host inputs of the previous build, once this one has stopped using them
-    HCK(hipStreamSynchronize(s), "mrf_build: sync");
+    if (!c->b_host_in.empty()) HCK(hipStreamSynchronize(s), "mrf_build: sync");
     for (auto& b : c->b_host_in) free_buf(b);
     c->b_host_in.clear();
     c->n_scenes = n_scenes;
@@ -493,7 +487,7 @@ static int build_impl(mrf_ctx* c, const mrf_scene* scenes, int32_t n_scenes, con
     const int64_t Tcap = Tn + reserve * (int64_t)((sl.W + kTileW - 1) / kTileW) * ((sl.H + kTileW - 1) / kTileW);
     HCK(ensure(c->b_counts, sizeof(int32_t) * (size_t)Rcap), "mrf_build: alloc counts");
     HCK(ensure(c->b_rowptr, sizeof(int64_t) * (size_t)(Rcap + 1)), "mrf_build: alloc row_ptr");
-    const size_t sbytes = scan_tmp_bytes(R + 1);
+    const size_t sbytes = scan_tmp_bytes((R > Tn ? R : Tn) + 1);
     HCK(ensure(c->b_misc, sbytes), "mrf_build: alloc scan");
     if (p->sparse_bricks) {
         HCK(ensure(c->b_bricks, (size_t)((NB + 3) / 4) * 4), "mrf_build: alloc brick mask");
@@ -503,54 +497,42 @@ static int build_impl(mrf_ctx* c, const mrf_scene* scenes, int32_t n_scenes, con
     HCK(launch_trace_count(c, s), "mrf_build: trace count");
     HCK(scan_exclusive_i32((const int32_t*)c->b_counts.p, (int64_t*)c->b_rowptr.p, R, c->b_misc.p, sbytes, s),
         "mrf_build: scan");
-    int64_t E = 0;
-    HCK(hipMemcpyAsync(&E, (int64_t*)c->b_rowptr.p + R, sizeof(int64_t), hipMemcpyDeviceToHost, s),
-        "mrf_build: read E");
-    HCK(hipStreamSynchronize(s), "mrf_build: sync");
-    c->E = E;
 
     // tiles of 4x4 rays, slot bases = exclusive scan of 16 * longest ray
     const int64_t T = c->T;
     HCK(ensure(c->b_tiles, sizeof(TileDev) * (size_t)Tcap), "mrf_build: alloc tiles");
     HCK(ensure(c->b_tbase, sizeof(int64_t) * (size_t)(Tcap + 1)), "mrf_build: alloc tile bases");
     HCK(ensure(c->b_tmp64, sizeof(int32_t) * (size_t)(T + 1)), "mrf_build: alloc");
-    const size_t tbytes = scan_tmp_bytes(T + 1);
-    HCK(ensure(c->b_misc, tbytes > sbytes ? tbytes : sbytes), "mrf_build: alloc scan");
     HCK(launch_tiles(c, (int32_t*)c->b_tmp64.p, s), "mrf_build: tiles");
     HCK(scan_exclusive_i32((const int32_t*)c->b_tmp64.p, (int64_t*)c->b_tbase.p, T, c->b_misc.p, c->b_misc.cap, s),
         "mrf_build: tile scan");
     HCK(launch_tile_bases(c, s), "mrf_build: tile bases");
-    int64_t S = 0;
-    HCK(hipMemcpyAsync(&S, (int64_t*)c->b_tbase.p + T, sizeof(int64_t), hipMemcpyDeviceToHost, s),
-        "mrf_build: read S");
+
+    // one readback: the slots and edges of every frame, which size everything below
+    const size_t nf = c->frames_h.size();
+    HCK(ensure(c->b_export, 2 * sizeof(int64_t) * nf), "mrf_build: alloc");
+    HCK(launch_frame_counts(c, (int64_t*)c->b_export.p, s), "mrf_build: per-frame counts");
+    std::vector<int64_t> h(2 * nf);
+    HCK(hipMemcpyAsync(h.data(), c->b_export.p, 2 * sizeof(int64_t) * nf, hipMemcpyDeviceToHost, s),
+        "mrf_build: read counts");
     HCK(hipStreamSynchronize(s), "mrf_build: sync");
-    if (frame_slots || frame_edges) {
-        // count only: per-frame slots and edges, and the context keeps no graph
-        c->S = S;
-        const size_t nf = c->frames_h.size();
-        HCK(ensure(c->b_export, 2 * sizeof(int64_t) * nf), "mrf_count: alloc");
-        HCK(launch_frame_counts(c, (int64_t*)c->b_export.p, s), "mrf_count: per-frame counts");
-        std::vector<int64_t> h(2 * nf);
-        HCK(hipMemcpyAsync(h.data(), c->b_export.p, 2 * sizeof(int64_t) * nf, hipMemcpyDeviceToHost, s),
-            "mrf_count: read counts");
-        HCK(hipStreamSynchronize(s), "mrf_count: sync");
+    int64_t S = 0, E = 0;
+    for (size_t f = 0; f < nf; ++f) {
+        S += h[2 * f];
+        E += h[2 * f + 1];
+    }
+    c->E = E;
+    c->S = S;
+    if (frame_slots || frame_edges) {   // count only: the context keeps no graph
         for (size_t f = 0; f < nf; ++f) {
             if (frame_slots) frame_slots[f] = h[2 * f];
             if (frame_edges) frame_edges[f] = h[2 * f + 1];
         }
         return MRF_OK;
     }
-    c->S = S;
     {
         // slot groups: runs of whole scenes with fewer than 2^group_log2 slots each; a
         // voxel's list entries hold slots relative to their group's first slot
-        const size_t nf = c->frames_h.size();
-        HCK(ensure(c->b_export, 2 * sizeof(int64_t) * nf), "mrf_build: alloc");
-        HCK(launch_frame_counts(c, (int64_t*)c->b_export.p, s), "mrf_build: per-frame counts");
-        std::vector<int64_t> h(2 * nf);
-        HCK(hipMemcpyAsync(h.data(), c->b_export.p, 2 * sizeof(int64_t) * nf, hipMemcpyDeviceToHost, s),
-            "mrf_build: read counts");
-        HCK(hipStreamSynchronize(s), "mrf_build: sync");
         std::vector<int64_t> scene_slots(c->n_scenes, 0);
         for (size_t f = 0; f < nf; ++f) scene_slots[c->frames_h[f].scene] += h[2 * f];
         const int64_t limit = int64_t(1) << c->group_log2;
@@ -636,7 +618,7 @@ static int build_impl(mrf_ctx* c, const mrf_scene* scenes, int32_t n_scenes, con
                            s),
             "mrf_build: group positions");
     }
-    HCK(hipStreamSynchronize(s), "mrf_build: sync");
+    if (c->sg.n > 1) HCK(hipStreamSynchronize(s), "mrf_build: sync");
     {
         hipError_t e = build_classes(c, s);
         if (e == hipErrorInvalidConfiguration) return fail(MRF_ERANGE, "mrf_build: " + g_err);

@@ -956,43 +956,6 @@ hipError_t launch_vptr_from_sorted(const uint32_t* sorted_keys, int64_t n, int64
 
 // ============================================================== work lists
 
-// length class of every tile (255: no edges)
-__global__ void tile_class_k(const TileDev* __restrict__ tiles, int64_t T, uint8_t* __restrict__ cls)
-{
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= T) return;
-    const int n = tiles[t].len;
-    uint8_t c = 255;
-    if (n > 0) {
-        c = kRayClasses;   // too long: reported as an error by the host
-        for (int k = 0; k < kRayClasses; ++k)
-            if (n <= kRayCap[k]) {
-                c = (uint8_t)k;
-                break;
-            }
-    }
-    cls[t] = c;
-}
-
-// degree class of every brick-major key (kVoxClasses: too large, 255: empty)
-__global__ void vox_class_k(const int64_t* __restrict__ vptr, int64_t Vk, uint8_t* __restrict__ cls)
-{
-    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v >= Vk) return;
-    const int64_t m = vptr[v + 1] - vptr[v];
-    uint8_t c = 255;
-    if (m > 0) {
-        c = kVoxClasses - 1;
-        for (int k = 0; k < kVoxClasses - 1; ++k)
-            if (m <= kVoxCap[k]) {
-                c = (uint8_t)k;
-                break;
-            }
-        if (m > 2147483647LL) c = kVoxClasses;
-    }
-    cls[v] = c;
-}
-
 // linear voxel id of a brick-major key (keys of padding voxels never appear)
 __device__ uint32_t key_to_voxel(const SceneDev* __restrict__ scenes, int ns, uint32_t key)
 {
@@ -1007,19 +970,6 @@ __device__ uint32_t key_to_voxel(const SceneDev* __restrict__ scenes, int ns, ui
     const int bz = (int)(brick / ((int64_t)sd.nb[0] * sd.nb[1]));
     const int i = bx * 8 + (l & 7), j = by * 8 + ((l >> 3) & 7), k = bz * 8 + (l >> 6);
     return (uint32_t)(sd.voxel_base + i + (int64_t)sd.n[0] * (j + (int64_t)sd.n[1] * k));
-}
-
-__global__ void vox_desc_k(const SceneDev* __restrict__ scenes, int ns, const uint32_t* __restrict__ keys, int64_t n,
-                           const int64_t* __restrict__ vptr, VoxDev* __restrict__ desc)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const uint32_t key = keys[i];
-    VoxDev d;
-    d.start = vptr[key];
-    d.m = (int32_t)(vptr[key + 1] - d.start);
-    d.v = key_to_voxel(scenes, ns, key);
-    desc[i] = d;
 }
 
 // brick-major key of a linear voxel id
@@ -1078,262 +1028,376 @@ __global__ void canon_edges_k(const FrameDev* __restrict__ frames, int nf, const
     for (int64_t k = 0; k < m; ++k) out[d + k] = in[s0 + kTile * k];
 }
 
-__global__ void compact_k(const uint8_t* __restrict__ cls, int64_t n, uint8_t c,
-                          const int64_t* __restrict__ pos, uint32_t* __restrict__ list)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n && cls[i] == c) list[pos[i]] = (uint32_t)i;
-}
-
 }  // namespace mrf
 
 namespace mrf {
 
-// lower_bound of every frame's first ray id in every class list
-__global__ void frame_offsets_k(const uint32_t* const* __restrict__ lists, const int64_t* __restrict__ cnt,
-                                const int64_t* __restrict__ fbase, int32_t nf, int64_t* __restrict__ out)
+// Stable partition of items 0 .. n-1 into classes 0 .. NC-1 (class 255: left
+// out), class-major, ascending inside a class: a count per block and class, a
+// scan of each class over the blocks, and a placement that classifies again.
+// A block takes kPartItems items, each of its waves a contiguous quarter in
+// rounds of 64; ranks inside a round are wave ballots.  F gives the items of a
+// block (range), an item's class (cls), takes its statistics (note, with the
+// block's LDS counters) and places it (put).  One read of the items per kernel
+// and no host step between: partitioning class by class (a flag scan of every
+// item, a readback and a compaction each, 25 times per build) took 1.05 of the
+// 1.34 ms of a 64x48 frame's build and inference and 1.9 of 24 ms at 8 VGA
+// keyframes and 9.4e6 voxels.
+constexpr int kPartRounds = 16;
+constexpr int kPartItems = 256 * kPartRounds;
+constexpr int kPartMaxClasses = 16;
+
+// Statistics of the work lists: items, edges and rays per class, log2
+// histograms and maxima of ray lengths and voxel degrees.
+struct ListStats {
+    unsigned long long tiles[kPartMaxClasses], tile_edges[kPartMaxClasses], tile_rays[kPartMaxClasses];
+    unsigned long long voxels[kPartMaxClasses], vox_edges[kPartMaxClasses];
+    unsigned long long ray_hist[16], deg_hist[24], max_ray, max_deg;
+};
+
+struct PartLds {
+    unsigned long long edges[kPartMaxClasses];
+    uint32_t rays[kPartMaxClasses], hist[24], top;
+};
+
+__device__ __forceinline__ int vox_class(int64_t m)
 {
-    const int f = blockIdx.x * blockDim.x + threadIdx.x;
-    const int c = blockIdx.y;
-    if (f > nf) return;
-    const uint32_t* L = lists[c];
-    int64_t lo = 0, hi = cnt[c];
-    const int64_t key = fbase[f];
-    while (lo < hi) {
-        const int64_t mid = (lo + hi) >> 1;
-        if ((int64_t)L[mid] < key)
-            lo = mid + 1;
-        else
-            hi = mid;
-    }
-    out[(int64_t)c * (nf + 1) + f] = lo;
+    if (m <= 0) return 255;
+    if (m > 2147483647LL) return kVoxClasses;   // reported as an error by the host
+    int c = kVoxClasses - 1;
+#pragma unroll
+    for (int k = kVoxClasses - 2; k >= 0; --k)
+        if (m <= kVoxCap[k]) c = k;
+    return c;
 }
 
-// log2 histograms of ray lengths and voxel degrees (integer atomics only)
-__global__ void hist_k(const int32_t* __restrict__ counts, int64_t R, const int64_t* __restrict__ vptr,
-                       int64_t V, unsigned long long* __restrict__ h)
-{
-    __shared__ unsigned long long loc[16 + 24 + 2];
-    for (int i = threadIdx.x; i < 42; i += blockDim.x) loc[i] = 0;
-    __syncthreads();
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < R) {
-        const int n = counts[i];
-        if (n > 0) {
-            const int b = min(15, 31 - __clz(n));
-            atomicAdd(&loc[b], 1ull);
-            atomicMax(&loc[40], (unsigned long long)n);
-        }
+// tiles of rays by their longest ray; blocks do not span frames (bpf blocks each)
+struct TileItems {
+    static constexpr int NC = kRayClasses + 1;   // and tiles that are too long
+    static_assert(NC <= kPartMaxClasses, "classes");
+    const TileDev* tiles;
+    const int32_t* counts;
+    const FrameDev* frames;
+    int64_t T;
+    int nf, bpf;
+    uint32_t* list;
+    ListStats* st;
+    __device__ void range(int64_t b, int64_t& i0, int64_t& i1) const
+    {
+        const int f = (int)(b / bpf);
+        i0 = frames[f].tile_base + (b - (int64_t)f * bpf) * kPartItems;
+        i1 = f + 1 < nf ? frames[f + 1].tile_base : T;
     }
-    if (i < V) {
-        const int64_t m = vptr[i + 1] - vptr[i];
-        if (m > 0) {
-            const int b = min(23, 63 - __clzll(m));
-            atomicAdd(&loc[16 + b], 1ull);
-            atomicMax(&loc[41], (unsigned long long)m);
-        }
+    __device__ int cls(int64_t i) const
+    {
+        const int n = tiles[i].len;
+        if (n <= 0) return 255;
+        int c = kRayClasses;   // too long: reported as an error by the host
+#pragma unroll
+        for (int k = kRayClasses - 1; k >= 0; --k)
+            if (n <= kRayCap[k]) c = k;
+        return c;
     }
-    __syncthreads();
-    for (int k = threadIdx.x; k < 42; k += blockDim.x) {
-        if (loc[k] == 0) continue;
-        if (k >= 40)
-            atomicMax(&h[k], loc[k]);
-        else
-            atomicAdd(&h[k], loc[k]);
-    }
-}
-
-// total edges and rays of the tiles of one class list (integer atomics: exact)
-__global__ void tile_class_edges_k(const uint32_t* __restrict__ list, int64_t n, const TileDev* __restrict__ tiles,
-                                   const int32_t* __restrict__ counts, unsigned long long* __restrict__ out_e,
-                                   unsigned long long* __restrict__ out_r)
-{
-    __shared__ unsigned long long acc, accr;
-    if (threadIdx.x == 0) acc = accr = 0;
-    __syncthreads();
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) {
-        const TileDev td = tiles[list[i]];
-        unsigned long long sum = 0, nr = 0;
+    __device__ void note(int64_t i, int c, PartLds& l) const
+    {
+        const TileDev td = tiles[i];
+        uint32_t e = 0, nr = 0, mx = 0;
         for (int a = 0; a < td.nv; ++a)
             for (int b = 0; b < td.nu; ++b) {
                 const int x = counts[td.ray0 + a * td.W + b];
-                sum += (unsigned long long)x;
-                nr += x > 0;
+                if (x <= 0) continue;
+                e += (uint32_t)x;
+                ++nr;
+                mx = max(mx, (uint32_t)x);
+                atomicAdd(&l.hist[min(15, 31 - __clz(x))], 1u);
             }
-        atomicAdd(&acc, sum);
-        atomicAdd(&accr, nr);
+        atomicAdd(&l.edges[c], (unsigned long long)e);
+        atomicAdd(&l.rays[c], nr);
+        atomicMax(&l.top, mx);
     }
+    __device__ void flush(const PartLds& l, int t) const
+    {
+        if (t < NC && l.edges[t]) atomicAdd(&st->tile_edges[t], l.edges[t]);
+        if (t < NC && l.rays[t]) atomicAdd(&st->tile_rays[t], (unsigned long long)l.rays[t]);
+        if (t < 16 && l.hist[t]) atomicAdd(&st->ray_hist[t], (unsigned long long)l.hist[t]);
+        if (t == 0 && l.top) atomicMax(&st->max_ray, (unsigned long long)l.top);
+    }
+    __device__ void put(int64_t at, int64_t i, int c) const
+    {
+        if (c < kRayClasses) list[at] = (uint32_t)i;
+    }
+};
+
+// brick-major voxel keys by degree
+struct VoxItems {
+    static constexpr int NC = kVoxClasses + 1;   // and voxels of too many edges
+    static_assert(NC <= kPartMaxClasses, "classes");
+    const int64_t* vptr;
+    int64_t n;
+    const SceneDev* scenes;
+    int ns;
+    VoxDev* desc;
+    ListStats* st;
+    __device__ void range(int64_t b, int64_t& i0, int64_t& i1) const
+    {
+        i0 = b * kPartItems;
+        i1 = n;
+    }
+    __device__ int cls(int64_t i) const { return vox_class(vptr[i + 1] - vptr[i]); }
+    __device__ void note(int64_t i, int c, PartLds& l) const
+    {
+        const int64_t m = vptr[i + 1] - vptr[i];
+        atomicAdd(&l.edges[c], (unsigned long long)m);
+        atomicAdd(&l.hist[min(23, 63 - __clzll(m))], 1u);
+        atomicMax(&l.top, (uint32_t)min(m, (int64_t)0xffffffffLL));
+    }
+    __device__ void flush(const PartLds& l, int t) const
+    {
+        if (t < NC && l.edges[t]) atomicAdd(&st->vox_edges[t], l.edges[t]);
+        if (t < 24 && l.hist[t]) atomicAdd(&st->deg_hist[t], (unsigned long long)l.hist[t]);
+        if (t == 0 && l.top) atomicMax(&st->max_deg, (unsigned long long)l.top);
+    }
+    __device__ void put(int64_t at, int64_t i, int c) const
+    {
+        if (c >= kVoxClasses) return;
+        const int64_t s = vptr[i];
+        desc[at] = VoxDev{s, (int32_t)(vptr[i + 1] - s), key_to_voxel(scenes, ns, (uint32_t)i)};
+    }
+};
+
+// (keyframe, voxel) pairs by edge count
+struct PairItems {
+    static constexpr int NC = kVoxClasses;
+    const uint32_t* pstart;
+    int64_t n;
+    VoxDev* desc;
+    __device__ void range(int64_t b, int64_t& i0, int64_t& i1) const
+    {
+        i0 = b * kPartItems;
+        i1 = n;
+    }
+    __device__ int cls(int64_t i) const { return vox_class((int64_t)pstart[i + 1] - pstart[i]); }
+    __device__ void note(int64_t, int, PartLds&) const {}
+    __device__ void flush(const PartLds&, int) const {}
+    __device__ void put(int64_t at, int64_t i, int) const
+    {
+        desc[at] = VoxDev{(int64_t)pstart[i], (int32_t)(pstart[i + 1] - pstart[i]), (uint32_t)i};
+    }
+};
+
+template <class F>
+__global__ __launch_bounds__(256) void part_count_k(const F f, int64_t nb, uint32_t* __restrict__ bcnt)
+{
+    __shared__ PartLds l;
+    __shared__ uint32_t wc[4][kPartMaxClasses];
+    for (int i = threadIdx.x; i < (int)(sizeof(PartLds) / 4); i += 256) ((uint32_t*)&l)[i] = 0;
     __syncthreads();
-    if (threadIdx.x == 0 && acc) {
-        atomicAdd(out_e, acc);
-        atomicAdd(out_r, accr);
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int64_t i0, i1;
+    f.range(blockIdx.x, i0, i1);
+    uint32_t cnt[F::NC] = {0};
+    for (int r = 0; r < kPartRounds; ++r) {
+        const int64_t i = i0 + (w * kPartRounds + r) * 64 + lane;
+        const int c = i < i1 ? f.cls(i) : 255;
+        if (c < F::NC) f.note(i, c, l);
+#pragma unroll
+        for (int k = 0; k < F::NC; ++k) cnt[k] += (uint32_t)__popcll(__ballot(c == k));
+    }
+#pragma unroll
+    for (int k = 0; k < F::NC; ++k)
+        if (lane == k) wc[w][k] = cnt[k];
+    __syncthreads();
+    if (threadIdx.x < F::NC) {
+        uint32_t t = 0;
+        for (int q = 0; q < 4; ++q) t += wc[q][threadIdx.x];
+        bcnt[(int64_t)threadIdx.x * nb + blockIdx.x] = t;
+    }
+    f.flush(l, threadIdx.x);
+}
+
+// exclusive scan over the blocks of each class (one wave per class, in place),
+// the class totals, and with fo the value at every bpf-th block (a frame's first)
+__global__ __launch_bounds__(64 * kPartMaxClasses) void part_scan_k(uint32_t* __restrict__ bcnt, int64_t nb, int nc,
+                                                                    unsigned long long* __restrict__ tot,
+                                                                    int64_t* __restrict__ fo, int bpf, int nf)
+{
+    const int k = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (k >= nc) return;
+    uint32_t* p = bcnt + (int64_t)k * nb;
+    uint32_t carry = 0;
+    for (int64_t b0 = 0; b0 < nb; b0 += 256) {
+        uint32_t x[4], t = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int64_t b = b0 + 4 * lane + q;
+            x[q] = b < nb ? p[b] : 0u;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) t += x[q];
+        uint32_t incl = t;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t y = __shfl_up(incl, d, 64);
+            if (lane >= d) incl += y;
+        }
+        uint32_t run = carry + incl - t;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int64_t b = b0 + 4 * lane + q;
+            if (b < nb) {
+                p[b] = run;
+                if (fo && b % bpf == 0) fo[(int64_t)k * (nf + 1) + b / bpf] = run;
+            }
+            run += x[q];
+        }
+        carry += __shfl(incl, 63, 64);
+    }
+    if (lane == 0) {
+        tot[k] = carry;
+        if (fo) fo[(int64_t)k * (nf + 1) + nf] = carry;
     }
 }
 
-// total edges of the items of one class list (integer atomics: exact)
-__global__ void class_edges_k(const uint32_t* __restrict__ list, int64_t n, const int64_t* __restrict__ ptr,
-                              unsigned long long* __restrict__ out)
+template <class F>
+__global__ __launch_bounds__(256) void part_place_k(const F f, int64_t nb, const uint32_t* __restrict__ boff,
+                                                    const unsigned long long* __restrict__ tot)
 {
-    __shared__ unsigned long long acc;
-    if (threadIdx.x == 0) acc = 0;
-    __syncthreads();
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) {
-        const uint32_t x = list[i];
-        atomicAdd(&acc, (unsigned long long)(ptr[x + 1] - ptr[x]));
+    __shared__ uint32_t wc[4][kPartMaxClasses];
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int64_t i0, i1;
+    f.range(blockIdx.x, i0, i1);
+    i0 += (int64_t)w * kPartRounds * 64;
+    int cl[kPartRounds];
+    uint32_t cnt[F::NC] = {0};
+#pragma unroll
+    for (int r = 0; r < kPartRounds; ++r) {
+        const int64_t i = i0 + r * 64 + lane;
+        cl[r] = i < i1 ? f.cls(i) : 255;
     }
+#pragma unroll
+    for (int r = 0; r < kPartRounds; ++r)
+#pragma unroll
+        for (int k = 0; k < F::NC; ++k) cnt[k] += (uint32_t)__popcll(__ballot(cl[r] == k));
+#pragma unroll
+    for (int k = 0; k < F::NC; ++k)
+        if (lane == k) wc[w][k] = cnt[k];
     __syncthreads();
-    if (threadIdx.x == 0 && acc) atomicAdd(out, acc);
+    uint32_t at[F::NC];   // next position of this wave's items of class k (totals are below 2^32)
+    uint32_t base = 0;
+#pragma unroll
+    for (int k = 0; k < F::NC; ++k) {
+        at[k] = base + boff[(int64_t)k * nb + blockIdx.x];
+        for (int q = 0; q < w; ++q) at[k] += wc[q][k];
+        base += (uint32_t)tot[k];
+    }
+    const uint64_t below = lane ? (~0ull) >> (64 - lane) : 0ull;
+#pragma unroll
+    for (int r = 0; r < kPartRounds; ++r) {
+        uint32_t pos = 0;
+#pragma unroll
+        for (int k = 0; k < F::NC; ++k) {
+            const uint64_t m = __ballot(cl[r] == k);
+            if (cl[r] == k) pos = at[k] + (uint32_t)__popcll(m & below);
+            at[k] += (uint32_t)__popcll(m);
+        }
+        if (cl[r] < F::NC) f.put(pos, i0 + r * 64 + lane, cl[r]);
+    }
 }
 
-static hipError_t partition(const uint8_t* cls, int64_t n, uint8_t c, int64_t* pos, void* tmp,
-                            size_t tmp_bytes, DevBuf& list, int64_t* count, hipStream_t s)
+template <class F>
+static hipError_t partition(const F& f, int64_t nb, uint32_t* bcnt, unsigned long long* tot, int64_t* fo, int bpf,
+                            int nf, hipStream_t s)
 {
-    if (tmp_bytes < scan_tmp_bytes(n)) return hipErrorInvalidValue;
-    hipError_t e = scan_rec(LoadEqU8{cls, c}, n, pos, (int64_t*)tmp, s);
-    if (e != hipSuccess) return e;
-    int64_t total = 0;
-    if ((e = hipMemcpyAsync(&total, pos + n, sizeof(int64_t), hipMemcpyDeviceToHost, s)) != hipSuccess) return e;
-    if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
-    *count = total;
-    if ((e = ensure(list, (size_t)(total > 0 ? total : 1) * sizeof(uint32_t))) != hipSuccess) return e;
-    if (total > 0)
-        hipLaunchKernelGGL(compact_k, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, s, cls, n, c,
-                           (const int64_t*)pos, (uint32_t*)list.p);
+    if (nb > 0) hipLaunchKernelGGL(part_count_k<F>, dim3((unsigned)nb), dim3(256), 0, s, f, nb, bcnt);
+    hipLaunchKernelGGL(part_scan_k, dim3(1), dim3(64 * kPartMaxClasses), 0, s, bcnt, nb, F::NC, tot, fo, bpf, nf);
+    if (nb > 0)
+        hipLaunchKernelGGL(part_place_k<F>, dim3((unsigned)nb), dim3(256), 0, s, f, nb, (const uint32_t*)bcnt,
+                           (const unsigned long long*)tot);
     return hipGetLastError();
 }
 
 hipError_t build_classes(mrf_ctx* c, hipStream_t s)
 {
     hipError_t e;
-    const int64_t nmax = std::max(c->R, std::max(c->Vk, c->T));
-    if ((e = ensure(c->b_cls, (size_t)(nmax + 1))) != hipSuccess) return e;
-    if ((e = ensure(c->b_tmp64, (size_t)(nmax + 2) * sizeof(int64_t))) != hipSuccess) return e;
-    const size_t sbytes = scan_tmp_bytes(nmax + 1);
-    if ((e = ensure(c->b_misc, sbytes)) != hipSuccess) return e;
-    uint8_t* cls = (uint8_t*)c->b_cls.p;
-    int64_t* pos = (int64_t*)c->b_tmp64.p;
+    const int nf = c->n_frames;
+    const int bpf = (int)std::max<int64_t>(1, cdiv(c->max_tpf, kPartItems));
+    const int64_t tb = (int64_t)bpf * nf, vb = cdiv(c->Vk, kPartItems);
+    // statistics | frame offsets of every tile class | per-block counts
+    const size_t fo_bytes = sizeof(int64_t) * (size_t)TileItems::NC * (nf + 1);
+    const size_t head = sizeof(ListStats) + fo_bytes;
+    if ((e = ensure(c->b_part, head + sizeof(uint32_t) * (size_t)(TileItems::NC * tb + VoxItems::NC * vb))) !=
+        hipSuccess)
+        return e;
+    const int64_t nvox = std::min(c->V, c->E);   // at most this many touched voxels
+    if ((e = ensure(c->b_ray_list, sizeof(uint32_t) * (size_t)c->T)) != hipSuccess) return e;
+    if ((e = ensure(c->b_vox_desc, sizeof(VoxDev) * (size_t)nvox)) != hipSuccess) return e;
+    ListStats* st = (ListStats*)c->b_part.p;
+    int64_t* fo = (int64_t*)(st + 1);
+    uint32_t* tcnt = (uint32_t*)((char*)c->b_part.p + head);
+    uint32_t* vcnt = tcnt + (size_t)TileItems::NC * tb;
+    if ((e = launch_fill_u32((uint32_t*)st, 0u, (int64_t)(sizeof(ListStats) / 4), s)) != hipSuccess) return e;
+    const TileItems ti{(const TileDev*)c->b_tiles.p, (const int32_t*)c->b_counts.p, (const FrameDev*)c->b_frames.p,
+                       c->T, nf, bpf, (uint32_t*)c->b_ray_list.p, st};
+    if ((e = partition(ti, tb, tcnt, st->tiles, fo, bpf, nf, s)) != hipSuccess) return e;
+    const VoxItems vi{(const int64_t*)c->b_vptr.p, c->Vk, (const SceneDev*)c->b_scenes.p, c->n_scenes,
+                      (VoxDev*)c->b_vox_desc.p, st};
+    if ((e = partition(vi, vb, vcnt, st->voxels, nullptr, 1, 0, s)) != hipSuccess) return e;
 
-    // tiles of rays, by their longest ray
-    if (c->T > 0)
-        hipLaunchKernelGGL(tile_class_k, dim3((unsigned)cdiv(c->T, 256)), dim3(256), 0, s,
-                           (const TileDev*)c->b_tiles.p, c->T, cls);
-    for (int k = 0; k < kRayClasses; ++k)
-        if ((e = partition(cls, c->T, (uint8_t)k, pos, c->b_misc.p, sbytes, c->b_ray_list[k], &c->ray_cnt[k], s)) !=
-            hipSuccess)
-            return e;
-    {
-        DevBuf tmp;
-        int64_t too_long = 0;
-        e = partition(cls, c->T, (uint8_t)kRayClasses, pos, c->b_misc.p, sbytes, tmp, &too_long, s);
-        hipFree(tmp.p);
-        if (e != hipSuccess) return e;
-        if (too_long > 0) {
-            set_error("a ray crosses more than 2048 voxels");
-            return hipErrorInvalidConfiguration;
-        }
+    // one readback: class sizes, statistics, and per-frame offsets of the tile lists (plain schedule)
+    std::vector<char> hb(head);
+    if ((e = hipMemcpyAsync(hb.data(), st, head, hipMemcpyDeviceToHost, s)) != hipSuccess) return e;
+    if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
+    const ListStats& h = *(const ListStats*)hb.data();
+    if (h.tiles[kRayClasses] > 0) {
+        set_error("a ray crosses more than 2048 voxels");
+        return hipErrorInvalidConfiguration;
     }
-    // voxels, by brick-major key
-    if (c->Vk > 0)
-        hipLaunchKernelGGL(vox_class_k, dim3((unsigned)cdiv(c->Vk, 256)), dim3(256), 0, s,
-                           (const int64_t*)c->b_vptr.p, c->Vk, cls);
+    if (h.voxels[kVoxClasses] > 0) {
+        set_error("a voxel is crossed by more than 2^31 - 1 rays");
+        return hipErrorInvalidConfiguration;
+    }
+    int64_t off = 0;
+    for (int k = 0; k < kRayClasses; ++k) {
+        c->ray_off[k] = off;
+        off += c->ray_cnt[k] = (int64_t)h.tiles[k];
+        c->ray_cls_edges[k] = (int64_t)h.tile_edges[k];
+        c->ray_cls_rays[k] = (int64_t)h.tile_rays[k];
+    }
+    off = 0;
     for (int k = 0; k < kVoxClasses; ++k) {
-        if ((e = partition(cls, c->Vk, (uint8_t)k, pos, c->b_misc.p, sbytes, c->b_vox_list[k], &c->vox_cnt[k], s)) !=
-            hipSuccess)
-            return e;
-        const int64_t n = c->vox_cnt[k];
-        if ((e = ensure(c->b_vox_desc[k], (size_t)(n > 0 ? n : 1) * sizeof(VoxDev))) != hipSuccess) return e;
-        if (n > 0)
-            hipLaunchKernelGGL(vox_desc_k, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, s,
-                               (const SceneDev*)c->b_scenes.p, c->n_scenes, (const uint32_t*)c->b_vox_list[k].p, n,
-                               (const int64_t*)c->b_vptr.p, (VoxDev*)c->b_vox_desc[k].p);
+        c->vox_off[k] = off;
+        off += c->vox_cnt[k] = (int64_t)h.voxels[k];
+        c->vox_cls_edges[k] = (int64_t)h.vox_edges[k];
     }
-    {
-        DevBuf tmp;
-        int64_t too_big = 0;
-        e = partition(cls, c->Vk, (uint8_t)kVoxClasses, pos, c->b_misc.p, sbytes, tmp, &too_big, s);
-        hipFree(tmp.p);
-        if (e != hipSuccess) return e;
-        if (too_big > 0) {
-            set_error("a voxel is crossed by more than 2^31 - 1 rays");
-            return hipErrorInvalidConfiguration;
-        }
-    }
+    const int64_t* hfo = (const int64_t*)(hb.data() + sizeof(ListStats));
+    c->frame_ray_off.assign(hfo, hfo + (size_t)(nf + 1) * kRayClasses);
+    for (int i = 0; i < 16; ++i) c->stats.ray_len_hist[i] = (int64_t)h.ray_hist[i];
+    for (int i = 0; i < 24; ++i) c->stats.voxel_degree_hist[i] = (int64_t)h.deg_hist[i];
+    c->stats.max_ray_len = (int64_t)h.max_ray;
+    c->stats.max_voxel_degree = (int64_t)h.max_deg;
+    return hipSuccess;
+}
 
-    // per-frame offsets of every ray class list (plain schedule)
-    {
-        const int nf = c->n_frames;
-        std::vector<int64_t> fbase(nf + 1);
-        for (int f = 0; f < nf; ++f) fbase[f] = c->frames_h[f].tile_base;
-        fbase[nf] = c->T;
-        std::vector<const uint32_t*> lists(kRayClasses);
-        for (int k = 0; k < kRayClasses; ++k) lists[k] = (const uint32_t*)c->b_ray_list[k].p;
-        // fbase (nf+1) | counts (classes) | offsets ((nf+1) * classes) | list pointers (classes)
-        const size_t need = sizeof(int64_t) * ((size_t)(nf + 1) * (kRayClasses + 1) + kRayClasses) +
-                            sizeof(void*) * kRayClasses;
-        if ((e = ensure(c->b_frame_list, need)) != hipSuccess) return e;
-        char* base = (char*)c->b_frame_list.p;
-        int64_t* d_fbase = (int64_t*)base;
-        int64_t* d_cnt = d_fbase + (nf + 1);
-        int64_t* d_out = d_cnt + kRayClasses;
-        const uint32_t** d_lists = (const uint32_t**)(d_out + (size_t)(nf + 1) * kRayClasses);
-        hipMemcpyAsync(d_fbase, fbase.data(), sizeof(int64_t) * (nf + 1), hipMemcpyHostToDevice, s);
-        hipMemcpyAsync(d_cnt, c->ray_cnt, sizeof(int64_t) * kRayClasses, hipMemcpyHostToDevice, s);
-        hipMemcpyAsync(d_lists, lists.data(), sizeof(void*) * kRayClasses, hipMemcpyHostToDevice, s);
-        hipLaunchKernelGGL(frame_offsets_k, dim3((unsigned)cdiv(nf + 1, 64), kRayClasses), dim3(64), 0, s,
-                           d_lists, (const int64_t*)d_cnt, (const int64_t*)d_fbase, nf, d_out);
-        c->frame_ray_off.assign((size_t)(nf + 1) * kRayClasses, 0);
-        if ((e = hipMemcpyAsync(c->frame_ray_off.data(), d_out, sizeof(int64_t) * (nf + 1) * kRayClasses,
-                                hipMemcpyDeviceToHost, s)) != hipSuccess)
-            return e;
-        // the host arrays above are read by the copies: finish before they go away
-        if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
+// the pairs [pstart[p], pstart[p + 1]) by edge count (b_pair_desc)
+static hipError_t partition_pairs(mrf_ctx* c, const uint32_t* pstart, int64_t P, hipStream_t s)
+{
+    hipError_t e;
+    const int64_t nb = cdiv(P, kPartItems);
+    const size_t head = sizeof(unsigned long long) * kPartMaxClasses;
+    if ((e = ensure(c->b_part, head + sizeof(uint32_t) * (size_t)(PairItems::NC * nb))) != hipSuccess) return e;
+    unsigned long long* tot = (unsigned long long*)c->b_part.p;
+    e = partition(PairItems{pstart, P, (VoxDev*)c->b_pair_desc.p}, nb, (uint32_t*)((char*)c->b_part.p + head), tot,
+                  nullptr, 1, 0, s);
+    unsigned long long h[kPartMaxClasses];
+    if (e == hipSuccess) e = hipMemcpyAsync(h, tot, head, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return e;
+    int64_t off = 0;
+    for (int k = 0; k < kVoxClasses; ++k) {
+        c->pair_off[k] = off;
+        off += c->pair_cnt[k] = (int64_t)h[k];
     }
-    // edges per work class (for the profiler's byte counts)
-    {
-        if ((e = ensure(c->b_sigpart, 64 * sizeof(double) * 4096)) != hipSuccess) return e;
-        unsigned long long* d = (unsigned long long*)c->b_sigpart.p + 64;
-        const int nc = 2 * kRayClasses + kVoxClasses;
-        hipMemsetAsync(d, 0, nc * sizeof(unsigned long long), s);
-        for (int k = 0; k < kRayClasses; ++k)
-            if (c->ray_cnt[k] > 0)
-                hipLaunchKernelGGL(tile_class_edges_k, dim3((unsigned)cdiv(c->ray_cnt[k], 256)), dim3(256), 0, s,
-                                   (const uint32_t*)c->b_ray_list[k].p, c->ray_cnt[k], (const TileDev*)c->b_tiles.p,
-                                   (const int32_t*)c->b_counts.p, d + k, d + kRayClasses + kVoxClasses + k);
-        for (int k = 0; k < kVoxClasses; ++k) {
-            const int64_t n = c->vox_cnt[k];
-            if (n > 0)
-                hipLaunchKernelGGL(class_edges_k, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, s,
-                                   (const uint32_t*)c->b_vox_list[k].p, n, (const int64_t*)c->b_vptr.p,
-                                   d + kRayClasses + k);
-        }
-        unsigned long long hh[2 * kRayClasses + kVoxClasses];
-        if ((e = hipMemcpyAsync(hh, d, sizeof(hh), hipMemcpyDeviceToHost, s)) != hipSuccess) return e;
-        if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
-        for (int k = 0; k < kRayClasses; ++k) c->ray_cls_edges[k] = (int64_t)hh[k];
-        for (int k = 0; k < kVoxClasses; ++k) c->vox_cls_edges[k] = (int64_t)hh[kRayClasses + k];
-        for (int k = 0; k < kRayClasses; ++k) c->ray_cls_rays[k] = (int64_t)hh[kRayClasses + kVoxClasses + k];
-    }
-    // histograms
-    {
-        unsigned long long* d_h = (unsigned long long*)c->b_sigpart.p;
-        if ((e = ensure(c->b_sigpart, 64 * sizeof(double) * 4096)) != hipSuccess) return e;
-        d_h = (unsigned long long*)c->b_sigpart.p;
-        hipMemsetAsync(d_h, 0, 42 * sizeof(unsigned long long), s);
-        const int64_t nmx = c->R > c->Vk ? c->R : c->Vk;
-        if (nmx > 0)
-            hipLaunchKernelGGL(hist_k, dim3((unsigned)cdiv(nmx, 256)), dim3(256), 0, s,
-                               (const int32_t*)c->b_counts.p, c->R, (const int64_t*)c->b_vptr.p, c->Vk, d_h);
-        unsigned long long hh[42];
-        if ((e = hipMemcpyAsync(hh, d_h, sizeof(hh), hipMemcpyDeviceToHost, s)) != hipSuccess) return e;
-        if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
-        for (int i = 0; i < 16; ++i) c->stats.ray_len_hist[i] = (int64_t)hh[i];
-        for (int i = 0; i < 24; ++i) c->stats.voxel_degree_hist[i] = (int64_t)hh[16 + i];
-        c->stats.max_ray_len = (int64_t)hh[40];
-        c->stats.max_voxel_degree = (int64_t)hh[41];
-    }
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 // ============================================================== adding keyframes
@@ -1491,40 +1555,15 @@ __global__ void pair_init_k(const LoadPairStart ld, int64_t E, const uint32_t* _
     px[p] = (uint32_t)(xb[f] + (int64_t)key_to_voxel(scenes, ns, ld.keys[j]));
 }
 
-// edge-count class of every pair (as the voxel classes)
-__global__ void pair_class_k(const uint32_t* __restrict__ pstart, int64_t P, uint8_t* __restrict__ cls)
-{
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= P) return;
-    const int64_t m = (int64_t)pstart[p + 1] - pstart[p];
-    uint8_t c = kVoxClasses - 1;
-    for (int k = 0; k < kVoxClasses - 1; ++k)
-        if (m <= kVoxCap[k]) {
-            c = (uint8_t)k;
-            break;
-        }
-    cls[p] = c;
-}
-
-__global__ void pair_desc_k(const uint32_t* __restrict__ list, int64_t n, const uint32_t* __restrict__ pstart,
-                            VoxDev* __restrict__ desc)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const uint32_t p = list[i];
-    desc[i] = VoxDev{(int64_t)pstart[p], (int32_t)(pstart[p + 1] - pstart[p]), p};
-}
-
-// the pairs of every touched voxel of one class list: [pos[vptr[key]], pos[vptr[key + 1]])
-__global__ void kf_vox_k(const SceneDev* __restrict__ scenes, int ns, const uint32_t* __restrict__ keys, int64_t n,
-                         const int64_t* __restrict__ vptr, const uint32_t* __restrict__ pos,
+// the pairs of every touched voxel (work item of the voxel phase): [pos[start], pos[start + m])
+__global__ void kf_vox_k(const VoxDev* __restrict__ vox, int64_t n, const uint32_t* __restrict__ pos,
                          VoxDev* __restrict__ desc)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
-    const uint32_t key = keys[i];
-    const uint32_t p0 = pos[vptr[key]], p1 = pos[vptr[key + 1]];
-    desc[i] = VoxDev{(int64_t)p0, (int32_t)(p1 - p0), key_to_voxel(scenes, ns, key)};
+    const VoxDev d = vox[i];
+    const uint32_t p0 = pos[d.start], p1 = pos[d.start + d.m];
+    desc[i] = VoxDev{(int64_t)p0, (int32_t)(p1 - p0), d.v};
 }
 
 // weight of entry j = chord length / its pair's summed chord length (equal
@@ -1593,45 +1632,17 @@ hipError_t build_keyframe_pairs(mrf_ctx* c, hipStream_t s)
                        (uint32_t*)c->b_pair_x.p);
 
     // pairs by edge count, as VoxDev work items of the voxel-phase kernels
-    if ((e = ensure(c->b_cls, (size_t)(P + 1))) != hipSuccess) return e;
-    if ((e = ensure(c->b_tmp64, (size_t)(P + 2) * sizeof(int64_t))) != hipSuccess) return e;
-    const size_t pb = scan_tmp_bytes(P + 1);
-    if ((e = ensure(c->b_misc, pb > c->b_misc.cap ? pb : c->b_misc.cap)) != hipSuccess) return e;
-    uint8_t* cls = (uint8_t*)c->b_cls.p;
-    if (P > 0)
-        hipLaunchKernelGGL(pair_class_k, dim3((unsigned)cdiv(P, 256)), dim3(256), 0, s, (const uint32_t*)pstart, P,
-                           cls);
-    DevBuf list;
-    for (int k = 0; k < kVoxClasses; ++k) {
-        e = partition(cls, P, (uint8_t)k, (int64_t*)c->b_tmp64.p, c->b_misc.p, c->b_misc.cap, list, &c->pair_cnt[k],
-                      s);
-        const int64_t n = c->pair_cnt[k];
-        if (e == hipSuccess) e = ensure(c->b_pair_desc[k], (size_t)(n > 0 ? n : 1) * sizeof(VoxDev));
-        if (e == hipSuccess && n > 0)
-            hipLaunchKernelGGL(pair_desc_k, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, s, (const uint32_t*)list.p, n,
-                               (const uint32_t*)pstart, (VoxDev*)c->b_pair_desc[k].p);
-        if (e == hipSuccess) e = hipStreamSynchronize(s);   // list is rewritten by the next class
-        if (e != hipSuccess) {
-            hipFree(list.p);
-            return e;
-        }
-    }
-    hipFree(list.p);
+    if ((e = ensure(c->b_pair_desc, (size_t)(P > 0 ? P : 1) * sizeof(VoxDev))) != hipSuccess) return e;
+    if ((e = partition_pairs(c, pstart, P, s)) != hipSuccess) return e;
 
-    // touched voxels with their pair ranges, class by class
+    // touched voxels with their pair ranges, in the voxel lists' order
     int64_t nv = 0;
     for (int k = 0; k < kVoxClasses; ++k) nv += c->vox_cnt[k];
     c->n_kf_vox = nv;
     if ((e = ensure(c->b_kf_vox, (size_t)(nv > 0 ? nv : 1) * sizeof(VoxDev))) != hipSuccess) return e;
-    int64_t off = 0;
-    for (int k = 0; k < kVoxClasses; ++k) {
-        const int64_t n = c->vox_cnt[k];
-        if (n > 0)
-            hipLaunchKernelGGL(kf_vox_k, dim3((unsigned)cdiv(n, 256)), dim3(256), 0, s, (const SceneDev*)c->b_scenes.p,
-                               c->n_scenes, (const uint32_t*)c->b_vox_list[k].p, n, (const int64_t*)c->b_vptr.p,
-                               (const uint32_t*)pos, (VoxDev*)c->b_kf_vox.p + off);
-        off += n;
-    }
+    if (nv > 0)
+        hipLaunchKernelGGL(kf_vox_k, dim3((unsigned)cdiv(nv, 256)), dim3(256), 0, s, (const VoxDev*)c->b_vox_desc.p,
+                           nv, (const uint32_t*)pos, (VoxDev*)c->b_kf_vox.p);
 
     // weights: chord length over the pair's summed chord length, in list order;
     // the chord lengths (slot order, b_kflen) are summed per pair by the pair phase

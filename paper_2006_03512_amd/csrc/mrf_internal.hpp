@@ -318,7 +318,7 @@ struct mrf_ctx {
     // buffers (raw device pointers into `bufs`)
     mrf::DevBuf b_scenes, b_frames, b_counts, b_rowptr, b_col, b_delta, b_bin, b_tin, b_tout,
         b_g, b_lam, b_ell, b_vedge, b_vptr, b_theta, b_L, b_thetabar, b_sigma, b_bias, b_ckpt,
-        b_ellbar, b_lambar, b_gsum, b_tmp64, b_cls, b_sigpart, b_misc;
+        b_ellbar, b_lambar, b_gsum, b_tmp64, b_part, b_sigpart, b_misc;
     mrf::DevBuf b_tiles, b_tbase;
     mrf::DevBuf b_tsum;   // per-voxel totals of the sweeps (theta + incoming ray messages), float2 pairs
     mrf::DevBuf b_theta2; // the prior log-odds as total pairs (theta, 0): the first sweep's lambda
@@ -344,16 +344,14 @@ struct mrf_ctx {
     mrf::DevBuf b_kfws;           // reverse pass: per edge slot, the edge's share of its pair's weight
     int kfws_ready = 0;           // b_kfws holds the current build's weights
     mrf::DevBuf b_kf_vox;         // per touched voxel: VoxDev over its pairs (start, count, voxel id)
-    mrf::DevBuf b_pair_desc[mrf::kVoxClasses];   // pairs by edge-count class: VoxDev (start, m, pair id)
-    int64_t pair_cnt[mrf::kVoxClasses] = {0};
+    mrf::DevBuf b_pair_desc;      // pairs by edge-count class: VoxDev (start, m, pair id), class-major
+    int64_t pair_off[mrf::kVoxClasses] = {0}, pair_cnt[mrf::kVoxClasses] = {0};
     int64_t n_kf_vox = 0;
-    mrf::DevBuf b_ray_list[mrf::kRayClasses];     // tile ids by tile length class
-    mrf::DevBuf b_vox_list[mrf::kVoxClasses];     // brick-major keys
-    mrf::DevBuf b_vox_desc[mrf::kVoxClasses];     // matching VoxDev descriptors
-    mrf::DevBuf b_frame_list;     // per-frame ray lists for the plain schedule
+    mrf::DevBuf b_ray_list;       // tile ids by tile length class, class-major
+    mrf::DevBuf b_vox_desc;       // touched voxels by degree class: VoxDev, class-major, brick-major keys inside
 
-    int64_t ray_cnt[mrf::kRayClasses] = {0};       // tiles per class
-    int64_t vox_cnt[mrf::kVoxClasses] = {0};
+    int64_t ray_off[mrf::kRayClasses] = {0}, ray_cnt[mrf::kRayClasses] = {0};   // tiles of a class: list range
+    int64_t vox_off[mrf::kVoxClasses] = {0}, vox_cnt[mrf::kVoxClasses] = {0};
     int64_t ray_cls_edges[mrf::kRayClasses] = {0};
     int64_t vox_cls_edges[mrf::kVoxClasses] = {0};
     std::vector<int64_t> frame_ray_off;   // plain schedule: tiles of frame f at [off[f], off[f+1])

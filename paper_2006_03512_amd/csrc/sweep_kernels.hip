@@ -511,7 +511,7 @@ static void launch_voxel_class(mrf_ctx* c, const float* in, VoxOut out, hipStrea
 {
     if (c->vox_cnt[K] <= 0) return;
     ProfScope ps(c, KID_VOX0 + K, s);
-    launch_seg_class<K, false>((const VoxDev*)c->b_vox_desc[K].p, c->vox_cnt[K], (const uint32_t*)c->b_vedge.p,
+    launch_seg_class<K, false>((const VoxDev*)c->b_vox_desc.p + c->vox_off[K], c->vox_cnt[K], (const uint32_t*)c->b_vedge.p,
                                c->sg, in, out, nullptr, s);
 }
 
@@ -527,7 +527,7 @@ hipError_t launch_voxel_phase(mrf_ctx* c, const float* in, VoxOut out, hipStream
     const int kc = kVoxClasses - 1;
     if (c->vox_cnt[kc] > 0) {
         ProfScope ps(c, KID_VOX0 + kc, s);
-        launch_seg_chunked<false>((const VoxDev*)c->b_vox_desc[kc].p, c->vox_cnt[kc], (const uint32_t*)c->b_vedge.p,
+        launch_seg_chunked<false>((const VoxDev*)c->b_vox_desc.p + c->vox_off[kc], c->vox_cnt[kc], (const uint32_t*)c->b_vedge.p,
                                   c->sg, in, out, nullptr, s);
     }
     return hipGetLastError();
@@ -546,9 +546,9 @@ template <int... K>
 static void pair_classes(std::integer_sequence<int, K...>, mrf_ctx* c, const float* in, VoxOut out,
                          const float* w, hipStream_t s)
 {
-    ((w ? launch_seg_class<K, true>((const VoxDev*)c->b_pair_desc[K].p, c->pair_cnt[K],
+    ((w ? launch_seg_class<K, true>((const VoxDev*)c->b_pair_desc.p + c->pair_off[K], c->pair_cnt[K],
                                     (const uint32_t*)c->b_vedge.p, c->sg, in, out, w, s)
-        : launch_seg_class<K, false>((const VoxDev*)c->b_pair_desc[K].p, c->pair_cnt[K],
+        : launch_seg_class<K, false>((const VoxDev*)c->b_pair_desc.p + c->pair_off[K], c->pair_cnt[K],
                                      (const uint32_t*)c->b_vedge.p, c->sg, in, out, nullptr, s)),
      ...);
 }
@@ -559,7 +559,7 @@ hipError_t launch_pair_phase(mrf_ctx* c, const float* in, const float* w, double
     ProfScope ps(c, KID_PAIR, s);
     pair_classes(std::make_integer_sequence<int, kVoxClasses - 1>{}, c, in, out, w, s);
     const int kc = kVoxClasses - 1;
-    const VoxDev* d = (const VoxDev*)c->b_pair_desc[kc].p;
+    const VoxDev* d = (const VoxDev*)c->b_pair_desc.p + c->pair_off[kc];
     if (w)
         launch_seg_chunked<true>(d, c->pair_cnt[kc], (const uint32_t*)c->b_vedge.p, c->sg, in, out, w, s);
     else
@@ -795,7 +795,7 @@ static void launch_ray_shape_t(const mrf_ctx* c, int64_t off, int64_t n, const R
     constexpr int G = kFwdShapes[Q][I].g;
     if constexpr (G != 0) {
         constexpr int CAP = kRayCap[Q];
-        const uint32_t* list = (const uint32_t*)c->b_ray_list[Q].p + off;
+        const uint32_t* list = (const uint32_t*)c->b_ray_list.p + c->ray_off[Q] + off;
         if constexpr (ray_class_lds(Q)) {
             hipLaunchKernelGGL((ray_lds_k<G, CAP / G, KF>), dim3((unsigned)n), dim3(kTile * G), 0, s, list, n,
                                (const TileDev*)c->b_tiles.p, (const int32_t*)c->b_counts.p,

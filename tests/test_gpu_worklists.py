@@ -1,0 +1,81 @@
+"""Work lists of the build (tiles by ray length, voxels and keyframe pairs by degree): every item in
+exactly one list, statistics as the exported incidence gives them, at list sizes around the
+partition's blocks of 4096 items."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2006_03512_amd import scenes
+
+pytestmark = pytest.mark.gpu
+
+
+def _scene(seed, w, h, grid, frames=1):
+    f = 0.9 * max(w, h)
+    return scenes.random_scene(seed, grid=grid, voxel=2.0 / max(grid), n_frames=frames,
+                               intr=scenes.Intrinsics(w, h, f, f, (w - 1) / 2, (h - 1) / 2))
+
+
+# (image, grid, frames) of each scene: one tile; 4096 tiles a frame and one more row; key spaces of
+# 4096 (8 bricks), 4608 and 8192 keys; frames whose blocks of tiles are partly empty
+CASES = {
+    "one tile": [((4, 4), (16, 16, 16), 1)],
+    "4096 tiles, 4096 keys": [((256, 256), (16, 16, 16), 1)],
+    "4160 tiles, 4608 keys": [((260, 256), (24, 24, 8), 2)],
+    "ragged, mixed images": [((259, 253), (17, 15, 9), 1), ((5, 3), (31, 16, 16), 3)],
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_lists_hold_every_item_once(name):
+    from paper_2006_03512_amd import RayMRF
+    scs = [_scene(70 + i, *wh, g, nf) for i, (wh, g, nf) in enumerate(CASES[name])]
+    p0 = scs[0].params
+    for s in scs:
+        s.params = p0
+    m = RayMRF()
+    st = m.build(scs, keyframe_average=True)
+    inc = {k: v.cpu().numpy() for k, v in m.export_incidence().items()}
+    lens, deg = np.diff(inc["row_ptr"]), np.diff(inc["vptr"])
+    lens, deg_t = lens[lens > 0], deg[deg > 0]
+    assert st.n_edges == lens.sum() == deg.sum() and st.n_kept_rays == lens.size
+    assert st.n_touched_voxels == deg_t.size
+    assert st.max_ray_len == lens.max() and st.max_voxel_degree == deg_t.max()
+    assert st.ray_len_hist == np.bincount(np.log2(lens).astype(int), minlength=16)[:16].tolist()
+    assert st.voxel_degree_hist == np.bincount(np.log2(deg_t).astype(int), minlength=24)[:24].tolist()
+
+    rng = np.random.default_rng(3)
+    theta = torch.from_numpy(rng.normal(-2, 0.5, st.n_voxels).astype(np.float32)).cuda()
+    sigma = torch.from_numpy(scs[0].sigma_table.astype(np.float32)).cuda()
+    m.infer(theta, sigma, 2)
+    _, logit = m.marginals()
+    ell = m.export_edges()["ell"].cpu().numpy().astype(np.float64)
+    # belief = prior + every incoming message, summed in FP64 and rounded once to FP32
+    want, mag = theta.cpu().numpy().astype(np.float64), np.zeros(st.n_voxels)
+    np.add.at(want, inc["col"], ell)
+    np.add.at(mag, inc["col"], np.abs(ell))
+    err = np.abs(logit.cpu().numpy() - want)
+    assert np.all(err <= 2.0 ** -23 * np.abs(want) + 2.0 ** -52 * deg.max() * (mag + 10))
+
+    m.infer_keyframe_avg(theta, sigma, 1)
+    _, logit = m.marginals()   # one averaged message of each keyframe: every pair in one list
+    ell = m.export_edges()["ell"].cpu().numpy().astype(np.float64)
+    hw = np.concatenate([np.full(s.n_rays, s.depth[0].size) for s in scs])
+    frame = np.concatenate([np.arange(s.n_rays) // s.depth[0].size for s in scs])
+    first = np.cumsum([0] + [s.n_frames for s in scs])
+    frame += np.concatenate([np.full(s.n_rays, first[i]) for i, s in enumerate(scs)])
+    assert hw.size == st.n_rays
+    pair = frame[np.repeat(np.arange(st.n_rays), np.diff(inc["row_ptr"]))] * st.n_voxels + inc["col"]
+    uniq, which = np.unique(pair, return_inverse=True)
+    assert st.n_keyframe_pairs == uniq.size
+    lo, hi = np.full(uniq.size, np.inf), np.full(uniq.size, -np.inf)
+    np.minimum.at(lo, which, ell)
+    np.maximum.at(hi, which, ell)
+    # an average lies between its messages (weights sum to 1 within an FP32 rounding per edge)
+    want_lo, want_hi = theta.cpu().numpy().astype(np.float64), theta.cpu().numpy().astype(np.float64)
+    np.add.at(want_lo, uniq % st.n_voxels, lo)
+    np.add.at(want_hi, uniq % st.n_voxels, hi)
+    slack = 2.0 ** -20 * (np.abs(want_lo) + np.abs(want_hi) + mag.max() + 1)
+    got = logit.cpu().numpy()
+    assert np.all(got >= want_lo - slack) and np.all(got <= want_hi + slack)
+    m.close()
