@@ -72,13 +72,6 @@ std::vector<uint64_t> graph_key(const mrf_ctx* c, int K, int keep)
     return k;
 }
 
-int bits_for(int64_t maxval)
-{
-    int b = 1;
-    while (b < 63 && (int64_t(1) << b) <= maxval) ++b;
-    return b;
-}
-
 }  // namespace
 
 namespace mrf {
@@ -594,24 +587,12 @@ static int build_impl(mrf_ctx* c, const mrf_scene* scenes, int32_t n_scenes, con
 
     // every slot is written: edges by the traversal, the rest as padding (no voxel,
     // no bin, sort key past every voxel)
-    HCK(launch_trace_emit(c, s), "mrf_build: trace emit");
+    HCK(launch_trace_emit(c, !incidence_by_runs(S), s), "mrf_build: trace emit");
 
-    // voxel -> ray incidence by a stable LSD radix sort of (brick-major voxel key,
-    // slot); the emit pass left the keys in the potentials buffer, and the
-    // message buffers are free during build and hold the sort's ping-pong
-    const int64_t nh = (int64_t)radix_hist_entries(S);
-    HCK(ensure(c->b_tmp64, sizeof(int64_t) * (size_t)(nh + 1) + sizeof(int32_t) * (size_t)nh),
-        "mrf_build: alloc sort tables");
-    int64_t* offs = (int64_t*)c->b_tmp64.p;
-    int32_t* hist = (int32_t*)(offs + nh + 1);
-    const size_t sb2 = radix_tmp_bytes(S);
-    HCK(ensure(c->b_misc, sb2 > c->b_misc.cap ? sb2 : c->b_misc.cap), "mrf_build: alloc sort scan");
-    HCK(radix_sort_pairs((const uint32_t*)c->b_g.p, (uint32_t*)c->b_lam.p, (uint32_t*)c->b_ell.p,
-                         (uint32_t*)c->b_ellbar.p, (uint32_t*)c->b_gsum.p, (uint32_t*)c->b_lambar.p,
-                         (uint32_t*)c->b_vedge.p, S, bits_for(Vk), hist, offs, c->b_misc.p, c->b_misc.cap, s, c->sg),
-        "mrf_build: radix sort");
-    HCK(launch_vptr_from_sorted((const uint32_t*)c->b_lambar.p, S, Vk, (int64_t*)c->b_vptr.p, s),
-        "mrf_build: vptr");
+    // voxel -> ray incidence; the message buffers are free during the build and hold
+    // the sort's data (b_lambar: the sorted keys, for the keyframe pairs)
+    HCK(build_incidence(c, 0, S, E, (uint32_t*)c->b_lambar.p, (uint32_t*)c->b_vedge.p, (int64_t*)c->b_vptr.p, c->sg, s),
+        "mrf_build: incidence");
     for (int g = 1; g < c->sg.n; ++g) {   // list position of each group's first key
         const int64_t k0 = c->scenes_h[c->group_scene[g]].key_base;
         HCK(hipMemcpyAsync(&c->sg.pos[g], (const int64_t*)c->b_vptr.p + k0, sizeof(int64_t), hipMemcpyDeviceToHost,
@@ -810,30 +791,15 @@ int mrf_add_frames(mrf_ctx* c, int32_t n_frames, const float* depth, const doubl
     HCK(ensure(c->b_ellbar, e4), "mrf_add_frames: alloc");
     HCK(ensure(c->b_lambar, e4), "mrf_add_frames: alloc");
     HCK(ensure(c->b_gsum, e4), "mrf_add_frames: alloc");
-    HCK(launch_trace_emit(c, s, f0, n_frames), "mrf_add_frames: trace emit");
+    HCK(launch_trace_emit(c, !incidence_by_runs(S1 - S0), s, f0, n_frames), "mrf_add_frames: trace emit");
 
-    // the new slots sorted by voxel key on their own (keys were left in b_g), then merged
-    // behind each voxel's existing entries
-    const int64_t n1 = S1 - S0;
-    const int64_t nh = (int64_t)radix_hist_entries(n1);
-    HCK(ensure(c->b_tmp64, sizeof(int64_t) * (size_t)(nh + 1) + sizeof(int32_t) * (size_t)nh),
-        "mrf_add_frames: alloc sort tables");
-    int64_t* offs = (int64_t*)c->b_tmp64.p;
-    int32_t* hist = (int32_t*)(offs + nh + 1);
-    sb = radix_tmp_bytes(n1);
-    HCK(ensure(c->b_misc, sb > c->b_misc.cap ? sb : c->b_misc.cap), "mrf_add_frames: alloc sort scan");
+    // the new slots sorted by voxel key on their own, then merged behind each voxel's
+    // existing entries
     uint32_t* nkeys = (uint32_t*)c->b_lambar.p;   // sorted new keys
     uint32_t* nvals = (uint32_t*)c->b_gsum.p;     // their slots less S0
-    // temporaries in b_export: the new keys' vptr (Vk + 1 int64), then the sort's spare values
-    const size_t vpb = sizeof(int64_t) * (size_t)(c->Vk + 1);
-    hipError_t e = ensure(c->b_export, vpb + sizeof(uint32_t) * (size_t)n1 + 64);
+    hipError_t e = ensure(c->b_export, sizeof(int64_t) * (size_t)(c->Vk + 1));
     int64_t* nvptr = (int64_t*)c->b_export.p;
-    uint32_t* vals_b = (uint32_t*)((char*)c->b_export.p + (vpb + 63) / 64 * 64);
-    if (e == hipSuccess)
-        e = radix_sort_pairs((const uint32_t*)c->b_g.p + S0, (uint32_t*)c->b_lam.p, (uint32_t*)c->b_ell.p,
-                             (uint32_t*)c->b_ellbar.p, vals_b, nkeys, nvals, n1, bits_for(c->Vk), hist, offs,
-                             c->b_misc.p, c->b_misc.cap, s);
-    if (e == hipSuccess) e = launch_vptr_from_sorted(nkeys, n1, c->Vk, nvptr, s);
+    if (e == hipSuccess) e = build_incidence(c, S0, S1 - S0, E1 - E0, nkeys, nvals, nvptr, SlotGroups{}, s);
     uint32_t* okeys = (uint32_t*)c->b_ell.p;      // keys of the existing entries
     uint32_t* merged = (uint32_t*)c->b_lam.p;
     if (e == hipSuccess) e = launch_entry_keys(c, (const uint32_t*)c->b_vedge.p, E0, okeys, s);

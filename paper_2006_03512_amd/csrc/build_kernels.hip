@@ -338,7 +338,7 @@ struct EdgeEmit {
         if (q < 0.0) q = 0.0;
         if (q > 63.0) q = 63.0;
         col[e] = vbase + vi + sd->n[0] * (vj + sd->n[1] * vk);
-        key[e] = brick_key(*sd, vi, vj, vk);
+        if (key) key[e] = brick_key(*sd, vi, vj, vk);
         delta[e] = (float)(Z - d);
         bin[e] = (uint8_t)q;
         if (tin) {
@@ -354,7 +354,8 @@ struct EdgeEmit {
 // per-slot array (a row-major pixel order would write 16-byte pieces of 16 lines).
 // Each lane then marks its column's slots past its ray, up to the tile's length, as
 // padding (no voxel, no bin, sort key pad_key past every voxel); lanes of pixels
-// outside the image pad their whole column.
+// outside the image pad their whole column.  Sort keys are written where the
+// slots themselves are sorted (key not null).
 __global__ __launch_bounds__(256) void trace_emit_k(const SceneDev* __restrict__ scenes,
                                                     const FrameDev* __restrict__ frames, BuildDev bp,
                                                     const int32_t* __restrict__ counts,
@@ -393,7 +394,7 @@ __global__ __launch_bounds__(256) void trace_emit_k(const SceneDev* __restrict__
     for (int k = m; k < len; ++k) {
         const int64_t e = slot0 + (int64_t)kTile * k;
         col[e] = -1;
-        key[e] = pad_key;
+        if (key) key[e] = pad_key;
         delta[e] = 0.0f;
         bin[e] = 255;
     }
@@ -504,7 +505,7 @@ hipError_t launch_scatter_by_slot(const uint32_t* slot, const float* in, int64_t
     return hipGetLastError();
 }
 
-hipError_t launch_trace_emit(mrf_ctx* c, hipStream_t s, int f0, int nf)
+hipError_t launch_trace_emit(mrf_ctx* c, bool keys, hipStream_t s, int f0, int nf)
 {
     if (nf < 0) nf = c->n_frames - f0;
     if (nf <= 0) return hipSuccess;
@@ -512,7 +513,7 @@ hipError_t launch_trace_emit(mrf_ctx* c, hipStream_t s, int f0, int nf)
     hipLaunchKernelGGL(trace_emit_k, grid, dim3(256), 0, s, (const SceneDev*)c->b_scenes.p,
                        (const FrameDev*)c->b_frames.p + f0, c->bp, (const int32_t*)c->b_counts.p,
                        (const int64_t*)c->b_tbase.p, (const TileDev*)c->b_tiles.p, (uint32_t)c->Vk,
-                       (int32_t*)c->b_col.p, (uint32_t*)c->b_g.p, (float*)c->b_delta.p, (uint8_t*)c->b_bin.p,
+                       (int32_t*)c->b_col.p, keys ? (uint32_t*)c->b_g.p : nullptr, (float*)c->b_delta.p, (uint8_t*)c->b_bin.p,
                        c->keep_chords ? (double*)c->b_tin.p : nullptr,
                        c->keep_chords ? (double*)c->b_tout.p : nullptr, c->kf ? (float*)c->b_kflen.p : nullptr);
     return hipGetLastError();
@@ -794,18 +795,22 @@ __global__ __launch_bounds__(256) void rs_offsets_k(const int32_t* __restrict__ 
 // t's run of a digit ends where tile t+1's begins, so consecutive tiles run on
 // one XCD (block remap) and their shared lines merge in its L2.  hist
 // and offs hold the tile's digit counts and output offsets (tile-major rows
-// of 256).
+// of 256).  MASK: items carry a second value of 16 bits.
+template <bool MASK>
 __global__ __launch_bounds__(RS_T) void rs_scatter_k(const uint32_t* __restrict__ keys_in,
                                                      const uint32_t* __restrict__ vals_in, int64_t n,
                                                      int shift, const int32_t* __restrict__ hist,
                                                      const int64_t* __restrict__ offs,
                                                      uint32_t* __restrict__ keys_out,
-                                                     uint32_t* __restrict__ vals_out, const SlotGroups groups)
+                                                     uint32_t* __restrict__ vals_out, const SlotGroups groups,
+                                                     const uint16_t* __restrict__ masks_in,
+                                                     uint16_t* __restrict__ masks_out)
 {
     constexpr int NW = RS_T / 64;
     constexpr int WI = RS_IPT * 64;   // items per wave
     __shared__ uint32_t lk[RS_TILE];
     __shared__ uint32_t lv[RS_TILE];
+    __shared__ uint16_t lm[MASK ? RS_TILE : 1];
     __shared__ int64_t boff[256];
     __shared__ int32_t dstart[256];
     __shared__ int32_t wcnt[NW][256];
@@ -818,14 +823,16 @@ __global__ __launch_bounds__(RS_T) void rs_scatter_k(const uint32_t* __restrict_
     const int64_t rem = n - wstart;
     const int nvw = rem <= 0 ? 0 : (rem < WI ? (int)rem : WI);
     uint32_t kr[RS_IPT], vr[RS_IPT];
+    uint16_t mr[MASK ? RS_IPT : 1];
 #pragma unroll
     for (int r = 0; r < RS_IPT; ++r) {
         const int64_t i = wstart + r * 64 + lane;
         const int64_t ic = i < n ? i : n - 1;
         kr[r] = keys_in[ic];
-        if (vals_in) vr[r] = vals_in[ic];
+        if (MASK || vals_in) vr[r] = vals_in[ic];
+        if constexpr (MASK) mr[r] = masks_in[ic];
     }
-    if (!vals_in) {   // first pass: the values are the slots, relative to their group's first slot
+    if (!MASK && !vals_in) {   // first pass: the values are the slots, relative to their group's first slot
         if (groups.n > 1) {
 #pragma unroll
             for (int r = 0; r < RS_IPT; ++r) {
@@ -882,6 +889,7 @@ __global__ __launch_bounds__(RS_T) void rs_scatter_k(const uint32_t* __restrict_
         if (valid) {
             lk[b + rank] = kr[r];
             lv[b + rank] = vr[r];
+            if constexpr (MASK) lm[b + rank] = mr[r];
         }
         if (valid && rank == 0) wcnt[w][d] = b + (rc[r] >> 8);
     }
@@ -893,7 +901,37 @@ __global__ __launch_bounds__(RS_T) void rs_scatter_k(const uint32_t* __restrict_
         const int64_t pos = boff[d] + (j - dstart[d]);
         keys_out[pos] = key;
         vals_out[pos] = lv[j];
+        if constexpr (MASK) masks_out[pos] = lm[j];
     }
+}
+
+// n sort passes from keys / vals (/ masks) A into B, B into A, ...; tables: hist and
+// offs (radix_hist_entries(n)), tmp (radix_tmp_bytes(n)).
+struct RadixTables {
+    int32_t* hist;
+    int64_t* offs;
+    int64_t* tmp;
+};
+
+template <bool MASK>
+static hipError_t radix_pass(const uint32_t* sk, const uint32_t* sv, const uint16_t* sm, uint32_t* dk, uint32_t* dv,
+                             uint16_t* dm, int64_t n, int shift, const RadixTables& t, const SlotGroups& groups,
+                             hipStream_t s)
+{
+    if ((uintptr_t)sk % 16 != 0) return hipErrorInvalidValue;   // rs_hist_k's 16-byte loads
+    const int64_t nb = cdiv(n, RS_TILE);
+    const int64_t nch = cdiv(nb, RS_CB);
+    int64_t* csum = t.tmp;
+    int64_t* coff = csum + 256 * nch;
+    int64_t* dtot = coff + 256 * nch;
+    hipLaunchKernelGGL(rs_hist_k, dim3((unsigned)nb), dim3(RS_T), 0, s, sk, n, shift, t.hist, nb);
+    hipLaunchKernelGGL(rs_colsum_k, dim3((unsigned)nch), dim3(256), 0, s, (const int32_t*)t.hist, nb, csum);
+    hipLaunchKernelGGL(rs_colscan_k, dim3(256), dim3(256), 0, s, (const int64_t*)csum, nch, coff, dtot);
+    hipLaunchKernelGGL(rs_offsets_k, dim3((unsigned)nch), dim3(256), 0, s, (const int32_t*)t.hist, nb,
+                       (const int64_t*)coff, (const int64_t*)dtot, t.offs);
+    hipLaunchKernelGGL(rs_scatter_k<MASK>, dim3((unsigned)nb), dim3(RS_T), 0, s, sk, sv, n, shift,
+                       (const int32_t*)t.hist, (const int64_t*)t.offs, dk, dv, groups, sm, dm);
+    return hipGetLastError();
 }
 
 hipError_t radix_sort_pairs(const uint32_t* keys_in, uint32_t* keys_a, uint32_t* vals_a, uint32_t* keys_b,
@@ -903,32 +941,302 @@ hipError_t radix_sort_pairs(const uint32_t* keys_in, uint32_t* keys_a, uint32_t*
 {
     if (n == 0) return hipSuccess;
     const int passes = key_bits <= 8 ? 1 : (key_bits + 7) / 8;
-    const int64_t nb = cdiv(n, RS_TILE);
-    const int64_t nch = cdiv(nb, RS_CB);
     if (tmp_bytes < radix_tmp_bytes(n)) return hipErrorInvalidValue;
-    for (const uint32_t* k : {keys_in, (const uint32_t*)keys_a, (const uint32_t*)keys_b})   // rs_hist_k's 16-byte loads
-        if ((uintptr_t)k % 16 != 0) return hipErrorInvalidValue;
-    int64_t* csum = (int64_t*)tmp;
-    int64_t* coff = csum + 256 * nch;
-    int64_t* dtot = coff + 256 * nch;
+    const RadixTables t{hist, offs, (int64_t*)tmp};
     const uint32_t* sk = keys_in;
     const uint32_t* sv = nullptr;
     for (int p = 0; p < passes; ++p) {
         uint32_t* dk = (p == passes - 1) ? keys_out : ((p & 1) ? keys_b : keys_a);
         uint32_t* dv = (p == passes - 1) ? vals_out : ((p & 1) ? vals_b : vals_a);
-        hipLaunchKernelGGL(rs_hist_k, dim3((unsigned)nb), dim3(RS_T), 0, s, sk, n, 8 * p, hist, nb);
-        hipLaunchKernelGGL(rs_colsum_k, dim3((unsigned)nch), dim3(256), 0, s, (const int32_t*)hist, nb, csum);
-        hipLaunchKernelGGL(rs_colscan_k, dim3(256), dim3(256), 0, s, (const int64_t*)csum, nch, coff, dtot);
-        hipLaunchKernelGGL(rs_offsets_k, dim3((unsigned)nch), dim3(256), 0, s, (const int32_t*)hist, nb,
-                           (const int64_t*)coff, (const int64_t*)dtot, offs);
-        hipLaunchKernelGGL(rs_scatter_k, dim3((unsigned)nb), dim3(RS_T), 0, s, sk, sv, n, 8 * p,
-                           (const int32_t*)hist, (const int64_t*)offs, dk, dv, groups);
-        hipError_t e = hipGetLastError();
+        const hipError_t e = radix_pass<false>(sk, sv, nullptr, dk, dv, nullptr, n, 8 * p, t, groups, s);
         if (e != hipSuccess) return e;
         sk = dk;
         sv = dv;
     }
     return hipSuccess;
+}
+
+// ------------------------------------------------------------ runs
+//
+// The 16 rays of a tile cross the same few voxels at a step: a row of 16 slots
+// holds about 3 different voxels.  Sorting one item per (row, voxel) -- a run:
+// its key, row and the 16-bit mask of its lanes -- instead of one per slot, and
+// writing the runs out as list entries afterwards, gives the same lists: a
+// (row, voxel) pair is one run, so runs of a voxel in row order, lanes
+// ascending inside, are its slots in order.  Padding slots make no run.
+// Three passes over 5.2e8 slots (8 VGA frames at 2 cm) took 7.6 ms of HBM-bound
+// sorting; finding, packing, sorting and expanding their runs takes 4.8.
+
+constexpr int kRunRows = 256;                   // rows per block of runs_find_k, 64 per wave
+constexpr int kRunSlots = kTile * kRunRows;
+
+__device__ __forceinline__ uint32_t voxel_key32(const SceneDev* __restrict__ scenes, int ns, uint32_t v)
+{
+    int sc = 0;
+    while (sc + 1 < ns && (int64_t)v >= scenes[sc + 1].voxel_base) ++sc;
+    const SceneDev& sd = scenes[sc];
+    const uint32_t local = v - (uint32_t)sd.voxel_base;
+    const uint32_t nx = (uint32_t)sd.n[0], nxy = nx * (uint32_t)sd.n[1];
+    const uint32_t k = local / nxy, rem = local - k * nxy;
+    const uint32_t j = rem / nx, i = rem - j * nx;
+    const uint32_t brick = ((k >> 3) * (uint32_t)sd.nb[1] + (j >> 3)) * (uint32_t)sd.nb[0] + (i >> 3);
+    return (uint32_t)sd.key_base + brick * 512u + ((k & 7) * 8 + (j & 7)) * 8 + (i & 7);
+}
+
+// bit j of the result: lane (i + j) mod 16 of the row holds another value than lane i
+template <int J>
+__device__ __forceinline__ uint32_t row_differs(uint32_t v)
+{
+    const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x120 + (16 - J), 0xF, 0xF, false);   // row_ror
+    return min(v ^ o, 1u) << J;
+}
+
+template <int... J>
+__device__ __forceinline__ uint32_t row_differs_all(uint32_t v, std::integer_sequence<int, J...>)
+{
+    return (row_differs<J + 1>(v) | ...);
+}
+
+// The runs of kRunRows rows, in row order, at [block * kRunSlots, + bcnt[block])
+// of gkey / ginfo (lane mask | row of the block << 16).  Bound by its reads of
+// col and the 15 lane comparisons of a row (45 instructions per 64 slots); keys
+// are computed after the runs are compacted in LDS, one per run.
+__global__ __launch_bounds__(256) void runs_find_k(const int32_t* __restrict__ col, int64_t n,
+                                                   const SceneDev* __restrict__ scenes, int ns,
+                                                   uint32_t* __restrict__ gkey, uint32_t* __restrict__ ginfo,
+                                                   int32_t* __restrict__ bcnt)
+{
+    constexpr int NR = kRunRows / 16;   // rounds of 4 rows per wave
+    __shared__ uint32_t lv[4][64 * NR], li[4][64 * NR];
+    __shared__ int wcnt[4];
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t b0 = (int64_t)blockIdx.x * kRunSlots;
+    const int64_t w0 = b0 + w * 64 * NR;
+    uint32_t v[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        const int64_t at = w0 + r * 64 + lane;   // n is a multiple of 16: a row lies wholly inside or outside
+        v[r] = at < n ? (uint32_t)col[at] : 0xffffffffu;
+    }
+    const int i = lane & 15;
+    const uint64_t below = lane ? (~0ull) >> (64 - lane) : 0ull;
+    int cnt = 0;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        const uint32_t rel = ~row_differs_all(v[r], std::make_integer_sequence<int, 15>{}) & 0xffffu;
+        const uint32_t mask = ((rel | (rel << 16)) >> (16 - i)) & 0xffffu;   // lanes holding this lane's voxel
+        const bool lead = (int32_t)v[r] >= 0 && (mask & ((1u << i) - 1u)) == 0u;
+        const uint64_t b = __ballot(lead);
+        if (lead) {
+            const int at = cnt + __popcll(b & below);
+            lv[w][at] = v[r];
+            li[w][at] = mask | ((uint32_t)(w * (kRunRows / 4) + r * 4 + (lane >> 4)) << 16);
+        }
+        cnt += __popcll(b);
+    }
+    if (lane == 0) wcnt[w] = cnt;
+    __syncthreads();
+    int off = 0, tot = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        if (q < w) off += wcnt[q];
+        tot += wcnt[q];
+    }
+    for (int j = lane; j < cnt; j += 64) {
+        gkey[b0 + off + j] = voxel_key32(scenes, ns, lv[w][j]);
+        ginfo[b0 + off + j] = li[w][j];
+    }
+    if (threadIdx.x == 0) bcnt[blockIdx.x] = tot;
+}
+
+// the blocks' runs, one after the other
+__global__ __launch_bounds__(256) void runs_pack_k(const uint32_t* __restrict__ gkey,
+                                                   const uint32_t* __restrict__ ginfo,
+                                                   const int32_t* __restrict__ bcnt, const int64_t* __restrict__ boff,
+                                                   uint32_t* __restrict__ key, uint32_t* __restrict__ row,
+                                                   uint16_t* __restrict__ mask)
+{
+    const int64_t g = (int64_t)blockIdx.x * kRunSlots, d = boff[blockIdx.x];
+    const int cnt = bcnt[blockIdx.x];
+    for (int j = threadIdx.x; j < cnt; j += 256) {
+        const uint32_t x = ginfo[g + j];
+        key[d + j] = gkey[g + j];
+        row[d + j] = (uint32_t)blockIdx.x * kRunRows + (x >> 16);
+        mask[d + j] = (uint16_t)(x & 0xffffu);
+    }
+}
+
+struct LoadPop {
+    const uint16_t* p;
+    __device__ int64_t operator()(int64_t i) const { return __popc((uint32_t)p[i]); }
+};
+
+// Sorted runs written out as list entries: a block takes SC_TILE runs (boff[block]
+// entries before them), a wave 64 of them at a time through LDS, so that the
+// entries leave as contiguous stores.  The first run of a key sets vptr[key].
+__global__ __launch_bounds__(256) void runs_expand_k(const uint32_t* __restrict__ key,
+                                                     const uint32_t* __restrict__ row,
+                                                     const uint16_t* __restrict__ mask, int64_t n,
+                                                     const int64_t* __restrict__ boff, const SlotGroups groups,
+                                                     uint32_t* __restrict__ keys, uint32_t* __restrict__ vals,
+                                                     int64_t* __restrict__ vptr)
+{
+    constexpr int NR = SC_TILE / 256;   // rounds of 64 runs per wave
+    __shared__ uint32_t lv[4][64 * kTile], lk[4][64 * kTile];
+    __shared__ int wsum[4];
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t r0 = (int64_t)blockIdx.x * SC_TILE + w * 64 * NR;
+    uint32_t k[NR], rw[NR], m[NR];
+    bool first[NR];
+    int sum = 0;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        const int64_t at = r0 + r * 64 + lane, ic = at < n ? at : n - 1;
+        k[r] = key[ic];
+        rw[r] = row[ic];
+        m[r] = at < n ? mask[ic] : 0u;
+        first[r] = at < n && (ic == 0 || key[ic - 1] != k[r]);
+        sum += __popc(m[r]);
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) sum += __shfl_xor(sum, d, 64);
+    if (lane == 0) wsum[w] = sum;
+    __syncthreads();
+    int64_t out = boff[blockIdx.x];
+    for (int q = 0; q < w; ++q) out += wsum[q];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        int incl = __popc(m[r]);
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int y = __shfl_up(incl, d, 64);
+            if (lane >= d) incl += y;
+        }
+        int at = incl - __popc(m[r]);
+        if (first[r]) vptr[k[r]] = out + at;
+        const int64_t slot0 = (int64_t)rw[r] * kTile;
+        const uint32_t rel = (uint32_t)(slot0 - (groups.n > 1 ? group_slot_base_of_slot(groups, slot0) : 0));
+        for (uint32_t x = m[r]; x; x &= x - 1, ++at) {
+            lv[w][at] = rel + (uint32_t)__ffs(x) - 1u;
+            if (keys) lk[w][at] = k[r];
+        }
+        // LDS accesses of one wave complete in order: the fences keep the compiler
+        // from moving the reads above the writes, and the next round's writes above them
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const int tot = __shfl(incl, 63, 64);
+        for (int j = lane; j < tot; j += 64) {
+            vals[out + j] = lv[w][j];
+            if (keys) keys[out + j] = lk[w][j];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        out += tot;
+    }
+}
+
+// vptr of the keys without a run (all ones so far): that of the next key with one,
+// found among the sorted runs, or the number of entries
+__global__ void vptr_gaps_k(const uint32_t* __restrict__ key, int64_t n, int64_t V, int64_t entries, int64_t* vptr)
+{
+    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (v > V || vptr[v] != -1) return;
+    int64_t lo = 0, hi = n;
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if ((int64_t)key[mid] < v)
+            lo = mid + 1;
+        else
+            hi = mid;
+    }
+    vptr[v] = lo < n ? vptr[key[lo]] : entries;
+}
+
+// Slots are sorted one by one where there are few of them: the runs cost six more
+// launches and a readback of their number.  Build + 3 sweeps + marginals of one frame
+// in us, slot by slot and by runs: 64x48 (2e5 slots) 623 and 672, 128x96 (1e6) 887 and
+// 871, 320x240 (7e6) 1206 and 1176, 640x480 (2.4e7) 2075 and 1922; 2 cm voxels (6e7)
+// 4427 and 3855.
+bool incidence_by_runs(int64_t n) { return n >= (int64_t(1) << 19); }
+
+static int key_bits(int64_t maxval)
+{
+    int b = 1;
+    while (b < 63 && (int64_t(1) << b) <= maxval) ++b;
+    return b;
+}
+
+hipError_t build_incidence(mrf_ctx* c, int64_t s0, int64_t n, int64_t edges, uint32_t* keys, uint32_t* vals,
+                           int64_t* vptr, const SlotGroups& groups, hipStream_t s)
+{
+    hipError_t e;
+    const int bits = key_bits(c->Vk);
+    if (!incidence_by_runs(n)) {
+        const int64_t nh = (int64_t)radix_hist_entries(n);
+        if ((e = ensure(c->b_tmp64, sizeof(int64_t) * (size_t)(nh + 1) + sizeof(int32_t) * (size_t)nh)) != hipSuccess)
+            return e;
+        int64_t* offs = (int64_t*)c->b_tmp64.p;
+        const size_t tb = (radix_tmp_bytes(n) + 255) / 256 * 256;   // then the sort's spare values
+        if ((e = ensure(c->b_misc, tb + sizeof(uint32_t) * (size_t)n)) != hipSuccess) return e;
+        e = radix_sort_pairs((const uint32_t*)c->b_g.p + s0, (uint32_t*)c->b_lam.p, (uint32_t*)c->b_ell.p,
+                             (uint32_t*)c->b_ellbar.p, (uint32_t*)((char*)c->b_misc.p + tb), keys, vals, n, bits,
+                             (int32_t*)(offs + nh + 1), offs, c->b_misc.p, tb, s, groups);
+        return e == hipSuccess ? launch_vptr_from_sorted(keys, n, c->Vk, vptr, s) : e;
+    }
+    // runs are found per block (b_g and a buffer outside the first list), packed into a
+    // list and sorted between the lists (b_lam, b_ell) and (b_lambar, b_gsum), masks in the
+    // halves of b_ellbar; the first list is the one from which the passes end in (b_lam, b_ell)
+    const int passes = (bits + 7) / 8;
+    const int64_t nb = cdiv(n, kRunSlots);
+    const size_t cnt_bytes = sizeof(int64_t) * (size_t)(nb + 1) + sizeof(int32_t) * (size_t)nb;
+    const int64_t nh = (int64_t)radix_hist_entries(n);   // as if every slot were a run
+    const size_t tab_bytes = sizeof(int64_t) * (size_t)(nh + 1) + sizeof(int32_t) * (size_t)nh;
+    if ((e = ensure(c->b_tmp64, std::max(cnt_bytes, tab_bytes))) != hipSuccess) return e;
+    const int64_t nb2 = cdiv(n, SC_TILE);
+    const size_t sb = std::max(std::max(scan_tmp_bytes(nb), radix_tmp_bytes(n)),
+                               sizeof(int64_t) * (size_t)(2 * nb2 + 1) + scan_tmp_bytes(nb2));
+    if ((e = ensure(c->b_misc, sb)) != hipSuccess) return e;
+    int64_t* boff = (int64_t*)c->b_tmp64.p;
+    int32_t* bcnt = (int32_t*)(boff + nb + 1);
+    uint32_t* lk[2] = {(uint32_t*)c->b_lam.p, (uint32_t*)c->b_lambar.p};
+    uint32_t* lr[2] = {(uint32_t*)c->b_ell.p, (uint32_t*)c->b_gsum.p};
+    uint16_t* lm[2] = {(uint16_t*)c->b_ellbar.p, (uint16_t*)c->b_ellbar.p + n};
+    const int first = passes & 1;
+    uint32_t* gkey = (uint32_t*)c->b_g.p;
+    uint32_t* ginfo = first ? lk[0] : lr[1];
+    hipLaunchKernelGGL(runs_find_k, dim3((unsigned)nb), dim3(256), 0, s, (const int32_t*)c->b_col.p + s0, n,
+                       (const SceneDev*)c->b_scenes.p, c->n_scenes, gkey, ginfo, bcnt);
+    if ((e = scan_exclusive_i32(bcnt, boff, nb, c->b_misc.p, c->b_misc.cap, s)) != hipSuccess) return e;
+    int64_t nr = 0;
+    if ((e = hipMemcpyAsync(&nr, boff + nb, sizeof(int64_t), hipMemcpyDeviceToHost, s)) != hipSuccess) return e;
+    if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
+    if ((e = launch_fill_u32((uint32_t*)vptr, 0xffffffffu, 2 * (c->Vk + 1), s)) != hipSuccess) return e;
+    if (nr > 0) {
+        hipLaunchKernelGGL(runs_pack_k, dim3((unsigned)nb), dim3(256), 0, s, (const uint32_t*)gkey,
+                           (const uint32_t*)ginfo, (const int32_t*)bcnt, (const int64_t*)boff, lk[first], lr[first],
+                           lm[first]);
+        const int64_t nhr = (int64_t)radix_hist_entries(nr);
+        int64_t* offs = (int64_t*)c->b_tmp64.p;
+        const RadixTables t{(int32_t*)(offs + nhr + 1), offs, (int64_t*)c->b_misc.p};
+        int at = first;
+        for (int p = 0; p < passes; ++p, at ^= 1)
+            if ((e = radix_pass<true>(lk[at], lr[at], lm[at], lk[at ^ 1], lr[at ^ 1], lm[at ^ 1], nr, 8 * p, t,
+                                      SlotGroups{}, s)) != hipSuccess)
+                return e;
+        const int64_t nbr = cdiv(nr, SC_TILE);
+        int64_t* bsum = (int64_t*)c->b_misc.p;
+        int64_t* eoff = bsum + nbr;
+        hipLaunchKernelGGL(scan_reduce_k<LoadPop>, dim3((unsigned)nbr), dim3(SC_T), 0, s, LoadPop{lm[0]}, nr, bsum);
+        if ((e = scan_rec(LoadI64{bsum}, nbr, eoff, eoff + nbr + 1, s)) != hipSuccess) return e;
+        hipLaunchKernelGGL(runs_expand_k, dim3((unsigned)nbr), dim3(256), 0, s, (const uint32_t*)lk[0],
+                           (const uint32_t*)lr[0], (const uint16_t*)lm[0], nr, (const int64_t*)eoff, groups, keys,
+                           vals, vptr);
+    }
+    hipLaunchKernelGGL(vptr_gaps_k, dim3((unsigned)cdiv(c->Vk + 1, 256)), dim3(256), 0, s, (const uint32_t*)lk[0], nr,
+                       c->Vk, edges, vptr);
+    return hipGetLastError();
 }
 
 // vptr[v] = first position whose key >= v (binary search), v in [0, V]

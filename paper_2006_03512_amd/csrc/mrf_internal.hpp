@@ -403,7 +403,8 @@ hipError_t ensure(DevBuf& b, size_t bytes);
 // build_kernels.hip
 // the count and emit passes over frames [f0, f0 + nf) (nf < 0: to the last frame)
 hipError_t launch_trace_count(mrf_ctx* c, hipStream_t s, int f0 = 0, int nf = -1);
-hipError_t launch_trace_emit(mrf_ctx* c, hipStream_t s, int f0 = 0, int nf = -1);
+// keys: also the sort keys of the slots, in b_g
+hipError_t launch_trace_emit(mrf_ctx* c, bool keys, hipStream_t s, int f0 = 0, int nf = -1);
 // per frame f: out[2 f] = its edge slots, out[2 f + 1] = its edges (after the count
 // pass and the tile bases)
 hipError_t launch_frame_counts(const mrf_ctx* c, int64_t* out, hipStream_t s);
@@ -419,6 +420,15 @@ hipError_t radix_sort_pairs(const uint32_t* keys_in, uint32_t* keys_a, uint32_t*
                             const SlotGroups& groups = SlotGroups{});
 size_t radix_hist_entries(int64_t n);
 size_t radix_tmp_bytes(int64_t n);   // tmp bytes radix_sort_pairs needs for n items
+// Voxel -> ray lists of the slots [s0, s0 + n) (n edges of them): vals[j] the slots
+// sorted stably by brick-major voxel key, less s0 and the first slot of their group;
+// keys[j] (may be null) their keys; vptr[k] the first entry of key k (k <= Vk).  The
+// per-slot message buffers hold the sort's data (keys may be b_lambar, vals any buffer
+// but b_g, b_lam, b_ell, b_ellbar).  incidence_by_runs: which of two routes n slots
+// take; the other one needs the sort keys that the emit pass leaves in b_g.
+bool incidence_by_runs(int64_t n);
+hipError_t build_incidence(mrf_ctx* c, int64_t s0, int64_t n, int64_t edges, uint32_t* keys, uint32_t* vals,
+                           int64_t* vptr, const SlotGroups& groups, hipStream_t s);
 hipError_t launch_vptr_from_sorted(const uint32_t* sorted_keys, int64_t n, int64_t V, int64_t* vptr,
                                    hipStream_t s);
 hipError_t build_classes(mrf_ctx* c, hipStream_t s);

@@ -22,6 +22,9 @@ CASES = {
     "one tile": [((4, 4), (16, 16, 16), 1)],
     "4096 tiles, 4096 keys": [((256, 256), (16, 16, 16), 1)],
     "4160 tiles, 4608 keys": [((260, 256), (24, 24, 8), 2)],
+    # enough edge slots for the incidence to be sorted by runs (2^19), ragged rows and two scenes
+    "runs": [((260, 256), (64, 60, 50), 2)],
+    "runs, two scenes": [((257, 131), (33, 47, 21), 2), ((63, 66), (64, 17, 9), 3)],
     "ragged, mixed images": [((259, 253), (17, 15, 9), 1), ((5, 3), (31, 16, 16), 3)],
 }
 
