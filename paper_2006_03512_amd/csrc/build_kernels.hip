@@ -657,7 +657,10 @@ hipError_t scan_exclusive_i32(const int32_t* in, int64_t* out, int64_t n, void* 
 constexpr int RS_T = MRF_RS_T, RS_IPT = MRF_RS_IPT, RS_TILE = RS_T * RS_IPT;
 static_assert(RS_T == 256 && RS_IPT % 4 == 0, "radix tile shape: one thread per digit");
 
-constexpr int RS_CB = 256;   // tiles per chunk of the digit-offset scan
+// Tiles per chunk of the digit-offset scan: each chunk is a serial walk of its tiles,
+// so short chunks keep more blocks busy (one VGA frame's 4e6 runs, 1000 tiles: chunks of
+// 256 took 39 us per pass, of 32 take 9).
+constexpr int RS_CB = 32;
 
 size_t radix_hist_entries(int64_t n) { return (size_t)256 * (size_t)cdiv(n > 0 ? n : 1, RS_TILE); }
 
@@ -1343,7 +1346,7 @@ namespace mrf {
 // Stable partition of items 0 .. n-1 into classes 0 .. NC-1 (class 255: left
 // out), class-major, ascending inside a class: a count per block and class, a
 // scan of each class over the blocks, and a placement that classifies again.
-// A block takes kPartItems items, each of its waves a contiguous quarter in
+// A block takes 256 R items, each of its waves a contiguous quarter in
 // rounds of 64; ranks inside a round are wave ballots.  F gives the items of a
 // block (range), an item's class (cls), takes its statistics (note, with the
 // block's LDS counters) and places it (put).  One read of the items per kernel
@@ -1351,8 +1354,12 @@ namespace mrf {
 // item, a readback and a compaction each, 25 times per build) took 1.05 of the
 // 1.34 ms of a 64x48 frame's build and inference and 1.9 of 24 ms at 8 VGA
 // keyframes and 9.4e6 voxels.
-constexpr int kPartRounds = 16;
-constexpr int kPartItems = 256 * kPartRounds;
+// A wave takes R rounds: 16 where there are blocks enough (fewer block counts to
+// scan), 2 below 2^20 items, whose few blocks would each walk serially (the tiles of a
+// VGA frame, 19200 items: 155 us with 16 rounds, 23 with 2).
+template <int R>
+constexpr int part_items() { return 256 * R; }
+static int part_rounds(int64_t n) { return n < (int64_t(1) << 20) ? 2 : 16; }
 constexpr int kPartMaxClasses = 16;
 
 // Statistics of the work lists: items, edges and rays per class, log2
@@ -1390,10 +1397,10 @@ struct TileItems {
     int nf, bpf;
     uint32_t* list;
     ListStats* st;
-    __device__ void range(int64_t b, int64_t& i0, int64_t& i1) const
+    __device__ void range(int64_t b, int items, int64_t& i0, int64_t& i1) const
     {
         const int f = (int)(b / bpf);
-        i0 = frames[f].tile_base + (b - (int64_t)f * bpf) * kPartItems;
+        i0 = frames[f].tile_base + (b - (int64_t)f * bpf) * items;
         i1 = f + 1 < nf ? frames[f + 1].tile_base : T;
     }
     __device__ int cls(int64_t i) const
@@ -1446,9 +1453,9 @@ struct VoxItems {
     int ns;
     VoxDev* desc;
     ListStats* st;
-    __device__ void range(int64_t b, int64_t& i0, int64_t& i1) const
+    __device__ void range(int64_t b, int items, int64_t& i0, int64_t& i1) const
     {
-        i0 = b * kPartItems;
+        i0 = b * items;
         i1 = n;
     }
     __device__ int cls(int64_t i) const { return vox_class(vptr[i + 1] - vptr[i]); }
@@ -1479,9 +1486,9 @@ struct PairItems {
     const uint32_t* pstart;
     int64_t n;
     VoxDev* desc;
-    __device__ void range(int64_t b, int64_t& i0, int64_t& i1) const
+    __device__ void range(int64_t b, int items, int64_t& i0, int64_t& i1) const
     {
-        i0 = b * kPartItems;
+        i0 = b * items;
         i1 = n;
     }
     __device__ int cls(int64_t i) const { return vox_class((int64_t)pstart[i + 1] - pstart[i]); }
@@ -1493,7 +1500,7 @@ struct PairItems {
     }
 };
 
-template <class F>
+template <class F, int R>
 __global__ __launch_bounds__(256) void part_count_k(const F f, int64_t nb, uint32_t* __restrict__ bcnt)
 {
     __shared__ PartLds l;
@@ -1502,14 +1509,20 @@ __global__ __launch_bounds__(256) void part_count_k(const F f, int64_t nb, uint3
     __syncthreads();
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int64_t i0, i1;
-    f.range(blockIdx.x, i0, i1);
-    uint32_t cnt[F::NC] = {0};
-    for (int r = 0; r < kPartRounds; ++r) {
-        const int64_t i = i0 + (w * kPartRounds + r) * 64 + lane;
-        const int c = i < i1 ? f.cls(i) : 255;
-        if (c < F::NC) f.note(i, c, l);
+    f.range(blockIdx.x, part_items<R>(), i0, i1);
+    i0 += (int64_t)w * R * 64;
+    int cl[R];
 #pragma unroll
-        for (int k = 0; k < F::NC; ++k) cnt[k] += (uint32_t)__popcll(__ballot(c == k));
+    for (int r = 0; r < R; ++r) {
+        const int64_t i = i0 + r * 64 + lane;
+        cl[r] = i < i1 ? f.cls(i) : 255;
+    }
+    uint32_t cnt[F::NC] = {0};
+#pragma unroll 2
+    for (int r = 0; r < R; ++r) {
+        if (cl[r] < F::NC) f.note(i0 + r * 64 + lane, cl[r], l);
+#pragma unroll
+        for (int k = 0; k < F::NC; ++k) cnt[k] += (uint32_t)__popcll(__ballot(cl[r] == k));
     }
 #pragma unroll
     for (int k = 0; k < F::NC; ++k)
@@ -1566,24 +1579,24 @@ __global__ __launch_bounds__(64 * kPartMaxClasses) void part_scan_k(uint32_t* __
     }
 }
 
-template <class F>
+template <class F, int R>
 __global__ __launch_bounds__(256) void part_place_k(const F f, int64_t nb, const uint32_t* __restrict__ boff,
                                                     const unsigned long long* __restrict__ tot)
 {
     __shared__ uint32_t wc[4][kPartMaxClasses];
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int64_t i0, i1;
-    f.range(blockIdx.x, i0, i1);
-    i0 += (int64_t)w * kPartRounds * 64;
-    int cl[kPartRounds];
+    f.range(blockIdx.x, part_items<R>(), i0, i1);
+    i0 += (int64_t)w * R * 64;
+    int cl[R];
     uint32_t cnt[F::NC] = {0};
 #pragma unroll
-    for (int r = 0; r < kPartRounds; ++r) {
+    for (int r = 0; r < R; ++r) {
         const int64_t i = i0 + r * 64 + lane;
         cl[r] = i < i1 ? f.cls(i) : 255;
     }
 #pragma unroll
-    for (int r = 0; r < kPartRounds; ++r)
+    for (int r = 0; r < R; ++r)
 #pragma unroll
         for (int k = 0; k < F::NC; ++k) cnt[k] += (uint32_t)__popcll(__ballot(cl[r] == k));
 #pragma unroll
@@ -1600,7 +1613,7 @@ __global__ __launch_bounds__(256) void part_place_k(const F f, int64_t nb, const
     }
     const uint64_t below = lane ? (~0ull) >> (64 - lane) : 0ull;
 #pragma unroll
-    for (int r = 0; r < kPartRounds; ++r) {
+    for (int r = 0; r < R; ++r) {
         uint32_t pos = 0;
 #pragma unroll
         for (int k = 0; k < F::NC; ++k) {
@@ -1612,24 +1625,33 @@ __global__ __launch_bounds__(256) void part_place_k(const F f, int64_t nb, const
     }
 }
 
-template <class F>
-static hipError_t partition(const F& f, int64_t nb, uint32_t* bcnt, unsigned long long* tot, int64_t* fo, int bpf,
-                            int nf, hipStream_t s)
+template <class F, int R>
+static hipError_t partition_r(const F& f, int64_t nb, uint32_t* bcnt, unsigned long long* tot, int64_t* fo, int bpf,
+                              int nf, hipStream_t s)
 {
-    if (nb > 0) hipLaunchKernelGGL(part_count_k<F>, dim3((unsigned)nb), dim3(256), 0, s, f, nb, bcnt);
+    if (nb > 0) hipLaunchKernelGGL((part_count_k<F, R>), dim3((unsigned)nb), dim3(256), 0, s, f, nb, bcnt);
     hipLaunchKernelGGL(part_scan_k, dim3(1), dim3(64 * kPartMaxClasses), 0, s, bcnt, nb, F::NC, tot, fo, bpf, nf);
     if (nb > 0)
-        hipLaunchKernelGGL(part_place_k<F>, dim3((unsigned)nb), dim3(256), 0, s, f, nb, (const uint32_t*)bcnt,
+        hipLaunchKernelGGL((part_place_k<F, R>), dim3((unsigned)nb), dim3(256), 0, s, f, nb, (const uint32_t*)bcnt,
                            (const unsigned long long*)tot);
     return hipGetLastError();
+}
+
+template <class F>
+static hipError_t partition(const F& f, int rounds, int64_t nb, uint32_t* bcnt, unsigned long long* tot, int64_t* fo,
+                            int bpf, int nf, hipStream_t s)
+{
+    return rounds == 2 ? partition_r<F, 2>(f, nb, bcnt, tot, fo, bpf, nf, s)
+                       : partition_r<F, 16>(f, nb, bcnt, tot, fo, bpf, nf, s);
 }
 
 hipError_t build_classes(mrf_ctx* c, hipStream_t s)
 {
     hipError_t e;
     const int nf = c->n_frames;
-    const int bpf = (int)std::max<int64_t>(1, cdiv(c->max_tpf, kPartItems));
-    const int64_t tb = (int64_t)bpf * nf, vb = cdiv(c->Vk, kPartItems);
+    const int tr = part_rounds(c->T), vr = part_rounds(c->Vk);
+    const int bpf = (int)std::max<int64_t>(1, cdiv(c->max_tpf, 256 * tr));
+    const int64_t tb = (int64_t)bpf * nf, vb = cdiv(c->Vk, 256 * vr);
     // statistics | frame offsets of every tile class | per-block counts
     const size_t fo_bytes = sizeof(int64_t) * (size_t)TileItems::NC * (nf + 1);
     const size_t head = sizeof(ListStats) + fo_bytes;
@@ -1646,10 +1668,10 @@ hipError_t build_classes(mrf_ctx* c, hipStream_t s)
     if ((e = launch_fill_u32((uint32_t*)st, 0u, (int64_t)(sizeof(ListStats) / 4), s)) != hipSuccess) return e;
     const TileItems ti{(const TileDev*)c->b_tiles.p, (const int32_t*)c->b_counts.p, (const FrameDev*)c->b_frames.p,
                        c->T, nf, bpf, (uint32_t*)c->b_ray_list.p, st};
-    if ((e = partition(ti, tb, tcnt, st->tiles, fo, bpf, nf, s)) != hipSuccess) return e;
+    if ((e = partition(ti, tr, tb, tcnt, st->tiles, fo, bpf, nf, s)) != hipSuccess) return e;
     const VoxItems vi{(const int64_t*)c->b_vptr.p, c->Vk, (const SceneDev*)c->b_scenes.p, c->n_scenes,
                       (VoxDev*)c->b_vox_desc.p, st};
-    if ((e = partition(vi, vb, vcnt, st->voxels, nullptr, 1, 0, s)) != hipSuccess) return e;
+    if ((e = partition(vi, vr, vb, vcnt, st->voxels, nullptr, 1, 0, s)) != hipSuccess) return e;
 
     // one readback: class sizes, statistics, and per-frame offsets of the tile lists (plain schedule)
     std::vector<char> hb(head);
@@ -1690,11 +1712,12 @@ hipError_t build_classes(mrf_ctx* c, hipStream_t s)
 static hipError_t partition_pairs(mrf_ctx* c, const uint32_t* pstart, int64_t P, hipStream_t s)
 {
     hipError_t e;
-    const int64_t nb = cdiv(P, kPartItems);
+    const int rounds = part_rounds(P);
+    const int64_t nb = cdiv(P, 256 * rounds);
     const size_t head = sizeof(unsigned long long) * kPartMaxClasses;
     if ((e = ensure(c->b_part, head + sizeof(uint32_t) * (size_t)(PairItems::NC * nb))) != hipSuccess) return e;
     unsigned long long* tot = (unsigned long long*)c->b_part.p;
-    e = partition(PairItems{pstart, P, (VoxDev*)c->b_pair_desc.p}, nb, (uint32_t*)((char*)c->b_part.p + head), tot,
+    e = partition(PairItems{pstart, P, (VoxDev*)c->b_pair_desc.p}, rounds, nb, (uint32_t*)((char*)c->b_part.p + head), tot,
                   nullptr, 1, 0, s);
     unsigned long long h[kPartMaxClasses];
     if (e == hipSuccess) e = hipMemcpyAsync(h, tot, head, hipMemcpyDeviceToHost, s);
