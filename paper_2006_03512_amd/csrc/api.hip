@@ -49,16 +49,19 @@ std::vector<uint64_t> graph_key(const mrf_ctx* c, int K, int keep)
     std::vector<uint64_t> k = {(uint64_t)K, (uint64_t)keep, (uint64_t)c->E, (uint64_t)c->R, (uint64_t)c->V,
                                (uint64_t)c->Vk, (uint64_t)c->S, (uint64_t)c->T};
     for (int i = 0; i < mrf::kRayClasses; ++i) k.push_back((uint64_t)c->ray_cnt[i]);
-    for (int i = 0; i < mrf::kVoxClasses; ++i) k.push_back((uint64_t)c->vox_cnt[i]);
     for (int i = 0; i < mrf::kRayClasses; ++i) k.push_back((uint64_t)c->fwd_sel[i]);
     const mrf::DevBuf* bufs[] = {&c->b_rowptr, &c->b_col,   &c->b_delta, &c->b_bin,  &c->b_g,    &c->b_lam,
                                  &c->b_ell,    &c->b_vedge, &c->b_vptr,  &c->b_theta, &c->b_L,   &c->b_sigma, &c->b_bias,
                                  &c->b_ckpt,   &c->b_tsum,  &c->b_tbar,  &c->b_tiles, &c->b_counts, &c->b_theta2,
                                  &c->b_kfw,    &c->b_pair_m, &c->b_pair_x, &c->b_kfx, &c->b_kfxb, &c->b_kf_vox};
     for (const mrf::DevBuf* b : bufs) k.push_back((uint64_t)(uintptr_t)b->p);
-    for (const mrf::DevBuf* b : {&c->b_ray_list, &c->b_vox_desc, &c->b_pair_desc})
-        k.push_back((uint64_t)(uintptr_t)b->p);
-    for (int i = 0; i < mrf::kVoxClasses; ++i) k.push_back((uint64_t)c->pair_cnt[i]);
+    for (const mrf::DevBuf* b : {&c->b_ray_list, &c->b_hubsum}) k.push_back((uint64_t)(uintptr_t)b->p);
+    for (const mrf::SegList* l : {&c->vox, &c->pair}) {
+        k.push_back((uint64_t)(uintptr_t)l->desc.p);
+        k.push_back((uint64_t)(uintptr_t)l->hub.p);
+        k.push_back((uint64_t)l->n_pieces);
+        for (int i = 0; i < mrf::kVoxClasses; ++i) k.push_back((uint64_t)l->cnt[i]);
+    }
     k.push_back((uint64_t)c->n_kf_vox);
     k.push_back((uint64_t)c->cell_px);
     k.push_back((uint64_t)c->n_cells);
@@ -258,7 +261,7 @@ void mrf_destroy(mrf_ctx* c)
                      &c->b_vptr, &c->b_theta, &c->b_theta2, &c->b_L, &c->b_thetabar, &c->b_sigma, &c->b_bias,
                      &c->b_ckpt, &c->b_tsum, &c->b_tbar, &c->b_metric, &c->b_bricks,
                      &c->b_ellbar, &c->b_lambar, &c->b_gsum, &c->b_tmp64, &c->b_part, &c->b_sigpart,
-                     &c->b_misc, &c->b_ray_list, &c->b_vox_desc, &c->b_pair_desc, &c->b_tiles, &c->b_tbase, &c->b_export,
+                     &c->b_misc, &c->b_ray_list, &c->vox.desc, &c->vox.hub, &c->pair.desc, &c->pair.hub, &c->b_hubsum, &c->b_tiles, &c->b_tbase, &c->b_export,
                      &c->b_kfw, &c->b_kflen, &c->b_pair_m, &c->b_pair_x, &c->b_kfx, &c->b_kfxb, &c->b_kf_vox,
                      &c->b_kfxr, &c->b_kfy, &c->b_kfws};
     for (DevBuf* b : all) free_buf(*b);
@@ -462,7 +465,8 @@ static int build_impl(mrf_ctx* c, const mrf_scene* scenes, int32_t n_scenes, con
         return fail(MRF_EINVAL, "mrf_build: group_slots_log2 must be 0 or lie in [12, 32]");
     c->group_log2 = p->group_slots_log2 ? p->group_slots_log2 : 32;
     c->n_pairs = c->n_kfx = c->n_kf_vox = 0;
-    for (int k = 0; k < kVoxClasses; ++k) c->pair_cnt[k] = 0;
+    for (int k = 0; k < kVoxClasses; ++k) c->pair.cnt[k] = 0;
+    c->pair.n_pieces = 0;
     c->n_cells = sensor_cells(c->scenes_h, c->cell_px);
 
     HCK(ensure(c->b_scenes, sizeof(SceneDev) * c->scenes_h.size()), "mrf_build: alloc");
@@ -632,7 +636,7 @@ static void update_stats(mrf_ctx* c)
     st.n_slot_groups = c->sg.n;
     st.n_tiles = c->T;
     st.n_touched_voxels = 0;
-    for (int k = 0; k < kVoxClasses; ++k) st.n_touched_voxels += c->vox_cnt[k];
+    for (int k = 0; k < kVoxClasses; ++k) st.n_touched_voxels += c->vox.cnt[k];
     // voxel phase: vedge 4 + gathered ell 4 per edge, descriptor 16 + theta 4 + total 4 per
     // touched voxel; ray phase: col 4 + own ell 4 + g 4 + ell 4 per edge, total 4 per touched
     // voxel, count 4 per kept ray, list 4 + descriptor 32 per tile
@@ -1203,14 +1207,7 @@ extern "C" {
 
 static std::string kid_name(const mrf_ctx* c, int k)
 {
-    if (k >= KID_VOX0 && k < KID_VOX0 + kVoxClasses) {
-        const int q = k - KID_VOX0;
-        if (q == kVoxClasses - 1) return "voxel_chunked_k";
-        if (kVoxNW[q] == 0)
-            return "voxel_small_k<" + std::to_string(kVoxCap[q]) + "," + std::to_string(kVoxVPW[q]) + ">";
-        return "voxel_k<" + std::to_string(kVoxNW[q]) + "," + std::to_string(kVoxCap[q] / (64 * kVoxNW[q])) + "," +
-               std::to_string(kVoxVPW[q]) + ">";
-    }
+    if (k == KID_VOX) return "seg_sum_k";
     auto ray_name = [](const char* direct, const char* lds, int q, RayShape sh, bool adj) {
         std::string n = std::string(ray_class_lds(q) ? lds : direct) + "<" + std::to_string(sh.g) + "," +
                         std::to_string(kRayCap[q] / sh.g);
@@ -1237,11 +1234,10 @@ static void kid_bytes(const mrf_ctx* c, int k, double* bytes, int64_t* edges)
 {
     *bytes = 0.0;
     *edges = 0;
-    if (k >= KID_VOX0 && k < KID_VOX0 + kVoxClasses) {
-        const int q = k - KID_VOX0;
+    if (k == KID_VOX) {
         // per edge: vedge 4 + gathered message 4; per voxel: descriptor 16 + base 4 + total 4
-        *edges = c->vox_cls_edges[q];
-        *bytes = 8.0 * (double)*edges + 24.0 * (double)c->vox_cnt[q];
+        *edges = c->E;
+        *bytes = 8.0 * (double)*edges + 24.0 * (double)c->stats.n_touched_voxels;
     } else if (k >= KID_RAY0 && k < KID_RAY0 + kRayClasses) {
         const int q = k - KID_RAY0;
         // per edge: col 4 + own ell 4 + g 4 + ell 4 (voxel totals: counted once per voxel

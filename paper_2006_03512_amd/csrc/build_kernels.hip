@@ -1366,14 +1366,16 @@ constexpr int kPartMaxClasses = 16;
 // histograms and maxima of ray lengths and voxel degrees.
 struct ListStats {
     unsigned long long tiles[kPartMaxClasses], tile_edges[kPartMaxClasses], tile_rays[kPartMaxClasses];
-    unsigned long long voxels[kPartMaxClasses], vox_edges[kPartMaxClasses];
-    unsigned long long ray_hist[16], deg_hist[24], max_ray, max_deg;
+    unsigned long long voxels[kPartMaxClasses];
+    unsigned long long ray_hist[16], deg_hist[24], max_ray, max_deg, pieces;
 };
 
 struct PartLds {
     unsigned long long edges[kPartMaxClasses];
-    uint32_t rays[kPartMaxClasses], hist[24], top;
+    uint32_t rays[kPartMaxClasses], hist[24], top, pieces;
 };
+
+__device__ __forceinline__ int64_t seg_pieces(int64_t m) { return (m + kSegPiece - 1) / kSegPiece; }
 
 __device__ __forceinline__ int vox_class(int64_t m)
 {
@@ -1462,13 +1464,13 @@ struct VoxItems {
     __device__ void note(int64_t i, int c, PartLds& l) const
     {
         const int64_t m = vptr[i + 1] - vptr[i];
-        atomicAdd(&l.edges[c], (unsigned long long)m);
+        if (m > kSegPiece) atomicAdd(&l.pieces, (uint32_t)min(seg_pieces(m), (int64_t)1 << 20));
         atomicAdd(&l.hist[min(23, 63 - __clzll(m))], 1u);
         atomicMax(&l.top, (uint32_t)min(m, (int64_t)0xffffffffLL));
     }
     __device__ void flush(const PartLds& l, int t) const
     {
-        if (t < NC && l.edges[t]) atomicAdd(&st->vox_edges[t], l.edges[t]);
+        if (t == 1 && l.pieces) atomicAdd(&st->pieces, (unsigned long long)l.pieces);
         if (t < 24 && l.hist[t]) atomicAdd(&st->deg_hist[t], (unsigned long long)l.hist[t]);
         if (t == 0 && l.top) atomicMax(&st->max_deg, (unsigned long long)l.top);
     }
@@ -1492,8 +1494,16 @@ struct PairItems {
         i1 = n;
     }
     __device__ int cls(int64_t i) const { return vox_class((int64_t)pstart[i + 1] - pstart[i]); }
-    __device__ void note(int64_t, int, PartLds&) const {}
-    __device__ void flush(const PartLds&, int) const {}
+    unsigned long long* pieces;
+    __device__ void note(int64_t i, int, PartLds& l) const
+    {
+        const int64_t m = (int64_t)pstart[i + 1] - pstart[i];
+        if (m > kSegPiece) atomicAdd(&l.pieces, (uint32_t)seg_pieces(m));
+    }
+    __device__ void flush(const PartLds& l, int t) const
+    {
+        if (t == 0 && l.pieces) atomicAdd(pieces, (unsigned long long)l.pieces);
+    }
     __device__ void put(int64_t at, int64_t i, int) const
     {
         desc[at] = VoxDev{(int64_t)pstart[i], (int32_t)(pstart[i + 1] - pstart[i]), (uint32_t)i};
@@ -1645,6 +1655,48 @@ static hipError_t partition(const F& f, int rounds, int64_t nb, uint32_t* bcnt, 
                        : partition_r<F, 16>(f, nb, bcnt, tot, fo, bpf, nf, s);
 }
 
+// The hub segments hubs[0, n) cut into pieces of kSegPiece edges (one block): the
+// pieces in order, then per hub its range of them (at[np + i]).
+__global__ __launch_bounds__(SC_T) void hub_pieces_k(const VoxDev* __restrict__ hubs, int64_t n, int64_t np,
+                                                     VoxDev* __restrict__ at)
+{
+    int64_t carry = 0;
+    for (int64_t i0 = 0; i0 < n; i0 += SC_T) {
+        const int64_t i = i0 + threadIdx.x;
+        const VoxDev d = hubs[i < n ? i : n - 1];
+        const int64_t k = i < n ? seg_pieces(d.m) : 0;
+        int64_t tot;
+        const int64_t first = carry + block_excl_scan_i64(k, &tot);
+        carry += tot;
+        if (i >= n) continue;
+        at[np + i] = VoxDev{first, (int32_t)k, d.v};
+        for (int64_t p = 0; p < k; ++p) {
+            const int64_t left = d.m - p * kSegPiece;
+            at[first + p] = VoxDev{d.start + p * kSegPiece, (int32_t)(left < kSegPiece ? left : kSegPiece),
+                                   (uint32_t)(first + p)};
+        }
+    }
+}
+
+// class sizes of a partitioned list, and its hubs' pieces
+static hipError_t finish_segments(mrf_ctx* c, SegList& l, const unsigned long long* cnt, int64_t pieces, hipStream_t s)
+{
+    int64_t off = 0;
+    for (int k = 0; k < kVoxClasses; ++k) {
+        l.off[k] = off;
+        off += l.cnt[k] = (int64_t)cnt[k];
+    }
+    const int64_t nh = l.cnt[kVoxClasses - 1];
+    l.n_pieces = pieces;
+    if (nh == 0) return hipSuccess;
+    hipError_t e = ensure(l.hub, sizeof(VoxDev) * (size_t)(pieces + nh));
+    if (e == hipSuccess) e = ensure(c->b_hubsum, sizeof(double) * (size_t)pieces);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(hub_pieces_k, dim3(1), dim3(SC_T), 0, s, (const VoxDev*)l.desc.p + l.off[kVoxClasses - 1], nh,
+                       pieces, (VoxDev*)l.hub.p);
+    return hipGetLastError();
+}
+
 hipError_t build_classes(mrf_ctx* c, hipStream_t s)
 {
     hipError_t e;
@@ -1660,7 +1712,7 @@ hipError_t build_classes(mrf_ctx* c, hipStream_t s)
         return e;
     const int64_t nvox = std::min(c->V, c->E);   // at most this many touched voxels
     if ((e = ensure(c->b_ray_list, sizeof(uint32_t) * (size_t)c->T)) != hipSuccess) return e;
-    if ((e = ensure(c->b_vox_desc, sizeof(VoxDev) * (size_t)nvox)) != hipSuccess) return e;
+    if ((e = ensure(c->vox.desc, sizeof(VoxDev) * (size_t)nvox)) != hipSuccess) return e;
     ListStats* st = (ListStats*)c->b_part.p;
     int64_t* fo = (int64_t*)(st + 1);
     uint32_t* tcnt = (uint32_t*)((char*)c->b_part.p + head);
@@ -1670,7 +1722,7 @@ hipError_t build_classes(mrf_ctx* c, hipStream_t s)
                        c->T, nf, bpf, (uint32_t*)c->b_ray_list.p, st};
     if ((e = partition(ti, tr, tb, tcnt, st->tiles, fo, bpf, nf, s)) != hipSuccess) return e;
     const VoxItems vi{(const int64_t*)c->b_vptr.p, c->Vk, (const SceneDev*)c->b_scenes.p, c->n_scenes,
-                      (VoxDev*)c->b_vox_desc.p, st};
+                      (VoxDev*)c->vox.desc.p, st};
     if ((e = partition(vi, vr, vb, vcnt, st->voxels, nullptr, 1, 0, s)) != hipSuccess) return e;
 
     // one readback: class sizes, statistics, and per-frame offsets of the tile lists (plain schedule)
@@ -1693,12 +1745,7 @@ hipError_t build_classes(mrf_ctx* c, hipStream_t s)
         c->ray_cls_edges[k] = (int64_t)h.tile_edges[k];
         c->ray_cls_rays[k] = (int64_t)h.tile_rays[k];
     }
-    off = 0;
-    for (int k = 0; k < kVoxClasses; ++k) {
-        c->vox_off[k] = off;
-        off += c->vox_cnt[k] = (int64_t)h.voxels[k];
-        c->vox_cls_edges[k] = (int64_t)h.vox_edges[k];
-    }
+    if ((e = finish_segments(c, c->vox, h.voxels, (int64_t)h.pieces, s)) != hipSuccess) return e;
     const int64_t* hfo = (const int64_t*)(hb.data() + sizeof(ListStats));
     c->frame_ray_off.assign(hfo, hfo + (size_t)(nf + 1) * kRayClasses);
     for (int i = 0; i < 16; ++i) c->stats.ray_len_hist[i] = (int64_t)h.ray_hist[i];
@@ -1714,21 +1761,17 @@ static hipError_t partition_pairs(mrf_ctx* c, const uint32_t* pstart, int64_t P,
     hipError_t e;
     const int rounds = part_rounds(P);
     const int64_t nb = cdiv(P, 256 * rounds);
-    const size_t head = sizeof(unsigned long long) * kPartMaxClasses;
+    const size_t head = sizeof(unsigned long long) * (kPartMaxClasses + 1);   // class sizes, hub pieces
     if ((e = ensure(c->b_part, head + sizeof(uint32_t) * (size_t)(PairItems::NC * nb))) != hipSuccess) return e;
     unsigned long long* tot = (unsigned long long*)c->b_part.p;
-    e = partition(PairItems{pstart, P, (VoxDev*)c->b_pair_desc.p}, rounds, nb, (uint32_t*)((char*)c->b_part.p + head), tot,
-                  nullptr, 1, 0, s);
-    unsigned long long h[kPartMaxClasses];
+    if ((e = launch_fill_u32((uint32_t*)tot, 0u, (int64_t)(head / 4), s)) != hipSuccess) return e;
+    e = partition(PairItems{pstart, P, (VoxDev*)c->pair.desc.p, tot + kPartMaxClasses}, rounds, nb,
+                  (uint32_t*)((char*)c->b_part.p + head), tot, nullptr, 1, 0, s);
+    unsigned long long h[kPartMaxClasses + 1];
     if (e == hipSuccess) e = hipMemcpyAsync(h, tot, head, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return e;
-    int64_t off = 0;
-    for (int k = 0; k < kVoxClasses; ++k) {
-        c->pair_off[k] = off;
-        off += c->pair_cnt[k] = (int64_t)h[k];
-    }
-    return hipSuccess;
+    return finish_segments(c, c->pair, h, (int64_t)h[kPartMaxClasses], s);
 }
 
 // ============================================================== adding keyframes
@@ -1963,16 +2006,16 @@ hipError_t build_keyframe_pairs(mrf_ctx* c, hipStream_t s)
                        (uint32_t*)c->b_pair_x.p);
 
     // pairs by edge count, as VoxDev work items of the voxel-phase kernels
-    if ((e = ensure(c->b_pair_desc, (size_t)(P > 0 ? P : 1) * sizeof(VoxDev))) != hipSuccess) return e;
+    if ((e = ensure(c->pair.desc, (size_t)(P > 0 ? P : 1) * sizeof(VoxDev))) != hipSuccess) return e;
     if ((e = partition_pairs(c, pstart, P, s)) != hipSuccess) return e;
 
     // touched voxels with their pair ranges, in the voxel lists' order
     int64_t nv = 0;
-    for (int k = 0; k < kVoxClasses; ++k) nv += c->vox_cnt[k];
+    for (int k = 0; k < kVoxClasses; ++k) nv += c->vox.cnt[k];
     c->n_kf_vox = nv;
     if ((e = ensure(c->b_kf_vox, (size_t)(nv > 0 ? nv : 1) * sizeof(VoxDev))) != hipSuccess) return e;
     if (nv > 0)
-        hipLaunchKernelGGL(kf_vox_k, dim3((unsigned)cdiv(nv, 256)), dim3(256), 0, s, (const VoxDev*)c->b_vox_desc.p,
+        hipLaunchKernelGGL(kf_vox_k, dim3((unsigned)cdiv(nv, 256)), dim3(256), 0, s, (const VoxDev*)c->vox.desc.p,
                            nv, (const uint32_t*)pos, (VoxDev*)c->b_kf_vox.p);
 
     // weights: chord length over the pair's summed chord length, in list order;

@@ -83,44 +83,16 @@ static_assert(ray_shapes_valid(), "ray shapes: 16, 32 or 64 lanes dividing the c
 constexpr int kTileW = 4;
 constexpr int kTile = kTileW * kTileW;
 
-// Voxel work classes by degree: (waves per voxel NW, items per lane IPL =
-// capacity / (64 NW), voxels per wave VPW); each wave owns 64*IPL consecutive
-// edges of a voxel, and a one-wave class (NW = 1) walks VPW voxels per wave
-// (a packed class, NW = 0: VPW voxels per lane group) with every load issued
-// first.  Above the last class a 1024-thread block walks the voxel in
-// 1024-edge pieces.
-#ifndef MRF_VOX_CAPS
-#define MRF_VOX_CAPS 16, 32, 64, 128, 256, 1024, 4096, 16384, 32768
-#define MRF_VOX_NW 0, 0, 1, 1, 1, 1, 4, 16, 16
-#define MRF_VOX_VPW 4, 4, 8, 4, 4, 1, 1, 1, 1
-#endif
-// Degree capacity of each single-pass class and its waves per voxel; NW = 0
-// packs 64 / cap voxels into a wave (cap = 16 or 32 lanes per voxel, one edge
-// per lane).
-constexpr int kVoxCap[] = {MRF_VOX_CAPS};
-constexpr int kVoxNW[] = {MRF_VOX_NW};
-constexpr int kVoxVPW[] = {MRF_VOX_VPW};
-constexpr int kVoxClasses = (int)(sizeof(kVoxCap) / sizeof(int)) + 1;   // + the chunked class
-static_assert(sizeof(kVoxNW) == sizeof(kVoxCap) && sizeof(kVoxVPW) == sizeof(kVoxCap),
-              "one wave count and one voxels-per-wave count per voxel class");
-constexpr bool vox_classes_valid()
-{
-    for (int k = 0; k + 1 < kVoxClasses; ++k) {
-        if (kVoxNW[k] == 0) {
-            if (kVoxCap[k] != 16 && kVoxCap[k] != 32) return false;
-        } else if (kVoxCap[k] % (64 * kVoxNW[k]) != 0 || kVoxCap[k] / (64 * kVoxNW[k]) > 32 || kVoxNW[k] > 16) {
-            return false;
-        }
-        if (kVoxVPW[k] < 1 || kVoxVPW[k] > 32 || (kVoxNW[k] > 1 && kVoxVPW[k] != 1)) return false;
-        if (kVoxNW[k] == 1 && kVoxVPW[k] * (kVoxCap[k] / 64) > 32) return false;
-        if (k > 0 && kVoxCap[k] <= kVoxCap[k - 1]) return false;
-    }
-    return true;
-}
-static_assert(vox_classes_valid(), "voxel classes: increasing capacities; 16 or 32 lanes per packed voxel, or "
-                                   "64 NW IPL edges with IPL <= 32, NW <= 16; several voxels per wave or "
-                                   "group only with NW <= 1, at most 32 items per lane in all");
-constexpr int kVoxChunk = 1024;   // piece of a hub voxel (16 items per lane)
+// Work classes of the voxel phase by degree (seg_sum_k): capacities, and the
+// segments that a lane group (capacities 16 and 32) or a wave walks with every
+// load issued first.  Above the last capacity a segment is cut into pieces of
+// kSegPiece edges.
+constexpr int kVoxCap[] = {16, 32, 64, 128, 256, 1024, 4096};
+constexpr int kVoxVPW[] = {4, 4, 8, 4, 4, 1, 1};
+constexpr int kVoxClasses = (int)(sizeof(kVoxCap) / sizeof(int)) + 1;   // + the hubs
+constexpr int kSegPiece = 4096;
+static_assert(kVoxClasses == 8 && kVoxCap[0] == 16 && kVoxCap[1] == 32 && kVoxCap[6] == kSegPiece,
+              "seg_sum_k names its classes");
 
 // Voxels are keyed brick-major (8^3 bricks) for the voxel -> ray incidence so
 // that one brick's voxels, which share most of their rays, are adjacent.
@@ -210,12 +182,26 @@ struct VoxOut {
     double* dsum = nullptr;   // dsum[v] = sum_v (FP64)
 };
 
+struct DevBuf {
+    void* p = nullptr;
+    size_t cap = 0;
+};
+
 // Work item of the voxel kernels: one voxel's edge list vedge[start, start + m)
 // and its linear id.
 struct VoxDev {
     int64_t start;
     int32_t m;
     uint32_t v;
+};
+
+// Segments of the voxel -> ray list by class (class-major in desc); hub: the pieces of
+// the last class's segments (VoxDev, v the piece's number), then its segments again as
+// VoxDev over their pieces.
+struct SegList {
+    DevBuf desc, hub;
+    int64_t off[kVoxClasses] = {0}, cnt[kVoxClasses] = {0};
+    int64_t n_pieces = 0;
 };
 
 struct BuildDev {
@@ -226,10 +212,6 @@ struct BuildDev {
     int32_t skip;              // sparse grid: step over unallocated bricks brick by brick
 };
 
-struct DevBuf {
-    void* p = nullptr;
-    size_t cap = 0;
-};
 
 // Edge slots in groups of whole scenes with fewer than 2^32 slots each (one group
 // unless the batch has 2^32 slots or more): a voxel's list entry holds its slot
@@ -265,8 +247,8 @@ __host__ __device__ __forceinline__ int64_t group_slot_base_of_slot(const SlotGr
 
 // Kernel launches that the profiler can time individually.
 enum KernelId {
-    KID_VOX0 = 0,
-    KID_RAY0 = KID_VOX0 + kVoxClasses, KID_ADJ0 = KID_RAY0 + kRayClasses,
+    KID_VOX = 0,
+    KID_RAY0, KID_ADJ0 = KID_RAY0 + kRayClasses,
     KID_POT = KID_ADJ0 + kRayClasses, KID_SIGMA, KID_PAIR, KID_KFVOX, KID_COUNT
 };
 
@@ -344,16 +326,14 @@ struct mrf_ctx {
     mrf::DevBuf b_kfws;           // reverse pass: per edge slot, the edge's share of its pair's weight
     int kfws_ready = 0;           // b_kfws holds the current build's weights
     mrf::DevBuf b_kf_vox;         // per touched voxel: VoxDev over its pairs (start, count, voxel id)
-    mrf::DevBuf b_pair_desc;      // pairs by edge-count class: VoxDev (start, m, pair id), class-major
-    int64_t pair_off[mrf::kVoxClasses] = {0}, pair_cnt[mrf::kVoxClasses] = {0};
+    mrf::SegList pair;            // pairs by edge count: VoxDev (start, m, pair id)
     int64_t n_kf_vox = 0;
     mrf::DevBuf b_ray_list;       // tile ids by tile length class, class-major
-    mrf::DevBuf b_vox_desc;       // touched voxels by degree class: VoxDev, class-major, brick-major keys inside
+    mrf::SegList vox;             // touched voxels by degree: VoxDev, brick-major keys inside a class
+    mrf::DevBuf b_hubsum;         // sums of the hub pieces (FP64)
 
     int64_t ray_off[mrf::kRayClasses] = {0}, ray_cnt[mrf::kRayClasses] = {0};   // tiles of a class: list range
-    int64_t vox_off[mrf::kVoxClasses] = {0}, vox_cnt[mrf::kVoxClasses] = {0};
     int64_t ray_cls_edges[mrf::kRayClasses] = {0};
-    int64_t vox_cls_edges[mrf::kVoxClasses] = {0};
     std::vector<int64_t> frame_ray_off;   // plain schedule: tiles of frame f at [off[f], off[f+1])
     int64_t ray_cls_rays[mrf::kRayClasses] = {0};
 

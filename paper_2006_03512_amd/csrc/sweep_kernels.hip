@@ -253,45 +253,6 @@ hipError_t launch_potentials(mrf_ctx* c, hipStream_t s)
 // pair and the edge's own term by the ray kernels as they stage their tiles
 // (no per-edge scatter here).
 
-// FP64 sum over items base + 64 k + l (k < N, l the lane) of the edge list
-// [s, s+m) of one voxel (0 past m).  Branchless, with item indices clamped to
-// m - 1 (m >= 1), so that every load is issued before the first wait.
-// An item's term: in[vedge[j]], times the list-order weight w[j] when the
-// sum is weighted (per-keyframe averages); the product of two FP32 values is
-// exact in FP64.
-template <bool WT>
-__device__ __forceinline__ double vox_term(float x, const float* __restrict__ w, int64_t j)
-{
-    if constexpr (WT)
-        return (double)x * (double)w[j];
-    else
-        return (double)x;
-}
-
-template <int N, bool WT = false>
-__device__ __forceinline__ double vox_lane_sum(int64_t s, int m, int base, const uint32_t* __restrict__ vedge,
-                                               const float* __restrict__ in, const float* __restrict__ w = nullptr)
-{
-    const int l = threadIdx.x & 63;
-    uint32_t e[N];
-    float x[N], wt[N];
-#pragma unroll
-    for (int k = 0; k < N; ++k) e[k] = vedge[s + min(base + k * 64 + l, m - 1)];
-    if constexpr (WT) {
-#pragma unroll
-        for (int k = 0; k < N; ++k) wt[k] = w[s + min(base + k * 64 + l, m - 1)];
-    }
-#pragma unroll
-    for (int k = 0; k < N; ++k) x[k] = in[e[k]];
-    double a = 0.0;
-#pragma unroll
-    for (int k = 0; k < N; ++k) {
-        const double t = WT ? (double)x[k] * (double)wt[k] : (double)x[k];
-        a += base + k * 64 + l < m ? t : 0.0;
-    }
-    return a;
-}
-
 __device__ __forceinline__ void vox_store(uint32_t v, double sum, const VoxOut& o)
 {
     const double t = (o.base ? (double)o.base[v] : 0.0) + sum;
@@ -301,111 +262,31 @@ __device__ __forceinline__ void vox_store(uint32_t v, double sum, const VoxOut& 
     if (o.dsum) o.dsum[v] = sum;
 }
 
-// One voxel's edge list [s, s+m) summed by NW waves, each owning 64*IPL
-// consecutive edges (striped over its lanes); the wave sums meet in LDS and
-// are added in wave order.  NW == 1: four waves per 256-thread block, each
-// summing VPW consecutive voxels of the list with all their loads issued
-// before the first wait (more bytes in flight per wave for low degrees).
-// Voxels arrive in brick-major order and blocks are remapped so each XCD
-// takes a contiguous range of them.
-template <int NW, int IPL, int VPW, bool WT = false, bool MG = false>
-__global__ __launch_bounds__(NW == 1 ? 256 : 64 * NW) void voxel_k(const VoxDev* __restrict__ vd, int64_t n,
-                                                                   const uint32_t* __restrict__ vedge,
-                                                                   const float* __restrict__ in, VoxOut out,
-                                                                   const float* __restrict__ w,
-                                                                   const SlotGroups sg)
-{
-    static_assert(NW == 1 || VPW == 1, "several voxels per wave only with one wave per voxel");
-    // the wave index is uniform across the wave: said so, the voxel descriptors
-    // below become scalar loads and their address and group arithmetic scalar
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
-    const int64_t lb = xcd_block(blockIdx.x, gridDim.x);
-    if constexpr (NW == 1) {
-        const int64_t v0 = (lb * 4 + wv) * VPW;
-        if (v0 >= n) return;   // whole wave
-        VoxDev d[VPW];
-#pragma unroll
-        for (int u = 0; u < VPW; ++u) d[u] = vd[min(v0 + u, n - 1)];   // past the list: a repeat, not stored
-        uint32_t e[VPW][IPL];
-        float x[VPW][IPL], wt[VPW][IPL];
-#pragma unroll
-        for (int u = 0; u < VPW; ++u)
-#pragma unroll
-            for (int k = 0; k < IPL; ++k) e[u][k] = vedge[d[u].start + min(k * 64 + l, d[u].m - 1)];
-        if constexpr (WT) {
-#pragma unroll
-            for (int u = 0; u < VPW; ++u)
-#pragma unroll
-                for (int k = 0; k < IPL; ++k) wt[u][k] = w[d[u].start + min(k * 64 + l, d[u].m - 1)];
-        }
-#pragma unroll
-        for (int u = 0; u < VPW; ++u) {
-            const float* ing = in + (MG ? group_slot_base(sg, d[u].start) : 0);
-#pragma unroll
-            for (int k = 0; k < IPL; ++k) x[u][k] = ing[e[u][k]];
-        }
-        double a[VPW];
-#pragma unroll
-        for (int u = 0; u < VPW; ++u) {
-            a[u] = 0.0;
-#pragma unroll
-            for (int k = 0; k < IPL; ++k) {
-                const double t = WT ? (double)x[u][k] * (double)wt[u][k] : (double)x[u][k];
-                a[u] += k * 64 + l < d[u].m ? t : 0.0;
-            }
-        }
-        if constexpr (VPW == 1) {
-            const double t = dgroup_sum_d<64>(a[0]);
-            if (l == 0) vox_store(d[0].v, t, out);
-        } else {
-            // the wave's VPW x 64 lane sums transposed through LDS: voxel u
-            // goes to the LG = 64 / VPW lanes [u LG, (u + 1) LG), lane p of
-            // them adding the sums of lanes [p VPW, (p + 1) VPW) in order, then
-            // a group sum over the LG lanes (one reduction for all voxels)
-            constexpr int LG = 64 / VPW;
-            static_assert(LG == 8 || LG == 16, "four or eight voxels per wave");
-            __shared__ double red[4][VPW][64];
-#pragma unroll
-            for (int u = 0; u < VPW; ++u) red[wv][u][l] = a[u];
-            // LDS accesses of one wave complete in order: the fences only keep
-            // the compiler from moving the reads above the writes
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            const int u = l / LG, p = l % LG;
-            double t = 0.0;
-#pragma unroll
-            for (int j = 0; j < VPW; ++j) t += red[wv][u][p * VPW + j];
-            t = dgroup_sum_d<LG>(t);   // at the group's first lane
-            if (p == 0 && v0 + u < n) vox_store(vd[v0 + u].v, t, out);
-        }
-    } else {
-        const int64_t vi = lb;
-        if (vi >= n) return;   // whole block
-        const VoxDev d = vd[vi];
-        const double a = dgroup_sum_d<64>(
-            vox_lane_sum<IPL, WT>(d.start, d.m, wv * 64 * IPL, vedge, in + (MG ? group_slot_base(sg, d.start) : 0), w));
-        __shared__ double wsum[NW];
-        if (l == 0) wsum[wv] = a;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            double tot = 0.0;
-            for (int q = 0; q < NW; ++q) tot += wsum[q];
-            vox_store(d.v, tot, out);
-        }
-    }
-}
+// How a segment (a voxel's edge list, or a keyframe pair's) is summed, by class:
+//   0, 1  at most G = 16 or 32 edges: 64 / G lane groups per wave, each walking
+//         kVoxVPW consecutive segments (lane l holds edge l of each);
+//   2..5  at most 64, 128, 256, 1024 edges: one wave walks kVoxVPW consecutive
+//         segments, 64 edges a round;
+//   6     at most 4096: the four waves of a block, 1024 edges each;
+//   7     more: pieces of 4096 edges (b_*_hub), each summed as a class-6 segment
+//         into psum, then added in order by hub_sum_k.
+// Every class issues all its loads before the first wait (indices clamped inside
+// the list): the phase waits on its gathers, so bytes in flight count.  Segments
+// come in brick-major order and each XCD takes a contiguous range of a class's
+// blocks.  All classes run in one launch, the longest first: with a launch each, a
+// 640x480 frame's sweep spent 144 us in ten kernels that each drained before the
+// next, 63 of them in one 1024-thread block walking the camera's voxel (3e5 edges);
+// one launch with the hubs in pieces takes 47 us, and at 5e8 edges 1.13 ms (3.6 TB/s of
+// list and messages) instead of 1.19.  Eight waves per SIMD are asked for where the
+// registers allow it without spills: with the 82 registers that the compiler takes by
+// itself the unweighted kernel runs 1.27 ms.
 
-// Voxels of at most G edges (G = 16 or 32): 64 / G lane groups per wave, 256
-// / G per block, each group summing VPG consecutive voxels of the list (lane
-// l holds edge l of each; group reductions), every load issued first.
-template <int G, int VPG, bool WT = false, bool MG = false>
-__global__ __launch_bounds__(256) void voxel_small_k(const VoxDev* __restrict__ vd, int64_t n,
-                                                     const uint32_t* __restrict__ vedge, const float* __restrict__ in,
-                                                     VoxOut out, const float* __restrict__ w, const SlotGroups sg)
+template <int G, int VPG, bool WT, bool MG>
+__device__ __forceinline__ void seg_group(int64_t lb, const VoxDev* __restrict__ vd, int64_t n,
+                                          const uint32_t* __restrict__ vedge, const float* __restrict__ in,
+                                          const VoxOut& out, const float* __restrict__ w, const SlotGroups& sg)
 {
     constexpr int GPB = 256 / G;   // groups per block
-    const int64_t lb = xcd_block(blockIdx.x, gridDim.x);
     if (lb * GPB * VPG >= n) return;   // whole block
     const int64_t v0 = (lb * GPB + (int)threadIdx.x / G) * VPG;
     const int l = (int)threadIdx.x % G;
@@ -430,107 +311,212 @@ __global__ __launch_bounds__(256) void voxel_small_k(const VoxDev* __restrict__ 
     }
 }
 
-// One 1024-thread block per voxel of degree above the largest single-pass
-// class: wave w sums pieces w, w + 16, ... of 1024 edges in order, and the 16
-// wave sums are added in wave order.
-template <bool WT = false, bool MG = false>
-__global__ __launch_bounds__(1024) void voxel_chunked_k(const VoxDev* __restrict__ vd, int64_t n,
-                                                        const uint32_t* __restrict__ vedge,
-                                                        const float* __restrict__ in, VoxOut out,
-                                                        const float* __restrict__ w, const SlotGroups sg)
+constexpr int kSegRed = 8 * 64;   // doubles of LDS per wave
+
+template <int IPL, int VPW, bool WT, bool MG>
+__device__ __forceinline__ void seg_wave(int64_t lb, const VoxDev* __restrict__ vd, int64_t n,
+                                         const uint32_t* __restrict__ vedge, const float* __restrict__ in,
+                                         const VoxOut& out, const float* __restrict__ w, const SlotGroups& sg,
+                                         double* red)
 {
-    __shared__ double wsum[16];
-    const int64_t b = xcd_block(blockIdx.x, gridDim.x);
-    if (b >= n) return;
-    const int wv = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const VoxDev d = vd[b];
-    const int nch = (d.m + kVoxChunk - 1) / kVoxChunk;
+    // the wave index is uniform across the wave: said so, the descriptors below
+    // become scalar loads and their address and group arithmetic scalar
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+    const int64_t v0 = (lb * 4 + wv) * VPW;
+    if (v0 >= n) return;   // whole wave
+    VoxDev d[VPW];
+#pragma unroll
+    for (int u = 0; u < VPW; ++u) d[u] = vd[min(v0 + u, n - 1)];   // past the list: a repeat, not stored
+    uint32_t e[VPW][IPL];
+    float x[VPW][IPL], wt[VPW][IPL];
+#pragma unroll
+    for (int u = 0; u < VPW; ++u)
+#pragma unroll
+        for (int k = 0; k < IPL; ++k) e[u][k] = vedge[d[u].start + min(k * 64 + l, d[u].m - 1)];
+    if constexpr (WT) {
+#pragma unroll
+        for (int u = 0; u < VPW; ++u)
+#pragma unroll
+            for (int k = 0; k < IPL; ++k) wt[u][k] = w[d[u].start + min(k * 64 + l, d[u].m - 1)];
+    }
+#pragma unroll
+    for (int u = 0; u < VPW; ++u) {
+        const float* ing = in + (MG ? group_slot_base(sg, d[u].start) : 0);
+#pragma unroll
+        for (int k = 0; k < IPL; ++k) x[u][k] = ing[e[u][k]];
+    }
+    double a[VPW];
+#pragma unroll
+    for (int u = 0; u < VPW; ++u) {
+        a[u] = 0.0;
+#pragma unroll
+        for (int k = 0; k < IPL; ++k) {
+            const double t = WT ? (double)x[u][k] * (double)wt[u][k] : (double)x[u][k];
+            a[u] += k * 64 + l < d[u].m ? t : 0.0;
+        }
+    }
+    if constexpr (VPW == 1) {
+        const double t = dgroup_sum_d<64>(a[0]);
+        if (l == 0) vox_store(d[0].v, t, out);
+    } else {
+        // the wave's VPW x 64 lane sums transposed through LDS: segment u goes to
+        // the LG = 64 / VPW lanes [u LG, (u + 1) LG), lane p of them adding the
+        // sums of lanes [p VPW, (p + 1) VPW) in order, then a group sum over the LG
+        // lanes (one reduction for all segments)
+        constexpr int LG = 64 / VPW;
+        static_assert((LG == 8 || LG == 16) && VPW * 64 <= kSegRed, "four or eight segments per wave");
+        double* r = red + wv * kSegRed;
+#pragma unroll
+        for (int u = 0; u < VPW; ++u) r[u * 64 + l] = a[u];
+        // LDS accesses of one wave complete in order: the fences only keep the
+        // compiler from moving the reads above the writes
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const int u = l / LG, p = l % LG;
+        double t = 0.0;
+#pragma unroll
+        for (int j = 0; j < VPW; ++j) t += r[u * 64 + p * VPW + j];
+        t = dgroup_sum_d<LG>(t);   // at the group's first lane
+        if (p == 0 && v0 + u < n) vox_store(vd[v0 + u].v, t, out);
+    }
+}
+
+// one segment of at most 4096 edges by the block's four waves
+template <bool WT, bool MG>
+__device__ __forceinline__ void seg_block(int64_t lb, const VoxDev* __restrict__ vd, int64_t n,
+                                          const uint32_t* __restrict__ vedge, const float* __restrict__ in,
+                                          const VoxOut& out, const float* __restrict__ w, const SlotGroups& sg,
+                                          double* red)
+{
+    constexpr int IPL = kSegPiece / 256;
+    if (lb >= n) return;   // whole block
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+    const VoxDev d = vd[lb];
     const float* ing = in + (MG ? group_slot_base(sg, d.start) : 0);
+    const int base = wv * 64 * IPL;
+    uint32_t e[IPL];
+    float x[IPL], wt[IPL];
+#pragma unroll
+    for (int k = 0; k < IPL; ++k) e[k] = vedge[d.start + min(base + k * 64 + l, d.m - 1)];
+    if constexpr (WT) {
+#pragma unroll
+        for (int k = 0; k < IPL; ++k) wt[k] = w[d.start + min(base + k * 64 + l, d.m - 1)];
+    }
+#pragma unroll
+    for (int k = 0; k < IPL; ++k) x[k] = ing[e[k]];
     double a = 0.0;
-    for (int c = wv; c < nch; c += 16)
-        a += vox_lane_sum<kVoxChunk / 64, WT>(d.start, d.m, c * kVoxChunk, vedge, ing, w);
+#pragma unroll
+    for (int k = 0; k < IPL; ++k) {
+        const double t = WT ? (double)x[k] * (double)wt[k] : (double)x[k];
+        a += base + k * 64 + l < d.m ? t : 0.0;
+    }
     a = dgroup_sum_d<64>(a);
-    if (l == 0) wsum[wv] = a;
+    if (l == 0) red[wv] = a;
     __syncthreads();
     if (threadIdx.x == 0) {
         double tot = 0.0;
-        for (int q = 0; q < 16; ++q) tot += wsum[q];
+        for (int q = 0; q < 4; ++q) tot += red[q];
         vox_store(d.v, tot, out);
     }
 }
 
-// Class K of a segment list (voxels, or keyframe pairs with weights w) with n
-// work items described by desc.  MG: several slot groups (each voxel's list
-// entries are relative to its group's first slot); a single group, the common
-// case, skips the group lookup.
-template <int K, bool WT, bool MG>
-static void launch_seg_class_t(const VoxDev* desc, int64_t n, const uint32_t* vedge, const SlotGroups& sg,
-                               const float* in, VoxOut out, const float* w, hipStream_t s)
+// Work of one launch: class k's segments are desc[off[k], off[k] + cnt[k]) (class 7:
+// the hub pieces), its blocks [blk[k], blk[k + 1]) counted from class 7 downwards;
+// every blk is a multiple of 8, so a block's XCD is that of its place in the class.
+struct SegWork {
+    const VoxDev* desc;
+    const VoxDev* pieces;
+    double* psum;
+    int64_t off[kVoxClasses], cnt[kVoxClasses];
+    uint32_t blk[kVoxClasses + 1];
+};
+
+template <bool WT, bool MG>
+__global__ __launch_bounds__(256, WT ? (MG ? 5 : 6) : 8) void seg_sum_k(const SegWork s, const uint32_t* __restrict__ vedge,
+                                                 const float* __restrict__ in, VoxOut out,
+                                                 const float* __restrict__ w, const SlotGroups sg)
 {
-    constexpr int NW = kVoxNW[K];
-    if constexpr (NW == 0) {
-        constexpr int G = kVoxCap[K];
-        constexpr int VPG = kVoxVPW[K];
-        hipLaunchKernelGGL((voxel_small_k<G, VPG, WT, MG>), dim3(nblk(n, 256 / G * VPG)), dim3(256), 0, s, desc, n,
-                           vedge, in, out, w, sg);
-    } else {
-        constexpr int IPL = kVoxCap[K] / (64 * NW);
-        constexpr int VPW = kVoxVPW[K];
-        const unsigned blocks = NW == 1 ? nblk(n, 4 * VPW) : (unsigned)n;
-        hipLaunchKernelGGL((voxel_k<NW, IPL, VPW, WT, MG>), dim3(blocks), dim3(NW == 1 ? 256 : 64 * NW), 0, s, desc,
-                           n, vedge, in, out, w, sg);
+    __shared__ double red[4 * kSegRed];
+    int k = kVoxClasses - 1;   // uniform: the class whose blocks hold this one
+    while (k > 0 && blockIdx.x >= s.blk[kVoxClasses - k]) --k;
+    const uint32_t b0 = s.blk[kVoxClasses - 1 - k], nb = s.blk[kVoxClasses - k] - b0;
+    const int64_t lb = xcd_block(blockIdx.x - b0, nb);
+    const VoxDev* d = s.desc + s.off[k];
+    const int64_t n = s.cnt[k];
+    switch (k) {
+        case 0: seg_group<kVoxCap[0], kVoxVPW[0], WT, MG>(lb, d, n, vedge, in, out, w, sg); break;
+        case 1: seg_group<kVoxCap[1], kVoxVPW[1], WT, MG>(lb, d, n, vedge, in, out, w, sg); break;
+        case 2: seg_wave<kVoxCap[2] / 64, kVoxVPW[2], WT, MG>(lb, d, n, vedge, in, out, w, sg, red); break;
+        case 3: seg_wave<kVoxCap[3] / 64, kVoxVPW[3], WT, MG>(lb, d, n, vedge, in, out, w, sg, red); break;
+        case 4: seg_wave<kVoxCap[4] / 64, kVoxVPW[4], WT, MG>(lb, d, n, vedge, in, out, w, sg, red); break;
+        case 5: seg_wave<kVoxCap[5] / 64, kVoxVPW[5], WT, MG>(lb, d, n, vedge, in, out, w, sg, red); break;
+        case 6: seg_block<WT, MG>(lb, d, n, vedge, in, out, w, sg, red); break;
+        default: {
+            const VoxOut po{nullptr, nullptr, nullptr, nullptr, s.psum};
+            seg_block<WT, MG>(lb, s.pieces, n, vedge, in, po, w, sg, red);
+        }
     }
 }
 
-template <int K, bool WT>
-static void launch_seg_class(const VoxDev* desc, int64_t n, const uint32_t* vedge, const SlotGroups& sg,
-                             const float* in, VoxOut out, const float* w, hipStream_t s)
+// the hubs' sums from their pieces' (one wave a hub: lane l adds pieces l, l + 64, ...
+// in order, then the lanes)
+__global__ __launch_bounds__(256) void hub_sum_k(const VoxDev* __restrict__ hubs, int64_t n,
+                                                 const double* __restrict__ psum, VoxOut out)
 {
-    if (n <= 0) return;
-    if (sg.n > 1)
-        launch_seg_class_t<K, WT, true>(desc, n, vedge, sg, in, out, w, s);
+    const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (i >= n) return;   // whole wave
+    const int l = threadIdx.x & 63;
+    const VoxDev d = hubs[i];
+    double a = 0.0;
+    for (int p = l; p < d.m; p += 64) a += psum[d.start + p];
+    a = dgroup_sum_d<64>(a);
+    if (l == 0) vox_store(d.v, a, out);
+}
+
+// segments per block of class k
+static int64_t seg_per_block(int k)
+{
+    if (k >= kVoxClasses - 2) return 1;
+    return kVoxCap[k] <= 32 ? (int64_t)(256 / kVoxCap[k]) * kVoxVPW[k] : 4 * kVoxVPW[k];
+}
+
+static hipError_t seg_sum(mrf_ctx* c, const SegList& l, const float* in, const VoxOut& out, const float* w,
+                          hipStream_t s)
+{
+    SegWork k{};
+    k.desc = (const VoxDev*)l.desc.p;
+    k.pieces = (const VoxDev*)l.hub.p;
+    k.psum = (double*)c->b_hubsum.p;
+    int64_t blocks = 0;
+    for (int q = kVoxClasses - 1; q >= 0; --q) {
+        k.off[q] = l.off[q];
+        k.cnt[q] = q == kVoxClasses - 1 ? l.n_pieces : l.cnt[q];
+        blocks += (nblk(k.cnt[q], (int)seg_per_block(q)) + 7) / 8 * 8;
+        k.blk[kVoxClasses - q] = (uint32_t)blocks;
+    }
+    if (blocks == 0) return hipSuccess;
+    const dim3 g((unsigned)blocks), b(256);
+    const uint32_t* ve = (const uint32_t*)c->b_vedge.p;
+    if (w && c->sg.n > 1)
+        hipLaunchKernelGGL((seg_sum_k<true, true>), g, b, 0, s, k, ve, in, out, w, c->sg);
+    else if (w)
+        hipLaunchKernelGGL((seg_sum_k<true, false>), g, b, 0, s, k, ve, in, out, w, c->sg);
+    else if (c->sg.n > 1)
+        hipLaunchKernelGGL((seg_sum_k<false, true>), g, b, 0, s, k, ve, in, out, w, c->sg);
     else
-        launch_seg_class_t<K, WT, false>(desc, n, vedge, sg, in, out, w, s);
-}
-
-template <bool WT>
-static void launch_seg_chunked(const VoxDev* desc, int64_t n, const uint32_t* vedge, const SlotGroups& sg,
-                               const float* in, VoxOut out, const float* w, hipStream_t s)
-{
-    if (n <= 0) return;
-    if (sg.n > 1)
-        hipLaunchKernelGGL((voxel_chunked_k<WT, true>), dim3((unsigned)n), dim3(1024), 0, s, desc, n, vedge, in, out,
-                           w, sg);
-    else
-        hipLaunchKernelGGL((voxel_chunked_k<WT, false>), dim3((unsigned)n), dim3(1024), 0, s, desc, n, vedge, in,
-                           out, w, sg);
-}
-
-template <int K>
-static void launch_voxel_class(mrf_ctx* c, const float* in, VoxOut out, hipStream_t s)
-{
-    if (c->vox_cnt[K] <= 0) return;
-    ProfScope ps(c, KID_VOX0 + K, s);
-    launch_seg_class<K, false>((const VoxDev*)c->b_vox_desc.p + c->vox_off[K], c->vox_cnt[K], (const uint32_t*)c->b_vedge.p,
-                               c->sg, in, out, nullptr, s);
-}
-
-template <int... K>
-static void voxel_classes(std::integer_sequence<int, K...>, mrf_ctx* c, const float* in, VoxOut out, hipStream_t s)
-{
-    (launch_voxel_class<K>(c, in, out, s), ...);
+        hipLaunchKernelGGL((seg_sum_k<false, false>), g, b, 0, s, k, ve, in, out, w, c->sg);
+    const int64_t nh = l.cnt[kVoxClasses - 1];
+    if (nh > 0)
+        hipLaunchKernelGGL(hub_sum_k, dim3(nblk(nh, 4)), b, 0, s, (const VoxDev*)l.hub.p + l.n_pieces, nh,
+                           (const double*)c->b_hubsum.p, out);
+    return hipGetLastError();
 }
 
 hipError_t launch_voxel_phase(mrf_ctx* c, const float* in, VoxOut out, hipStream_t s)
 {
-    voxel_classes(std::make_integer_sequence<int, kVoxClasses - 1>{}, c, in, out, s);
-    const int kc = kVoxClasses - 1;
-    if (c->vox_cnt[kc] > 0) {
-        ProfScope ps(c, KID_VOX0 + kc, s);
-        launch_seg_chunked<false>((const VoxDev*)c->b_vox_desc.p + c->vox_off[kc], c->vox_cnt[kc], (const uint32_t*)c->b_vedge.p,
-                                  c->sg, in, out, nullptr, s);
-    }
-    return hipGetLastError();
+    ProfScope ps(c, KID_VOX, s);
+    return seg_sum(c, c->vox, in, out, nullptr, s);
 }
 
 // ------------------------------------------------------------ keyframe pairs
@@ -542,29 +528,10 @@ hipError_t launch_voxel_phase(mrf_ctx* c, const float* in, VoxOut out, hipStream
 // every M (FP64, fixed order); the voxel step sums them per voxel and writes,
 // per pair, x = fl(T - M_fv) into keyframe f's message buffer.
 
-template <int... K>
-static void pair_classes(std::integer_sequence<int, K...>, mrf_ctx* c, const float* in, VoxOut out,
-                         const float* w, hipStream_t s)
-{
-    ((w ? launch_seg_class<K, true>((const VoxDev*)c->b_pair_desc.p + c->pair_off[K], c->pair_cnt[K],
-                                    (const uint32_t*)c->b_vedge.p, c->sg, in, out, w, s)
-        : launch_seg_class<K, false>((const VoxDev*)c->b_pair_desc.p + c->pair_off[K], c->pair_cnt[K],
-                                     (const uint32_t*)c->b_vedge.p, c->sg, in, out, nullptr, s)),
-     ...);
-}
-
 hipError_t launch_pair_phase(mrf_ctx* c, const float* in, const float* w, double* M, hipStream_t s)
 {
-    VoxOut out{nullptr, nullptr, nullptr, nullptr, M};
     ProfScope ps(c, KID_PAIR, s);
-    pair_classes(std::make_integer_sequence<int, kVoxClasses - 1>{}, c, in, out, w, s);
-    const int kc = kVoxClasses - 1;
-    const VoxDev* d = (const VoxDev*)c->b_pair_desc.p + c->pair_off[kc];
-    if (w)
-        launch_seg_chunked<true>(d, c->pair_cnt[kc], (const uint32_t*)c->b_vedge.p, c->sg, in, out, w, s);
-    else
-        launch_seg_chunked<false>(d, c->pair_cnt[kc], (const uint32_t*)c->b_vedge.p, c->sg, in, out, nullptr, s);
-    return hipGetLastError();
+    return seg_sum(c, c->pair, in, VoxOut{nullptr, nullptr, nullptr, nullptr, M}, w, s);
 }
 
 // One 16-lane group per touched voxel: T = theta_v + the sum of the voxel's
