@@ -1119,13 +1119,12 @@ int mrf_depth_distribution(mrf_ctx* c, float* prob, int32_t* mode_step, float* m
     if (!c->inferred) return fail(MRF_ESTATE, "mrf_depth_distribution: call mrf_infer first");
     hipStream_t s = (hipStream_t)stream;
     HCK(hipSetDevice(c->device), "mrf_depth_distribution: hipSetDevice");
-    float* q = prob ? (float*)c->b_ellbar.p : nullptr;   // slot order, then canonical edge order
     const KfSrc kfs{(const float*)c->b_kfx.p, (const int64_t*)c->b_kfxb.p};
     ExclSrc lam = final_lam(c);
     if (c->kf_inferred) lam = ExclSrc{(const float2*)c->b_theta2.p, nullptr};   // one sweep: the prior
-    HCK(launch_depth_distribution(c, lam, c->kf_inferred && c->K > 1 ? &kfs : nullptr, q, mode_step, mean_depth, s),
+    HCK(launch_depth_distribution(c, lam, c->kf_inferred && c->K > 1 ? &kfs : nullptr, prob, mode_step, mean_depth,
+                                  s),
         "mrf_depth_distribution");
-    if (prob) HCK(export_canonical_edges(c, q, prob, 4, s), "mrf_depth_distribution: export");
     return MRF_OK;
 }
 

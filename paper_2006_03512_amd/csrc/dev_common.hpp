@@ -495,6 +495,28 @@ __device__ __forceinline__ double dgroup_sum_d(double x)
     return x;
 }
 
+// Exclusive prefix sums over each group of G = 16, 32 or 64 lanes, in FP64.
+template <int G>
+__device__ __forceinline__ double dexcl_scan_d(double x)
+{
+    static_assert(G == 16 || G == 32 || G == 64, "groups are rows, half-waves or waves");
+    x = dpp_d<DPP_ROW_SHR1>(0.0, x) + x;
+    x = dpp_d<DPP_ROW_SHR2>(0.0, x) + x;
+    x = dpp_d<DPP_ROW_SHR4>(0.0, x) + x;
+    x = dpp_d<DPP_ROW_SHR8>(0.0, x) + x;
+    const int row = (threadIdx.x & 63) >> 4;
+    if (G == 32) {
+        const double r0 = readlane_d(x, 15), r2 = readlane_d(x, 47);
+        if (row & 1) x = (row == 1 ? r0 : r2) + x;
+    }
+    if (G == 64) {
+        const double r0 = readlane_d(x, 15), r1 = readlane_d(x, 31), r2 = readlane_d(x, 47);
+        if (row) x = (row == 1 ? r0 : row == 2 ? r0 + r1 : (r0 + r1) + r2) + x;
+    }
+    x = G == 16 ? dpp_d<DPP_ROW_SHR1>(0.0, x) : dpp_d<DPP_WAVE_SHR1>(0.0, x);
+    return (threadIdx.x & (G - 1)) == 0 ? 0.0 : x;
+}
+
 // sum over a wave in FP64, the same value in every lane
 __device__ __forceinline__ double wave_sum_d(double x) { return readlane_d(dgroup_sum_d<64>(x), 0); }
 

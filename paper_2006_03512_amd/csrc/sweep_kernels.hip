@@ -917,32 +917,153 @@ namespace mrf {
 // III-C): the measurement came from voxel i's depth with weight
 // nu(d_i) mu_i(1) prod_{k<i} mu_k(0), mu the voxel -> ray messages of the last
 // sweep, normalised over the ray (the all-empty configuration has potential
-// zero).  One thread per ray walks its steps twice: the log2 weights W_i =
-// log2 mu_i(1) + log2 nu_i + P_i, with the visibility P_i summed in FP64, give
-// the running maximum (the mode, first on ties) and the normaliser; then
-// q_i = 2^(W_i - max) / sum and the mean depth sum_i q_i d_i, d_i = Z - delta_i.
-__global__ __launch_bounds__(256) void depth_dist_k(const TileDev* __restrict__ tiles, int64_t T,
+// zero).  With the log2 weights W_i = log2 mu_i(1) + log2 nu_i + P_i, the
+// visibility P_i summed in FP64, the mode is the first largest W_i,
+// q_i = 2^(W_i - max) / sum, and the mean depth sum_i q_i d_i, d_i = Z - delta_i.
+
+// One group of G lanes per ray, one block per tile, staged through LDS like
+// ray_lds_k; lane l holds steps [l IPL, (l + 1) IPL).  The probabilities go back
+// through the ray's LDS column and leave as contiguous runs in canonical edge
+// order.  Bound by its five accesses of 4 bytes an edge: 1.1e8 edges (2 VGA
+// frames at 2 cm) in 576 us, 3.9 TB/s; a thread per ray walking its steps twice, and a
+// gather from slot to canonical order after it, took 4036.
+template <int G, int IPL, bool KF>
+__global__ __launch_bounds__(kTile * G) void depth_lds_k(const uint32_t* __restrict__ list, int64_t ntiles,
+                                                         const TileDev* __restrict__ tiles,
+                                                         const FrameDev* __restrict__ frames,
+                                                         const int32_t* __restrict__ counts,
+                                                         const int64_t* __restrict__ row_ptr,
+                                                         const int32_t* __restrict__ col, ExclDev lam, KfSrc kf,
+                                                         const float* __restrict__ g,
+                                                         const float* __restrict__ delta, float* __restrict__ prob,
+                                                         int32_t* __restrict__ mode, float* __restrict__ mean)
+{
+    constexpr int NT = kTile * G;
+    __shared__ float sl[kTile * G * IPL];
+    __shared__ float sg[kTile * G * IPL];
+    const int64_t ti = xcd_block(blockIdx.x, gridDim.x);
+    if (ti >= ntiles) return;   // whole block
+    const TileDev td = tiles[list[ti]];
+    const int nf = kTile * td.len;   // 1 <= td.len <= G * IPL by class
+    const int i = (int)threadIdx.x / G;   // this group's ray: lane i of the tile
+    const int gl = (int)threadIdx.x % G;
+    const int i0 = gl * IPL;
+    const int cb = lds_col(i0, gl, i);
+    const int m = tile_ray_len(td, counts, i);
+    float vd[IPL];
+    {
+        int32_t vc[IPL];
+        float vo[IPL], vg[IPL], vt[IPL];
+        float2 vp[IPL];
+        tile_fetch_i<NT, IPL>(col, td.base, nf, vc);
+        if constexpr (!KF) tile_fetch<NT, IPL>(lam.own, td.base, nf, vo);
+        tile_fetch<NT, IPL>(g, td.base, nf, vg);
+        tile_fetch<NT, IPL>(delta, td.base, nf, vd);
+        if constexpr (KF) {
+            const float* xf = kf.x + kf.xb[td.frame];
+#pragma unroll
+            for (int r = 0; r < IPL; ++r) vt[r] = vc[r] >= 0 ? xf[vc[r]] : 0.0f;
+        } else {
+#pragma unroll
+            for (int r = 0; r < IPL; ++r) vp[r] = lam.tot[max(vc[r], 0)];
+#pragma unroll
+            for (int r = 0; r < IPL; ++r) vt[r] = excl_value(vc[r], vp[r], vo[r], lam.has_own);
+        }
+        tile_to_lds<NT, IPL, IPL>(sl, vt);
+        tile_to_lds<NT, IPL, IPL>(sg, vg);
+    }
+    __syncthreads();
+    double W[IPL];
+    double P = 0.0;
+#pragma unroll
+    for (int j = 0; j < IPL; ++j) {   // column rows are inside the LDS tile even past the ray
+        float al, be, gg;
+        load_step(sl[cb + kTile * j], sg[cb + kTile * j], i0 + j < m, al, be, gg);
+        W[j] = ((double)be + (double)gg) + P;   // past the ray: log 0
+        P += (double)al;
+    }
+    __syncthreads();   // every group has its g: reuse sg for delta
+    tile_to_lds<NT, IPL, IPL>(sg, vd);
+    __syncthreads();
+    const double before = dexcl_scan_d<G>(P);   // log2 visibility up to the lane's first step
+    double M = -__builtin_huge_val();
+    int best = 0;
+#pragma unroll
+    for (int j = 0; j < IPL; ++j) {
+        W[j] += before;
+        if (i0 + j < m && W[j] > M) {
+            M = W[j];
+            best = i0 + j;
+        }
+    }
+#pragma unroll
+    for (int d = 1; d < G; d <<= 1) {
+        const double oM = __shfl_xor(M, d, G);
+        const int ob = __shfl_xor(best, d, G);
+        if (oM > M || (oM == M && ob < best)) {
+            M = oM;
+            best = ob;
+        }
+    }
+    float q[IPL];
+    double S = 0.0;
+#pragma unroll
+    for (int j = 0; j < IPL; ++j) {
+        q[j] = i0 + j < m ? ex2((float)(W[j] - M)) : 0.0f;
+        S += (double)q[j];
+    }
+#pragma unroll
+    for (int d = 1; d < G; d <<= 1) S += __shfl_xor(S, d, G);
+    const double inv = 1.0 / S;
+    const int64_t r = td.ray0 + (int64_t)(i / kTileW) * td.W + (i & (kTileW - 1));
+    const int64_t at = m > 0 ? row_ptr[r] : 0;
+    double mq = 0.0;
+    if (mean) {
+        const FrameDev fr = frames[td.frame];
+        const double Z = m > 0 ? (double)fr.depth[r - fr.ray_base] : 0.0;
+#pragma unroll
+        for (int j = 0; j < IPL; ++j)
+            if (i0 + j < m) mq += ((double)q[j] * inv) * (Z - (double)sg[cb + kTile * j]);
+#pragma unroll
+        for (int d = 1; d < G; d <<= 1) mq += __shfl_xor(mq, d, G);
+    }
+    if (m > 0 && gl == 0) {
+        if (mode) mode[r] = best;
+        if (mean) mean[r] = (float)mq;
+    }
+    if (!prob) return;
+#pragma unroll
+    for (int j = 0; j < IPL; ++j) sl[cb + kTile * j] = (float)((double)q[j] * inv);
+    // the group reads back its own column: accesses of one wave complete in order
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int j = 0; j < IPL; ++j) {
+        const int k = j * G + gl;
+        if (k < m) prob[at + k] = sl[lds_at<IPL>(k, i)];
+    }
+}
+
+// Tiles longer than a block's LDS holds: one thread per ray, two walks of its steps.
+__global__ __launch_bounds__(256) void depth_dist_k(const uint32_t* __restrict__ list, int64_t ntiles,
+                                                    const TileDev* __restrict__ tiles,
                                                     const FrameDev* __restrict__ frames,
                                                     const int32_t* __restrict__ counts,
+                                                    const int64_t* __restrict__ row_ptr,
                                                     const int32_t* __restrict__ col, ExclDev lam, KfSrc kf,
                                                     int is_kf, const float* __restrict__ g,
-                                                    const float* __restrict__ delta, float* __restrict__ q,
+                                                    const float* __restrict__ delta, float* __restrict__ prob,
                                                     int32_t* __restrict__ mode, float* __restrict__ mean)
 {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t ti = t / kTile;
-    if (ti >= T) return;
+    if (ti >= ntiles) return;
     const int i = (int)(t % kTile);
-    const TileDev td = tiles[ti];
-    const int ux = i & (kTileW - 1), vy = i / kTileW;
-    if (ux >= td.nu || vy >= td.nv) return;
-    const int64_t r = td.ray0 + (int64_t)vy * td.W + ux;
-    const int m = counts[r];
-    if (m == 0) {
-        if (mode) mode[r] = -1;
-        if (mean) mean[r] = __builtin_nanf("");
-        return;
-    }
+    const TileDev td = tiles[list[ti]];
+    const int m = tile_ray_len(td, counts, i);
+    if (m == 0) return;
+    const int64_t r = td.ray0 + (int64_t)(i / kTileW) * td.W + (i & (kTileW - 1));
     const int64_t s0 = td.base + i;
     const float* xf = is_kf ? kf.x + kf.xb[td.frame] : nullptr;
     auto weight = [&](int k, double& P) {   // W_k (log2), then P += log2 mu_k(0)
@@ -970,26 +1091,71 @@ __global__ __launch_bounds__(256) void depth_dist_k(const TileDev* __restrict__ 
     if (mode) mode[r] = best;
     const FrameDev fr = frames[td.frame];
     const double Z = (double)fr.depth[r - fr.ray_base];
+    const int64_t d0 = row_ptr[r];
     double mq = 0.0;
     P = 0.0;
     for (int k = 0; k < m; ++k) {
         const double W = weight(k, P);
         const double qk = (double)ex2((float)(W - M)) / S;
-        if (q) q[s0 + (int64_t)kTile * k] = (float)qk;
+        if (prob) prob[d0 + k] = (float)qk;
         mq += qk * (Z - (double)delta[s0 + (int64_t)kTile * k]);
     }
     if (mean) mean[r] = (float)mq;
 }
 
-hipError_t launch_depth_distribution(const mrf_ctx* c, ExclSrc lam, const KfSrc* kf, float* q, int32_t* mode,
+// rays without voxels
+__global__ void depth_none_k(const int32_t* __restrict__ counts, int64_t R, int32_t* __restrict__ mode,
+                             float* __restrict__ mean)
+{
+    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (r >= R || counts[r] > 0) return;
+    if (mode) mode[r] = -1;
+    if (mean) mean[r] = __builtin_nanf("");
+}
+
+// The depth messages of one class's tiles; classes of LDS tiles take the class's
+// default forward shape.
+template <int Q, bool KF>
+static void launch_depth_class(const mrf_ctx* c, const ExclDev& lam, const KfSrc& kf, float* prob, int32_t* mode,
+                               float* mean, hipStream_t s)
+{
+    const int64_t n = c->ray_cnt[Q];
+    if (n <= 0) return;
+    const uint32_t* list = (const uint32_t*)c->b_ray_list.p + c->ray_off[Q];
+    const TileDev* tiles = (const TileDev*)c->b_tiles.p;
+    const FrameDev* frames = (const FrameDev*)c->b_frames.p;
+    const int32_t* counts = (const int32_t*)c->b_counts.p;
+    const int64_t* rp = (const int64_t*)c->b_rowptr.p;
+    const int32_t* col = (const int32_t*)c->b_col.p;
+    const float *g = (const float*)c->b_g.p, *delta = (const float*)c->b_delta.p;
+    if constexpr (kRayCap[Q] <= kLdsMaxCap) {
+        constexpr int G = kFwdShapes[Q][0].g;
+        hipLaunchKernelGGL((depth_lds_k<G, kRayCap[Q] / G, KF>), dim3((unsigned)n), dim3(kTile * G), 0, s, list, n,
+                           tiles, frames, counts, rp, col, lam, kf, g, delta, prob, mode, mean);
+    } else {
+        hipLaunchKernelGGL(depth_dist_k, dim3(nblk(n * kTile, 256)), dim3(256), 0, s, list, n, tiles, frames, counts,
+                           rp, col, lam, kf, KF ? 1 : 0, g, delta, prob, mode, mean);
+    }
+}
+
+template <bool KF, int... Q>
+static void depth_classes(std::integer_sequence<int, Q...>, const mrf_ctx* c, const ExclDev& lam, const KfSrc& kf,
+                          float* prob, int32_t* mode, float* mean, hipStream_t s)
+{
+    (launch_depth_class<Q, KF>(c, lam, kf, prob, mode, mean, s), ...);
+}
+
+hipError_t launch_depth_distribution(const mrf_ctx* c, ExclSrc lam, const KfSrc* kf, float* prob, int32_t* mode,
                                      float* mean, hipStream_t s)
 {
-    if (c->T <= 0) return hipSuccess;
-    const int64_t n = c->T * kTile;
-    hipLaunchKernelGGL(depth_dist_k, dim3(nblk(n, 256)), dim3(256), 0, s, (const TileDev*)c->b_tiles.p, c->T,
-                       (const FrameDev*)c->b_frames.p, (const int32_t*)c->b_counts.p, (const int32_t*)c->b_col.p,
-                       excl_dev(c, lam), kf ? *kf : KfSrc{nullptr, nullptr}, kf ? 1 : 0, (const float*)c->b_g.p,
-                       (const float*)c->b_delta.p, q, mode, mean);
+    if (c->R > 0 && (mode || mean))
+        hipLaunchKernelGGL(depth_none_k, dim3(nblk(c->R, 256)), dim3(256), 0, s, (const int32_t*)c->b_counts.p, c->R,
+                           mode, mean);
+    constexpr auto classes = std::make_integer_sequence<int, kRayClasses>{};
+    if (kf)
+        depth_classes<true>(classes, c, excl_dev(c, lam), *kf, prob, mode, mean, s);
+    else
+        depth_classes<false>(classes, c, excl_dev(c, lam), KfSrc{nullptr, nullptr}, prob, mode, mean, s);
     return hipGetLastError();
 }
 
