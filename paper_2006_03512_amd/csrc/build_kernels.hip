@@ -230,6 +230,171 @@ __device__ int walk(const SceneDev& sd, const Ray& r, const uint8_t* bricks, Emi
     return k;
 }
 
+// ------------------------------------------------------------ dense walk
+//
+// A quotient n / w with fixed w, rounded once as the division is, from the
+// correctly rounded reciprocal y = 1 / w (Markstein's theorem): q0 = n y is within
+// 2 ulp of the quotient; q1 = q0 + (n - w q0) y is within half an ulp and 2^-51 of
+// one, so n - w q1 is exact in an FMA and q1 + (n - w q1) y rounds to the rounded
+// quotient, unless w's significand lies within 4 ulp of 2 (no quotient is a rounding
+// tie, and the correction's error, at most (1/2 + 2^-51) ulp(q) w |y - 1/w|, stays
+// below the distance of n / w from the nearest tie for every other w).  Nothing may
+// underflow or overflow: quot_exact checks the ray and its grid.  Five operations
+// where the division takes eleven, one of them a quarter-rate reciprocal.
+__device__ __forceinline__ double quot(double n, double w, double y)
+{
+    const double q0 = n * y;
+    const double q1 = __builtin_fma(__builtin_fma(-w, q0, n), y, q0);
+    return __builtin_fma(__builtin_fma(-w, q1, n), y, q1);
+}
+
+// x is 0 or 2^lo <= |x| < 2^hi
+__device__ __forceinline__ bool exponent_in(double x, int lo, int hi)
+{
+    const int e = (int)((__builtin_bit_cast(uint64_t, x) >> 52) & 2047u) - 1023;
+    return x == 0.0 || (e >= lo && e < hi);
+}
+
+// Whether quot() gives every boundary time of the ray along one axis: faces o + i h and
+// their distances to c are 0 or of magnitude in [2^-900, 2^900) (sums of multiples of
+// 2^-852), w of magnitude in [2^-100, 2^100) with a significand below 2 - 2^-48.
+__device__ __forceinline__ bool quot_exact(double o, double h, double c, double w)
+{
+    if (w == 0.0) return true;   // never divided by
+    const uint64_t m = __builtin_bit_cast(uint64_t, w) & ((1ull << 52) - 1);
+    return exponent_in(w, -100, 100) && m < (1ull << 52) - 16 && exponent_in(o, -500, 500) &&
+           exponent_in(h, -500, 500) && exponent_in(c, -800, 800);
+}
+
+// One axis of the walk: the next boundary's time t and number f (boundary f lies at
+// o + f h; the voxel index plus one when the ray runs upwards), and its constants.
+struct WalkAxis {
+    double t, f, s, c, w, y;
+    int dl, di;   // steps of the linear voxel id and of the index
+    template <bool FAST>
+    __device__ __forceinline__ void time(double o, double h)
+    {
+        const double n = (o + f * h) - c;
+        t = FAST ? quot(n, w, y) : n / w;
+    }
+    template <bool FAST>
+    __device__ __forceinline__ void step(double o, double h)
+    {
+        f += s;
+        time<FAST>(o, h);
+    }
+};
+
+template <bool FAST>
+__device__ __forceinline__ WalkAxis walk_axis(const SceneDev& sd, const Ray& r, int a, int idx, int stride)
+{
+    WalkAxis x;
+    const bool up = r.w[a] > 0.0;
+    x.w = r.w[a];
+    x.c = r.c[a];
+    x.y = FAST ? 1.0 / x.w : 0.0;
+    x.s = up ? 1.0 : -1.0;
+    x.di = up ? 1 : -1;
+    x.dl = up ? stride : -stride;
+    x.f = (double)(up ? idx + 1 : idx);
+    if (x.w != 0.0)
+        x.time<FAST>(sd.o[a], sd.h);
+    else
+        x.t = __builtin_huge_val();
+    return x;
+}
+
+// walk() on a dense grid: the same voxels, chords and order, with the axes in named
+// registers (arrays indexed by the stepped axis were placed in LDS: several dependent
+// LDS accesses per step) and quot() for the boundary times.  The walk needs no test of
+// the grid's end: the ray's end te is at most the grid exit, which is the smallest of
+// the axes' last boundary times (the same expression), so it stops there first; the
+// test of the linear id only keeps an index out of range from ever being used.
+// emit(k, i, j, kz, lin, t_in, t_out).  5e8 steps (8 VGA frames at 2 cm): count pass
+// 1.18 ms with walk() and 0.78 (VALU-bound), emit pass 1.89 and 1.82 (its stores of 4, 4
+// and 1 bytes a step); the metric's walk of 4 frames to the grid exit 1.15 and 0.70; one
+// 64x48 frame, a chain of steps, 46 + 65 us and 24 + 42.
+template <bool FAST, class Emit>
+__device__ __forceinline__ int walk_dense(const SceneDev& sd, const Ray& r, Emit&& emit)
+{
+    int idx[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const double p = r.c[a] + r.ts * r.w[a];
+        double q = floor((p - sd.o[a]) / sd.h);
+        if (q < 0.0) q = 0.0;
+        if (q > (double)(sd.n[a] - 1)) q = (double)(sd.n[a] - 1);
+        idx[a] = (int)q;
+    }
+    const int nx = sd.n[0], nxy = sd.n[0] * sd.n[1];
+    const uint32_t nvox = (uint32_t)nxy * (uint32_t)sd.n[2];
+    int i = idx[0], j = idx[1], kz = idx[2];
+    int lin = i + nx * j + nxy * kz;
+    WalkAxis X = walk_axis<FAST>(sd, r, 0, i, 1), Y = walk_axis<FAST>(sd, r, 1, j, nx),
+             Z = walk_axis<FAST>(sd, r, 2, kz, nxy);
+    const double ox = sd.o[0], oy = sd.o[1], oz = sd.o[2], h = sd.h;
+    double tin = r.ts;
+    int k = 0;
+    for (;;) {
+        const bool ax = X.t <= Y.t && X.t <= Z.t;   // ties step the lowest axis
+        const bool ay = !ax && Y.t <= Z.t;
+        const double tm = ax ? X.t : ay ? Y.t : Z.t;
+        const double tout = tm < r.te ? tm : r.te;
+        if (tout > tin) {
+            emit(k, i, j, kz, lin, tin, tout);
+            ++k;
+        }
+        if (tm >= r.te) break;
+        if (tm > tin) tin = tm;
+        // one branch per axis: lanes that step different axes run them one after the
+        // other, still fewer instructions than selecting every operand by axis
+        if (ax) {
+            lin += X.dl;
+            i += X.di;
+            X.step<FAST>(ox, h);
+        } else if (ay) {
+            lin += Y.dl;
+            j += Y.di;
+            Y.step<FAST>(oy, h);
+        } else {
+            lin += Z.dl;
+            kz += Z.di;
+            Z.step<FAST>(oz, h);
+        }
+        if ((uint32_t)lin >= nvox) break;
+    }
+    return k;
+}
+
+template <class Emit>
+__device__ __forceinline__ int walk_dense(const SceneDev& sd, const Ray& r, Emit&& emit)
+{
+    bool fast = true;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) fast = fast && quot_exact(sd.o[a], sd.h, r.c[a], r.w[a]);
+    if (fast) return walk_dense<true>(sd, r, emit);
+    return walk_dense<false>(sd, r, emit);
+}
+
+// Pixel (u, v) of thread t of block b: 16 x 16 pixels a block, 8 x 8 a wave, so that a
+// wave's rays are of like length and cross the same voxels.
+__device__ __forceinline__ bool block_pixel(const SceneDev& sd, int b, int t, int& u, int& v)
+{
+    const int nbx = (sd.W + 15) / 16;
+    const int by = b / nbx, bx = b - by * nbx;
+    u = bx * 16 + ((t >> 6) & 1) * 8 + (t & 7);
+    v = by * 16 + (t >> 7) * 8 + ((t >> 3) & 7);
+    return u < sd.W && v < sd.H;
+}
+
+// most blocks of 16 x 16 pixels of any scene's image
+static int pixel_blocks(const mrf_ctx* c)
+{
+    int n = 0;
+    for (const auto& sd : c->scenes_h) n = std::max(n, ((sd.W + 15) / 16) * ((sd.H + 15) / 16));
+    return n;
+}
+
 __device__ __forceinline__ const uint8_t* scene_bricks(const BuildDev& bp, const SceneDev& sd)
 {
     return bp.bricks ? bp.bricks + sd.brick_off : nullptr;
@@ -279,20 +444,27 @@ __global__ __launch_bounds__(256) void brick_mark_k(const SceneDev* __restrict__
 
 struct NoEmit {
     __device__ void operator()(int, int, int, int, double, double) const {}
+    __device__ void operator()(int, int, int, int, int, double, double) const {}
 };
 
+template <bool DENSE>
 __global__ __launch_bounds__(256) void trace_count_k(const SceneDev* __restrict__ scenes,
                                                      const FrameDev* __restrict__ frames,
                                                      BuildDev bp, int32_t* __restrict__ counts)
 {
     const FrameDev fr = frames[blockIdx.y];
     const SceneDev& sd = scenes[fr.scene];
-    const int pix = blockIdx.x * 256 + threadIdx.x;
-    if (pix >= sd.W * sd.H) return;
-    const int v = pix / sd.W, u = pix - v * sd.W;
+    int u, v;
+    if (!block_pixel(sd, blockIdx.x, threadIdx.x, u, v)) return;
+    const int pix = v * sd.W + u;
     Ray r;
     int m = 0;
-    if (setup_ray(sd, bp, fr.T, fr.depth[pix], v, u, r)) m = walk(sd, r, scene_bricks(bp, sd), NoEmit{}, bp.skip);
+    if (setup_ray(sd, bp, fr.T, fr.depth[pix], v, u, r)) {
+        if constexpr (DENSE)
+            m = walk_dense(sd, r, NoEmit{});
+        else
+            m = walk(sd, r, scene_bricks(bp, sd), NoEmit{}, bp.skip);
+    }
     counts[fr.ray_base + pix] = m >= bp.min_vox ? m : 0;
 }
 
@@ -303,6 +475,7 @@ __device__ __forceinline__ uint32_t brick_key(const SceneDev& sd, int i, int j, 
     return (uint32_t)(sd.key_base + brick * 512 + ((k & 7) * 8 + (j & 7)) * 8 + (i & 7));
 }
 
+template <bool KEY>
 struct EdgeEmit {
     int32_t* col;
     uint32_t* key;
@@ -332,13 +505,17 @@ struct EdgeEmit {
     }
     __device__ void operator()(int k, int vi, int vj, int vk, double ti, double to) const
     {
+        (*this)(k, vi, vj, vk, vi + sd->n[0] * (vj + sd->n[1] * vk), ti, to);
+    }
+    __device__ void operator()(int k, int vi, int vj, int vk, int lin, double ti, double to) const
+    {
         const int64_t e = base + (int64_t)kTile * k;   // step k of this ray's tile lane
         const double d = (ti + to) * 0.5;   // voxel depth: chord midpoint
         double q = bin_of(d);
         if (q < 0.0) q = 0.0;
         if (q > 63.0) q = 63.0;
-        col[e] = vbase + vi + sd->n[0] * (vj + sd->n[1] * vk);
-        if (key) key[e] = brick_key(*sd, vi, vj, vk);
+        col[e] = vbase + lin;
+        if constexpr (KEY) key[e] = brick_key(*sd, vi, vj, vk);
         delta[e] = (float)(Z - d);
         bin[e] = (uint8_t)q;
         if (tin) {
@@ -355,7 +532,8 @@ struct EdgeEmit {
 // Each lane then marks its column's slots past its ray, up to the tile's length, as
 // padding (no voxel, no bin, sort key pad_key past every voxel); lanes of pixels
 // outside the image pad their whole column.  Sort keys are written where the
-// slots themselves are sorted (key not null).
+// slots themselves are sorted (KEY).
+template <bool DENSE, bool KEY>
 __global__ __launch_bounds__(256) void trace_emit_k(const SceneDev* __restrict__ scenes,
                                                     const FrameDev* __restrict__ frames, BuildDev bp,
                                                     const int32_t* __restrict__ counts,
@@ -386,15 +564,18 @@ __global__ __launch_bounds__(256) void trace_emit_k(const SceneDev* __restrict__
             wn = wn + ray.w[1] * ray.w[1];
             wn = wn + ray.w[2] * ray.w[2];
             const double dbin = bp.dmax / 64.0;
-            EdgeEmit em{col,   key,   delta, bin, tin, tout, wlen, &sd, slot0, (int32_t)sd.voxel_base, ray.Z,
+            EdgeEmit<KEY> em{col,   key,   delta, bin, tin, tout, wlen, &sd, slot0, (int32_t)sd.voxel_base, ray.Z,
                         dbin,  sqrt(wn), 1.0 / dbin};
-            walk(sd, ray, scene_bricks(bp, sd), em, bp.skip);
+            if constexpr (DENSE)
+                walk_dense(sd, ray, em);
+            else
+                walk(sd, ray, scene_bricks(bp, sd), em, bp.skip);
         }
     }
     for (int k = m; k < len; ++k) {
         const int64_t e = slot0 + (int64_t)kTile * k;
         col[e] = -1;
-        if (key) key[e] = pad_key;
+        if constexpr (KEY) key[e] = pad_key;
         delta[e] = 0.0f;
         bin[e] = 255;
     }
@@ -452,9 +633,14 @@ hipError_t launch_trace_count(mrf_ctx* c, hipStream_t s, int f0, int nf)
 {
     if (nf < 0) nf = c->n_frames - f0;
     if (nf <= 0) return hipSuccess;
-    dim3 grid((c->max_hw + 255) / 256, nf);
-    hipLaunchKernelGGL(trace_count_k, grid, dim3(256), 0, s, (const SceneDev*)c->b_scenes.p,
-                       (const FrameDev*)c->b_frames.p + f0, c->bp, (int32_t*)c->b_counts.p);
+    const dim3 grid(pixel_blocks(c), nf);
+    const SceneDev* sc = (const SceneDev*)c->b_scenes.p;
+    const FrameDev* fr = (const FrameDev*)c->b_frames.p + f0;
+    int32_t* counts = (int32_t*)c->b_counts.p;
+    if (c->bp.bricks)
+        hipLaunchKernelGGL(trace_count_k<false>, grid, dim3(256), 0, s, sc, fr, c->bp, counts);
+    else
+        hipLaunchKernelGGL(trace_count_k<true>, grid, dim3(256), 0, s, sc, fr, c->bp, counts);
     return hipGetLastError();
 }
 
@@ -505,17 +691,26 @@ hipError_t launch_scatter_by_slot(const uint32_t* slot, const float* in, int64_t
     return hipGetLastError();
 }
 
+template <bool DENSE, bool KEY>
+static void launch_emit_t(mrf_ctx* c, hipStream_t s, int f0, int nf)
+{
+    const dim3 grid((unsigned)((c->max_tpf + 256 / kTile - 1) / (256 / kTile)), nf);
+    hipLaunchKernelGGL((trace_emit_k<DENSE, KEY>), grid, dim3(256), 0, s, (const SceneDev*)c->b_scenes.p,
+                       (const FrameDev*)c->b_frames.p + f0, c->bp, (const int32_t*)c->b_counts.p,
+                       (const int64_t*)c->b_tbase.p, (const TileDev*)c->b_tiles.p, (uint32_t)c->Vk,
+                       (int32_t*)c->b_col.p, (uint32_t*)c->b_g.p, (float*)c->b_delta.p, (uint8_t*)c->b_bin.p,
+                       c->keep_chords ? (double*)c->b_tin.p : nullptr,
+                       c->keep_chords ? (double*)c->b_tout.p : nullptr, c->kf ? (float*)c->b_kflen.p : nullptr);
+}
+
 hipError_t launch_trace_emit(mrf_ctx* c, bool keys, hipStream_t s, int f0, int nf)
 {
     if (nf < 0) nf = c->n_frames - f0;
     if (nf <= 0) return hipSuccess;
-    dim3 grid((unsigned)((c->max_tpf + 256 / kTile - 1) / (256 / kTile)), nf);
-    hipLaunchKernelGGL(trace_emit_k, grid, dim3(256), 0, s, (const SceneDev*)c->b_scenes.p,
-                       (const FrameDev*)c->b_frames.p + f0, c->bp, (const int32_t*)c->b_counts.p,
-                       (const int64_t*)c->b_tbase.p, (const TileDev*)c->b_tiles.p, (uint32_t)c->Vk,
-                       (int32_t*)c->b_col.p, keys ? (uint32_t*)c->b_g.p : nullptr, (float*)c->b_delta.p, (uint8_t*)c->b_bin.p,
-                       c->keep_chords ? (double*)c->b_tin.p : nullptr,
-                       c->keep_chords ? (double*)c->b_tout.p : nullptr, c->kf ? (float*)c->b_kflen.p : nullptr);
+    if (c->bp.bricks)
+        keys ? launch_emit_t<false, true>(c, s, f0, nf) : launch_emit_t<false, false>(c, s, f0, nf);
+    else
+        keys ? launch_emit_t<true, true>(c, s, f0, nf) : launch_emit_t<true, false>(c, s, f0, nf);
     return hipGetLastError();
 }
 
@@ -1613,6 +1808,10 @@ __global__ __launch_bounds__(256) void part_place_k(const F f, int64_t nb, const
     for (int k = 0; k < F::NC; ++k)
         if (lane == k) wc[w][k] = cnt[k];
     __syncthreads();
+    // the ballots of the second walk are taken again: kept from the first (R NC masks)
+    // they would spill
+#pragma unroll
+    for (int r = 0; r < R; ++r) asm volatile("" : "+v"(cl[r]));
     uint32_t at[F::NC];   // next position of this wave's items of class k (totals are below 2^32)
     uint32_t base = 0;
 #pragma unroll
@@ -2137,16 +2336,14 @@ hipError_t launch_frame_counts(const mrf_ctx* c, int64_t* out, hipStream_t s)
 // Sec. III-D: a voxel is a region of constant occlusion density alpha, chosen
 // so that crossing one voxel side h blocks a ray with the voxel's occupancy
 // probability: alpha = -ln(1 - p) / h = softplus(L) / h for log-odds L.  Per
-// voxel of one scene, FP64: alpha and log alpha.
-__global__ void metric_alpha_k(const float* __restrict__ logit, int64_t n, double inv_h,
-                               double* __restrict__ alpha, double* __restrict__ lalpha)
+// voxel of one scene, FP64: (alpha, log alpha), one 16-byte gather per step.
+__global__ void metric_alpha_k(const float* __restrict__ logit, int64_t n, double inv_h, double2* __restrict__ alpha)
 {
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const double x = (double)logit[i];
         const double sp = (x > 0.0 ? x : 0.0) + log1p(exp(-fabs(x)));
         const double a = sp * inv_h;
-        alpha[i] = a;
-        lalpha[i] = log(a);
+        alpha[i] = make_double2(a, log(a));
     }
 }
 
@@ -2155,20 +2352,17 @@ __global__ void metric_alpha_k(const float* __restrict__ logit, int64_t n, doubl
 // a voxel, so its maximum is at the entry of the voxel maximising
 // log alpha_n - sum_{i<n} alpha_i l_i (the first on ties).
 struct MetricEmit {
-    const double* alpha;
-    const double* lalpha;
-    int64_t vb;              // the scene's first global voxel id
-    int32_t nx, ny;
+    const double2* alpha;    // of the scene's voxels
     double wn;               // |w|: Euclidean length per unit of z-depth
     double acc = 0.0;        // sum of alpha_i l_i so far
     double best = -__builtin_huge_val();
     double btin = 0.0, btout = 0.0;
 
-    __device__ void operator()(int, int i, int j, int kz, double tin, double tout)
+    __device__ void operator()(int, int, int, int, int lin, double tin, double tout)
     {
-        const int64_t v = vb + (int64_t)(i + nx * (j + ny * kz));
-        const double a = alpha[v];
-        const double lw = lalpha[v] - acc;
+        const double2 al = alpha[lin];
+        const double a = al.x;
+        const double lw = al.y - acc;
         if (lw > best) {
             best = lw;
             btin = tin;
@@ -2193,18 +2387,16 @@ struct MetricEmit {
 // atomic per block.
 __global__ __launch_bounds__(256) void accuracy_k(const SceneDev* __restrict__ scenes,
                                                   const FrameDev* __restrict__ frames, BuildDev bp,
-                                                  const double* __restrict__ alpha,
-                                                  const double* __restrict__ lalpha, double lvmin,
+                                                  const double2* __restrict__ alpha, double lvmin,
                                                   const float* __restrict__ ref, double tol,
                                                   int8_t* __restrict__ code, double* __restrict__ surf,
                                                   unsigned long long* __restrict__ counts)
 {
     const FrameDev fr = frames[blockIdx.y];
     const SceneDev& sd = scenes[fr.scene];
-    const int pix = blockIdx.x * 256 + threadIdx.x;
-    int ev = 0, ok = 0;
-    if (pix < sd.W * sd.H) {
-        const int v = pix / sd.W, u = pix - v * sd.W;
+    int ev = 0, ok = 0, u, v;
+    if (block_pixel(sd, blockIdx.x, threadIdx.x, u, v)) {
+        const int pix = v * sd.W + u;
         Ray r;
         double ts, texit;
         int8_t cd = -1;
@@ -2214,13 +2406,9 @@ __global__ __launch_bounds__(256) void accuracy_k(const SceneDev* __restrict__ s
             r.ts = ts;
             r.te = texit;
             MetricEmit m;
-            m.alpha = alpha;
-            m.lalpha = lalpha;
-            m.vb = sd.voxel_base;
-            m.nx = sd.n[0];
-            m.ny = sd.n[1];
+            m.alpha = alpha + sd.voxel_base;
             m.wn = sqrt(r.w[0] * r.w[0] + r.w[1] * r.w[1] + r.w[2] * r.w[2]);
-            walk(sd, r, nullptr, m);   // the metric walks the whole grid
+            walk_dense(sd, r, m);   // the metric walks the whole grid
             if (-m.acc >= lvmin) {
                 cd = r.Z > texit ? 1 : 0;
                 sf = __builtin_huge_val();
@@ -2253,23 +2441,22 @@ __global__ __launch_bounds__(256) void accuracy_k(const SceneDev* __restrict__ s
 hipError_t launch_accuracy(mrf_ctx* c, const float* logit, double vis_min, const float* ref, double tol,
                            int8_t* code, double* surf, int64_t* counts, double* work, hipStream_t s)
 {
-    double* alpha = work;
-    double* lalpha = alpha + c->V;
+    double2* alpha = (double2*)work;
     for (const SceneDev& sd : c->scenes_h) {
         const int64_t n = (int64_t)sd.n[0] * sd.n[1] * sd.n[2];
         int64_t b = (n + 255) / 256;
         if (b > 65536) b = 65536;
         hipLaunchKernelGGL(metric_alpha_k, dim3((unsigned)b), dim3(256), 0, s, logit + sd.voxel_base, n, 1.0 / sd.h,
-                           alpha + sd.voxel_base, lalpha + sd.voxel_base);
+                           alpha + sd.voxel_base);
     }
     if (counts) {
         hipError_t e = launch_fill_u32((uint32_t*)counts, 0u, 4 * (int64_t)c->n_scenes, s);
         if (e != hipSuccess) return e;
     }
-    dim3 grid((c->max_hw + 255) / 256, c->n_frames);
+    const dim3 grid(pixel_blocks(c), c->n_frames);
     hipLaunchKernelGGL(accuracy_k, grid, dim3(256), 0, s, (const SceneDev*)c->b_scenes.p,
-                       (const FrameDev*)c->b_frames.p, c->bp, (const double*)alpha, (const double*)lalpha,
-                       std::log(vis_min), ref, tol, code, surf, (unsigned long long*)counts);
+                       (const FrameDev*)c->b_frames.p, c->bp, (const double2*)alpha, std::log(vis_min), ref, tol, code,
+                       surf, (unsigned long long*)counts);
     return hipGetLastError();
 }
 
