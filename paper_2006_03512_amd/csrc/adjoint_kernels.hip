@@ -215,25 +215,27 @@ __global__ __launch_bounds__(256) void ray_adj_k(const uint32_t* __restrict__ li
 // array); each group writes lambda-bar and g-bar into its rays' columns (zeros
 // past the ray), and the block stores lambda-bar and accumulates the g-bar sum
 // coalesced.
+// LDS words of one tile: two images, or three with several rays per group
+template <int G, int IPL, int RPW>
+constexpr int adj_lds_words()
+{
+    return (RPW > 1 ? 3 : 2) * kTile * G * IPL;
+}
+
 template <int G, int IPL, int RPW, bool KF>
-__global__ __launch_bounds__(kTile * G / RPW) void ray_adj_lds_k(const uint32_t* __restrict__ list, int64_t ntiles,
-                                                                 const TileDev* __restrict__ tiles,
-                                                                 const int32_t* __restrict__ counts,
-                                                                 const int32_t* __restrict__ col, ExclDev lam,
-                                                                 const float* __restrict__ g, ExclDev eb, AdjKf kfa,
-                                                                 float* __restrict__ lambar, float* __restrict__ gsum,
-                                                                 int first)
+__device__ __forceinline__ void ray_adj_tile(const TileDev& td, const int32_t* __restrict__ counts,
+                                             const int32_t* __restrict__ col, const ExclDev& lam,
+                                             const float* __restrict__ g, const ExclDev& eb, const AdjKf& kfa,
+                                             float* __restrict__ lambar, float* __restrict__ gsum, int first,
+                                             float* lds)
 {
     constexpr int NT = kTile * G / RPW;   // threads
     constexpr int NG = kTile / RPW;       // groups
     constexpr int NR = IPL * RPW;         // staging rounds per thread
     constexpr int CAP = G * IPL;
-    __shared__ float sa[kTile * CAP];
-    __shared__ float sb[kTile * CAP];
-    __shared__ float se[RPW > 1 ? kTile * CAP : 1];
-    const int64_t ti = xcd_block(blockIdx.x, gridDim.x);
-    if (ti >= ntiles) return;   // whole block
-    const TileDev td = tiles[list[ti]];
+    float* sa = lds;
+    float* sb = lds + kTile * CAP;
+    float* se = lds + 2 * kTile * CAP;    // RPW > 1 only
     const int nf = kTile * td.len;   // 1 <= td.len <= G * IPL by class
     const int grp = (int)threadIdx.x / G;
     const int gl = (int)threadIdx.x % G;
@@ -323,6 +325,46 @@ __global__ __launch_bounds__(kTile * G / RPW) void ray_adj_lds_k(const uint32_t*
         [&](int r, int at) { return first ? sb[at] : vs[r] + sb[at]; }, td.base, nf);
 }
 
+template <int G, int IPL, int RPW, bool KF>
+__global__ __launch_bounds__(kTile * G / RPW) void ray_adj_lds_k(const uint32_t* __restrict__ list, int64_t ntiles,
+                                                                 const TileDev* __restrict__ tiles,
+                                                                 const int32_t* __restrict__ counts,
+                                                                 const int32_t* __restrict__ col, ExclDev lam,
+                                                                 const float* __restrict__ g, ExclDev eb, AdjKf kfa,
+                                                                 float* __restrict__ lambar, float* __restrict__ gsum,
+                                                                 int first)
+{
+    __shared__ float lds[adj_lds_words<G, IPL, RPW>()];
+    const int64_t ti = xcd_block(blockIdx.x, gridDim.x);
+    if (ti >= ntiles) return;   // whole block
+    const TileDev td = tiles[list[ti]];
+    ray_adj_tile<G, IPL, RPW, KF>(td, counts, col, lam, g, eb, kfa, lambar, gsum, first, lds);
+}
+
+// The short classes of a small graph in one launch (as ray_small_k).
+template <bool KF>
+__global__ __launch_bounds__(256) void ray_adj_small_k(const SmallTiles st, const TileDev* __restrict__ tiles,
+                                                       const int32_t* __restrict__ counts,
+                                                       const int32_t* __restrict__ col, ExclDev lam,
+                                                       const float* __restrict__ g, ExclDev eb, AdjKf kfa,
+                                                       float* __restrict__ lambar, float* __restrict__ gsum, int first)
+{
+    __shared__ float lds[adj_lds_words<32, kRayCap[4] / 32, 2>()];
+    int k = 0;   // uniform: the class whose blocks hold this one
+    while (k + 1 < kSmallClasses && blockIdx.x >= st.blk[k + 1]) ++k;
+    const int q = kSmallClasses - 1 - k;
+    const int64_t lt = xcd_block(blockIdx.x - st.blk[k], st.blk[k + 1] - st.blk[k]);
+    if (lt >= st.cnt[q]) return;   // whole block
+    const TileDev td = tiles[st.list[st.off[q] + lt]];
+    switch (q) {
+        case 0: ray_adj_tile<16, kRayCap[0] / 16, 1, KF>(td, counts, col, lam, g, eb, kfa, lambar, gsum, first, lds); break;
+        case 1: ray_adj_tile<16, kRayCap[1] / 16, 1, KF>(td, counts, col, lam, g, eb, kfa, lambar, gsum, first, lds); break;
+        case 2: ray_adj_tile<16, kRayCap[2] / 16, 1, KF>(td, counts, col, lam, g, eb, kfa, lambar, gsum, first, lds); break;
+        case 3: ray_adj_tile<16, kRayCap[3] / 16, 1, KF>(td, counts, col, lam, g, eb, kfa, lambar, gsum, first, lds); break;
+        default: ray_adj_tile<32, kRayCap[4] / 32, 2, KF>(td, counts, col, lam, g, eb, kfa, lambar, gsum, first, lds);
+    }
+}
+
 // The reverse pass's per-edge inputs: the voxel totals less the own terms, or
 // (is_kf) the keyframe buffers.
 struct AdjSrc {
@@ -371,6 +413,19 @@ static void launch_adj_sel(int sel, const mrf_ctx* c, const AdjSrc& a, float* la
     ((sel == I ? launch_adj_shape<Q, I>(c, a, lambar, gsum, first, s) : void()), ...);
 }
 
+// the reverse ray phase: a small graph's short classes in one launch, the rest per class
+static void adj_small(const mrf_ctx* c, const AdjSrc& a, float* lambar, float* gsum, int first, SmallTiles& st,
+                      hipStream_t s)
+{
+    const int64_t blocks = small_tiles(c, c->adj_sel, kSmallTilesAdj, st);
+    if (blocks == 0) return;
+    ProfScope ps(c, KID_ADJS, s);
+    const auto kernel = a.is_kf ? ray_adj_small_k<true> : ray_adj_small_k<false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, s, st, (const TileDev*)c->b_tiles.p,
+                       (const int32_t*)c->b_counts.p, (const int32_t*)c->b_col.p, a.lam, (const float*)c->b_g.p, a.eb,
+                       a.kf, lambar, gsum, first);
+}
+
 template <int Q>
 static void launch_adj_class(const mrf_ctx* c, int sel, const AdjSrc& a, float* lambar, float* gsum, int first,
                              hipStream_t s)
@@ -384,7 +439,12 @@ template <int... Q>
 static void adj_classes(std::integer_sequence<int, Q...>, const mrf_ctx* c, const AdjSrc& a, float* lambar,
                         float* gsum, int first, hipStream_t s)
 {
-    (launch_adj_class<Q>(c, c->adj_sel[Q], a, lambar, gsum, first, s), ...);
+    SmallTiles st;
+    adj_small(c, a, lambar, gsum, first, st, s);
+    ((Q < kSmallClasses && st.cnt[Q < kSmallClasses ? Q : 0] > 0
+          ? void()
+          : launch_adj_class<Q>(c, c->adj_sel[Q], a, lambar, gsum, first, s)),
+     ...);
 }
 
 hipError_t launch_ray_adjoint(mrf_ctx* c, ExclSrc lam, ExclSrc ellbar, float* lambar, float* gsum, bool first,

@@ -1223,6 +1223,8 @@ static std::string kid_name(const mrf_ctx* c, int k)
     }
     if (k == KID_PAIR) return "keyframe pair averages";
     if (k == KID_KFVOX) return "kf_voxel_k";
+    if (k == KID_RAYS) return "ray_small_k";
+    if (k == KID_ADJS) return "ray_adj_small_k";
     if (k == KID_POT) return "potentials_k";
     if (k == KID_SIGMA) return "sigma_grad_k<false>";   // the profile asks for no bias gradient
     return "?";
@@ -1245,6 +1247,18 @@ static void kid_bytes(const mrf_ctx* c, int k, double* bytes, int64_t* edges)
         *edges = c->ray_cls_edges[q];
         *bytes = (c->kf_inferred ? 12.0 : 16.0) * (double)*edges + 4.0 * (double)c->ray_cls_rays[q] +
                  36.0 * (double)c->ray_cnt[q];
+    } else if (k == KID_RAYS || k == KID_ADJS) {   // as the classes they hold
+        SmallTiles st;
+        const bool adj = k == KID_ADJS;
+        small_tiles(c, adj ? c->adj_sel : c->fwd_sel, adj ? kSmallTilesAdj : kSmallTilesFwd, st);
+        for (int q = 0; q < kSmallClasses; ++q) {
+            if (st.cnt[q] == 0) continue;
+            double b = 0.0;
+            int64_t e = 0;
+            kid_bytes(c, (adj ? KID_ADJ0 : KID_RAY0) + q, &b, &e);
+            *bytes += b;
+            *edges += e;
+        }
     } else if (k == KID_PAIR) {
         // per edge: vedge 4 + weight 4 + gathered ell 4; per pair: descriptor 16 + average 8
         *edges = c->E;
@@ -1398,6 +1412,7 @@ int mrf_autotune(mrf_ctx* c, int32_t reps, void* stream)
     hipError_t e = hipEventCreate(&ev[1]);
     // after per-keyframe averaged sweeps: their ray phase only (the reverse
     // shapes are tuned on the exact scheme's sweeps)
+    static constexpr int kDefaults[kRayClasses] = {0};
     const bool kf = c->kf_inferred != 0;
     const KfSrc kfs{(const float*)c->b_kfx.p, (const int64_t*)c->b_kfxb.p};
     for (int adj = 0; adj < (kf ? 1 : 2) && e == hipSuccess; ++adj) {
@@ -1424,6 +1439,8 @@ int mrf_autotune(mrf_ctx* c, int32_t reps, void* stream)
                     best_ms = ms;
                 }
             }
+            SmallTiles st;   // a small graph's one launch beats any class's own
+            if (q < kSmallClasses && small_tiles(c, kDefaults, adj ? kSmallTilesAdj : kSmallTilesFwd, st) > 0) best = 0;
             if (adj)
                 c->adj_sel[q] = best;
             else

@@ -76,6 +76,18 @@ constexpr bool ray_shapes_valid()
 static_assert(ray_shapes_valid(), "ray shapes: 16, 32 or 64 lanes dividing the capacity; 2 rays per group only "
                                   "in reverse LDS classes; direct classes hold a ray in one group");
 
+// Small graphs: the classes up to kSmallClasses - 1 (tiles of at most 256 steps) run in
+// one launch of 256-thread blocks per phase (ray_small_k, ray_adj_small_k) instead of one
+// launch per class; a class whose selected shape is not the default keeps its own launch.  A
+// launch per class and one launch, us for 10 sweeps of one frame: 160x120 (1200 tiles)
+// 410 and 306, 320x240 (4800) 649 and 543, two of 333x251 (10500) 1161 and 1107, 640x480
+// (19200) 1654 and 1700: the longest class's registers and LDS, which all blocks then
+// take, cost more than the launches.  The reverse kernels need more of both: 3 sweeps
+// and reverse pass, 383 and 331, 624 and 577, 1097 and 1122, 1488 and 1664.
+constexpr int kSmallClasses = 5;
+constexpr int64_t kSmallTilesFwd = 12288, kSmallTilesAdj = 8192;
+static_assert(kRayCap[kSmallClasses - 1] == 256, "classes of one launch");
+
 // Edges are stored in tiles of 4x4 pixels, step-major: slot of (ray lane i,
 // step k) = tile_base + 16 k + i.  Rays of one camera reach a voxel after the
 // same number of 3D-DDA steps, so the edges a voxel receives from one tile
@@ -245,11 +257,20 @@ __host__ __device__ __forceinline__ int64_t group_slot_base_of_slot(const SlotGr
     return b;
 }
 
+// Blocks of one launch over several tile classes: class q's tiles list[off[q], + cnt[q])
+// take the blocks [blk[k], blk[k] + cnt[q]) with k counted from the longest class down;
+// every blk is a multiple of 8, so a block's XCD is that of its place in the class.
+struct SmallTiles {
+    const uint32_t* list;
+    int64_t off[kSmallClasses], cnt[kSmallClasses];
+    uint32_t blk[kSmallClasses + 1];
+};
+
 // Kernel launches that the profiler can time individually.
 enum KernelId {
     KID_VOX = 0,
     KID_RAY0, KID_ADJ0 = KID_RAY0 + kRayClasses,
-    KID_POT = KID_ADJ0 + kRayClasses, KID_SIGMA, KID_PAIR, KID_KFVOX, KID_COUNT
+    KID_POT = KID_ADJ0 + kRayClasses, KID_RAYS, KID_ADJS, KID_SIGMA, KID_PAIR, KID_KFVOX, KID_COUNT
 };
 
 // HIP events recorded around launches on the stream they run on.
@@ -435,6 +456,23 @@ hipError_t launch_scatter_by_slot(const uint32_t* slot, const float* in, int64_t
 // their weights, work classes and message-buffer indices (after build_classes,
 // with the sorted voxel keys still in b_lambar and chord lengths in b_kfw)
 hipError_t build_keyframe_pairs(mrf_ctx* c, hipStream_t s);
+
+// the classes of a small graph's one launch (none: a large graph); blocks in all
+inline int64_t small_tiles(const mrf_ctx* c, const int* sel, int64_t limit, SmallTiles& t)
+{
+    t = SmallTiles{};
+    t.list = (const uint32_t*)c->b_ray_list.p;
+    int64_t n = 0, blocks = 0;
+    for (int q = 0; q < kSmallClasses; ++q) n += c->ray_cnt[q];
+    for (int k = 0; k < kSmallClasses; ++k) {
+        const int q = kSmallClasses - 1 - k;
+        t.off[q] = c->ray_off[q];
+        t.cnt[q] = n <= limit && sel[q] == 0 ? c->ray_cnt[q] : 0;
+        blocks += (t.cnt[q] + 7) / 8 * 8;
+        t.blk[k + 1] = (uint32_t)blocks;
+    }
+    return blocks;
+}
 
 inline ExclDev excl_dev(const mrf_ctx* c, ExclSrc x)
 {

@@ -698,18 +698,11 @@ __global__ __launch_bounds__(256) void ray_k(const uint32_t* __restrict__ list, 
 // on its LDS column and writes ell back into that column (0 past the ray),
 // and the block stores the tile coalesced.
 template <int G, int IPL, bool KF>
-__global__ __launch_bounds__(kTile * G) void ray_lds_k(const uint32_t* __restrict__ list, int64_t ntiles,
-                                                       const TileDev* __restrict__ tiles,
-                                                       const int32_t* __restrict__ counts,
-                                                       const int32_t* __restrict__ col, ExclDev lam, KfSrc kf,
-                                                       const float* __restrict__ g, float* __restrict__ ell)
+__device__ __forceinline__ void ray_tile(const TileDev& td, const int32_t* __restrict__ counts,
+                                         const int32_t* __restrict__ col, const ExclDev& lam, const KfSrc& kf,
+                                         const float* __restrict__ g, float* __restrict__ ell, float* sl, float* sg)
 {
     constexpr int NT = kTile * G;
-    __shared__ float sl[kTile * G * IPL];
-    __shared__ float sg[kTile * G * IPL];
-    const int64_t ti = xcd_block(blockIdx.x, gridDim.x);
-    if (ti >= ntiles) return;   // whole block
-    const TileDev td = tiles[list[ti]];
     const int nf = kTile * td.len;   // 1 <= td.len <= G * IPL by class
     const int i = (int)threadIdx.x / G;   // this group's ray: lane i of the tile
     const int gl = (int)threadIdx.x % G;
@@ -746,6 +739,48 @@ __global__ __launch_bounds__(kTile * G) void ray_lds_k(const uint32_t* __restric
     }
     __syncthreads();
     tile_store<NT, IPL, IPL>(ell, td.base, nf, [&](int, int at) { return sl[at]; });
+}
+
+template <int G, int IPL, bool KF>
+__global__ __launch_bounds__(kTile * G) void ray_lds_k(const uint32_t* __restrict__ list, int64_t ntiles,
+                                                       const TileDev* __restrict__ tiles,
+                                                       const int32_t* __restrict__ counts,
+                                                       const int32_t* __restrict__ col, ExclDev lam, KfSrc kf,
+                                                       const float* __restrict__ g, float* __restrict__ ell)
+{
+    __shared__ float sl[kTile * G * IPL];
+    __shared__ float sg[kTile * G * IPL];
+    const int64_t ti = xcd_block(blockIdx.x, gridDim.x);
+    if (ti >= ntiles) return;   // whole block
+    const TileDev td = tiles[list[ti]];
+    ray_tile<G, IPL, KF>(td, counts, col, lam, kf, g, ell, sl, sg);
+}
+
+// The short classes of a small graph in one launch, a block per tile.  Such a phase is
+// a few microseconds of launch, dependent loads and scans whatever its tiles: one launch
+// of them instead of one per class.
+template <bool KF>
+__global__ __launch_bounds__(256) void ray_small_k(const SmallTiles st, const TileDev* __restrict__ tiles,
+                                                   const int32_t* __restrict__ counts,
+                                                   const int32_t* __restrict__ col, ExclDev lam, KfSrc kf,
+                                                   const float* __restrict__ g, float* __restrict__ ell)
+{
+    constexpr int CAP = kRayCap[kSmallClasses - 1];
+    __shared__ float sl[kTile * CAP];
+    __shared__ float sg[kTile * CAP];
+    int k = 0;   // uniform: the class whose blocks hold this one
+    while (k + 1 < kSmallClasses && blockIdx.x >= st.blk[k + 1]) ++k;
+    const int q = kSmallClasses - 1 - k;
+    const int64_t lt = xcd_block(blockIdx.x - st.blk[k], st.blk[k + 1] - st.blk[k]);
+    if (lt >= st.cnt[q]) return;   // whole block
+    const TileDev td = tiles[st.list[st.off[q] + lt]];
+    switch (q) {
+        case 0: ray_tile<16, kRayCap[0] / 16, KF>(td, counts, col, lam, kf, g, ell, sl, sg); break;
+        case 1: ray_tile<16, kRayCap[1] / 16, KF>(td, counts, col, lam, kf, g, ell, sl, sg); break;
+        case 2: ray_tile<16, kRayCap[2] / 16, KF>(td, counts, col, lam, kf, g, ell, sl, sg); break;
+        case 3: ray_tile<16, kRayCap[3] / 16, KF>(td, counts, col, lam, kf, g, ell, sl, sg); break;
+        default: ray_tile<16, kRayCap[4] / 16, KF>(td, counts, col, lam, kf, g, ell, sl, sg);
+    }
 }
 
 // The voxel -> ray messages one ray-phase launch reads: per-edge exclusion
@@ -853,7 +888,17 @@ static hipError_t ray_phase(mrf_ctx* c, const RaySrc& src, float* ell, bool plai
 {
     int64_t off[kRayClasses] = {0}, cnt[kRayClasses];
     if (!plain) {
-        for (int k = 0; k < kRayClasses; ++k) cnt[k] = c->ray_cnt[k];
+        SmallTiles st;
+        const int64_t blocks = small_tiles(c, c->fwd_sel, kSmallTilesFwd, st);
+        for (int k = 0; k < kRayClasses; ++k)
+            cnt[k] = k < kSmallClasses && st.cnt[k] > 0 ? 0 : c->ray_cnt[k];
+        if (blocks > 0) {
+            ProfScope ps(c, KID_RAYS, s);
+            const auto kernel = src.is_kf ? ray_small_k<true> : ray_small_k<false>;
+            hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, s, st, (const TileDev*)c->b_tiles.p,
+                               (const int32_t*)c->b_counts.p, (const int32_t*)c->b_col.p, src.lam, src.kf,
+                               (const float*)c->b_g.p, ell);
+        }
         ray_classes(c, off, cnt, src, ell, false, s);
     } else {
         // the plain per-frame schedule: one launch per frame (per class), untuned shapes

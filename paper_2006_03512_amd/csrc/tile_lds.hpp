@@ -191,13 +191,12 @@ __device__ __forceinline__ float excl_value(int32_t col, float2 t, float own, in
 }
 
 // The fetched values into the LDS image of the tile (layout lds_at<IPL>).
-// Every round is written, also past nf: the image holds NT NR words, and its
+// Every round is written, also past nf: the image holds at least NT NR words, and its
 // words past the tile are never read as data (the rays' steps end inside it).
 // No branch, so the rounds' LDS words are computed once for all arrays.
-template <int NT, int NR, int IPL, int N>
-__device__ __forceinline__ void tile_to_lds(float (&lds)[N], const float (&v)[NR])
+template <int NT, int NR, int IPL>
+__device__ __forceinline__ void tile_to_lds(float* lds, const float (&v)[NR])
 {
-    static_assert(N >= NT * NR, "the LDS image holds every round");
     constexpr int W = tile_vec<NR>();
 #pragma unroll
     for (int q = 0; q < NR / W; ++q) {
