@@ -149,7 +149,6 @@ static hipError_t enqueue_forward(mrf_ctx* c, int K, int keep, bool plain, hipSt
 {
     hipError_t e;
     const float* theta = (const float*)c->b_theta.p;
-    if ((e = launch_pair(theta, (float2*)c->b_theta2.p, c->V, s)) != hipSuccess) return e;
     if ((e = launch_potentials(c, s)) != hipSuccess) return e;
     for (int k = 1; k <= K; ++k) {
         if (k > 1 && (e = launch_voxel_phase(c, ell_slot(c, K, k - 1, keep),
@@ -158,7 +157,6 @@ static hipError_t enqueue_forward(mrf_ctx* c, int K, int keep, bool plain, hipSt
         if ((e = launch_ray_phase(c, lam_src(c, K, k, keep), ell_slot(c, K, k, keep), plain, s)) != hipSuccess)
             return e;
     }
-    if ((e = launch_copy((float*)c->b_L.p, theta, c->V, s)) != hipSuccess) return e;
     return launch_voxel_phase(c, ell_slot(c, K, K, keep), VoxOut{theta, nullptr, (float*)c->b_L.p, nullptr}, s);
 }
 
@@ -178,7 +176,6 @@ static hipError_t enqueue_forward_kf(mrf_ctx* c, int K, int keep, bool plain, hi
     double* Mlast = (double*)c->b_pair_m.p;
     float* x = (float*)c->b_kfx.p;
     const KfSrc kf{x, (const int64_t*)c->b_kfxb.p};
-    if ((e = launch_pair(theta, (float2*)c->b_theta2.p, c->V, s)) != hipSuccess) return e;
     if ((e = launch_potentials(c, s)) != hipSuccess) return e;
     for (int k = 1; k <= K; ++k) {
         float* ell = ell_slot(c, K, k, false);
@@ -192,9 +189,25 @@ static hipError_t enqueue_forward_kf(mrf_ctx* c, int K, int keep, bool plain, hi
         }
         if (e != hipSuccess) return e;
     }
-    if ((e = launch_copy((float*)c->b_L.p, theta, c->V, s)) != hipSuccess) return e;
     if ((e = launch_pair_phase(c, (const float*)c->b_ell.p, w, Mlast, s)) != hipSuccess) return e;
     return launch_kf_voxel(c, Mlast, theta, nullptr, (float*)c->b_L.p, s);
+}
+
+// The captured sweeps run on the caller's stream (an internal stream beside it costs an
+// event and a wait on each side: 116 us for 5 sweeps of a 64x48 frame, 66 without them and
+// with the inputs in one launch).  Launches of one context on
+// different streams stay in order, as they were on one internal stream.
+static hipError_t after_last_graph(mrf_ctx* c, hipStream_t s)
+{
+    return c->launched ? hipStreamWaitEvent(s, c->ev_out, 0) : hipSuccess;
+}
+
+static hipError_t launch_graph(mrf_ctx* c, hipStream_t s)
+{
+    hipError_t e = hipGraphLaunch(c->gexec, s);
+    if (e == hipSuccess) e = hipEventRecord(c->ev_out, s);
+    if (e == hipSuccess) c->launched = 1;
+    return e;
 }
 
 static const float* final_ell(const mrf_ctx* c) { return c->inferred ? (const float*)c->b_ell.p : nullptr; }
@@ -234,7 +247,6 @@ int mrf_create(mrf_ctx** out)
     // device with the device current (a failed lookup only disables that call)
     if (e == hipSuccess) static_scratch_init(c->device);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->aux, hipStreamNonBlocking);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_in, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_out, hipEventDisableTiming);
     if (e != hipSuccess) {
         int rc = hip_fail(e, "mrf_create");
@@ -266,7 +278,6 @@ void mrf_destroy(mrf_ctx* c)
                      &c->b_kfxr, &c->b_kfy, &c->b_kfws};
     for (DevBuf* b : all) free_buf(*b);
     for (auto& b : c->b_host_in) free_buf(b);
-    if (c->ev_in) hipEventDestroy(c->ev_in);
     if (c->ev_out) hipEventDestroy(c->ev_out);
     if (c->aux) hipStreamDestroy(c->aux);
     delete c;
@@ -857,12 +868,8 @@ int mrf_infer_sensor(mrf_ctx* c, const float* prior_logit, const float* sigma_ta
             HCK(ensure(c->b_tsum, need_tot), "mrf_infer: alloc voxel totals");
         }
     }
-    HCK(launch_copy((float*)c->b_theta.p, prior_logit, c->V, s), "mrf_infer: copy prior");
-    HCK(launch_copy((float*)c->b_sigma.p, sigma_table, table_entries(c), s), "mrf_infer: copy sigma");
-    if (bias_table)
-        HCK(launch_copy((float*)c->b_bias.p, bias_table, table_entries(c), s), "mrf_infer: copy bias");
-    else
-        HCK(launch_fill((float*)c->b_bias.p, 0.0f, table_entries(c), s), "mrf_infer: zero bias");
+    HCK(after_last_graph(c, s), "mrf_infer: wait");
+    HCK(launch_infer_inputs(c, prior_logit, sigma_table, bias_table, s), "mrf_infer: inputs");
     if (c->schedule == MRF_SCHED_PLAIN) {
         HCK(enqueue_forward(c, sweeps, keep, true, s), "mrf_infer: sweeps");
     } else {
@@ -884,11 +891,7 @@ int mrf_infer_sensor(mrf_ctx* c, const float* prior_logit, const float* sigma_ta
             c->g_ckpt = keep;
             c->g_key = key;
         }
-        HCK(hipEventRecord(c->ev_in, s), "mrf_infer: event");
-        HCK(hipStreamWaitEvent(c->aux, c->ev_in, 0), "mrf_infer: wait");
-        HCK(hipGraphLaunch(c->gexec, c->aux), "mrf_infer: graph launch");
-        HCK(hipEventRecord(c->ev_out, c->aux), "mrf_infer: event");
-        HCK(hipStreamWaitEvent(s, c->ev_out, 0), "mrf_infer: wait");
+        HCK(launch_graph(c, s), "mrf_infer: graph launch");
     }
     c->inferred = 1;
     c->kf_inferred = 0;
@@ -918,12 +921,8 @@ int mrf_infer_keyframe_avg(mrf_ctx* c, const float* prior_logit, const float* si
             HCK(ensure(c->b_ckpt, need), "mrf_infer_keyframe_avg: alloc checkpoints");
         }
     }
-    HCK(launch_copy((float*)c->b_theta.p, prior_logit, c->V, s), "mrf_infer_keyframe_avg: copy prior");
-    HCK(launch_copy((float*)c->b_sigma.p, sigma_table, table_entries(c), s), "mrf_infer_keyframe_avg: copy sigma");
-    if (bias_table)
-        HCK(launch_copy((float*)c->b_bias.p, bias_table, table_entries(c), s), "mrf_infer_keyframe_avg: copy bias");
-    else
-        HCK(launch_fill((float*)c->b_bias.p, 0.0f, table_entries(c), s), "mrf_infer_keyframe_avg: zero bias");
+    HCK(after_last_graph(c, s), "mrf_infer_keyframe_avg: wait");
+    HCK(launch_infer_inputs(c, prior_logit, sigma_table, bias_table, s), "mrf_infer_keyframe_avg: inputs");
     if (c->schedule == MRF_SCHED_PLAIN) {
         HCK(enqueue_forward_kf(c, sweeps, keep, true, s), "mrf_infer_keyframe_avg: sweeps");
     } else {
@@ -947,11 +946,7 @@ int mrf_infer_keyframe_avg(mrf_ctx* c, const float* prior_logit, const float* si
             c->g_ckpt = keep;
             c->g_key = key;
         }
-        HCK(hipEventRecord(c->ev_in, s), "mrf_infer_keyframe_avg: event");
-        HCK(hipStreamWaitEvent(c->aux, c->ev_in, 0), "mrf_infer_keyframe_avg: wait");
-        HCK(hipGraphLaunch(c->gexec, c->aux), "mrf_infer_keyframe_avg: graph launch");
-        HCK(hipEventRecord(c->ev_out, c->aux), "mrf_infer_keyframe_avg: event");
-        HCK(hipStreamWaitEvent(s, c->ev_out, 0), "mrf_infer_keyframe_avg: wait");
+        HCK(launch_graph(c, s), "mrf_infer_keyframe_avg: graph launch");
     }
     c->inferred = 1;
     c->kf_inferred = 1;
@@ -968,8 +963,7 @@ int mrf_marginals(mrf_ctx* c, float* p, float* logit, void* stream)
     if (!c) return fail(MRF_EINVAL, "mrf_marginals: null context");
     if (!c->inferred) return fail(MRF_ESTATE, "mrf_marginals: call mrf_infer first");
     hipStream_t s = (hipStream_t)stream;
-    if (p) HCK(launch_sigmoid((const float*)c->b_L.p, p, c->V, s), "mrf_marginals");
-    if (logit) HCK(launch_copy(logit, (const float*)c->b_L.p, c->V, s), "mrf_marginals");
+    HCK(launch_marginals((const float*)c->b_L.p, p, logit, c->V, s), "mrf_marginals");
     return MRF_OK;
 }
 
@@ -1040,8 +1034,7 @@ int mrf_backward_sensor(mrf_ctx* c, const float* dlogit, float* dprior, float* d
     float2* seed = tbar + c->V;
     float* lbuf[2] = {(float*)c->b_lambar.p, (float*)c->b_ellbar.p};
     // d loss / d theta starts at d loss / d L; d loss / d ell^(K)_e = d loss / d L_v(e)
-    HCK(launch_copy(thetabar, dlogit, c->V, s), "mrf_backward: seed");
-    HCK(launch_pair(dlogit, seed, c->V, s), "mrf_backward: seed");
+    HCK(launch_reverse_seed(dlogit, thetabar, seed, c->V, s), "mrf_backward: seed");
     ExclSrc eb{seed, nullptr};
     hipError_t e = hipSuccess;
     for (int k = K; k >= 1 && e == hipSuccess; --k) {

@@ -293,8 +293,9 @@ struct Profiler {
 
 struct mrf_ctx {
     int device = 0;
-    hipStream_t aux = nullptr;    // internal stream used for graph capture/launch
-    hipEvent_t ev_in = nullptr, ev_out = nullptr;
+    hipStream_t aux = nullptr;    // internal stream used for graph capture
+    hipEvent_t ev_out = nullptr;  // recorded after every graph launch
+    int launched = 0;
 
     // graph description
     int32_t n_scenes = 0;
@@ -486,8 +487,11 @@ hipError_t launch_copy(float* dst, const float* src, int64_t n, hipStream_t s);
 // voxel phase: per touched voxel v, sum_v = FP64 sum of in over its edges,
 // written as VoxOut describes
 hipError_t launch_voxel_phase(mrf_ctx* c, const float* in, VoxOut out, hipStream_t s);
-// out[v] = (in[v], 0): a per-voxel array as a total pair
-hipError_t launch_pair(const float* in, float2* out, int64_t n, hipStream_t s);
+// an inference's prior and tables into the context (theta, its pairs, the beliefs of
+// untouched voxels, sigma, bias); bias null: zero
+hipError_t launch_infer_inputs(mrf_ctx* c, const float* prior, const float* sigma, const float* bias, hipStream_t s);
+// thetabar = dlogit, seed = (dlogit, 0) when not null
+hipError_t launch_reverse_seed(const float* dlogit, float* thetabar, float2* seed, int64_t n, hipStream_t s);
 hipError_t launch_ray_phase(mrf_ctx* c, ExclSrc lam, float* ell, bool plain, hipStream_t s);
 // one class of the ray phase / reverse pass with launch shape `sel` (autotuner)
 hipError_t launch_ray_class_shape(const mrf_ctx* c, int q, int sel, ExclSrc lam, float* ell, hipStream_t s);
@@ -508,7 +512,8 @@ hipError_t launch_kf_voxel(mrf_ctx* c, const double* M, const float* theta, floa
 hipError_t launch_kf_voxel_rev(mrf_ctx* c, const double* sp, float* acc, float* y, hipStream_t s);
 // out_e = x[xb[frame of e] + col_e] on every edge slot (0 on padding)
 hipError_t launch_excl_kf(const mrf_ctx* c, KfSrc x, float* out, hipStream_t s);
-hipError_t launch_sigmoid(const float* L, float* p, int64_t n, hipStream_t s);
+// p = sigmoid(L), logit = L; either may be null
+hipError_t launch_marginals(const float* L, float* p, float* logit, int64_t n, hipStream_t s);
 
 // adjoint_kernels.hip
 // the reverse ray phase with per-keyframe averaged messages
