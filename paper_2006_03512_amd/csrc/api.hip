@@ -55,7 +55,8 @@ std::vector<uint64_t> graph_key(const mrf_ctx* c, int K, int keep)
                                  &c->b_ckpt,   &c->b_tsum,  &c->b_tbar,  &c->b_tiles, &c->b_counts, &c->b_theta2,
                                  &c->b_kfw,    &c->b_pair_m, &c->b_pair_x, &c->b_kfx, &c->b_kfxb, &c->b_kf_vox};
     for (const mrf::DevBuf* b : bufs) k.push_back((uint64_t)(uintptr_t)b->p);
-    for (const mrf::DevBuf* b : {&c->b_ray_list, &c->b_hubsum}) k.push_back((uint64_t)(uintptr_t)b->p);
+    k.push_back((uint64_t)c->by_runs);
+    for (const mrf::DevBuf* b : {&c->b_ray_list, &c->b_hubsum, &c->b_runrow, &c->b_runmask}) k.push_back((uint64_t)(uintptr_t)b->p);
     for (const mrf::SegList* l : {&c->vox, &c->pair}) {
         k.push_back((uint64_t)(uintptr_t)l->desc.p);
         k.push_back((uint64_t)(uintptr_t)l->hub.p);
@@ -273,7 +274,8 @@ void mrf_destroy(mrf_ctx* c)
                      &c->b_vptr, &c->b_theta, &c->b_theta2, &c->b_L, &c->b_thetabar, &c->b_sigma, &c->b_bias,
                      &c->b_ckpt, &c->b_tsum, &c->b_tbar, &c->b_metric, &c->b_bricks,
                      &c->b_ellbar, &c->b_lambar, &c->b_gsum, &c->b_tmp64, &c->b_part, &c->b_sigpart,
-                     &c->b_misc, &c->b_ray_list, &c->vox.desc, &c->vox.hub, &c->pair.desc, &c->pair.hub, &c->b_hubsum, &c->b_tiles, &c->b_tbase, &c->b_export,
+                     &c->b_misc, &c->b_ray_list, &c->vox.desc, &c->vox.hub, &c->pair.desc, &c->pair.hub, &c->b_hubsum, &c->b_runrow,
+                     &c->b_runmask, &c->b_rptr, &c->b_tiles, &c->b_tbase, &c->b_export,
                      &c->b_kfw, &c->b_kflen, &c->b_pair_m, &c->b_pair_x, &c->b_kfx, &c->b_kfxb, &c->b_kf_vox,
                      &c->b_kfxr, &c->b_kfy, &c->b_kfws};
     for (DevBuf* b : all) free_buf(*b);
@@ -582,7 +584,10 @@ static int build_impl(mrf_ctx* c, const mrf_scene* scenes, int32_t n_scenes, con
     // one entry more: the keyframe-pair build keeps an exclusive count of E + 1 entries in each
     HCK(ensure(c->b_lam, e4 + 16), "mrf_build: alloc lam");
     HCK(ensure(c->b_ell, e4 + 16), "mrf_build: alloc ell");
-    HCK(ensure(c->b_vedge, e4 + 16), "mrf_build: alloc vedge");
+    // large graphs keep their lists as runs, but not where keyframe pairs or further frames
+    // are built on the lists of edges
+    c->by_runs = incidence_by_runs(S) && !c->kf && reserve == 0 ? 1 : 0;
+    if (!c->by_runs) HCK(ensure(c->b_vedge, e4 + 16), "mrf_build: alloc vedge");
     HCK(ensure(c->b_ellbar, e4), "mrf_build: alloc ellbar");
     HCK(ensure(c->b_lambar, e4), "mrf_build: alloc lambar");
     HCK(ensure(c->b_gsum, e4), "mrf_build: alloc gsum");
@@ -606,7 +611,8 @@ static int build_impl(mrf_ctx* c, const mrf_scene* scenes, int32_t n_scenes, con
 
     // voxel -> ray incidence; the message buffers are free during the build and hold
     // the sort's data (b_lambar: the sorted keys, for the keyframe pairs)
-    HCK(build_incidence(c, 0, S, E, (uint32_t*)c->b_lambar.p, (uint32_t*)c->b_vedge.p, (int64_t*)c->b_vptr.p, c->sg, s),
+    HCK(build_incidence(c, 0, S, E, (uint32_t*)c->b_lambar.p, (uint32_t*)c->b_vedge.p, (int64_t*)c->b_vptr.p, c->sg,
+                        c->by_runs != 0, s),
         "mrf_build: incidence");
     for (int g = 1; g < c->sg.n; ++g) {   // list position of each group's first key
         const int64_t k0 = c->scenes_h[c->group_scene[g]].key_base;
@@ -720,6 +726,11 @@ int mrf_add_frames(mrf_ctx* c, int32_t n_frames, const float* depth, const doubl
     c->kfws_ready = 0;
     ++c->gen;
 
+    if (c->by_runs) {   // additions merge lists of edges
+        HCK(ensure(c->b_vedge, sizeof(uint32_t) * (size_t)c->E), "mrf_add_frames: alloc vedge");
+        HCK(expand_runs(c, (uint32_t*)c->b_vedge.p, s), "mrf_add_frames: lists");
+        c->by_runs = 0;
+    }
     const int last = c->n_scenes - 1;
     const SceneDev& sd = c->scenes_h[last];
     const int64_t hw = (int64_t)sd.W * sd.H;
@@ -814,7 +825,7 @@ int mrf_add_frames(mrf_ctx* c, int32_t n_frames, const float* depth, const doubl
     uint32_t* nvals = (uint32_t*)c->b_gsum.p;     // their slots less S0
     hipError_t e = ensure(c->b_export, sizeof(int64_t) * (size_t)(c->Vk + 1));
     int64_t* nvptr = (int64_t*)c->b_export.p;
-    if (e == hipSuccess) e = build_incidence(c, S0, S1 - S0, E1 - E0, nkeys, nvals, nvptr, SlotGroups{}, s);
+    if (e == hipSuccess) e = build_incidence(c, S0, S1 - S0, E1 - E0, nkeys, nvals, nvptr, SlotGroups{}, false, s);
     uint32_t* okeys = (uint32_t*)c->b_ell.p;      // keys of the existing entries
     uint32_t* merged = (uint32_t*)c->b_lam.p;
     if (e == hipSuccess) e = launch_entry_keys(c, (const uint32_t*)c->b_vedge.p, E0, okeys, s);
@@ -1199,7 +1210,7 @@ extern "C" {
 
 static std::string kid_name(const mrf_ctx* c, int k)
 {
-    if (k == KID_VOX) return "seg_sum_k";
+    if (k == KID_VOX) return c->by_runs ? "run_sum_k" : "seg_sum_k";
     auto ray_name = [](const char* direct, const char* lds, int q, RayShape sh, bool adj) {
         std::string n = std::string(ray_class_lds(q) ? lds : direct) + "<" + std::to_string(sh.g) + "," +
                         std::to_string(kRayCap[q] / sh.g);
@@ -1231,7 +1242,8 @@ static void kid_bytes(const mrf_ctx* c, int k, double* bytes, int64_t* edges)
     if (k == KID_VOX) {
         // per edge: vedge 4 + gathered message 4; per voxel: descriptor 16 + base 4 + total 4
         *edges = c->E;
-        *bytes = 8.0 * (double)*edges + 24.0 * (double)c->stats.n_touched_voxels;
+        *bytes = (c->by_runs ? 4.0 : 8.0) * (double)*edges + 24.0 * (double)c->stats.n_touched_voxels;
+        if (c->by_runs) *bytes += 6.0 * (double)c->n_runs;   // row 4 + mask 2 per run instead of vedge 4 per edge
     } else if (k >= KID_RAY0 && k < KID_RAY0 + kRayClasses) {
         const int q = k - KID_RAY0;
         // per edge: col 4 + own ell 4 + g 4 + ell 4 (voxel totals: counted once per voxel

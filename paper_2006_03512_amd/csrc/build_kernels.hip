@@ -1271,7 +1271,8 @@ struct LoadPop {
 
 // Sorted runs written out as list entries: a block takes SC_TILE runs (boff[block]
 // entries before them), a wave 64 of them at a time through LDS, so that the
-// entries leave as contiguous stores.  The first run of a key sets vptr[key].
+// entries leave as contiguous stores.  The first run of a key sets vptr[key] (key
+// null: not again).
 __global__ __launch_bounds__(256) void runs_expand_k(const uint32_t* __restrict__ key,
                                                      const uint32_t* __restrict__ row,
                                                      const uint16_t* __restrict__ mask, int64_t n,
@@ -1290,10 +1291,10 @@ __global__ __launch_bounds__(256) void runs_expand_k(const uint32_t* __restrict_
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
         const int64_t at = r0 + r * 64 + lane, ic = at < n ? at : n - 1;
-        k[r] = key[ic];
+        k[r] = key ? key[ic] : 0u;
         rw[r] = row[ic];
         m[r] = at < n ? mask[ic] : 0u;
-        first[r] = at < n && (ic == 0 || key[ic - 1] != k[r]);
+        first[r] = key && at < n && (ic == 0 || key[ic - 1] != k[r]);
         sum += __popc(m[r]);
     }
 #pragma unroll
@@ -1335,9 +1336,39 @@ __global__ __launch_bounds__(256) void runs_expand_k(const uint32_t* __restrict_
     }
 }
 
+// The first run of a key sets vptr[key] (its first entry) and rptr[key] (the run).
+__global__ __launch_bounds__(SC_T) void runs_mark_k(const uint32_t* __restrict__ key,
+                                                    const uint16_t* __restrict__ mask, int64_t n,
+                                                    const int64_t* __restrict__ boff, int64_t* __restrict__ vptr,
+                                                    uint32_t* __restrict__ rptr)
+{
+    const int64_t base = (int64_t)blockIdx.x * SC_TILE + (int64_t)threadIdx.x * SC_IPT;
+    uint32_t k[SC_IPT + 1];
+    int pc[SC_IPT], sum = 0;
+    k[0] = base > 0 && base - 1 < n ? key[base - 1] : 0xffffffffu;   // no voxel's key
+#pragma unroll
+    for (int q = 0; q < SC_IPT; ++q) {
+        const int64_t i = base + q;
+        k[q + 1] = i < n ? key[i] : 0u;
+        pc[q] = i < n ? __popc((uint32_t)mask[i]) : 0;
+        sum += pc[q];
+    }
+    int64_t tot;
+    int64_t at = boff[blockIdx.x] + block_excl_scan_i64(sum, &tot);
+#pragma unroll
+    for (int q = 0; q < SC_IPT; ++q) {
+        if (base + q < n && k[q] != k[q + 1]) {
+            vptr[k[q + 1]] = at;
+            rptr[k[q + 1]] = (uint32_t)(base + q);
+        }
+        at += pc[q];
+    }
+}
+
 // vptr of the keys without a run (all ones so far): that of the next key with one,
-// found among the sorted runs, or the number of entries
-__global__ void vptr_gaps_k(const uint32_t* __restrict__ key, int64_t n, int64_t V, int64_t entries, int64_t* vptr)
+// found among the sorted runs, or the number of entries; rptr (may be null) likewise
+__global__ void vptr_gaps_k(const uint32_t* __restrict__ key, int64_t n, int64_t V, int64_t entries, int64_t* vptr,
+                            uint32_t* rptr)
 {
     const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (v > V || vptr[v] != -1) return;
@@ -1350,6 +1381,7 @@ __global__ void vptr_gaps_k(const uint32_t* __restrict__ key, int64_t n, int64_t
             hi = mid;
     }
     vptr[v] = lo < n ? vptr[key[lo]] : entries;
+    if (rptr) rptr[v] = (uint32_t)lo;
 }
 
 // Slots are sorted one by one where there are few of them: the runs cost six more
@@ -1367,7 +1399,7 @@ static int key_bits(int64_t maxval)
 }
 
 hipError_t build_incidence(mrf_ctx* c, int64_t s0, int64_t n, int64_t edges, uint32_t* keys, uint32_t* vals,
-                           int64_t* vptr, const SlotGroups& groups, hipStream_t s)
+                           int64_t* vptr, const SlotGroups& groups, bool keep_runs, hipStream_t s)
 {
     hipError_t e;
     const int bits = key_bits(c->Vk);
@@ -1410,6 +1442,19 @@ hipError_t build_incidence(mrf_ctx* c, int64_t s0, int64_t n, int64_t edges, uin
     int64_t nr = 0;
     if ((e = hipMemcpyAsync(&nr, boff + nb, sizeof(int64_t), hipMemcpyDeviceToHost, s)) != hipSuccess) return e;
     if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
+    if (keep_runs && nr >= (int64_t(1) << 32)) {   // more than rptr's 32 bits: lists of edges after all
+        if ((e = ensure(c->b_vedge, sizeof(uint32_t) * (size_t)n + 16)) != hipSuccess) return e;
+        vals = (uint32_t*)c->b_vedge.p;
+        keep_runs = false;
+        c->by_runs = 0;
+    }
+    if (keep_runs) {
+        if ((e = ensure(c->b_runrow, sizeof(uint32_t) * (size_t)nr)) != hipSuccess) return e;
+        if ((e = ensure(c->b_runmask, sizeof(uint16_t) * (size_t)nr)) != hipSuccess) return e;
+        if ((e = ensure(c->b_rptr, sizeof(uint32_t) * (size_t)(c->Vk + 1))) != hipSuccess) return e;
+        c->n_runs = nr;
+    }
+    uint32_t* rptr = keep_runs ? (uint32_t*)c->b_rptr.p : nullptr;
     if ((e = launch_fill_u32((uint32_t*)vptr, 0xffffffffu, 2 * (c->Vk + 1), s)) != hipSuccess) return e;
     if (nr > 0) {
         hipLaunchKernelGGL(runs_pack_k, dim3((unsigned)nb), dim3(256), 0, s, (const uint32_t*)gkey,
@@ -1419,21 +1464,47 @@ hipError_t build_incidence(mrf_ctx* c, int64_t s0, int64_t n, int64_t edges, uin
         int64_t* offs = (int64_t*)c->b_tmp64.p;
         const RadixTables t{(int32_t*)(offs + nhr + 1), offs, (int64_t*)c->b_misc.p};
         int at = first;
-        for (int p = 0; p < passes; ++p, at ^= 1)
+        for (int p = 0; p < passes; ++p, at ^= 1) {
+            if (keep_runs && p == passes - 1) {   // the last pass: to where they stay (at ^ 1 is 0)
+                lr[0] = (uint32_t*)c->b_runrow.p;
+                lm[0] = (uint16_t*)c->b_runmask.p;
+            }
             if ((e = radix_pass<true>(lk[at], lr[at], lm[at], lk[at ^ 1], lr[at ^ 1], lm[at ^ 1], nr, 8 * p, t,
                                       SlotGroups{}, s)) != hipSuccess)
                 return e;
+        }
         const int64_t nbr = cdiv(nr, SC_TILE);
         int64_t* bsum = (int64_t*)c->b_misc.p;
         int64_t* eoff = bsum + nbr;
         hipLaunchKernelGGL(scan_reduce_k<LoadPop>, dim3((unsigned)nbr), dim3(SC_T), 0, s, LoadPop{lm[0]}, nr, bsum);
         if ((e = scan_rec(LoadI64{bsum}, nbr, eoff, eoff + nbr + 1, s)) != hipSuccess) return e;
-        hipLaunchKernelGGL(runs_expand_k, dim3((unsigned)nbr), dim3(256), 0, s, (const uint32_t*)lk[0],
-                           (const uint32_t*)lr[0], (const uint16_t*)lm[0], nr, (const int64_t*)eoff, groups, keys,
-                           vals, vptr);
+        if (keep_runs)
+            hipLaunchKernelGGL(runs_mark_k, dim3((unsigned)nbr), dim3(SC_T), 0, s, (const uint32_t*)lk[0],
+                               (const uint16_t*)lm[0], nr, (const int64_t*)eoff, vptr, rptr);
+        else
+            hipLaunchKernelGGL(runs_expand_k, dim3((unsigned)nbr), dim3(256), 0, s, (const uint32_t*)lk[0],
+                               (const uint32_t*)lr[0], (const uint16_t*)lm[0], nr, (const int64_t*)eoff, groups, keys,
+                               vals, vptr);
     }
     hipLaunchKernelGGL(vptr_gaps_k, dim3((unsigned)cdiv(c->Vk + 1, 256)), dim3(256), 0, s, (const uint32_t*)lk[0], nr,
-                       c->Vk, edges, vptr);
+                       c->Vk, edges, vptr, rptr);
+    return hipGetLastError();
+}
+
+hipError_t expand_runs(mrf_ctx* c, uint32_t* vals, hipStream_t s)
+{
+    if (c->n_runs == 0) return hipSuccess;
+    const int64_t nbr = cdiv(c->n_runs, SC_TILE);
+    hipError_t e = ensure(c->b_misc, sizeof(int64_t) * (size_t)(2 * nbr + 1) + scan_tmp_bytes(nbr));
+    if (e != hipSuccess) return e;
+    int64_t* bsum = (int64_t*)c->b_misc.p;
+    int64_t* eoff = bsum + nbr;
+    const uint16_t* mask = (const uint16_t*)c->b_runmask.p;
+    hipLaunchKernelGGL(scan_reduce_k<LoadPop>, dim3((unsigned)nbr), dim3(SC_T), 0, s, LoadPop{mask}, c->n_runs, bsum);
+    if ((e = scan_rec(LoadI64{bsum}, nbr, eoff, eoff + nbr + 1, s)) != hipSuccess) return e;
+    hipLaunchKernelGGL(runs_expand_k, dim3((unsigned)nbr), dim3(256), 0, s, (const uint32_t*)nullptr,
+                       (const uint32_t*)c->b_runrow.p, mask, c->n_runs, (const int64_t*)eoff, c->sg,
+                       (uint32_t*)nullptr, vals, (int64_t*)nullptr);
     return hipGetLastError();
 }
 
@@ -1570,7 +1641,7 @@ struct PartLds {
     uint32_t rays[kPartMaxClasses], hist[24], top, pieces;
 };
 
-__device__ __forceinline__ int64_t seg_pieces(int64_t m) { return (m + kSegPiece - 1) / kSegPiece; }
+__device__ __forceinline__ int64_t seg_pieces(int64_t m, int piece) { return (m + piece - 1) / piece; }
 
 __device__ __forceinline__ int vox_class(int64_t m)
 {
@@ -1640,11 +1711,12 @@ struct TileItems {
     }
 };
 
-// brick-major voxel keys by degree
+// brick-major voxel keys by degree, or by number of runs (rptr not null)
 struct VoxItems {
     static constexpr int NC = kVoxClasses + 1;   // and voxels of too many edges
     static_assert(NC <= kPartMaxClasses, "classes");
     const int64_t* vptr;
+    const uint32_t* rptr;
     int64_t n;
     const SceneDev* scenes;
     int ns;
@@ -1655,11 +1727,23 @@ struct VoxItems {
         i0 = b * items;
         i1 = n;
     }
-    __device__ int cls(int64_t i) const { return vox_class(vptr[i + 1] - vptr[i]); }
+    __device__ int cls(int64_t i) const
+    {
+        const int c = vox_class(vptr[i + 1] - vptr[i]);
+        if (!rptr || c >= kVoxClasses) return c;   // 255, or too many edges
+        const int64_t m = (int64_t)rptr[i + 1] - rptr[i];
+        int k = kVoxClasses - 1;
+#pragma unroll
+        for (int q = kRunClasses - 1; q >= 0; --q)
+            if (m <= kRunCap[q]) k = q;
+        return k;
+    }
     __device__ void note(int64_t i, int c, PartLds& l) const
     {
         const int64_t m = vptr[i + 1] - vptr[i];
-        if (m > kSegPiece) atomicAdd(&l.pieces, (uint32_t)min(seg_pieces(m), (int64_t)1 << 20));
+        const int64_t items = rptr ? (int64_t)rptr[i + 1] - rptr[i] : m;
+        const int piece = rptr ? kRunPiece : kSegPiece;
+        if (items > piece) atomicAdd(&l.pieces, (uint32_t)min(seg_pieces(items, piece), (int64_t)1 << 22));
         atomicAdd(&l.hist[min(23, 63 - __clzll(m))], 1u);
         atomicMax(&l.top, (uint32_t)min(m, (int64_t)0xffffffffLL));
     }
@@ -1672,8 +1756,9 @@ struct VoxItems {
     __device__ void put(int64_t at, int64_t i, int c) const
     {
         if (c >= kVoxClasses) return;
-        const int64_t s = vptr[i];
-        desc[at] = VoxDev{s, (int32_t)(vptr[i + 1] - s), key_to_voxel(scenes, ns, (uint32_t)i)};
+        const int64_t s = rptr ? (int64_t)rptr[i] : vptr[i];
+        const int64_t e = rptr ? (int64_t)rptr[i + 1] : vptr[i + 1];
+        desc[at] = VoxDev{s, (int32_t)(e - s), key_to_voxel(scenes, ns, (uint32_t)i)};
     }
 };
 
@@ -1693,7 +1778,7 @@ struct PairItems {
     __device__ void note(int64_t i, int, PartLds& l) const
     {
         const int64_t m = (int64_t)pstart[i + 1] - pstart[i];
-        if (m > kSegPiece) atomicAdd(&l.pieces, (uint32_t)seg_pieces(m));
+        if (m > kSegPiece) atomicAdd(&l.pieces, (uint32_t)seg_pieces(m, kSegPiece));
     }
     __device__ void flush(const PartLds& l, int t) const
     {
@@ -1854,31 +1939,31 @@ static hipError_t partition(const F& f, int rounds, int64_t nb, uint32_t* bcnt, 
                        : partition_r<F, 16>(f, nb, bcnt, tot, fo, bpf, nf, s);
 }
 
-// The hub segments hubs[0, n) cut into pieces of kSegPiece edges (one block): the
+// The hub segments hubs[0, n) cut into pieces of `piece` items (one block): the
 // pieces in order, then per hub its range of them (at[np + i]).
 __global__ __launch_bounds__(SC_T) void hub_pieces_k(const VoxDev* __restrict__ hubs, int64_t n, int64_t np,
-                                                     VoxDev* __restrict__ at)
+                                                     int piece, VoxDev* __restrict__ at)
 {
     int64_t carry = 0;
     for (int64_t i0 = 0; i0 < n; i0 += SC_T) {
         const int64_t i = i0 + threadIdx.x;
         const VoxDev d = hubs[i < n ? i : n - 1];
-        const int64_t k = i < n ? seg_pieces(d.m) : 0;
+        const int64_t k = i < n ? seg_pieces(d.m, piece) : 0;
         int64_t tot;
         const int64_t first = carry + block_excl_scan_i64(k, &tot);
         carry += tot;
         if (i >= n) continue;
         at[np + i] = VoxDev{first, (int32_t)k, d.v};
         for (int64_t p = 0; p < k; ++p) {
-            const int64_t left = d.m - p * kSegPiece;
-            at[first + p] = VoxDev{d.start + p * kSegPiece, (int32_t)(left < kSegPiece ? left : kSegPiece),
-                                   (uint32_t)(first + p)};
+            const int64_t left = d.m - p * piece;
+            at[first + p] = VoxDev{d.start + p * piece, (int32_t)(left < piece ? left : piece), (uint32_t)(first + p)};
         }
     }
 }
 
 // class sizes of a partitioned list, and its hubs' pieces
-static hipError_t finish_segments(mrf_ctx* c, SegList& l, const unsigned long long* cnt, int64_t pieces, hipStream_t s)
+static hipError_t finish_segments(mrf_ctx* c, SegList& l, const unsigned long long* cnt, int64_t pieces, int piece,
+                                  hipStream_t s)
 {
     int64_t off = 0;
     for (int k = 0; k < kVoxClasses; ++k) {
@@ -1892,7 +1977,7 @@ static hipError_t finish_segments(mrf_ctx* c, SegList& l, const unsigned long lo
     if (e == hipSuccess) e = ensure(c->b_hubsum, sizeof(double) * (size_t)pieces);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(hub_pieces_k, dim3(1), dim3(SC_T), 0, s, (const VoxDev*)l.desc.p + l.off[kVoxClasses - 1], nh,
-                       pieces, (VoxDev*)l.hub.p);
+                       pieces, piece, (VoxDev*)l.hub.p);
     return hipGetLastError();
 }
 
@@ -1920,7 +2005,7 @@ hipError_t build_classes(mrf_ctx* c, hipStream_t s)
     const TileItems ti{(const TileDev*)c->b_tiles.p, (const int32_t*)c->b_counts.p, (const FrameDev*)c->b_frames.p,
                        c->T, nf, bpf, (uint32_t*)c->b_ray_list.p, st};
     if ((e = partition(ti, tr, tb, tcnt, st->tiles, fo, bpf, nf, s)) != hipSuccess) return e;
-    const VoxItems vi{(const int64_t*)c->b_vptr.p, c->Vk, (const SceneDev*)c->b_scenes.p, c->n_scenes,
+    const VoxItems vi{(const int64_t*)c->b_vptr.p, c->by_runs ? (const uint32_t*)c->b_rptr.p : nullptr, c->Vk, (const SceneDev*)c->b_scenes.p, c->n_scenes,
                       (VoxDev*)c->vox.desc.p, st};
     if ((e = partition(vi, vr, vb, vcnt, st->voxels, nullptr, 1, 0, s)) != hipSuccess) return e;
 
@@ -1944,7 +2029,7 @@ hipError_t build_classes(mrf_ctx* c, hipStream_t s)
         c->ray_cls_edges[k] = (int64_t)h.tile_edges[k];
         c->ray_cls_rays[k] = (int64_t)h.tile_rays[k];
     }
-    if ((e = finish_segments(c, c->vox, h.voxels, (int64_t)h.pieces, s)) != hipSuccess) return e;
+    if ((e = finish_segments(c, c->vox, h.voxels, (int64_t)h.pieces, c->by_runs ? kRunPiece : kSegPiece, s)) != hipSuccess) return e;
     const int64_t* hfo = (const int64_t*)(hb.data() + sizeof(ListStats));
     c->frame_ray_off.assign(hfo, hfo + (size_t)(nf + 1) * kRayClasses);
     for (int i = 0; i < 16; ++i) c->stats.ray_len_hist[i] = (int64_t)h.ray_hist[i];
@@ -1970,7 +2055,7 @@ static hipError_t partition_pairs(mrf_ctx* c, const uint32_t* pstart, int64_t P,
     if (e == hipSuccess) e = hipMemcpyAsync(h, tot, head, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return e;
-    return finish_segments(c, c->pair, h, (int64_t)h[kPartMaxClasses], s);
+    return finish_segments(c, c->pair, h, (int64_t)h[kPartMaxClasses], kSegPiece, s);
 }
 
 // ============================================================== adding keyframes

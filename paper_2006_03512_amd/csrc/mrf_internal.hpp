@@ -103,6 +103,11 @@ constexpr int kVoxCap[] = {16, 32, 64, 128, 256, 1024, 4096};
 constexpr int kVoxVPW[] = {4, 4, 8, 4, 4, 1, 1};
 constexpr int kVoxClasses = (int)(sizeof(kVoxCap) / sizeof(int)) + 1;   // + the hubs
 constexpr int kSegPiece = 4096;
+// Classes 0..6 over runs (run_sum_k) by number of runs, and the pieces above them.
+constexpr int kRunCap[] = {4, 8, 16, 32, 64, 256, 1024};
+constexpr int kRunClasses = (int)(sizeof(kRunCap) / sizeof(int));
+constexpr int kRunPiece = 1024;
+static_assert(kRunClasses + 1 == kVoxClasses && kRunCap[kRunClasses - 1] == kRunPiece, "run_sum_k names its classes");
 static_assert(kVoxClasses == 8 && kVoxCap[0] == 16 && kVoxCap[1] == 32 && kVoxCap[6] == kSegPiece,
               "seg_sum_k names its classes");
 
@@ -353,6 +358,11 @@ struct mrf_ctx {
     mrf::DevBuf b_ray_list;       // tile ids by tile length class, class-major
     mrf::SegList vox;             // touched voxels by degree: VoxDev, brick-major keys inside a class
     mrf::DevBuf b_hubsum;         // sums of the hub pieces (FP64)
+    // voxel -> ray lists as runs instead of b_vedge (by_runs): row (slot / 16) and lane mask
+    // of every run, in voxel key order, and the first run of every key
+    int by_runs = 0;
+    int64_t n_runs = 0;
+    mrf::DevBuf b_runrow, b_runmask, b_rptr;
 
     int64_t ray_off[mrf::kRayClasses] = {0}, ray_cnt[mrf::kRayClasses] = {0};   // tiles of a class: list range
     int64_t ray_cls_edges[mrf::kRayClasses] = {0};
@@ -427,10 +437,14 @@ size_t radix_tmp_bytes(int64_t n);   // tmp bytes radix_sort_pairs needs for n i
 // keys[j] (may be null) their keys; vptr[k] the first entry of key k (k <= Vk).  The
 // per-slot message buffers hold the sort's data (keys may be b_lambar, vals any buffer
 // but b_g, b_lam, b_ell, b_ellbar).  incidence_by_runs: which of two routes n slots
-// take; the other one needs the sort keys that the emit pass leaves in b_g.
+// take; the other one needs the sort keys that the emit pass leaves in b_g.  With
+// keep_runs (a graph by runs, s0 = 0) the lists stay runs: b_runrow, b_runmask, b_rptr
+// and vptr are written, vals and keys are not.
 bool incidence_by_runs(int64_t n);
 hipError_t build_incidence(mrf_ctx* c, int64_t s0, int64_t n, int64_t edges, uint32_t* keys, uint32_t* vals,
-                           int64_t* vptr, const SlotGroups& groups, hipStream_t s);
+                           int64_t* vptr, const SlotGroups& groups, bool keep_runs, hipStream_t s);
+// the lists of a graph by runs written out to vals (c->E entries, as build_incidence)
+hipError_t expand_runs(mrf_ctx* c, uint32_t* vals, hipStream_t s);
 hipError_t launch_vptr_from_sorted(const uint32_t* sorted_keys, int64_t n, int64_t V, int64_t* vptr,
                                    hipStream_t s);
 hipError_t build_classes(mrf_ctx* c, hipStream_t s);

@@ -512,6 +512,169 @@ __global__ __launch_bounds__(256) void hub_sum_k(const VoxDev* __restrict__ hubs
     if (l == 0) vox_store(d.v, a, out);
 }
 
+// ------------------------------------------------------------ voxel phase over runs
+//
+// Large graphs keep the voxel -> ray lists as runs (a row of 16 slots, the mask of its
+// lanes that lie in the voxel): 6 bytes for the 8 to 12 edges of a run where the
+// list of edges takes 4 each, and a run's messages are one 64-byte line, loaded by 16
+// lanes at once instead of gathered.  A 16-lane group takes 16 runs at a time: lane l
+// loads run l's row and mask, and step j broadcasts run j's to the group (a DPP move),
+// whose lane l then loads message l of that row and adds it if its bit is set.  By
+// class (number of runs):
+//   0  at most 4: four segments per group;   1  at most 8: two per group;
+//   2  at most 16: one per group, two in turn;   3  at most 32: one per half-wave, two in turn;
+//   4  at most 64: one per wave, two in turn;   5  at most 256: one per wave;
+//   6  at most 1024: the four waves of a block;   7  more: pieces of 1024 runs.
+// Bound by HBM: 5e8 edges (8 VGA frames at 2 cm) in 0.84 ms where seg_sum_k takes
+// 1.13, 1.3e8 (3 rooms) in 0.173 and 0.275.
+
+template <int J>
+__device__ __forceinline__ uint32_t row_bcast(uint32_t x)
+{
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x150 + J, 0xF, 0xF, false);   // row_newbcast:J
+}
+
+// Messages of the group's 16 runs: x[j] = lane l's message of run j
+template <int... J>
+__device__ __forceinline__ void run_load(const float* __restrict__ in, uint32_t row, float (&x)[16],
+                                         std::integer_sequence<int, J...>)
+{
+    const int l = threadIdx.x & 15;
+    ((x[J] = in[(uint64_t)row_bcast<J>(row) * kTile + l]), ...);
+}
+
+// a[J / PER] += the messages whose mask bit is set
+template <int PER, int N, int... J>
+__device__ __forceinline__ void run_add(uint32_t mask, const float (&x)[16], double (&a)[N],
+                                        std::integer_sequence<int, J...>)
+{
+    const int l = threadIdx.x & 15;
+    ((a[J / PER] += (row_bcast<J>(mask) >> l) & 1u ? (double)x[J] : 0.0), ...);
+}
+
+constexpr auto kRunSteps = std::make_integer_sequence<int, 16>{};
+
+// classes 0 and 1: 16 / PER segments of at most PER runs per group
+template <int PER>
+__device__ __forceinline__ void run_parts(int64_t lb, const VoxDev* __restrict__ vd, int64_t n,
+                                          const uint32_t* __restrict__ rows, const uint16_t* __restrict__ masks,
+                                          const float* __restrict__ in, const VoxOut& out)
+{
+    constexpr int NS = 16 / PER;
+    const int l = threadIdx.x & 15, q = l % PER;
+    const int64_t vi = (lb * 16 + (int)(threadIdx.x >> 4)) * NS + l / PER;
+    const VoxDev d = vd[min(vi, n - 1)];   // past the list: a repeat, not stored
+    const int64_t at = d.start + min(q, d.m - 1);
+    const uint32_t row = rows[at];
+    const uint32_t mask = vi < n && q < d.m ? masks[at] : 0u;
+    float x[16];
+    run_load(in, row, x, kRunSteps);
+    double a[NS];
+#pragma unroll
+    for (int u = 0; u < NS; ++u) a[u] = 0.0;
+    run_add<PER>(mask, x, a, kRunSteps);
+    double t = 0.0;   // at the segment's first lane
+#pragma unroll
+    for (int u = 0; u < NS; ++u) {
+        const double s = __shfl(dgroup_sum_d<16>(a[u]), 0, 16);
+        t = l / PER == u ? s : t;
+    }
+    if (q == 0 && vi < n) vox_store(d.v, t, out);
+}
+
+// classes 2 to 4: one segment of at most G runs per G lanes, two in turn
+template <int G>
+__device__ __forceinline__ void run_group(int64_t lb, const VoxDev* __restrict__ vd, int64_t n,
+                                          const uint32_t* __restrict__ rows, const uint16_t* __restrict__ masks,
+                                          const float* __restrict__ in, const VoxOut& out)
+{
+    const int64_t v0 = (lb * (256 / G) + (int)(threadIdx.x / G)) * 2;
+    const int l = threadIdx.x & (G - 1);
+    VoxDev d[2];
+    uint32_t row[2], mask[2];
+    float x[2][16];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) d[u] = vd[min(v0 + u, n - 1)];   // past the list: a repeat, not stored
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int64_t at = d[u].start + min(l, d[u].m - 1);
+        row[u] = rows[at];
+        mask[u] = l < d[u].m ? masks[at] : 0u;
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) run_load(in, row[u], x[u], kRunSteps);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        double a[1] = {0.0};
+        run_add<16>(mask[u], x[u], a, kRunSteps);
+        const double t = dgroup_sum_d<G>(a[0]);
+        if (l == 0 && v0 + u < n) vox_store(d[u].v, t, out);
+    }
+}
+
+// 64 runs of a segment by a wave, lane i holding run base + i
+__device__ __forceinline__ double run_wave64(int64_t start, int m, int base, const uint32_t* __restrict__ rows,
+                                             const uint16_t* __restrict__ masks, const float* __restrict__ in)
+{
+    const int i = base + (int)(threadIdx.x & 63);
+    const int64_t at = start + min(i, m - 1);
+    const uint32_t row = rows[at];
+    const uint32_t mask = i < m ? masks[at] : 0u;
+    float x[16];
+    run_load(in, row, x, kRunSteps);
+    double a[1] = {0.0};
+    run_add<16>(mask, x, a, kRunSteps);
+    return a[0];
+}
+
+// runs [base, base + 256) of a segment by a wave
+__device__ __forceinline__ double run_wave256(const VoxDev& d, int base, const uint32_t* __restrict__ rows,
+                                              const uint16_t* __restrict__ masks, const float* __restrict__ in)
+{
+    double a = 0.0;
+    for (int t = base; t < base + 256 && t < d.m; t += 64) a += run_wave64(d.start, d.m, t, rows, masks, in);
+    return dgroup_sum_d<64>(a);
+}
+
+__global__ __launch_bounds__(256, 8) void run_sum_k(const SegWork s, const uint32_t* __restrict__ rows,
+                                                    const uint16_t* __restrict__ masks,
+                                                    const float* __restrict__ in, VoxOut out)
+{
+    __shared__ double red[4];
+    int k = kVoxClasses - 1;   // uniform: the class whose blocks hold this one
+    while (k > 0 && blockIdx.x >= s.blk[kVoxClasses - k]) --k;
+    const uint32_t b0 = s.blk[kVoxClasses - 1 - k], nb = s.blk[kVoxClasses - k] - b0;
+    const int64_t lb = xcd_block(blockIdx.x - b0, nb);
+    const VoxDev* d = k == kVoxClasses - 1 ? s.pieces : s.desc + s.off[k];
+    const int64_t n = s.cnt[k];
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    switch (k) {
+        case 0: run_parts<4>(lb, d, n, rows, masks, in, out); break;
+        case 1: run_parts<8>(lb, d, n, rows, masks, in, out); break;
+        case 2: run_group<16>(lb, d, n, rows, masks, in, out); break;
+        case 3: run_group<32>(lb, d, n, rows, masks, in, out); break;
+        case 4: run_group<64>(lb, d, n, rows, masks, in, out); break;
+        case 5: {
+            const int64_t v = lb * 4 + wv;
+            if (v >= n) return;   // whole wave
+            const double t = run_wave256(d[v], 0, rows, masks, in);
+            if ((threadIdx.x & 63) == 0) vox_store(d[v].v, t, out);
+            break;
+        }
+        default: {
+            if (lb >= n) return;   // whole block
+            const double t = run_wave256(d[lb], wv * 256, rows, masks, in);
+            if ((threadIdx.x & 63) == 0) red[wv] = t;
+            __syncthreads();
+            if (threadIdx.x == 0) {
+                const double sum = ((red[0] + red[1]) + red[2]) + red[3];
+                const VoxOut po{nullptr, nullptr, nullptr, nullptr, s.psum};
+                vox_store(d[lb].v, sum, k == kVoxClasses - 1 ? po : out);
+            }
+        }
+    }
+}
+
 // segments per block of class k
 static int64_t seg_per_block(int k)
 {
@@ -519,10 +682,16 @@ static int64_t seg_per_block(int k)
     return kVoxCap[k] <= 32 ? (int64_t)(256 / kVoxCap[k]) * kVoxVPW[k] : 4 * kVoxVPW[k];
 }
 
-static hipError_t seg_sum(mrf_ctx* c, const SegList& l, const float* in, const VoxOut& out, const float* w,
-                          hipStream_t s)
+static int64_t run_per_block(int k)
 {
-    SegWork k{};
+    constexpr int64_t per[kRunClasses] = {64, 32, 32, 16, 8, 4, 1};
+    return k < kRunClasses ? per[k] : 1;
+}
+
+// the work of one launch; returns its blocks
+static int64_t seg_work(const mrf_ctx* c, const SegList& l, int64_t (*per_block)(int), SegWork& k)
+{
+    k = SegWork{};
     k.desc = (const VoxDev*)l.desc.p;
     k.pieces = (const VoxDev*)l.hub.p;
     k.psum = (double*)c->b_hubsum.p;
@@ -530,9 +699,27 @@ static hipError_t seg_sum(mrf_ctx* c, const SegList& l, const float* in, const V
     for (int q = kVoxClasses - 1; q >= 0; --q) {
         k.off[q] = l.off[q];
         k.cnt[q] = q == kVoxClasses - 1 ? l.n_pieces : l.cnt[q];
-        blocks += (nblk(k.cnt[q], (int)seg_per_block(q)) + 7) / 8 * 8;
+        blocks += (nblk(k.cnt[q], (int)per_block(q)) + 7) / 8 * 8;
         k.blk[kVoxClasses - q] = (uint32_t)blocks;
     }
+    return blocks;
+}
+
+// the hubs of a launched segment list
+static hipError_t hub_sum(mrf_ctx* c, const SegList& l, const VoxOut& out, hipStream_t s)
+{
+    const int64_t nh = l.cnt[kVoxClasses - 1];
+    if (nh > 0)
+        hipLaunchKernelGGL(hub_sum_k, dim3(nblk(nh, 4)), dim3(256), 0, s, (const VoxDev*)l.hub.p + l.n_pieces, nh,
+                           (const double*)c->b_hubsum.p, out);
+    return hipGetLastError();
+}
+
+static hipError_t seg_sum(mrf_ctx* c, const SegList& l, const float* in, const VoxOut& out, const float* w,
+                          hipStream_t s)
+{
+    SegWork k;
+    const int64_t blocks = seg_work(c, l, seg_per_block, k);
     if (blocks == 0) return hipSuccess;
     const dim3 g((unsigned)blocks), b(256);
     const uint32_t* ve = (const uint32_t*)c->b_vedge.p;
@@ -544,17 +731,23 @@ static hipError_t seg_sum(mrf_ctx* c, const SegList& l, const float* in, const V
         hipLaunchKernelGGL((seg_sum_k<false, true>), g, b, 0, s, k, ve, in, out, w, c->sg);
     else
         hipLaunchKernelGGL((seg_sum_k<false, false>), g, b, 0, s, k, ve, in, out, w, c->sg);
-    const int64_t nh = l.cnt[kVoxClasses - 1];
-    if (nh > 0)
-        hipLaunchKernelGGL(hub_sum_k, dim3(nblk(nh, 4)), b, 0, s, (const VoxDev*)l.hub.p + l.n_pieces, nh,
-                           (const double*)c->b_hubsum.p, out);
-    return hipGetLastError();
+    return hub_sum(c, l, out, s);
+}
+
+static hipError_t run_sum(mrf_ctx* c, const float* in, const VoxOut& out, hipStream_t s)
+{
+    SegWork k;
+    const int64_t blocks = seg_work(c, c->vox, run_per_block, k);
+    if (blocks == 0) return hipSuccess;
+    hipLaunchKernelGGL(run_sum_k, dim3((unsigned)blocks), dim3(256), 0, s, k, (const uint32_t*)c->b_runrow.p,
+                       (const uint16_t*)c->b_runmask.p, in, out);
+    return hub_sum(c, c->vox, out, s);
 }
 
 hipError_t launch_voxel_phase(mrf_ctx* c, const float* in, VoxOut out, hipStream_t s)
 {
     ProfScope ps(c, KID_VOX, s);
-    return seg_sum(c, c->vox, in, out, nullptr, s);
+    return c->by_runs ? run_sum(c, in, out, s) : seg_sum(c, c->vox, in, out, nullptr, s);
 }
 
 // ------------------------------------------------------------ keyframe pairs

@@ -82,3 +82,61 @@ def test_lists_hold_every_item_once(name):
     got = logit.cpu().numpy()
     assert np.all(got >= want_lo - slack) and np.all(got <= want_hi + slack)
     m.close()
+
+
+# scenes whose voxels have few and many runs (grid sizes), hubs (many rays from one camera), several
+# slot groups, and images whose tiles are cut at both edges
+RUNS = {
+    "few runs": ([((260, 256), (96, 90, 40), 2)], 0),
+    "many runs, hubs": ([((301, 262), (20, 18, 12), 6)], 0),
+    "two groups": ([((257, 262), (40, 33, 21), 2), ((262, 257), (33, 47, 21), 2)], 22),
+}
+
+
+@pytest.mark.parametrize("name", list(RUNS))
+def test_large_graphs_sum_runs(name):
+    """Lists kept as runs (2^19 slots and more): beliefs and gradients as from the lists of edges (a build
+    that prepares keyframe pairs keeps those), frames added to such a graph as built with it."""
+    import dataclasses
+
+    from paper_2006_03512_amd import RayMRF
+    spec, log2 = RUNS[name]
+    scs = [_scene(90 + i, *wh, g, nf) for i, (wh, g, nf) in enumerate(spec)]
+    p0 = dataclasses.replace(scs[0].params, group_slots_log2=log2)
+    for s in scs:
+        s.params = p0
+    edges = log2 == 0   # keyframe pairs need one slot group
+    out = []
+    for kf in (False, True) if edges else (False,):
+        m = RayMRF()
+        st = m.build(scs, keyframe_average=kf)
+        assert st.n_slots >= 1 << 19 and (st.n_slot_groups > 1) == (log2 > 0)
+        rng = np.random.default_rng(3)
+        theta = torch.from_numpy(rng.normal(-2, 0.5, st.n_voxels).astype(np.float32)).cuda()
+        dL = torch.from_numpy(rng.normal(0, 1, st.n_voxels).astype(np.float32)).cuda()
+        sigma = torch.from_numpy(scs[0].sigma_table.astype(np.float32)).cuda()
+        m.infer(theta, sigma, 2, keep_checkpoints=True)
+        logit = m.marginals()[1]
+        out.append((logit, *m.backward(dL)))
+        if not kf:
+            col = m.export_incidence()["col"].cpu().numpy()
+            ell = m.export_edges()["ell"].cpu().numpy().astype(np.float64)
+            want, mag = theta.cpu().numpy().astype(np.float64), np.zeros(st.n_voxels)
+            np.add.at(want, col, ell)
+            np.add.at(mag, col, np.abs(ell))
+            err = np.abs(logit.cpu().numpy() - want)
+            # one rounding to FP32, and FP64 sums of up to max degree terms
+            assert np.all(err <= 2.0 ** -23 * np.abs(want) + 2.0 ** -52 * st.max_voxel_degree * (mag + 10))
+            sc = scs[-1]
+            d, T = sc.depth, sc.T_wc
+            part = [*scs[:-1], dataclasses.replace(sc, depth=d[:-1], T_wc=T[:-1])]
+            m2 = RayMRF()
+            m2.build(part)
+            m2.add_frames(d[-1:], T[-1:])
+            m2.infer(theta, sigma, 2, keep_checkpoints=True)
+            out.append((m2.marginals()[1], *m2.backward(dL)))
+            m2.close()
+        m.close()
+    for o in out[1:]:   # the sums' FP64 order is all that differs
+        for a, b in zip(out[0], o):
+            assert float((a.double() - b.double()).norm()) <= 1e-6 * float(b.double().norm())
