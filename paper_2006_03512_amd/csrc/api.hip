@@ -150,9 +150,9 @@ static hipError_t enqueue_forward(mrf_ctx* c, int K, int keep, bool plain, hipSt
 {
     hipError_t e;
     const float* theta = (const float*)c->b_theta.p;
-    if ((e = launch_potentials(c, s)) != hipSuccess) return e;
-    for (int k = 1; k <= K; ++k) {
-        if (k > 1 && (e = launch_voxel_phase(c, ell_slot(c, K, k - 1, keep),
+    if ((e = launch_first_sweep(c, ell_slot(c, K, 1, keep), plain, s)) != hipSuccess) return e;
+    for (int k = 2; k <= K; ++k) {
+        if ((e = launch_voxel_phase(c, ell_slot(c, K, k - 1, keep),
                                              VoxOut{theta, tot_slot(c, k, keep), nullptr, nullptr}, s)) != hipSuccess)
             return e;
         if ((e = launch_ray_phase(c, lam_src(c, K, k, keep), ell_slot(c, K, k, keep), plain, s)) != hipSuccess)
@@ -177,17 +177,12 @@ static hipError_t enqueue_forward_kf(mrf_ctx* c, int K, int keep, bool plain, hi
     double* Mlast = (double*)c->b_pair_m.p;
     float* x = (float*)c->b_kfx.p;
     const KfSrc kf{x, (const int64_t*)c->b_kfxb.p};
-    if ((e = launch_potentials(c, s)) != hipSuccess) return e;
-    for (int k = 1; k <= K; ++k) {
-        float* ell = ell_slot(c, K, k, false);
-        if (k == 1) {
-            e = launch_ray_phase(c, ExclSrc{(const float2*)c->b_theta2.p, nullptr}, ell, plain, s);
-        } else {
-            double* M = keep ? (double*)c->b_ckpt.p + (size_t)(k - 2) * (size_t)c->n_pairs : Mlast;
-            e = launch_pair_phase(c, ell_slot(c, K, k - 1, false), w, M, s);
-            if (e == hipSuccess) e = launch_kf_voxel(c, M, theta, x, nullptr, s);
-            if (e == hipSuccess) e = launch_ray_phase_kf(c, kf, ell, plain, s);
-        }
+    if ((e = launch_first_sweep(c, ell_slot(c, K, 1, false), plain, s)) != hipSuccess) return e;
+    for (int k = 2; k <= K; ++k) {
+        double* M = keep ? (double*)c->b_ckpt.p + (size_t)(k - 2) * (size_t)c->n_pairs : Mlast;
+        e = launch_pair_phase(c, ell_slot(c, K, k - 1, false), w, M, s);
+        if (e == hipSuccess) e = launch_kf_voxel(c, M, theta, x, nullptr, s);
+        if (e == hipSuccess) e = launch_ray_phase_kf(c, kf, ell_slot(c, K, k, false), plain, s);
         if (e != hipSuccess) return e;
     }
     if ((e = launch_pair_phase(c, (const float*)c->b_ell.p, w, Mlast, s)) != hipSuccess) return e;

@@ -19,12 +19,12 @@ constexpr int kMaxRayLen = 2048;      // longest ray factor a group can hold
 // Ray-length classes by tile length (longest ray of the tile), capacity cap.
 // A ray is held by a group of G lanes (16, 32 or 64), each holding IPL = cap / G
 // consecutive steps; in the reverse pass a group may walk RPW = 2 rays in turn.
-// Class 0 (cap 16) is G = 16 reading the tile directly; classes up to
-// kLdsMaxCap stage the tile through LDS; longer classes are G = 64, direct.
+// Classes up to kLdsMaxCap stage the tile through LDS; longer classes are G = 64,
+// reading the tile directly.
 constexpr int kRayClasses = 13;
 constexpr int kRayCap[kRayClasses] = {16, 64, 128, 192, 256, 320, 384, 512, 640, 768, 1024, 1536, 2048};
 constexpr int kLdsMaxCap = 512;
-constexpr bool ray_class_lds(int q) { return q > 0 && kRayCap[q] <= kLdsMaxCap; }
+constexpr bool ray_class_lds(int q) { return kRayCap[q] <= kLdsMaxCap; }
 
 // Candidate launch shapes of every class; the first is the default (fastest
 // on the 30-keyframe batch), mrf_autotune times them all on the built graph
@@ -176,6 +176,18 @@ struct ExclDev {
 struct KfSrc {
     const float* x;
     const int64_t* xb;
+};
+
+// The first sweep's sources: it reads every slot's measurement residual and sigma bin,
+// computes the potentials that later sweeps read (written to g), and its messages
+// lambda_e = theta of the voxel.
+struct PotSrc {
+    const float* delta;
+    const uint8_t* bin;
+    const float *sigma, *bias;
+    float* g;
+    const FrameDev* frames;   // region tables: cp > 0 pixels a side
+    int cp;
 };
 
 // Reverse pass with per-keyframe averaged messages: lambda_e as in KfSrc
@@ -507,6 +519,8 @@ hipError_t launch_infer_inputs(mrf_ctx* c, const float* prior, const float* sigm
 // thetabar = dlogit, seed = (dlogit, 0) when not null
 hipError_t launch_reverse_seed(const float* dlogit, float* thetabar, float2* seed, int64_t n, hipStream_t s);
 hipError_t launch_ray_phase(mrf_ctx* c, ExclSrc lam, float* ell, bool plain, hipStream_t s);
+// the potentials and the first sweep's ray phase (lambda = theta, b_theta2)
+hipError_t launch_first_sweep(mrf_ctx* c, float* ell, bool plain, hipStream_t s);
 // one class of the ray phase / reverse pass with launch shape `sel` (autotuner)
 hipError_t launch_ray_class_shape(const mrf_ctx* c, int q, int sel, ExclSrc lam, float* ell, hipStream_t s);
 hipError_t launch_adj_class_shape(const mrf_ctx* c, int q, int sel, ExclSrc lam, ExclSrc ellbar, float* lambar,

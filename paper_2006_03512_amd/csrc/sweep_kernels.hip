@@ -108,6 +108,12 @@ __global__ void reverse_seed_k(const float* __restrict__ dlogit, float* __restri
 // contiguous run; S is a multiple of 16, so a group lies wholly inside or
 // outside [0, S).  Grid-stride, so each block builds its tables once.
 // Padding slots (bin 255) are left as they are.
+__device__ __forceinline__ float potential(float delta, float inv, float cst, float mu)
+{
+    const float x = (delta - mu) * inv;   // residual about the predicted mean d + mu
+    return -0.5f * x * x - cst;
+}
+
 constexpr int kPotGroups = 4;   // potentials: groups of 4 slots in flight per lane
 
 __global__ __launch_bounds__(256) void potentials_k(const float* __restrict__ delta, const uint8_t* __restrict__ bin,
@@ -146,8 +152,7 @@ __global__ __launch_bounds__(256) void potentials_k(const float* __restrict__ de
                 const int b = (int)((bw[u] >> (8 * j)) & 255u);
                 const float dj = j == 0 ? dv[u].x : j == 1 ? dv[u].y : j == 2 ? dv[u].z : dv[u].w;
                 const int bb = b < kBins ? b : 0;
-                const float x = (dj - mu[bb]) * inv[bb];   // residual about the predicted mean d + mu
-                out[j] = -0.5f * x * x - cst[bb];
+                out[j] = potential(dj, inv[bb], cst[bb], mu[bb]);
                 all = all && b < kBins;
             }
             if (all) {
@@ -195,8 +200,7 @@ __global__ __launch_bounds__(256) void potentials_cells_k(const TileDev* __restr
                 const int b = (int)((bw >> (8 * j)) & 255u);
                 const float dj = j == 0 ? dv.x : j == 1 ? dv.y : j == 2 ? dv.z : dv.w;
                 const int bb = b < kBins ? b : 0;
-                const float x = (dj - mu[bb]) * inv[bb];
-                out[j] = -0.5f * x * x - cst[bb];
+                out[j] = potential(dj, inv[bb], cst[bb], mu[bb]);
                 all = all && b < kBins;
             }
             if (all) {
@@ -928,11 +932,71 @@ __global__ __launch_bounds__(256) void ray_k(const uint32_t* __restrict__ list, 
 // = tot[col] - own and g into LDS; every group runs the scans of its own ray
 // on its LDS column and writes ell back into that column (0 past the ray),
 // and the block stores the tile coalesced.
-template <int G, int IPL, bool KF>
+// Where a ray phase's messages come from: per-edge exclusion from the voxel totals, the
+// per-keyframe message buffers, or (FIRST) the prior, with the potentials still to be
+// computed.
+enum RayMode { RAY_EXCL, RAY_KF, RAY_FIRST };
+
+// The potentials of this thread's slots of the tile into vg and, for later sweeps, into
+// p.g (padding slots: any value).  The tile's table row is staged in tab (3 kBins words
+// of the LDS image, which is still unused).
+// In the first sweep's ray kernels they cost 5 bytes an edge read and 4 written beside
+// its col and ell; a pass of their own reads 5, writes 4 and has the sweep read 4 more:
+// 8 VGA frames at 2 cm (5.2e8 slots), potentials and first sweep 2.66 ms in two
+// passes and 2.03 in one.
+template <int NT, int NR>
+struct TilePotentials {
+    static constexpr int W = tile_vec<NR>();
+    float vd[NR];
+    uint32_t vb[NR / W];
+
+    __device__ __forceinline__ void fetch(const TileDev& td, int nf, const PotSrc& p)
+    {
+        tile_fetch<NT, NR>(p.delta, td.base, nf, vd);
+        const uint8_t* bp = p.bin + td.base;
+#pragma unroll
+        for (int q = 0; q < NR / W; ++q) {
+            const int iw = min((int)threadIdx.x + q * NT, nf / W - 1);
+            if constexpr (W == 4) vb[q] = *(const uint32_t*)(bp + (uint32_t)iw * 4u);
+            if constexpr (W == 2) vb[q] = *(const uint16_t*)(bp + (uint32_t)iw * 2u);
+            if constexpr (W == 1) vb[q] = bp[(uint32_t)iw];
+        }
+    }
+
+    __device__ __forceinline__ void compute(const TileDev& td, int nf, const PotSrc& p, float* tab, float (&vg)[NR])
+    {
+        if (threadIdx.x < kBins) {
+            const int64_t row = p.cp > 0 ? tile_cell(td, p.frames, p.cp) * kBins : 0;
+            const float s = p.sigma[row + threadIdx.x];
+            tab[threadIdx.x] = 1.0f / s;
+            tab[kBins + threadIdx.x] = logf(s) + 0.91893853320467274f;
+            tab[2 * kBins + threadIdx.x] = p.bias[row + threadIdx.x];
+        }
+        __syncthreads();
+        float* gp = p.g + td.base;
+#pragma unroll
+        for (int q = 0; q < NR / W; ++q) {
+            VecT<W, float> o;
+#pragma unroll
+            for (int b = 0; b < W; ++b) {
+                const uint32_t k = (vb[q] >> (8 * b)) & 255u;
+                const int kk = k < kBins ? (int)k : 0;
+                o.v[b] = vg[W * q + b] = potential(vd[W * q + b], tab[kk], tab[kBins + kk], tab[2 * kBins + kk]);
+            }
+            const int iw = (int)threadIdx.x + q * NT;
+            if (W * iw < nf) vec_at<W>(gp, iw) = o;
+        }
+        __syncthreads();   // tab is free again
+    }
+};
+
+template <int G, int IPL, RayMode MODE>
 __device__ __forceinline__ void ray_tile(const TileDev& td, const int32_t* __restrict__ counts,
                                          const int32_t* __restrict__ col, const ExclDev& lam, const KfSrc& kf,
-                                         const float* __restrict__ g, float* __restrict__ ell, float* sl, float* sg)
+                                         const PotSrc& pot, const float* __restrict__ g, float* __restrict__ ell,
+                                         float* sl, float* sg)
 {
+    constexpr bool KF = MODE == RAY_KF, FIRST = MODE == RAY_FIRST;
     constexpr int NT = kTile * G;
     const int nf = kTile * td.len;   // 1 <= td.len <= G * IPL by class
     const int i = (int)threadIdx.x / G;   // this group's ray: lane i of the tile
@@ -945,8 +1009,12 @@ __device__ __forceinline__ void ray_tile(const TileDev& td, const int32_t* __res
         float vo[IPL], vg[IPL], vt[IPL];
         float2 vp[IPL];
         tile_fetch_i<NT, IPL>(col, td.base, nf, vc);
-        if constexpr (!KF) tile_fetch<NT, IPL>(lam.own, td.base, nf, vo);
-        tile_fetch<NT, IPL>(g, td.base, nf, vg);
+        if constexpr (MODE == RAY_EXCL) tile_fetch<NT, IPL>(lam.own, td.base, nf, vo);
+        TilePotentials<NT, IPL> tp;
+        if constexpr (FIRST)
+            tp.fetch(td, nf, pot);
+        else
+            tile_fetch<NT, IPL>(g, td.base, nf, vg);
         if constexpr (KF) {
             const float* xf = kf.x + kf.xb[td.frame];
 #pragma unroll
@@ -955,8 +1023,10 @@ __device__ __forceinline__ void ray_tile(const TileDev& td, const int32_t* __res
 #pragma unroll
             for (int r = 0; r < IPL; ++r) vp[r] = lam.tot[max(vc[r], 0)];
 #pragma unroll
-            for (int r = 0; r < IPL; ++r) vt[r] = excl_value(vc[r], vp[r], vo[r], lam.has_own);
+            for (int r = 0; r < IPL; ++r)
+                vt[r] = FIRST ? excl_value(vc[r], vp[r], 0.0f, 0) : excl_value(vc[r], vp[r], vo[r], lam.has_own);
         }
+        if constexpr (FIRST) tp.compute(td, nf, pot, sl, vg);
         tile_to_lds<NT, IPL, IPL>(sl, vt);
         tile_to_lds<NT, IPL, IPL>(sg, vg);
     }
@@ -972,11 +1042,11 @@ __device__ __forceinline__ void ray_tile(const TileDev& td, const int32_t* __res
     tile_store<NT, IPL, IPL>(ell, td.base, nf, [&](int, int at) { return sl[at]; });
 }
 
-template <int G, int IPL, bool KF>
+template <int G, int IPL, RayMode MODE>
 __global__ __launch_bounds__(kTile * G) void ray_lds_k(const uint32_t* __restrict__ list, int64_t ntiles,
                                                        const TileDev* __restrict__ tiles,
                                                        const int32_t* __restrict__ counts,
-                                                       const int32_t* __restrict__ col, ExclDev lam, KfSrc kf,
+                                                       const int32_t* __restrict__ col, ExclDev lam, KfSrc kf, PotSrc pot,
                                                        const float* __restrict__ g, float* __restrict__ ell)
 {
     __shared__ float sl[kTile * G * IPL];
@@ -984,16 +1054,16 @@ __global__ __launch_bounds__(kTile * G) void ray_lds_k(const uint32_t* __restric
     const int64_t ti = xcd_block(blockIdx.x, gridDim.x);
     if (ti >= ntiles) return;   // whole block
     const TileDev td = tiles[list[ti]];
-    ray_tile<G, IPL, KF>(td, counts, col, lam, kf, g, ell, sl, sg);
+    ray_tile<G, IPL, MODE>(td, counts, col, lam, kf, pot, g, ell, sl, sg);
 }
 
 // The short classes of a small graph in one launch, a block per tile.  Such a phase is
 // a few microseconds of launch, dependent loads and scans whatever its tiles: one launch
 // of them instead of one per class.
-template <bool KF>
+template <RayMode MODE>
 __global__ __launch_bounds__(256) void ray_small_k(const SmallTiles st, const TileDev* __restrict__ tiles,
                                                    const int32_t* __restrict__ counts,
-                                                   const int32_t* __restrict__ col, ExclDev lam, KfSrc kf,
+                                                   const int32_t* __restrict__ col, ExclDev lam, KfSrc kf, PotSrc pot,
                                                    const float* __restrict__ g, float* __restrict__ ell)
 {
     constexpr int CAP = kRayCap[kSmallClasses - 1];
@@ -1006,23 +1076,23 @@ __global__ __launch_bounds__(256) void ray_small_k(const SmallTiles st, const Ti
     if (lt >= st.cnt[q]) return;   // whole block
     const TileDev td = tiles[st.list[st.off[q] + lt]];
     switch (q) {
-        case 0: ray_tile<16, kRayCap[0] / 16, KF>(td, counts, col, lam, kf, g, ell, sl, sg); break;
-        case 1: ray_tile<16, kRayCap[1] / 16, KF>(td, counts, col, lam, kf, g, ell, sl, sg); break;
-        case 2: ray_tile<16, kRayCap[2] / 16, KF>(td, counts, col, lam, kf, g, ell, sl, sg); break;
-        case 3: ray_tile<16, kRayCap[3] / 16, KF>(td, counts, col, lam, kf, g, ell, sl, sg); break;
-        default: ray_tile<16, kRayCap[4] / 16, KF>(td, counts, col, lam, kf, g, ell, sl, sg);
+        case 0: ray_tile<16, kRayCap[0] / 16, MODE>(td, counts, col, lam, kf, pot, g, ell, sl, sg); break;
+        case 1: ray_tile<16, kRayCap[1] / 16, MODE>(td, counts, col, lam, kf, pot, g, ell, sl, sg); break;
+        case 2: ray_tile<16, kRayCap[2] / 16, MODE>(td, counts, col, lam, kf, pot, g, ell, sl, sg); break;
+        case 3: ray_tile<16, kRayCap[3] / 16, MODE>(td, counts, col, lam, kf, pot, g, ell, sl, sg); break;
+        default: ray_tile<16, kRayCap[4] / 16, MODE>(td, counts, col, lam, kf, pot, g, ell, sl, sg);
     }
 }
 
-// The voxel -> ray messages one ray-phase launch reads: per-edge exclusion
-// from the voxel totals, or (kf) the per-keyframe message buffers.
+// The sources of one ray-phase launch.
 struct RaySrc {
     ExclDev lam;
     KfSrc kf;
-    bool is_kf;
+    PotSrc pot;
+    RayMode mode;
 };
 
-template <int Q, int I, bool KF>
+template <int Q, int I, RayMode MODE>
 static void launch_ray_shape_t(const mrf_ctx* c, int64_t off, int64_t n, const RaySrc& src, float* ell, hipStream_t s)
 {
     constexpr int G = kFwdShapes[Q][I].g;
@@ -1030,12 +1100,12 @@ static void launch_ray_shape_t(const mrf_ctx* c, int64_t off, int64_t n, const R
         constexpr int CAP = kRayCap[Q];
         const uint32_t* list = (const uint32_t*)c->b_ray_list.p + c->ray_off[Q] + off;
         if constexpr (ray_class_lds(Q)) {
-            hipLaunchKernelGGL((ray_lds_k<G, CAP / G, KF>), dim3((unsigned)n), dim3(kTile * G), 0, s, list, n,
+            hipLaunchKernelGGL((ray_lds_k<G, CAP / G, MODE>), dim3((unsigned)n), dim3(kTile * G), 0, s, list, n,
                                (const TileDev*)c->b_tiles.p, (const int32_t*)c->b_counts.p,
-                               (const int32_t*)c->b_col.p, src.lam, src.kf, (const float*)c->b_g.p, ell);
-        } else {
-            hipLaunchKernelGGL((ray_k<G, CAP / G, KF>), dim3((unsigned)(n * tile_blocks<G>())), dim3(256), 0, s,
-                               list, n, (const TileDev*)c->b_tiles.p, (const int32_t*)c->b_counts.p,
+                               (const int32_t*)c->b_col.p, src.lam, src.kf, src.pot, (const float*)c->b_g.p, ell);
+        } else {   // the potentials have their own pass where direct classes run
+            hipLaunchKernelGGL((ray_k<G, CAP / G, MODE == RAY_KF>), dim3((unsigned)(n * tile_blocks<G>())), dim3(256),
+                               0, s, list, n, (const TileDev*)c->b_tiles.p, (const int32_t*)c->b_counts.p,
                                (const int32_t*)c->b_col.p, src.lam, src.kf, (const float*)c->b_g.p, ell);
         }
     }
@@ -1044,10 +1114,11 @@ static void launch_ray_shape_t(const mrf_ctx* c, int64_t off, int64_t n, const R
 template <int Q, int I>
 static void launch_ray_shape(const mrf_ctx* c, int64_t off, int64_t n, const RaySrc& src, float* ell, hipStream_t s)
 {
-    if (src.is_kf)
-        launch_ray_shape_t<Q, I, true>(c, off, n, src, ell, s);
-    else
-        launch_ray_shape_t<Q, I, false>(c, off, n, src, ell, s);
+    switch (src.mode) {
+        case RAY_KF: launch_ray_shape_t<Q, I, RAY_KF>(c, off, n, src, ell, s); break;
+        case RAY_FIRST: launch_ray_shape_t<Q, I, RAY_FIRST>(c, off, n, src, ell, s); break;
+        default: launch_ray_shape_t<Q, I, RAY_EXCL>(c, off, n, src, ell, s);
+    }
 }
 
 template <int Q, int... I>
@@ -1107,12 +1178,12 @@ static hipError_t ray_class_shape(const mrf_ctx* c, int q, int sel, const RaySrc
 
 hipError_t launch_ray_class_shape(const mrf_ctx* c, int q, int sel, ExclSrc lam, float* ell, hipStream_t s)
 {
-    return ray_class_shape(c, q, sel, RaySrc{excl_dev(c, lam), KfSrc{nullptr, nullptr}, false}, ell, s);
+    return ray_class_shape(c, q, sel, RaySrc{excl_dev(c, lam), KfSrc{}, PotSrc{}, RAY_EXCL}, ell, s);
 }
 
 hipError_t launch_ray_class_shape_kf(const mrf_ctx* c, int q, int sel, KfSrc lam, float* ell, hipStream_t s)
 {
-    return ray_class_shape(c, q, sel, RaySrc{excl_dev(c, ExclSrc{nullptr, nullptr}), lam, true}, ell, s);
+    return ray_class_shape(c, q, sel, RaySrc{excl_dev(c, ExclSrc{nullptr, nullptr}), lam, PotSrc{}, RAY_KF}, ell, s);
 }
 
 static hipError_t ray_phase(mrf_ctx* c, const RaySrc& src, float* ell, bool plain, hipStream_t s)
@@ -1125,9 +1196,11 @@ static hipError_t ray_phase(mrf_ctx* c, const RaySrc& src, float* ell, bool plai
             cnt[k] = k < kSmallClasses && st.cnt[k] > 0 ? 0 : c->ray_cnt[k];
         if (blocks > 0) {
             ProfScope ps(c, KID_RAYS, s);
-            const auto kernel = src.is_kf ? ray_small_k<true> : ray_small_k<false>;
+            const auto kernel = src.mode == RAY_KF      ? ray_small_k<RAY_KF>
+                                : src.mode == RAY_FIRST ? ray_small_k<RAY_FIRST>
+                                                        : ray_small_k<RAY_EXCL>;
             hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, s, st, (const TileDev*)c->b_tiles.p,
-                               (const int32_t*)c->b_counts.p, (const int32_t*)c->b_col.p, src.lam, src.kf,
+                               (const int32_t*)c->b_counts.p, (const int32_t*)c->b_col.p, src.lam, src.kf, src.pot,
                                (const float*)c->b_g.p, ell);
         }
         ray_classes(c, off, cnt, src, ell, false, s);
@@ -1148,12 +1221,26 @@ static hipError_t ray_phase(mrf_ctx* c, const RaySrc& src, float* ell, bool plai
 
 hipError_t launch_ray_phase(mrf_ctx* c, ExclSrc lam_src, float* ell, bool plain, hipStream_t s)
 {
-    return ray_phase(c, RaySrc{excl_dev(c, lam_src), KfSrc{nullptr, nullptr}, false}, ell, plain, s);
+    return ray_phase(c, RaySrc{excl_dev(c, lam_src), KfSrc{}, PotSrc{}, RAY_EXCL}, ell, plain, s);
+}
+
+hipError_t launch_first_sweep(mrf_ctx* c, float* ell, bool plain, hipStream_t s)
+{
+    const ExclSrc theta{(const float2*)c->b_theta2.p, nullptr};
+    bool fused = !plain;   // and no tiles longer than the LDS classes hold
+    for (int q = 0; q < kRayClasses; ++q) fused = fused && (ray_class_lds(q) || c->ray_cnt[q] == 0);
+    if (!fused) {
+        const hipError_t e = launch_potentials(c, s);
+        return e == hipSuccess ? launch_ray_phase(c, theta, ell, plain, s) : e;
+    }
+    const PotSrc p{(const float*)c->b_delta.p, (const uint8_t*)c->b_bin.p, (const float*)c->b_sigma.p,
+                   (const float*)c->b_bias.p, (float*)c->b_g.p, (const FrameDev*)c->b_frames.p, c->cell_px};
+    return ray_phase(c, RaySrc{excl_dev(c, theta), KfSrc{}, p, RAY_FIRST}, ell, false, s);
 }
 
 hipError_t launch_ray_phase_kf(mrf_ctx* c, KfSrc lam, float* ell, bool plain, hipStream_t s)
 {
-    return ray_phase(c, RaySrc{excl_dev(c, ExclSrc{nullptr, nullptr}), lam, true}, ell, plain, s);
+    return ray_phase(c, RaySrc{excl_dev(c, ExclSrc{nullptr, nullptr}), lam, PotSrc{}, RAY_KF}, ell, plain, s);
 }
 
 // lambda_e of the per-keyframe messages on every slot (exports)
