@@ -222,12 +222,11 @@ constexpr int adj_lds_words()
     return (RPW > 1 ? 3 : 2) * kTile * G * IPL;
 }
 
-template <int G, int IPL, int RPW, bool KF>
+template <int G, int IPL, int RPW, bool KF, bool FIRST>
 __device__ __forceinline__ void ray_adj_tile(const TileDev& td, const int32_t* __restrict__ counts,
                                              const int32_t* __restrict__ col, const ExclDev& lam,
                                              const float* __restrict__ g, const ExclDev& eb, const AdjKf& kfa,
-                                             float* __restrict__ lambar, float* __restrict__ gsum, int first,
-                                             float* lds)
+                                             float* __restrict__ lambar, float* __restrict__ gsum, float* lds)
 {
     constexpr int NT = kTile * G / RPW;   // threads
     constexpr int NG = kTile / RPW;       // groups
@@ -281,11 +280,11 @@ __device__ __forceinline__ void ray_adj_tile(const TileDev& td, const int32_t* _
         if constexpr (RPW > 1) tile_to_lds<NT, NR, IPL>(se, ve);
     }
     __syncthreads();
-    // g-bar sums of earlier sweeps, fetched before the scans so that their
-    // latency hides behind them (unconditionally: a branch here would make
-    // the compiler wait for the loads at its end; unused on the first sweep)
+    // g-bar sums of earlier sweeps, fetched before the scans so that their latency
+    // hides behind them (none on the first reverse sweep, 4 of its 28 bytes an edge: a
+    // runtime branch here would make the compiler wait for the loads at its end)
     float vs[NR];
-    tile_fetch<NT, NR>(gsum, td.base, nf, vs);
+    if constexpr (!FIRST) tile_fetch<NT, NR>(gsum, td.base, nf, vs);
 #pragma unroll
     for (int r = 0; r < RPW; ++r) {
         const int i = grp + r * NG;   // this group's ray: lane i of the tile
@@ -322,32 +321,31 @@ __device__ __forceinline__ void ray_adj_tile(const TileDev& td, const int32_t* _
     __syncthreads();
     tile_store2<NT, NR, IPL>(
         lambar, [&](int, int at) { return sa[at]; }, gsum,
-        [&](int r, int at) { return first ? sb[at] : vs[r] + sb[at]; }, td.base, nf);
+        [&](int r, int at) { return FIRST ? sb[at] : vs[r] + sb[at]; }, td.base, nf);
 }
 
-template <int G, int IPL, int RPW, bool KF>
+template <int G, int IPL, int RPW, bool KF, bool FIRST>
 __global__ __launch_bounds__(kTile * G / RPW) void ray_adj_lds_k(const uint32_t* __restrict__ list, int64_t ntiles,
                                                                  const TileDev* __restrict__ tiles,
                                                                  const int32_t* __restrict__ counts,
                                                                  const int32_t* __restrict__ col, ExclDev lam,
                                                                  const float* __restrict__ g, ExclDev eb, AdjKf kfa,
-                                                                 float* __restrict__ lambar, float* __restrict__ gsum,
-                                                                 int first)
+                                                                 float* __restrict__ lambar, float* __restrict__ gsum)
 {
     __shared__ float lds[adj_lds_words<G, IPL, RPW>()];
     const int64_t ti = xcd_block(blockIdx.x, gridDim.x);
     if (ti >= ntiles) return;   // whole block
     const TileDev td = tiles[list[ti]];
-    ray_adj_tile<G, IPL, RPW, KF>(td, counts, col, lam, g, eb, kfa, lambar, gsum, first, lds);
+    ray_adj_tile<G, IPL, RPW, KF, FIRST>(td, counts, col, lam, g, eb, kfa, lambar, gsum, lds);
 }
 
 // The short classes of a small graph in one launch (as ray_small_k).
-template <bool KF>
+template <bool KF, bool FIRST>
 __global__ __launch_bounds__(256) void ray_adj_small_k(const SmallTiles st, const TileDev* __restrict__ tiles,
                                                        const int32_t* __restrict__ counts,
                                                        const int32_t* __restrict__ col, ExclDev lam,
                                                        const float* __restrict__ g, ExclDev eb, AdjKf kfa,
-                                                       float* __restrict__ lambar, float* __restrict__ gsum, int first)
+                                                       float* __restrict__ lambar, float* __restrict__ gsum)
 {
     __shared__ float lds[adj_lds_words<32, kRayCap[4] / 32, 2>()];
     int k = 0;   // uniform: the class whose blocks hold this one
@@ -357,11 +355,11 @@ __global__ __launch_bounds__(256) void ray_adj_small_k(const SmallTiles st, cons
     if (lt >= st.cnt[q]) return;   // whole block
     const TileDev td = tiles[st.list[st.off[q] + lt]];
     switch (q) {
-        case 0: ray_adj_tile<16, kRayCap[0] / 16, 1, KF>(td, counts, col, lam, g, eb, kfa, lambar, gsum, first, lds); break;
-        case 1: ray_adj_tile<16, kRayCap[1] / 16, 1, KF>(td, counts, col, lam, g, eb, kfa, lambar, gsum, first, lds); break;
-        case 2: ray_adj_tile<16, kRayCap[2] / 16, 1, KF>(td, counts, col, lam, g, eb, kfa, lambar, gsum, first, lds); break;
-        case 3: ray_adj_tile<16, kRayCap[3] / 16, 1, KF>(td, counts, col, lam, g, eb, kfa, lambar, gsum, first, lds); break;
-        default: ray_adj_tile<32, kRayCap[4] / 32, 2, KF>(td, counts, col, lam, g, eb, kfa, lambar, gsum, first, lds);
+        case 0: ray_adj_tile<16, kRayCap[0] / 16, 1, KF, FIRST>(td, counts, col, lam, g, eb, kfa, lambar, gsum, lds); break;
+        case 1: ray_adj_tile<16, kRayCap[1] / 16, 1, KF, FIRST>(td, counts, col, lam, g, eb, kfa, lambar, gsum, lds); break;
+        case 2: ray_adj_tile<16, kRayCap[2] / 16, 1, KF, FIRST>(td, counts, col, lam, g, eb, kfa, lambar, gsum, lds); break;
+        case 3: ray_adj_tile<16, kRayCap[3] / 16, 1, KF, FIRST>(td, counts, col, lam, g, eb, kfa, lambar, gsum, lds); break;
+        default: ray_adj_tile<32, kRayCap[4] / 32, 2, KF, FIRST>(td, counts, col, lam, g, eb, kfa, lambar, gsum, lds);
     }
 }
 
@@ -384,10 +382,11 @@ static void launch_adj_shape_t(const mrf_ctx* c, const AdjSrc& a, float* lambar,
         const uint32_t* list = (const uint32_t*)c->b_ray_list.p + c->ray_off[Q];
         if constexpr (ray_class_lds(Q)) {
             constexpr int RPW = kAdjShapes[Q][I].rpw;
-            hipLaunchKernelGGL((ray_adj_lds_k<G, CAP / G, RPW, KF>), dim3((unsigned)n), dim3(kTile * G / RPW), 0, s,
-                               list, n, (const TileDev*)c->b_tiles.p, (const int32_t*)c->b_counts.p,
-                               (const int32_t*)c->b_col.p, a.lam, (const float*)c->b_g.p, a.eb, a.kf, lambar, gsum,
-                               first);
+            const auto kernel = first ? ray_adj_lds_k<G, CAP / G, RPW, KF, true>
+                                      : ray_adj_lds_k<G, CAP / G, RPW, KF, false>;
+            hipLaunchKernelGGL(kernel, dim3((unsigned)n), dim3(kTile * G / RPW), 0, s, list, n,
+                               (const TileDev*)c->b_tiles.p, (const int32_t*)c->b_counts.p,
+                               (const int32_t*)c->b_col.p, a.lam, (const float*)c->b_g.p, a.eb, a.kf, lambar, gsum);
         } else {
             hipLaunchKernelGGL((ray_adj_k<G, CAP / G, KF>), dim3((unsigned)(n * tile_blocks<G>())), dim3(256), 0, s,
                                list, n, (const TileDev*)c->b_tiles.p, (const int32_t*)c->b_counts.p,
@@ -420,10 +419,11 @@ static void adj_small(const mrf_ctx* c, const AdjSrc& a, float* lambar, float* g
     const int64_t blocks = small_tiles(c, c->adj_sel, kSmallTilesAdj, st);
     if (blocks == 0) return;
     ProfScope ps(c, KID_ADJS, s);
-    const auto kernel = a.is_kf ? ray_adj_small_k<true> : ray_adj_small_k<false>;
+    const auto kernel = a.is_kf ? (first ? ray_adj_small_k<true, true> : ray_adj_small_k<true, false>)
+                                : (first ? ray_adj_small_k<false, true> : ray_adj_small_k<false, false>);
     hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(256), 0, s, st, (const TileDev*)c->b_tiles.p,
                        (const int32_t*)c->b_counts.p, (const int32_t*)c->b_col.p, a.lam, (const float*)c->b_g.p, a.eb,
-                       a.kf, lambar, gsum, first);
+                       a.kf, lambar, gsum);
 }
 
 template <int Q>
