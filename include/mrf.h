@@ -162,8 +162,7 @@ int mrf_build(mrf_ctx* ctx, const mrf_scene* scenes, int32_t n_scenes,
  * adds an image, then re-infers every keyframe): the result is the graph
  * mrf_build makes with these frames appended to that scene, bit for bit
  * (same ray ids, slots and voxel -> ray lists), but only the new frames are
- * traversed and sorted; their entries are merged behind each voxel's existing
- * ones.  depth: n_frames * H * W floats and T_wc: n_frames * 16 doubles
+ * traversed; the lists are sorted anew.  depth: n_frames * H * W floats and T_wc: n_frames * 16 doubles
  * (host or device, as in mrf_build), the last scene's camera model.  The last inference is
  * discarded.  Errors: MRF_ESTATE before mrf_build, MRF_EINVAL for a sparse grid
  * (its bricks depend on every frame: rebuild) or more than 65535 frames,

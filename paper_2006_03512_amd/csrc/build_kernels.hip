@@ -1271,8 +1271,7 @@ struct LoadPop {
 
 // Sorted runs written out as list entries: a block takes SC_TILE runs (boff[block]
 // entries before them), a wave 64 of them at a time through LDS, so that the
-// entries leave as contiguous stores.  The first run of a key sets vptr[key] (key
-// null: not again).
+// entries leave as contiguous stores.  The first run of a key sets vptr[key].
 __global__ __launch_bounds__(256) void runs_expand_k(const uint32_t* __restrict__ key,
                                                      const uint32_t* __restrict__ row,
                                                      const uint16_t* __restrict__ mask, int64_t n,
@@ -1291,10 +1290,10 @@ __global__ __launch_bounds__(256) void runs_expand_k(const uint32_t* __restrict_
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
         const int64_t at = r0 + r * 64 + lane, ic = at < n ? at : n - 1;
-        k[r] = key ? key[ic] : 0u;
+        k[r] = key[ic];
         rw[r] = row[ic];
         m[r] = at < n ? mask[ic] : 0u;
-        first[r] = key && at < n && (ic == 0 || key[ic - 1] != k[r]);
+        first[r] = at < n && (ic == 0 || key[ic - 1] != k[r]);
         sum += __popc(m[r]);
     }
 #pragma unroll
@@ -1317,7 +1316,7 @@ __global__ __launch_bounds__(256) void runs_expand_k(const uint32_t* __restrict_
         const uint32_t rel = (uint32_t)(slot0 - (groups.n > 1 ? group_slot_base_of_slot(groups, slot0) : 0));
         for (uint32_t x = m[r]; x; x &= x - 1, ++at) {
             lv[w][at] = rel + (uint32_t)__ffs(x) - 1u;
-            if (keys) lk[w][at] = k[r];
+            lk[w][at] = k[r];
         }
         // LDS accesses of one wave complete in order: the fences keep the compiler
         // from moving the reads above the writes, and the next round's writes above them
@@ -1327,7 +1326,7 @@ __global__ __launch_bounds__(256) void runs_expand_k(const uint32_t* __restrict_
         const int tot = __shfl(incl, 63, 64);
         for (int j = lane; j < tot; j += 64) {
             vals[out + j] = lv[w][j];
-            if (keys) keys[out + j] = lk[w][j];
+            keys[out + j] = lk[w][j];
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -1398,8 +1397,8 @@ static int key_bits(int64_t maxval)
     return b;
 }
 
-hipError_t build_incidence(mrf_ctx* c, int64_t s0, int64_t n, int64_t edges, uint32_t* keys, uint32_t* vals,
-                           int64_t* vptr, const SlotGroups& groups, bool keep_runs, hipStream_t s)
+hipError_t build_incidence(mrf_ctx* c, int64_t n, int64_t edges, uint32_t* keys, uint32_t* vals, int64_t* vptr,
+                           const SlotGroups& groups, bool keep_runs, hipStream_t s)
 {
     hipError_t e;
     const int bits = key_bits(c->Vk);
@@ -1410,7 +1409,7 @@ hipError_t build_incidence(mrf_ctx* c, int64_t s0, int64_t n, int64_t edges, uin
         int64_t* offs = (int64_t*)c->b_tmp64.p;
         const size_t tb = (radix_tmp_bytes(n) + 255) / 256 * 256;   // then the sort's spare values
         if ((e = ensure(c->b_misc, tb + sizeof(uint32_t) * (size_t)n)) != hipSuccess) return e;
-        e = radix_sort_pairs((const uint32_t*)c->b_g.p + s0, (uint32_t*)c->b_lam.p, (uint32_t*)c->b_ell.p,
+        e = radix_sort_pairs((const uint32_t*)c->b_g.p, (uint32_t*)c->b_lam.p, (uint32_t*)c->b_ell.p,
                              (uint32_t*)c->b_ellbar.p, (uint32_t*)((char*)c->b_misc.p + tb), keys, vals, n, bits,
                              (int32_t*)(offs + nh + 1), offs, c->b_misc.p, tb, s, groups);
         return e == hipSuccess ? launch_vptr_from_sorted(keys, n, c->Vk, vptr, s) : e;
@@ -1436,7 +1435,7 @@ hipError_t build_incidence(mrf_ctx* c, int64_t s0, int64_t n, int64_t edges, uin
     const int first = passes & 1;
     uint32_t* gkey = (uint32_t*)c->b_g.p;
     uint32_t* ginfo = first ? lk[0] : lr[1];
-    hipLaunchKernelGGL(runs_find_k, dim3((unsigned)nb), dim3(256), 0, s, (const int32_t*)c->b_col.p + s0, n,
+    hipLaunchKernelGGL(runs_find_k, dim3((unsigned)nb), dim3(256), 0, s, (const int32_t*)c->b_col.p, n,
                        (const SceneDev*)c->b_scenes.p, c->n_scenes, gkey, ginfo, bcnt);
     if ((e = scan_exclusive_i32(bcnt, boff, nb, c->b_misc.p, c->b_misc.cap, s)) != hipSuccess) return e;
     int64_t nr = 0;
@@ -1449,8 +1448,9 @@ hipError_t build_incidence(mrf_ctx* c, int64_t s0, int64_t n, int64_t edges, uin
         c->by_runs = 0;
     }
     if (keep_runs) {
-        if ((e = ensure(c->b_runrow, sizeof(uint32_t) * (size_t)nr)) != hipSuccess) return e;
-        if ((e = ensure(c->b_runmask, sizeof(uint16_t) * (size_t)nr)) != hipSuccess) return e;
+        const size_t nrr = (size_t)((double)nr * c->room);
+        if ((e = ensure(c->b_runrow, sizeof(uint32_t) * nrr)) != hipSuccess) return e;
+        if ((e = ensure(c->b_runmask, sizeof(uint16_t) * nrr)) != hipSuccess) return e;
         if ((e = ensure(c->b_rptr, sizeof(uint32_t) * (size_t)(c->Vk + 1))) != hipSuccess) return e;
         c->n_runs = nr;
     }
@@ -1488,23 +1488,6 @@ hipError_t build_incidence(mrf_ctx* c, int64_t s0, int64_t n, int64_t edges, uin
     }
     hipLaunchKernelGGL(vptr_gaps_k, dim3((unsigned)cdiv(c->Vk + 1, 256)), dim3(256), 0, s, (const uint32_t*)lk[0], nr,
                        c->Vk, edges, vptr, rptr);
-    return hipGetLastError();
-}
-
-hipError_t expand_runs(mrf_ctx* c, uint32_t* vals, hipStream_t s)
-{
-    if (c->n_runs == 0) return hipSuccess;
-    const int64_t nbr = cdiv(c->n_runs, SC_TILE);
-    hipError_t e = ensure(c->b_misc, sizeof(int64_t) * (size_t)(2 * nbr + 1) + scan_tmp_bytes(nbr));
-    if (e != hipSuccess) return e;
-    int64_t* bsum = (int64_t*)c->b_misc.p;
-    int64_t* eoff = bsum + nbr;
-    const uint16_t* mask = (const uint16_t*)c->b_runmask.p;
-    hipLaunchKernelGGL(scan_reduce_k<LoadPop>, dim3((unsigned)nbr), dim3(SC_T), 0, s, LoadPop{mask}, c->n_runs, bsum);
-    if ((e = scan_rec(LoadI64{bsum}, nbr, eoff, eoff + nbr + 1, s)) != hipSuccess) return e;
-    hipLaunchKernelGGL(runs_expand_k, dim3((unsigned)nbr), dim3(256), 0, s, (const uint32_t*)nullptr,
-                       (const uint32_t*)c->b_runrow.p, mask, c->n_runs, (const int64_t*)eoff, c->sg,
-                       (uint32_t*)nullptr, vals, (int64_t*)nullptr);
     return hipGetLastError();
 }
 
@@ -2060,42 +2043,14 @@ static hipError_t partition_pairs(mrf_ctx* c, const uint32_t* pstart, int64_t P,
 
 // ============================================================== adding keyframes
 //
-// Frames appended to the last scene add tiles and slots after every existing
-// one, so within a voxel's edge list (slots ascending) the existing entries come
-// first: with the new slots sorted by voxel key on their own, the merged list of
-// key k is the old list of k followed by the new one, at merged offset
-// old_vptr[k] + new_vptr[k].
+// Frames appended to the last scene add tiles and slots after every existing one; the
+// voxel -> ray lists are sorted anew.
 
-// brick-major key of the voxel of list entry j (col of its slot)
-__global__ void entry_keys_k(const SceneDev* __restrict__ scenes, int ns, const uint32_t* __restrict__ vedge,
-                             const int32_t* __restrict__ col, int64_t n, uint32_t* __restrict__ keys,
-                             const SlotGroups sg)
+__global__ void slot_keys_k(const SceneDev* __restrict__ scenes, int ns, const int32_t* __restrict__ col, int64_t n,
+                            uint32_t pad_key, uint32_t* __restrict__ keys)
 {
     for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n; j += (int64_t)gridDim.x * blockDim.x)
-        keys[j] = voxel_to_key(scenes, ns, col[group_slot_base(sg, j) + vedge[j]]);
-}
-
-// old entry j of key k moves to j + new_vptr[k]; new entry i (slot s_new0 + vals[i],
-// key keys_new[i] < Vk) to old_vptr[keys_new[i] + 1] + i
-__global__ void merge_old_k(const uint32_t* __restrict__ vedge_old, const uint32_t* __restrict__ keys_old, int64_t n,
-                            const int64_t* __restrict__ new_vptr, uint32_t* __restrict__ out)
-{
-    for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n; j += (int64_t)gridDim.x * blockDim.x)
-        out[j + new_vptr[keys_old[j]]] = vedge_old[j];
-}
-
-__global__ void merge_new_k(const uint32_t* __restrict__ vals, const uint32_t* __restrict__ keys_new, int64_t n,
-                            uint32_t s_new0, const int64_t* __restrict__ old_vptr, uint32_t* __restrict__ out)
-{
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        out[old_vptr[keys_new[i] + 1] + i] = s_new0 + vals[i];
-}
-
-// vptr_old[k] += new_vptr[k] over every key (k <= Vk)
-__global__ void add_vptr_k(int64_t* __restrict__ vptr, const int64_t* __restrict__ add, int64_t n)
-{
-    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x)
-        vptr[k] += add[k];
+        keys[j] = col[j] < 0 ? pad_key : voxel_key32(scenes, ns, (uint32_t)col[j]);
 }
 
 __global__ void add_i64_k(int64_t* __restrict__ p, int64_t v, int64_t n)
@@ -2118,26 +2073,11 @@ hipError_t launch_add_i64(int64_t* p, int64_t v, int64_t n, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_entry_keys(const mrf_ctx* c, const uint32_t* vedge, int64_t n, uint32_t* keys, hipStream_t s)
+hipError_t launch_slot_keys(const mrf_ctx* c, hipStream_t s)
 {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(entry_keys_k, dim3(grid_of(n)), dim3(256), 0, s, (const SceneDev*)c->b_scenes.p, c->n_scenes,
-                       vedge, (const int32_t*)c->b_col.p, n, keys, c->sg);
-    return hipGetLastError();
-}
-
-hipError_t launch_merge_incidence(const uint32_t* vedge_old, const uint32_t* keys_old, int64_t n_old,
-                                  const uint32_t* vals_new, const uint32_t* keys_new, int64_t n_new,
-                                  uint32_t s_new0, int64_t* vptr, int64_t* new_vptr, int64_t nkeys, uint32_t* out,
-                                  hipStream_t s)
-{
-    if (n_old > 0)
-        hipLaunchKernelGGL(merge_old_k, dim3(grid_of(n_old)), dim3(256), 0, s, vedge_old, keys_old, n_old,
-                           (const int64_t*)new_vptr, out);
-    if (n_new > 0)
-        hipLaunchKernelGGL(merge_new_k, dim3(grid_of(n_new)), dim3(256), 0, s, vals_new, keys_new, n_new, s_new0,
-                           (const int64_t*)vptr, out);
-    hipLaunchKernelGGL(add_vptr_k, dim3(grid_of(nkeys)), dim3(256), 0, s, vptr, (const int64_t*)new_vptr, nkeys);
+    if (c->S <= 0) return hipSuccess;
+    hipLaunchKernelGGL(slot_keys_k, dim3(grid_of(c->S)), dim3(256), 0, s, (const SceneDev*)c->b_scenes.p, c->n_scenes,
+                       (const int32_t*)c->b_col.p, c->S, (uint32_t)c->Vk, (uint32_t*)c->b_g.p);
     return hipGetLastError();
 }
 

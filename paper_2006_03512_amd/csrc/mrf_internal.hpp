@@ -374,6 +374,7 @@ struct mrf_ctx {
     // of every run, in voxel key order, and the first run of every key
     int by_runs = 0;
     int64_t n_runs = 0;
+    double room = 1.0;            // of the run buffers, for reserved frames
     mrf::DevBuf b_runrow, b_runmask, b_rptr;
 
     int64_t ray_off[mrf::kRayClasses] = {0}, ray_cnt[mrf::kRayClasses] = {0};   // tiles of a class: list range
@@ -444,19 +445,19 @@ hipError_t radix_sort_pairs(const uint32_t* keys_in, uint32_t* keys_a, uint32_t*
                             const SlotGroups& groups = SlotGroups{});
 size_t radix_hist_entries(int64_t n);
 size_t radix_tmp_bytes(int64_t n);   // tmp bytes radix_sort_pairs needs for n items
-// Voxel -> ray lists of the slots [s0, s0 + n) (n edges of them): vals[j] the slots
-// sorted stably by brick-major voxel key, less s0 and the first slot of their group;
-// keys[j] (may be null) their keys; vptr[k] the first entry of key k (k <= Vk).  The
-// per-slot message buffers hold the sort's data (keys may be b_lambar, vals any buffer
-// but b_g, b_lam, b_ell, b_ellbar).  incidence_by_runs: which of two routes n slots
-// take; the other one needs the sort keys that the emit pass leaves in b_g.  With
-// keep_runs (a graph by runs, s0 = 0) the lists stay runs: b_runrow, b_runmask, b_rptr
-// and vptr are written, vals and keys are not.
+// Voxel -> ray lists of the first n slots (n edges of them): vals[j] the slots sorted
+// stably by brick-major voxel key, less the first slot of their group; keys[j] their
+// keys; vptr[k] the first entry of key k (k <= Vk).  The per-slot message buffers hold
+// the sort's data (keys may be b_lambar, vals any buffer but b_g, b_lam, b_ell,
+// b_ellbar).  incidence_by_runs: which of two routes n slots take; the other one needs
+// the sort keys in b_g (the emit pass leaves them there, or launch_slot_keys).  With
+// keep_runs the lists stay runs: b_runrow, b_runmask, b_rptr and vptr are written, vals
+// and keys are not.
 bool incidence_by_runs(int64_t n);
-hipError_t build_incidence(mrf_ctx* c, int64_t s0, int64_t n, int64_t edges, uint32_t* keys, uint32_t* vals,
-                           int64_t* vptr, const SlotGroups& groups, bool keep_runs, hipStream_t s);
-// the lists of a graph by runs written out to vals (c->E entries, as build_incidence)
-hipError_t expand_runs(mrf_ctx* c, uint32_t* vals, hipStream_t s);
+hipError_t build_incidence(mrf_ctx* c, int64_t n, int64_t edges, uint32_t* keys, uint32_t* vals, int64_t* vptr,
+                           const SlotGroups& groups, bool keep_runs, hipStream_t s);
+// b_g[j] = sort key of slot j's voxel (padding: past every voxel), from col
+hipError_t launch_slot_keys(const mrf_ctx* c, hipStream_t s);
 hipError_t launch_vptr_from_sorted(const uint32_t* sorted_keys, int64_t n, int64_t V, int64_t* vptr,
                                    hipStream_t s);
 hipError_t build_classes(mrf_ctx* c, hipStream_t s);
@@ -468,14 +469,6 @@ hipError_t export_canonical_edges(const mrf_ctx* c, const void* in_slots, void* 
 hipError_t launch_tiles(mrf_ctx* c, int32_t* slots16, hipStream_t s, int f0 = 0, int nf = -1);
 hipError_t launch_tile_bases(mrf_ctx* c, hipStream_t s, int64_t t0 = 0);
 hipError_t launch_add_i64(int64_t* p, int64_t v, int64_t n, hipStream_t s);
-// keys[j] = brick-major key of the voxel of list entry j
-hipError_t launch_entry_keys(const mrf_ctx* c, const uint32_t* vedge, int64_t n, uint32_t* keys, hipStream_t s);
-// merged voxel -> ray list of the old entries (sorted, keys_old per entry) and the new
-// slots sorted on their own (vals relative to s_new0); vptr += new_vptr
-hipError_t launch_merge_incidence(const uint32_t* vedge_old, const uint32_t* keys_old, int64_t n_old,
-                                  const uint32_t* vals_new, const uint32_t* keys_new, int64_t n_new,
-                                  uint32_t s_new0, int64_t* vptr, int64_t* new_vptr, int64_t nkeys, uint32_t* out,
-                                  hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t s);
 // out[slot[j]] = in[j] for j < n (list order to slot order)
 hipError_t launch_scatter_by_slot(const uint32_t* slot, const float* in, int64_t n, float* out, hipStream_t s);
