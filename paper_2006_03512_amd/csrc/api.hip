@@ -161,6 +161,9 @@ static hipError_t enqueue_forward(mrf_ctx* c, int K, int keep, bool plain, hipSt
     return launch_voxel_phase(c, ell_slot(c, K, K, keep), VoxOut{theta, nullptr, (float*)c->b_L.p, nullptr}, s);
 }
 
+// The pair phase's weights: in slot order over runs, in list order over lists of edges.
+static const float* pair_weights(const mrf_ctx* c) { return (const float*)(c->by_runs ? c->b_kfws.p : c->b_kfw.p); }
+
 // Per-keyframe averaged messages (Sec. IV-A): the first sweep's lambda is the
 // prior (no incoming message yet); sweep k > 1 forms every keyframe's average
 // of the previous sweep's ray messages per voxel (pair phase) and from them each
@@ -173,7 +176,7 @@ static hipError_t enqueue_forward_kf(mrf_ctx* c, int K, int keep, bool plain, hi
 {
     hipError_t e;
     const float* theta = (const float*)c->b_theta.p;
-    const float* w = (const float*)c->b_kfw.p;
+    const float* w = pair_weights(c);
     double* Mlast = (double*)c->b_pair_m.p;
     float* x = (float*)c->b_kfx.p;
     const KfSrc kf{x, (const int64_t*)c->b_kfxb.p};
@@ -580,11 +583,10 @@ static int build_impl(mrf_ctx* c, const mrf_scene* scenes, int32_t n_scenes, con
     // one entry more: the keyframe-pair build keeps an exclusive count of E + 1 entries in each
     HCK(ensure(c->b_lam, e4 + 16), "mrf_build: alloc lam");
     HCK(ensure(c->b_ell, e4 + 16), "mrf_build: alloc ell");
-    // large graphs keep their lists as runs, but not where keyframe pairs are built on the
-    // lists of edges
-    c->by_runs = incidence_by_runs(S) && !c->kf ? 1 : 0;
+    // large graphs keep their lists as runs
+    c->by_runs = incidence_by_runs(S) ? 1 : 0;
     if (!c->by_runs) HCK(ensure(c->b_vedge, e4 + 16), "mrf_build: alloc vedge");
-    HCK(ensure(c->b_ellbar, e4), "mrf_build: alloc ellbar");
+    HCK(ensure(c->b_ellbar, e4 + 16), "mrf_build: alloc ellbar");
     HCK(ensure(c->b_lambar, e4), "mrf_build: alloc lambar");
     HCK(ensure(c->b_gsum, e4), "mrf_build: alloc gsum");
     if (c->kf) HCK(ensure(c->b_kflen, e4), "mrf_build: alloc chord lengths");
@@ -801,13 +803,13 @@ int mrf_add_frames(mrf_ctx* c, int32_t n_frames, const float* depth, const doubl
         HCK(grow_keep(c->b_tout, 2 * e4, 2 * k4, s), "mrf_add_frames: alloc t_out");
     }
     if (c->kf) HCK(grow_keep(c->b_kflen, e4, k4, s), "mrf_add_frames: alloc chord lengths");
-    c->by_runs = incidence_by_runs(S1) && !c->kf ? 1 : 0;
+    c->by_runs = incidence_by_runs(S1) ? 1 : 0;
     if (!c->by_runs) HCK(ensure(c->b_vedge, e4 + 16), "mrf_add_frames: alloc vedge");
     // message and scratch arrays: the old messages are stale once frames are added
     HCK(ensure(c->b_g, e4), "mrf_add_frames: alloc");
     HCK(ensure(c->b_lam, e4 + 16), "mrf_add_frames: alloc");
     HCK(ensure(c->b_ell, e4 + 16), "mrf_add_frames: alloc");
-    HCK(ensure(c->b_ellbar, e4), "mrf_add_frames: alloc");
+    HCK(ensure(c->b_ellbar, e4 + 16), "mrf_add_frames: alloc");
     HCK(ensure(c->b_lambar, e4), "mrf_add_frames: alloc");
     HCK(ensure(c->b_gsum, e4), "mrf_add_frames: alloc");
     // The lists are sorted anew, so that they are those of a build of all frames: less work
@@ -1248,7 +1250,9 @@ static void kid_bytes(const mrf_ctx* c, int k, double* bytes, int64_t* edges)
     } else if (k == KID_PAIR) {
         // per edge: vedge 4 + weight 4 + gathered ell 4; per pair: descriptor 16 + average 8
         *edges = c->E;
-        *bytes = 12.0 * (double)c->E + 24.0 * (double)c->n_pairs;
+        // (runs: row 4 + mask 2 per run instead of vedge)
+        *bytes = (c->by_runs ? 8.0 : 12.0) * (double)c->E + 24.0 * (double)c->n_pairs;
+        if (c->by_runs) *bytes += 6.0 * (double)c->n_runs;
     } else if (k == KID_KFVOX) {
         // per pair: average 8 + message index 4 + message 4; per voxel: descriptor 16 + theta 4
         *edges = c->E;
@@ -1288,7 +1292,7 @@ int mrf_profile_sweeps(mrf_ctx* c, int32_t reps, int32_t include_backward, mrf_k
         float* xs = (float*)c->b_export.p;
         const KfSrc kf{xs, (const int64_t*)c->b_kfxb.p};
         for (int r = 0; r < reps && e == hipSuccess; ++r) {
-            e = launch_pair_phase(c, ell_in, (const float*)c->b_kfw.p, (double*)c->b_pair_m.p, s);
+            e = launch_pair_phase(c, ell_in, pair_weights(c), (double*)c->b_pair_m.p, s);
             if (e == hipSuccess) e = launch_kf_voxel(c, (const double*)c->b_pair_m.p, theta, xs, nullptr, s);
             if (e == hipSuccess) e = launch_ray_phase_kf(c, kf, ell, false, s);
         }

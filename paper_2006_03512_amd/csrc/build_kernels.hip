@@ -1694,6 +1694,16 @@ struct TileItems {
     }
 };
 
+// class by number of runs
+__device__ __forceinline__ int run_class(int64_t m)
+{
+    int k = kVoxClasses - 1;
+#pragma unroll
+    for (int q = kRunClasses - 1; q >= 0; --q)
+        if (m <= kRunCap[q]) k = q;
+    return k;
+}
+
 // brick-major voxel keys by degree, or by number of runs (rptr not null)
 struct VoxItems {
     static constexpr int NC = kVoxClasses + 1;   // and voxels of too many edges
@@ -1714,12 +1724,7 @@ struct VoxItems {
     {
         const int c = vox_class(vptr[i + 1] - vptr[i]);
         if (!rptr || c >= kVoxClasses) return c;   // 255, or too many edges
-        const int64_t m = (int64_t)rptr[i + 1] - rptr[i];
-        int k = kVoxClasses - 1;
-#pragma unroll
-        for (int q = kRunClasses - 1; q >= 0; --q)
-            if (m <= kRunCap[q]) k = q;
-        return k;
+        return run_class((int64_t)rptr[i + 1] - rptr[i]);
     }
     __device__ void note(int64_t i, int c, PartLds& l) const
     {
@@ -1745,23 +1750,29 @@ struct VoxItems {
     }
 };
 
-// (keyframe, voxel) pairs by edge count
+// (keyframe, voxel) pairs by edge count, or by number of runs
 struct PairItems {
     static constexpr int NC = kVoxClasses;
     const uint32_t* pstart;
     int64_t n;
+    int runs;
     VoxDev* desc;
     __device__ void range(int64_t b, int items, int64_t& i0, int64_t& i1) const
     {
         i0 = b * items;
         i1 = n;
     }
-    __device__ int cls(int64_t i) const { return vox_class((int64_t)pstart[i + 1] - pstart[i]); }
+    __device__ int cls(int64_t i) const
+    {
+        const int64_t m = (int64_t)pstart[i + 1] - pstart[i];
+        return runs ? run_class(m) : vox_class(m);
+    }
     unsigned long long* pieces;
     __device__ void note(int64_t i, int, PartLds& l) const
     {
         const int64_t m = (int64_t)pstart[i + 1] - pstart[i];
-        if (m > kSegPiece) atomicAdd(&l.pieces, (uint32_t)seg_pieces(m, kSegPiece));
+        const int piece = runs ? kRunPiece : kSegPiece;
+        if (m > piece) atomicAdd(&l.pieces, (uint32_t)seg_pieces(m, piece));
     }
     __device__ void flush(const PartLds& l, int t) const
     {
@@ -2022,7 +2033,7 @@ hipError_t build_classes(mrf_ctx* c, hipStream_t s)
     return hipSuccess;
 }
 
-// the pairs [pstart[p], pstart[p + 1]) by edge count (b_pair_desc)
+// the pairs [pstart[p], pstart[p + 1]) of the lists (edges or runs) by size
 static hipError_t partition_pairs(mrf_ctx* c, const uint32_t* pstart, int64_t P, hipStream_t s)
 {
     hipError_t e;
@@ -2032,13 +2043,13 @@ static hipError_t partition_pairs(mrf_ctx* c, const uint32_t* pstart, int64_t P,
     if ((e = ensure(c->b_part, head + sizeof(uint32_t) * (size_t)(PairItems::NC * nb))) != hipSuccess) return e;
     unsigned long long* tot = (unsigned long long*)c->b_part.p;
     if ((e = launch_fill_u32((uint32_t*)tot, 0u, (int64_t)(head / 4), s)) != hipSuccess) return e;
-    e = partition(PairItems{pstart, P, (VoxDev*)c->pair.desc.p, tot + kPartMaxClasses}, rounds, nb,
+    e = partition(PairItems{pstart, P, c->by_runs, (VoxDev*)c->pair.desc.p, tot + kPartMaxClasses}, rounds, nb,
                   (uint32_t*)((char*)c->b_part.p + head), tot, nullptr, 1, 0, s);
     unsigned long long h[kPartMaxClasses + 1];
     if (e == hipSuccess) e = hipMemcpyAsync(h, tot, head, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return e;
-    return finish_segments(c, c->pair, h, (int64_t)h[kPartMaxClasses], kSegPiece, s);
+    return finish_segments(c, c->pair, h, (int64_t)h[kPartMaxClasses], c->by_runs ? kRunPiece : kSegPiece, s);
 }
 
 // ============================================================== adding keyframes
@@ -2085,9 +2096,12 @@ hipError_t launch_slot_keys(const mrf_ctx* c, hipStream_t s)
 //
 // Per-keyframe averaged messages (Sec. IV-A): the rays of one keyframe that
 // cross a voxel send it one message, the average of theirs weighted by the
-// length each travels in the voxel.  A voxel's edge list (slots ascending) is
-// grouped by keyframe, since slots are frame-major; each run of one keyframe
-// inside one voxel's list is a (keyframe, voxel) pair.
+// length each travels in the voxel.  A voxel's list (slots ascending) is grouped by
+// keyframe, since slots are frame-major; each stretch of one keyframe inside one
+// voxel's list is a (keyframe, voxel) pair.  A list of runs (16 slots of a row, so of
+// one keyframe) has a tenth of the entries of one of edges: lists and pairs of 4 VGA
+// frames at 4 cm (1.14e8 slots, the last one added) take 4.5 ms so, and 5.5 over the
+// list of edges.
 
 // first slot of every frame (frames occupy consecutive slot ranges in order);
 // fs[nf] = S
@@ -2101,12 +2115,12 @@ __global__ void frame_slots_k(const FrameDev* __restrict__ frames, int nf, const
 
 // frame holding slot x: the last f with fs[f] <= x (frames without edges
 // share their successor's first slot and are skipped)
-__device__ __forceinline__ int slot_frame(const int64_t* __restrict__ fs, int nf, uint32_t x)
+__device__ __forceinline__ int slot_frame(const int64_t* __restrict__ fs, int nf, int64_t x)
 {
     int lo = 0, hi = nf;   // fs[lo] <= x < fs[hi]
     while (hi - lo > 1) {
         const int mid = (lo + hi) >> 1;
-        if (fs[mid] <= (int64_t)x)
+        if (fs[mid] <= x)
             lo = mid;
         else
             hi = mid;
@@ -2114,15 +2128,15 @@ __device__ __forceinline__ int slot_frame(const int64_t* __restrict__ fs, int nf
     return lo;
 }
 
-// the frame (keyframe) of every entry of the voxel -> ray list
-__global__ void entry_frame_k(const uint32_t* __restrict__ vedge, int64_t n, const int64_t* __restrict__ fs, int nf,
-                              uint16_t* __restrict__ fr)
+// the frame (keyframe) of every entry of the voxel -> ray list (slots: a slot's, 1, or a row's, 16)
+__global__ void entry_frame_k(const uint32_t* __restrict__ entry, int slots, int64_t n,
+                              const int64_t* __restrict__ fs, int nf, uint16_t* __restrict__ fr)
 {
     for (int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; j < n; j += (int64_t)gridDim.x * blockDim.x)
-        fr[j] = (uint16_t)slot_frame(fs, nf, vedge[j]);
+        fr[j] = (uint16_t)slot_frame(fs, nf, (int64_t)entry[j] * slots);
 }
 
-// 1 where entry j of the voxel -> ray list starts a (keyframe, voxel) run
+// 1 where entry j of the voxel -> ray list starts a (keyframe, voxel) pair
 struct LoadPairStart {
     const uint16_t* fr;     // frame of each entry
     const uint32_t* keys;   // sorted voxel keys, aligned with the list
@@ -2177,6 +2191,27 @@ __global__ void pair_weight_k(const uint32_t* __restrict__ vedge, const uint32_t
     }
 }
 
+// The same over runs, in slot order: lane l of a 16-lane group takes lane l of a run's row.
+__global__ __launch_bounds__(256) void pair_weight_runs_k(const uint32_t* __restrict__ rows,
+                                                          const uint16_t* __restrict__ masks,
+                                                          const uint32_t* __restrict__ pos, int64_t n,
+                                                          const uint32_t* __restrict__ pstart,
+                                                          const float* __restrict__ len,
+                                                          const double* __restrict__ wsum, float* __restrict__ w)
+{
+    const int l = threadIdx.x & 15;
+    for (int64_t j = (int64_t)blockIdx.x * 16 + (threadIdx.x >> 4); j < n; j += (int64_t)gridDim.x * 16) {
+        if (!((masks[j] >> l) & 1u)) continue;
+        const uint32_t p = pos[j + 1] - 1;   // inclusive count of pair starts, less one
+        const double sw = wsum[p];
+        const int64_t at = (int64_t)rows[j] * kTile + l;
+        int m = 0;
+        if (!(sw > 0.0))
+            for (uint32_t r = pstart[p]; r < pstart[p + 1]; ++r) m += __popc((uint32_t)masks[r]);
+        w[at] = sw > 0.0 ? (float)((double)len[at] / sw) : (float)(1.0 / (double)m);
+    }
+}
+
 hipError_t build_keyframe_pairs(mrf_ctx* c, hipStream_t s)
 {
     hipError_t e;
@@ -2203,33 +2238,35 @@ hipError_t build_keyframe_pairs(mrf_ctx* c, hipStream_t s)
                        (const FrameDev*)c->b_frames.p, nf, (const int64_t*)c->b_tbase.p, c->T, d_fs);
     if ((e = ensure(c->b_kfx, sizeof(float) * (size_t)(nx > 0 ? nx : 1))) != hipSuccess) return e;
 
-    // pair starts: exclusive count over the voxel -> ray list (b_lam, E + 1 entries),
-    // keys sorted in b_lambar from the radix sort, each entry's frame in b_gsum
-    const uint32_t* vedge = (const uint32_t*)c->b_vedge.p;
-    uint16_t* fr = (uint16_t*)c->b_gsum.p;   // 2 E bytes of a per-slot array free during the build
-    if (E > 0) {
-        int64_t b = cdiv(E, 256);
-        if (b > 65536) b = 65536;
-        hipLaunchKernelGGL(entry_frame_k, dim3((unsigned)b), dim3(256), 0, s, vedge, E, (const int64_t*)d_fs, nf, fr);
-    }
-    const LoadPairStart ld{fr, (const uint32_t*)c->b_lambar.p};
-    uint32_t* pos = (uint32_t*)c->b_lam.p;
-    const size_t sb = scan_tmp_bytes(E);
+    // Pair starts: exclusive count over the entries (pos, n + 1 of them) from the sorted keys
+    // and each entry's frame, in per-slot arrays free during the build.  Lists of edges: keys
+    // in b_lambar, count in b_lam, pair starts in b_ell; runs: b_lam, b_ell, b_ellbar.
+    const bool runs = c->by_runs != 0;
+    const int64_t n = runs ? c->n_runs : E;
+    const uint32_t* entry = (const uint32_t*)(runs ? c->b_runrow.p : c->b_vedge.p);
+    uint16_t* fr = (uint16_t*)c->b_gsum.p;   // 2 n bytes
+    const unsigned nblocks = (unsigned)std::min<int64_t>(cdiv(n, 256), 65536);
+    if (n > 0)
+        hipLaunchKernelGGL(entry_frame_k, dim3(nblocks), dim3(256), 0, s, entry, runs ? kTile : 1, n,
+                           (const int64_t*)d_fs, nf, fr);
+    const LoadPairStart ld{fr, (const uint32_t*)(runs ? c->b_lam.p : c->b_lambar.p)};
+    uint32_t* pos = (uint32_t*)(runs ? c->b_ell.p : c->b_lam.p);
+    const size_t sb = scan_tmp_bytes(n);
     if ((e = ensure(c->b_misc, sb > c->b_misc.cap ? sb : c->b_misc.cap)) != hipSuccess) return e;
-    if ((e = scan_rec(ld, E, pos, (int64_t*)c->b_misc.p, s)) != hipSuccess) return e;
+    if ((e = scan_rec(ld, n, pos, (int64_t*)c->b_misc.p, s)) != hipSuccess) return e;
     uint32_t P32 = 0;
-    if ((e = hipMemcpyAsync(&P32, pos + E, sizeof(uint32_t), hipMemcpyDeviceToHost, s)) != hipSuccess) return e;
+    if ((e = hipMemcpyAsync(&P32, pos + n, sizeof(uint32_t), hipMemcpyDeviceToHost, s)) != hipSuccess) return e;
     if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
     const int64_t P = P32;
     c->n_pairs = P;
-    uint32_t* pstart = (uint32_t*)c->b_ell.p;   // P + 1 <= E + 1 entries
+    uint32_t* pstart = (uint32_t*)(runs ? c->b_ellbar.p : c->b_ell.p);   // P + 1 <= n + 1 entries
     if ((e = ensure(c->b_pair_x, sizeof(uint32_t) * (size_t)(P > 0 ? P : 1))) != hipSuccess) return e;
     if ((e = ensure(c->b_pair_m, sizeof(double) * (size_t)(P > 0 ? P : 1))) != hipSuccess) return e;
-    hipLaunchKernelGGL(pair_init_k, dim3((unsigned)cdiv(E + 1, 256)), dim3(256), 0, s, ld, E, (const uint32_t*)pos,
+    hipLaunchKernelGGL(pair_init_k, dim3((unsigned)cdiv(n + 1, 256)), dim3(256), 0, s, ld, n, (const uint32_t*)pos,
                        (const SceneDev*)c->b_scenes.p, c->n_scenes, (const int64_t*)d_xb, pstart,
                        (uint32_t*)c->b_pair_x.p);
 
-    // pairs by edge count, as VoxDev work items of the voxel-phase kernels
+    // pairs by size, as VoxDev work items of the voxel-phase kernels
     if ((e = ensure(c->pair.desc, (size_t)(P > 0 ? P : 1) * sizeof(VoxDev))) != hipSuccess) return e;
     if ((e = partition_pairs(c, pstart, P, s)) != hipSuccess) return e;
 
@@ -2242,18 +2279,27 @@ hipError_t build_keyframe_pairs(mrf_ctx* c, hipStream_t s)
         hipLaunchKernelGGL(kf_vox_k, dim3((unsigned)cdiv(nv, 256)), dim3(256), 0, s, (const VoxDev*)c->vox.desc.p,
                            nv, (const uint32_t*)pos, (VoxDev*)c->b_kf_vox.p);
 
-    // weights: chord length over the pair's summed chord length, in list order;
-    // the chord lengths (slot order, b_kflen) are summed per pair by the pair phase
+    // weights: chord length over the pair's summed chord length, which the pair phase
+    // forms from the chord lengths (slot order, b_kflen).  Lists of edges keep them in list
+    // order (b_kfw), runs in slot order (b_kfws, where the reverse pass reads them too).
     double* wsum = (double*)c->b_pair_m.p;
-    if ((e = ensure(c->b_kfw, sizeof(float) * (size_t)(E > 0 ? E : 1))) != hipSuccess) return e;
-    float* w = (float*)c->b_kfw.p;
     if ((e = launch_pair_phase(c, (const float*)c->b_kflen.p, nullptr, wsum, s)) != hipSuccess) return e;
-    if (E > 0) {
-        int64_t b = cdiv(E, 256);
-        if (b > 65536) b = 65536;
-        hipLaunchKernelGGL(pair_weight_k, dim3((unsigned)b), dim3(256), 0, s, vedge, (const uint32_t*)pos, E,
-                           (const uint32_t*)pstart, (const float*)c->b_kflen.p, (const double*)wsum, w);
+    if (runs) {
+        if ((e = ensure(c->b_kfws, sizeof(float) * (size_t)c->S)) != hipSuccess) return e;
+        if ((e = launch_fill((float*)c->b_kfws.p, 0.0f, c->S, s)) != hipSuccess) return e;
+        if (n > 0)
+            hipLaunchKernelGGL(pair_weight_runs_k, dim3((unsigned)std::min<int64_t>(cdiv(n, 16), 65536)), dim3(256), 0,
+                               s, entry, (const uint16_t*)c->b_runmask.p, (const uint32_t*)pos, n,
+                               (const uint32_t*)pstart, (const float*)c->b_kflen.p, (const double*)wsum,
+                               (float*)c->b_kfws.p);
+        c->kfws_ready = 1;
+        return hipGetLastError();
     }
+    if ((e = ensure(c->b_kfw, sizeof(float) * (size_t)(E > 0 ? E : 1))) != hipSuccess) return e;
+    if (E > 0)
+        hipLaunchKernelGGL(pair_weight_k, dim3(nblocks), dim3(256), 0, s, entry, (const uint32_t*)pos, E,
+                           (const uint32_t*)pstart, (const float*)c->b_kflen.p, (const double*)wsum,
+                           (float*)c->b_kfw.p);
     return hipGetLastError();
 }
 

@@ -356,16 +356,16 @@ struct mrf_ctx {
     int64_t n_pairs = 0;          // (keyframe, voxel) pairs with at least one edge
     int64_t n_kfx = 0;            // entries of the per-keyframe message buffers
     mrf::DevBuf b_kflen;          // per edge slot: chord length (Euclidean) of the edge
-    mrf::DevBuf b_kfw;            // per vedge entry: chord length / the pair's summed chord length
+    mrf::DevBuf b_kfw;            // lists of edges: per entry, chord length / the pair's summed chord length
     mrf::DevBuf b_pair_m;         // per pair: FP64 average message of the keyframe into the voxel
     mrf::DevBuf b_pair_x;         // per pair: index of its entry in b_kfx
     mrf::DevBuf b_kfx;            // per-keyframe voxel -> ray messages
     mrf::DevBuf b_kfxb;           // per frame: b_kfx base less its scene's first voxel id
     mrf::DevBuf b_kfxr, b_kfy;    // reverse pass: a sweep's rebuilt keyframe messages, the pair derivatives
-    mrf::DevBuf b_kfws;           // reverse pass: per edge slot, the edge's share of its pair's weight
+    mrf::DevBuf b_kfws;           // per edge slot: the same (reverse pass; over runs the forward one too)
     int kfws_ready = 0;           // b_kfws holds the current build's weights
     mrf::DevBuf b_kf_vox;         // per touched voxel: VoxDev over its pairs (start, count, voxel id)
-    mrf::SegList pair;            // pairs by edge count: VoxDev (start, m, pair id)
+    mrf::SegList pair;            // pairs by number of edges or runs: VoxDev (start, m, pair id)
     int64_t n_kf_vox = 0;
     mrf::DevBuf b_ray_list;       // tile ids by tile length class, class-major
     mrf::SegList vox;             // touched voxels by degree: VoxDev, brick-major keys inside a class
@@ -474,7 +474,8 @@ hipError_t launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t s);
 hipError_t launch_scatter_by_slot(const uint32_t* slot, const float* in, int64_t n, float* out, hipStream_t s);
 // per-keyframe averaged messages: (keyframe, voxel) pairs of the built graph,
 // their weights, work classes and message-buffer indices (after build_classes,
-// with the sorted voxel keys still in b_lambar and chord lengths in b_kfw)
+// with the sorted voxel keys still in b_lambar, or those of the runs in b_lam, and chord
+// lengths in b_kflen)
 hipError_t build_keyframe_pairs(mrf_ctx* c, hipStream_t s);
 
 // the classes of a small graph's one launch (none: a large graph); blocks in all

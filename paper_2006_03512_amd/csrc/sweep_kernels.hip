@@ -530,7 +530,9 @@ __global__ __launch_bounds__(256) void hub_sum_k(const VoxDev* __restrict__ hubs
 //   4  at most 64: one per wave, two in turn;   5  at most 256: one per wave;
 //   6  at most 1024: the four waves of a block;   7  more: pieces of 1024 runs.
 // Bound by HBM: 5e8 edges (8 VGA frames at 2 cm) in 0.84 ms where seg_sum_k takes
-// 1.13, 1.3e8 (3 rooms) in 0.173 and 0.275.
+// 1.13, 1.3e8 (3 rooms) in 0.173 and 0.275.  With weights (keyframe pairs) a run takes a
+// second line: 1e8 edges in 0.39 ms where the sums without weights take 0.21; sweeps and
+// their reverse 3.72 ms against 3.76 by the list of edges.
 
 template <int J>
 __device__ __forceinline__ uint32_t row_bcast(uint32_t x)
@@ -547,22 +549,24 @@ __device__ __forceinline__ void run_load(const float* __restrict__ in, uint32_t 
     ((x[J] = in[(uint64_t)row_bcast<J>(row) * kTile + l]), ...);
 }
 
-// a[J / PER] += the messages whose mask bit is set
-template <int PER, int N, int... J>
-__device__ __forceinline__ void run_add(uint32_t mask, const float (&x)[16], double (&a)[N],
-                                        std::integer_sequence<int, J...>)
+// a[J / PER] += the messages whose mask bit is set (WT: each times its weight)
+template <int PER, bool WT, int N, int... J>
+__device__ __forceinline__ void run_add(uint32_t mask, const float (&x)[16], const float (&w)[WT ? 16 : 1],
+                                        double (&a)[N], std::integer_sequence<int, J...>)
 {
     const int l = threadIdx.x & 15;
-    ((a[J / PER] += (row_bcast<J>(mask) >> l) & 1u ? (double)x[J] : 0.0), ...);
+    ((a[J / PER] += (row_bcast<J>(mask) >> l) & 1u ? (WT ? (double)x[J] * (double)w[WT ? J : 0] : (double)x[J]) : 0.0),
+     ...);
 }
 
 constexpr auto kRunSteps = std::make_integer_sequence<int, 16>{};
 
 // classes 0 and 1: 16 / PER segments of at most PER runs per group
-template <int PER>
+template <int PER, bool WT>
 __device__ __forceinline__ void run_parts(int64_t lb, const VoxDev* __restrict__ vd, int64_t n,
                                           const uint32_t* __restrict__ rows, const uint16_t* __restrict__ masks,
-                                          const float* __restrict__ in, const VoxOut& out)
+                                          const float* __restrict__ in, const float* __restrict__ w,
+                                          const VoxOut& out)
 {
     constexpr int NS = 16 / PER;
     const int l = threadIdx.x & 15, q = l % PER;
@@ -571,12 +575,13 @@ __device__ __forceinline__ void run_parts(int64_t lb, const VoxDev* __restrict__
     const int64_t at = d.start + min(q, d.m - 1);
     const uint32_t row = rows[at];
     const uint32_t mask = vi < n && q < d.m ? masks[at] : 0u;
-    float x[16];
+    float x[16], wx[WT ? 16 : 1];
     run_load(in, row, x, kRunSteps);
+    if constexpr (WT) run_load(w, row, wx, kRunSteps);
     double a[NS];
 #pragma unroll
     for (int u = 0; u < NS; ++u) a[u] = 0.0;
-    run_add<PER>(mask, x, a, kRunSteps);
+    run_add<PER, WT>(mask, x, wx, a, kRunSteps);
     double t = 0.0;   // at the segment's first lane
 #pragma unroll
     for (int u = 0; u < NS; ++u) {
@@ -586,63 +591,76 @@ __device__ __forceinline__ void run_parts(int64_t lb, const VoxDev* __restrict__
     if (q == 0 && vi < n) vox_store(d.v, t, out);
 }
 
-// classes 2 to 4: one segment of at most G runs per G lanes, two in turn
-template <int G>
+// classes 2 to 4: one segment of at most G runs per G lanes, two in turn (weighted: one,
+// for the registers that its weights take)
+template <int G, bool WT>
 __device__ __forceinline__ void run_group(int64_t lb, const VoxDev* __restrict__ vd, int64_t n,
                                           const uint32_t* __restrict__ rows, const uint16_t* __restrict__ masks,
-                                          const float* __restrict__ in, const VoxOut& out)
+                                          const float* __restrict__ in, const float* __restrict__ w,
+                                          const VoxOut& out)
 {
-    const int64_t v0 = (lb * (256 / G) + (int)(threadIdx.x / G)) * 2;
+    constexpr int U = WT ? 1 : 2;
+    const int64_t v0 = (lb * (256 / G) + (int)(threadIdx.x / G)) * U;
     const int l = threadIdx.x & (G - 1);
-    VoxDev d[2];
-    uint32_t row[2], mask[2];
-    float x[2][16];
+    VoxDev d[U];
+    uint32_t row[U], mask[U];
+    float x[U][16], wx[U][WT ? 16 : 1];
 #pragma unroll
-    for (int u = 0; u < 2; ++u) d[u] = vd[min(v0 + u, n - 1)];   // past the list: a repeat, not stored
+    for (int u = 0; u < U; ++u) d[u] = vd[min(v0 + u, n - 1)];   // past the list: a repeat, not stored
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
+    for (int u = 0; u < U; ++u) {
         const int64_t at = d[u].start + min(l, d[u].m - 1);
         row[u] = rows[at];
         mask[u] = l < d[u].m ? masks[at] : 0u;
     }
 #pragma unroll
-    for (int u = 0; u < 2; ++u) run_load(in, row[u], x[u], kRunSteps);
+    for (int u = 0; u < U; ++u) {
+        run_load(in, row[u], x[u], kRunSteps);
+        if constexpr (WT) run_load(w, row[u], wx[u], kRunSteps);
+    }
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
+    for (int u = 0; u < U; ++u) {
         double a[1] = {0.0};
-        run_add<16>(mask[u], x[u], a, kRunSteps);
+        run_add<16, WT>(mask[u], x[u], wx[u], a, kRunSteps);
         const double t = dgroup_sum_d<G>(a[0]);
         if (l == 0 && v0 + u < n) vox_store(d[u].v, t, out);
     }
 }
 
 // 64 runs of a segment by a wave, lane i holding run base + i
+template <bool WT>
 __device__ __forceinline__ double run_wave64(int64_t start, int m, int base, const uint32_t* __restrict__ rows,
-                                             const uint16_t* __restrict__ masks, const float* __restrict__ in)
+                                             const uint16_t* __restrict__ masks, const float* __restrict__ in,
+                                             const float* __restrict__ w)
 {
     const int i = base + (int)(threadIdx.x & 63);
     const int64_t at = start + min(i, m - 1);
     const uint32_t row = rows[at];
     const uint32_t mask = i < m ? masks[at] : 0u;
-    float x[16];
+    float x[16], wx[WT ? 16 : 1];
     run_load(in, row, x, kRunSteps);
+    if constexpr (WT) run_load(w, row, wx, kRunSteps);
     double a[1] = {0.0};
-    run_add<16>(mask, x, a, kRunSteps);
+    run_add<16, WT>(mask, x, wx, a, kRunSteps);
     return a[0];
 }
 
 // runs [base, base + 256) of a segment by a wave
+template <bool WT>
 __device__ __forceinline__ double run_wave256(const VoxDev& d, int base, const uint32_t* __restrict__ rows,
-                                              const uint16_t* __restrict__ masks, const float* __restrict__ in)
+                                              const uint16_t* __restrict__ masks, const float* __restrict__ in,
+                                              const float* __restrict__ w)
 {
     double a = 0.0;
-    for (int t = base; t < base + 256 && t < d.m; t += 64) a += run_wave64(d.start, d.m, t, rows, masks, in);
+    for (int t = base; t < base + 256 && t < d.m; t += 64) a += run_wave64<WT>(d.start, d.m, t, rows, masks, in, w);
     return dgroup_sum_d<64>(a);
 }
 
+template <bool WT>
 __global__ __launch_bounds__(256, 8) void run_sum_k(const SegWork s, const uint32_t* __restrict__ rows,
-                                                    const uint16_t* __restrict__ masks,
-                                                    const float* __restrict__ in, VoxOut out)
+                                                             const uint16_t* __restrict__ masks,
+                                                             const float* __restrict__ in,
+                                                             const float* __restrict__ w, VoxOut out)
 {
     __shared__ double red[4];
     int k = kVoxClasses - 1;   // uniform: the class whose blocks hold this one
@@ -653,21 +671,21 @@ __global__ __launch_bounds__(256, 8) void run_sum_k(const SegWork s, const uint3
     const int64_t n = s.cnt[k];
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     switch (k) {
-        case 0: run_parts<4>(lb, d, n, rows, masks, in, out); break;
-        case 1: run_parts<8>(lb, d, n, rows, masks, in, out); break;
-        case 2: run_group<16>(lb, d, n, rows, masks, in, out); break;
-        case 3: run_group<32>(lb, d, n, rows, masks, in, out); break;
-        case 4: run_group<64>(lb, d, n, rows, masks, in, out); break;
+        case 0: run_parts<4, WT>(lb, d, n, rows, masks, in, w, out); break;
+        case 1: run_parts<8, WT>(lb, d, n, rows, masks, in, w, out); break;
+        case 2: run_group<16, WT>(lb, d, n, rows, masks, in, w, out); break;
+        case 3: run_group<32, WT>(lb, d, n, rows, masks, in, w, out); break;
+        case 4: run_group<64, WT>(lb, d, n, rows, masks, in, w, out); break;
         case 5: {
             const int64_t v = lb * 4 + wv;
             if (v >= n) return;   // whole wave
-            const double t = run_wave256(d[v], 0, rows, masks, in);
+            const double t = run_wave256<WT>(d[v], 0, rows, masks, in, w);
             if ((threadIdx.x & 63) == 0) vox_store(d[v].v, t, out);
             break;
         }
         default: {
             if (lb >= n) return;   // whole block
-            const double t = run_wave256(d[lb], wv * 256, rows, masks, in);
+            const double t = run_wave256<WT>(d[lb], wv * 256, rows, masks, in, w);
             if ((threadIdx.x & 63) == 0) red[wv] = t;
             __syncthreads();
             if (threadIdx.x == 0) {
@@ -690,6 +708,11 @@ static int64_t run_per_block(int k)
 {
     constexpr int64_t per[kRunClasses] = {64, 32, 32, 16, 8, 4, 1};
     return k < kRunClasses ? per[k] : 1;
+}
+
+static int64_t run_per_block_weighted(int k)   // one in turn
+{
+    return k >= 2 && k <= 4 ? run_per_block(k) / 2 : run_per_block(k);
 }
 
 // the work of one launch; returns its blocks
@@ -738,20 +761,22 @@ static hipError_t seg_sum(mrf_ctx* c, const SegList& l, const float* in, const V
     return hub_sum(c, l, out, s);
 }
 
-static hipError_t run_sum(mrf_ctx* c, const float* in, const VoxOut& out, hipStream_t s)
+// w (slot order, may be null): every message times its weight
+static hipError_t run_sum(mrf_ctx* c, const SegList& l, const float* in, const VoxOut& out, const float* w,
+                          hipStream_t s)
 {
     SegWork k;
-    const int64_t blocks = seg_work(c, c->vox, run_per_block, k);
+    const int64_t blocks = seg_work(c, l, w ? run_per_block_weighted : run_per_block, k);
     if (blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(run_sum_k, dim3((unsigned)blocks), dim3(256), 0, s, k, (const uint32_t*)c->b_runrow.p,
-                       (const uint16_t*)c->b_runmask.p, in, out);
-    return hub_sum(c, c->vox, out, s);
+    hipLaunchKernelGGL(w ? run_sum_k<true> : run_sum_k<false>, dim3((unsigned)blocks), dim3(256), 0, s, k,
+                       (const uint32_t*)c->b_runrow.p, (const uint16_t*)c->b_runmask.p, in, w, out);
+    return hub_sum(c, l, out, s);
 }
 
 hipError_t launch_voxel_phase(mrf_ctx* c, const float* in, VoxOut out, hipStream_t s)
 {
     ProfScope ps(c, KID_VOX, s);
-    return c->by_runs ? run_sum(c, in, out, s) : seg_sum(c, c->vox, in, out, nullptr, s);
+    return c->by_runs ? run_sum(c, c->vox, in, out, nullptr, s) : seg_sum(c, c->vox, in, out, nullptr, s);
 }
 
 // ------------------------------------------------------------ keyframe pairs
@@ -766,7 +791,8 @@ hipError_t launch_voxel_phase(mrf_ctx* c, const float* in, VoxOut out, hipStream
 hipError_t launch_pair_phase(mrf_ctx* c, const float* in, const float* w, double* M, hipStream_t s)
 {
     ProfScope ps(c, KID_PAIR, s);
-    return seg_sum(c, c->pair, in, VoxOut{nullptr, nullptr, nullptr, nullptr, M}, w, s);
+    const VoxOut out{nullptr, nullptr, nullptr, nullptr, M};
+    return c->by_runs ? run_sum(c, c->pair, in, out, w, s) : seg_sum(c, c->pair, in, out, w, s);
 }
 
 // One 16-lane group per touched voxel: T = theta_v + the sum of the voxel's

@@ -95,8 +95,8 @@ RUNS = {
 
 @pytest.mark.parametrize("name", list(RUNS))
 def test_large_graphs_sum_runs(name):
-    """Lists kept as runs (2^19 slots and more): beliefs and gradients as from the lists of edges (a build
-    that prepares keyframe pairs keeps those), frames added to such a graph as built with it."""
+    """Lists kept as runs (2^19 slots and more): beliefs as the exported messages and chords give them, for
+    exact and per-keyframe averaged messages; frames added to such a graph as built with it."""
     import dataclasses
 
     from paper_2006_03512_amd import RayMRF
@@ -105,38 +105,58 @@ def test_large_graphs_sum_runs(name):
     p0 = dataclasses.replace(scs[0].params, group_slots_log2=log2)
     for s in scs:
         s.params = p0
-    edges = log2 == 0   # keyframe pairs need one slot group
+    kf = log2 == 0   # keyframe pairs need one slot group
+    sc = scs[-1]
+    part = [*scs[:-1], dataclasses.replace(sc, depth=sc.depth[:-1], T_wc=sc.T_wc[:-1])]
     out = []
-    for kf in (False, True) if edges else (False,):
+    for added in (False, True):
         m = RayMRF()
-        st = m.build(scs, keyframe_average=kf)
+        st = m.build(part if added else scs, keep_chords=True, keyframe_average=kf, reserve_frames=int(added))
+        if added:
+            st = m.add_frames(sc.depth[-1:], sc.T_wc[-1:])
         assert st.n_slots >= 1 << 19 and (st.n_slot_groups > 1) == (log2 > 0)
         rng = np.random.default_rng(3)
         theta = torch.from_numpy(rng.normal(-2, 0.5, st.n_voxels).astype(np.float32)).cuda()
         dL = torch.from_numpy(rng.normal(0, 1, st.n_voxels).astype(np.float32)).cuda()
         sigma = torch.from_numpy(scs[0].sigma_table.astype(np.float32)).cuda()
         m.infer(theta, sigma, 2, keep_checkpoints=True)
-        logit = m.marginals()[1]
-        out.append((logit, *m.backward(dL)))
-        if not kf:
-            col = m.export_incidence()["col"].cpu().numpy()
+        got = [m.marginals()[1], *m.backward(dL)]
+        inc = {k: v.cpu().numpy() for k, v in m.export_incidence().items()}
+        want = theta.cpu().numpy().astype(np.float64)
+        add = np.zeros(st.n_voxels)
+        ell = m.export_edges()["ell"].cpu().numpy().astype(np.float64)
+        np.add.at(add, inc["col"], ell)
+        mag = np.zeros(st.n_voxels)
+        np.add.at(mag, inc["col"], np.abs(ell))
+        err = np.abs(got[0].cpu().numpy() - (want + add))
+        # one rounding to FP32, and FP64 sums of up to max degree terms
+        assert np.all(err <= 2.0 ** -23 * np.abs(want + add) + 2.0 ** -52 * st.max_voxel_degree * (mag + 10))
+        if kf:
+            m.infer_keyframe_avg(theta, sigma, 2, keep_checkpoints=True)
+            got += [m.marginals()[1], *m.backward(dL)]
             ell = m.export_edges()["ell"].cpu().numpy().astype(np.float64)
-            want, mag = theta.cpu().numpy().astype(np.float64), np.zeros(st.n_voxels)
-            np.add.at(want, col, ell)
-            np.add.at(mag, col, np.abs(ell))
-            err = np.abs(logit.cpu().numpy() - want)
-            # one rounding to FP32, and FP64 sums of up to max degree terms
-            assert np.all(err <= 2.0 ** -23 * np.abs(want) + 2.0 ** -52 * st.max_voxel_degree * (mag + 10))
-            sc = scs[-1]
-            d, T = sc.depth, sc.T_wc
-            part = [*scs[:-1], dataclasses.replace(sc, depth=d[:-1], T_wc=T[:-1])]
-            m2 = RayMRF()
-            m2.build(part)
-            m2.add_frames(d[-1:], T[-1:])
-            m2.infer(theta, sigma, 2, keep_checkpoints=True)
-            out.append((m2.marginals()[1], *m2.backward(dL)))
-            m2.close()
+            r = np.repeat(np.arange(st.n_rays), np.diff(inc["row_ptr"]))
+            hw, w = sc.depth[0].size, sc.depth[0].shape[1]
+            it = sc.intr
+            ray = np.stack([(r % hw % w - it.cx) / it.fx, (r % hw // w - it.cy) / it.fy, np.ones(r.size)])
+            length = (inc["t_out"] - inc["t_in"]) * np.sqrt((ray ** 2).sum(0))
+            pair, which = np.unique((r // hw) * st.n_voxels + inc["col"], return_inverse=True)
+            assert st.n_keyframe_pairs == pair.size
+            total, avg, size = np.zeros(pair.size), np.zeros(pair.size), np.zeros(pair.size)
+            np.add.at(total, which, length)
+            np.add.at(avg, which, ell * length)
+            np.add.at(size, which, np.abs(ell) * length)
+            add, mag = np.zeros(st.n_voxels), np.zeros(st.n_voxels)
+            ok = total > 1e-30 * total.max()   # (a pair of chords without length has equal weights)
+            np.add.at(add, pair[ok] % st.n_voxels, (avg[ok] / total[ok]))
+            np.add.at(mag, pair[ok] % st.n_voxels, (size[ok] / total[ok]))
+            bad = np.zeros(st.n_voxels, bool)
+            bad[pair[~ok] % st.n_voxels] = True
+            assert bad.mean() < 0.01
+            err = np.abs(got[3].cpu().numpy() - (want + add))
+            # lengths, their sums and weights rounded to FP32: three roundings of each term, and one of the sum
+            assert np.all((err <= 2.0 ** -23 * np.abs(want + add) + 2.0 ** -22 * mag)[~bad])
+        out.append(got)
         m.close()
-    for o in out[1:]:   # the sums' FP64 order is all that differs
-        for a, b in zip(out[0], o):
-            assert float((a.double() - b.double()).norm()) <= 1e-6 * float(b.double().norm())
+    for a, b in zip(*out):   # the same lists, so the same sums
+        assert torch.equal(a, b)
