@@ -1,7 +1,8 @@
-"""Boundary times of the dense walk: the reciprocal form n y with two FMA corrections gives the rounded
+"""The dense walk and its count pass.  Boundary times: the reciprocal form n y with two FMA corrections gives the rounded
 quotient n / w (emulated here in exact rationals, an FMA rounding once), over the operands that the
 walk admits: w of magnitude in [2^-100, 2^100) with a significand below 2 - 2^-48, n zero or of
 magnitude in [2^-900, 2^900)."""
+import math
 import random
 from fractions import Fraction as Q
 
@@ -46,3 +47,124 @@ def test_reciprocal_quotient_is_the_division(exps):
         n *= rng.choice((1, -1))
         assert quot(n, w) == n / w, (n.hex(), w.hex())
     assert quot(0.0, 1.7) == 0.0 and quot(0.0, -1.7) == 0.0
+
+
+# ---- the number of voxels from the faces crossed along each axis
+
+def _ray(rng, kind, n, h, o):
+    """A ray (centre, direction, start, end) of the grid; kinds that share boundary times come from
+    centres on the lattice and directions of few bits, equal or integer multiples of each other."""
+    c = [o[a] + rng.uniform(-0.3, 1.3) * n[a] * h for a in range(3)]
+    w = [rng.uniform(-1, 1) for _ in range(3)]
+    if kind == 1:     # lattice centre, simple slopes
+        c = [o[a] + h * rng.randrange(-2, n[a] + 3) for a in range(3)]
+        w = [rng.choice((1.0, 0.5, 0.25, 0.75)) * rng.choice((1, -1)) for _ in range(3)]
+    elif kind == 2:   # two equal slopes, a parallel axis now and then
+        w[1] = rng.choice((1, -1)) * w[0]
+        c[1] = o[1] + rng.choice((1, -1)) * (c[0] - o[0])
+        if rng.random() < 0.3:
+            w[2] = 0.0
+    elif kind == 3:   # almost parallel to an axis
+        w[rng.randrange(3)] *= 2.0 ** -rng.randrange(5, 40)
+    elif kind == 4:   # almost shared times
+        w[1] = w[0] * (1 + rng.randint(-4, 4) * 2.0 ** -rng.choice((22, 30, 50, 52)))
+        c[1] = o[1] + (c[0] - o[0]) * (1 + rng.randint(-4, 4) * 2.0 ** -rng.choice((22, 30, 50, 52)))
+    ts, te = 0.0, float("inf")
+    for a in range(3):
+        lo, hi = o[a], o[a] + n[a] * h
+        if w[a] == 0.0:
+            if not lo <= c[a] < hi:
+                return None
+            continue
+        t0, t1 = (lo - c[a]) / w[a], (hi - c[a]) / w[a]
+        ts, te = max(ts, min(t0, t1)), min(te, max(t0, t1))
+    if rng.random() < 0.7:
+        te = min(te, ts + rng.random() * (te - ts))
+    return (c, w, ts, te) if te > ts else None
+
+
+def _first(n, h, o, c, w, ts, a):
+    q = math.floor((c[a] + ts * w[a] - o[a]) / h)
+    return float(min(max(q, 0), n[a] - 1))
+
+
+def _walk(n, h, o, ray):
+    c, w, ts, te = ray
+    f, t = [0.0] * 3, [float("inf")] * 3
+    for a in range(3):
+        f[a] = _first(n, h, o, c, w, ts, a) + (w[a] > 0)
+        if w[a] != 0.0:
+            t[a] = ((o[a] + f[a] * h) - c[a]) / w[a]
+    tin, k = ts, 0
+    while True:
+        a = min(range(3), key=lambda i: t[i])   # the lowest axis of a tie
+        k += min(t[a], te) > tin
+        if t[a] >= te:
+            return k
+        tin = max(tin, t[a])
+        f[a] += 1.0 if w[a] > 0 else -1.0
+        t[a] = ((o[a] + f[a] * h) - c[a]) / w[a]
+
+
+def _faces(n, h, o, ray):
+    c, w, ts, te = ray
+    rh = 1.0 / h
+    cnt, t0, y = [0] * 3, [0.0] * 3, [0.0] * 3
+    mh = [(abs(o[a]) + abs(c[a])) * rh + (n[a] + 2) for a in range(3)]
+    if not max(mh) < 2.0 ** 25:
+        return -1
+    for a in range(3):
+        if w[a] == 0.0:
+            continue
+        s = 1.0 if w[a] > 0 else -1.0
+        f0 = _first(n, h, o, c, w, ts, a) + (w[a] > 0)
+        y[a] = 1.0 / w[a]
+
+        def time(f):
+            return ((o[a] + f * h) - c[a]) / w[a]
+        e = math.ceil((((c[a] + te * w[a]) - o[a]) * rh - f0) * s)
+        if e > 1024:
+            return -1
+        m = max(e, 0)
+        if m > 0 and time(f0 + s * (m - 1)) >= te:
+            m -= 1
+        elif time(f0 + s * m) < te:
+            m += 1
+        if m == 0:
+            continue
+        t0[a] = time(f0)
+        if t0[a] <= ts:
+            m -= 1
+            t0[a] = time(f0 + s)
+            if t0[a] <= ts:
+                return -1
+        cnt[a] = m
+    for p, q in ((0, 1), (0, 2), (1, 2)):
+        if cnt[q] < cnt[p]:
+            p, q = q, p
+        if cnt[p] == 0:
+            continue
+        a = w[q] * abs(y[p])
+        if not mh[p] * abs(a) + mh[q] < 2.0 ** 25:
+            return -1
+        g = ((c[q] + t0[p] * w[q]) - o[q]) * rh
+        x = int((g - math.floor(g)) * 2.0 ** 32) + 2048
+        dx = int((a - math.floor(a)) * 2.0 ** 32)
+        if min((x + k * dx) & 0xffffffff for k in range((cnt[p] + 7) // 8 * 8)) <= 4096:
+            return -1
+    return sum(cnt) + 1
+
+
+@pytest.mark.parametrize("n,h,o", [((25, 25, 15), 0.2, (-2.5, -2.5, -0.3)), ((250, 240, 150), 0.02, (-2.5, 1.1, 0.0)),
+                                   ((1, 7, 64), 0.25, (0.0, -0.875, 8.0)), ((2000, 3, 3), 0.01, (100.0, -0.01, 0.0))])
+def test_voxels_counted_by_faces_are_those_walked(n, h, o):
+    rng = random.Random(11)
+    for kind in range(5):
+        rays = [r for r in (_ray(rng, kind, n, h, o) for _ in range(1200)) if r]
+        got = [_faces(n, h, o, r) for r in rays]
+        for r, g in zip(rays, got):
+            assert g < 0 or g == _walk(n, h, o, r), (kind, r)
+        if kind == 0:   # rays at random are counted: a shared time is seen in one of 8192
+            assert max(n) > 1024 or sum(g < 0 for g in got) <= 0.01 * len(got)
+        if kind == 1 and min(n) > 1:   # shared times are found
+            assert sum(g < 0 for g in got) > 0.2 * len(got)
