@@ -1275,31 +1275,29 @@ __device__ __forceinline__ uint32_t voxel_key32(const SceneDev* __restrict__ sce
     return (uint32_t)sd.key_base + brick * 512u + ((k & 7) * 8 + (j & 7)) * 8 + (i & 7);
 }
 
-// bit j of the result: lane (i + j) mod 16 of the row holds another value than lane i
-template <int J>
-__device__ __forceinline__ uint32_t row_differs(uint32_t v)
-{
-    const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x120 + (16 - J), 0xF, 0xF, false);   // row_ror
-    return min(v ^ o, 1u) << J;
-}
-
+// lanes (of four rows) that hold the value of a lower lane of their row; x not 0 in the
+// lanes that matter (a lane without a lane J below it compares with 0)
 template <int... J>
-__device__ __forceinline__ uint32_t row_differs_all(uint32_t v, std::integer_sequence<int, J...>)
+__device__ __forceinline__ uint64_t row_repeats(uint32_t x, std::integer_sequence<int, J...>)
 {
-    return (row_differs<J + 1>(v) | ...);
+    return (__ballot(x == (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111 + J, 0xF, 0xF, true)) | ...);   // row_shr
 }
 
 // The runs of kRunRows rows, in row order, at [block * kRunSlots, + bcnt[block])
-// of gkey / ginfo (lane mask | row of the block << 16).  Bound by its reads of
-// col and the 15 lane comparisons of a row (45 instructions per 64 slots); keys
-// are computed after the runs are compacted in LDS, one per run.
+// of gkey / ginfo (lane mask | row of the block << 16).  VALU-bound if every lane
+// forms its mask (15 comparisons and bits, 104 instructions per 64 slots: 1.32 ms for
+// 5.2e8 slots, 2.5 GB of traffic).  So the lanes only learn whether a lower one holds
+// their voxel (the comparisons' lane masks are joined by scalar operations); masks, from
+// the row's values in LDS, and keys are formed once the runs' first lanes are compacted:
+// 0.92 ms (1.02 with eight comparisons, every pair once: more scalar work than it saves).
 __global__ __launch_bounds__(256) void runs_find_k(const int32_t* __restrict__ col, int64_t n,
                                                    const SceneDev* __restrict__ scenes, int ns,
                                                    uint32_t* __restrict__ gkey, uint32_t* __restrict__ ginfo,
                                                    int32_t* __restrict__ bcnt)
 {
     constexpr int NR = kRunRows / 16;   // rounds of 4 rows per wave
-    __shared__ uint32_t lv[4][64 * NR], li[4][64 * NR];
+    __shared__ __attribute__((aligned(16))) uint32_t lv[4][64 * NR];
+    __shared__ uint16_t li[4][64 * NR];
     __shared__ int wcnt[4];
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t b0 = (int64_t)blockIdx.x * kRunSlots;
@@ -1310,20 +1308,14 @@ __global__ __launch_bounds__(256) void runs_find_k(const int32_t* __restrict__ c
         const int64_t at = w0 + r * 64 + lane;   // n is a multiple of 16: a row lies wholly inside or outside
         v[r] = at < n ? (uint32_t)col[at] : 0xffffffffu;
     }
-    const int i = lane & 15;
     const uint64_t below = lane ? (~0ull) >> (64 - lane) : 0ull;
     int cnt = 0;
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-        const uint32_t rel = ~row_differs_all(v[r], std::make_integer_sequence<int, 15>{}) & 0xffffu;
-        const uint32_t mask = ((rel | (rel << 16)) >> (16 - i)) & 0xffffu;   // lanes holding this lane's voxel
-        const bool lead = (int32_t)v[r] >= 0 && (mask & ((1u << i) - 1u)) == 0u;
-        const uint64_t b = __ballot(lead);
-        if (lead) {
-            const int at = cnt + __popcll(b & below);
-            lv[w][at] = v[r];
-            li[w][at] = mask | ((uint32_t)(w * (kRunRows / 4) + r * 4 + (lane >> 4)) << 16);
-        }
+        const uint64_t b =
+            __ballot((int32_t)v[r] >= 0) & ~row_repeats(v[r] + 1u, std::make_integer_sequence<int, 15>{});
+        lv[w][r * 64 + lane] = v[r];
+        if ((b >> lane) & 1u) li[w][cnt + __popcll(b & below)] = (uint16_t)(r * 64 + lane);
         cnt += __popcll(b);
     }
     if (lane == 0) wcnt[w] = cnt;
@@ -1335,8 +1327,18 @@ __global__ __launch_bounds__(256) void runs_find_k(const int32_t* __restrict__ c
         tot += wcnt[q];
     }
     for (int j = lane; j < cnt; j += 64) {
-        gkey[b0 + off + j] = voxel_key32(scenes, ns, lv[w][j]);
-        ginfo[b0 + off + j] = li[w][j];
+        const int at = li[w][j], row = at >> 4;
+        const uint32_t x = lv[w][at];
+        const uint4* rv = (const uint4*)&lv[w][row * 16];
+        uint32_t mask = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint4 y = rv[q];
+            mask |= (x == y.x ? 1u : 0u) << (4 * q) | (x == y.y ? 2u : 0u) << (4 * q) |
+                    (x == y.z ? 4u : 0u) << (4 * q) | (x == y.w ? 8u : 0u) << (4 * q);
+        }
+        gkey[b0 + off + j] = voxel_key32(scenes, ns, x);
+        ginfo[b0 + off + j] = mask | (uint32_t)(w * (kRunRows / 4) + row) << 16;
     }
     if (threadIdx.x == 0) bcnt[blockIdx.x] = tot;
 }
