@@ -1460,23 +1460,57 @@ __global__ __launch_bounds__(SC_T) void runs_mark_k(const uint32_t* __restrict__
     }
 }
 
-// vptr of the keys without a run (all ones so far): that of the next key with one,
-// found among the sorted runs, or the number of entries; rptr (may be null) likewise
-__global__ void vptr_gaps_k(const uint32_t* __restrict__ key, int64_t n, int64_t V, int64_t entries, int64_t* vptr,
-                            uint32_t* rptr)
+// vptr of the keys without a run (all ones so far): that of the next key with one, or the
+// number of entries; rptr (may be null) likewise.  A wave takes 1024 keys from the last to
+// the first, 64 at a time: the next key with a run is found in the lanes' mask, or is the
+// one that the keys before left, at first the first run past all of them (a search among
+// the sorted runs).  9.4e6 keys, half of them without a run: 39 us, with a search for
+// each of those 175; 1.2e6 keys 10.8 and 15.4.
+__global__ __launch_bounds__(256) void vptr_gaps_k(const uint32_t* __restrict__ key, int64_t n, int64_t V,
+                                                   int64_t entries, int64_t* __restrict__ vptr,
+                                                   uint32_t* __restrict__ rptr)
 {
-    const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (v > V || vptr[v] != -1) return;
-    int64_t lo = 0, hi = n;
+    constexpr int NR = 16;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t v0 = ((int64_t)blockIdx.x * 4 + w) * 64 * NR, v1 = v0 + 64 * NR;   // keys up to V
+    if (v0 > V) return;   // whole wave
+    int64_t x[NR];
+    uint32_t rp[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        const int64_t v = v0 + r * 64 + lane;
+        x[r] = v <= V ? vptr[v] : -1;
+        rp[r] = v <= V && rptr ? rptr[v] : 0u;
+    }
+    int64_t lo = 0, hi = n;   // the first run of a key of v1 or more
     while (lo < hi) {
         const int64_t mid = (lo + hi) >> 1;
-        if ((int64_t)key[mid] < v)
+        if ((int64_t)key[mid] < v1)
             lo = mid + 1;
         else
             hi = mid;
     }
-    vptr[v] = lo < n ? vptr[key[lo]] : entries;
-    if (rptr) rptr[v] = (uint32_t)lo;
+    int64_t nx = entries;
+    uint32_t nr = (uint32_t)lo;
+    if (lo < n) nx = vptr[key[lo]];   // a key with a run: no wave changes it
+#pragma unroll
+    for (int r = NR - 1; r >= 0; --r) {
+        const int64_t v = v0 + r * 64 + lane;
+        const uint64_t has = __ballot(x[r] != -1);
+        const uint64_t up = has >> lane;   // from this lane on
+        const int src = up ? lane + __ffsll((unsigned long long)up) - 1 : lane;
+        const int64_t sx = __shfl(x[r], src, 64);
+        const uint32_t sr = __shfl(rp[r], src, 64);
+        if (v <= V && x[r] == -1) {
+            vptr[v] = up ? sx : nx;
+            if (rptr) rptr[v] = up ? sr : nr;
+        }
+        if (has) {
+            const int f = __ffsll((unsigned long long)has) - 1;
+            nx = __shfl(x[r], f, 64);
+            nr = __shfl(rp[r], f, 64);
+        }
+    }
 }
 
 // Slots are sorted one by one where there are few of them: the runs cost six more
@@ -1582,7 +1616,7 @@ hipError_t build_incidence(mrf_ctx* c, int64_t n, int64_t edges, uint32_t* keys,
                                (const uint32_t*)lr[0], (const uint16_t*)lm[0], nr, (const int64_t*)eoff, groups, keys,
                                vals, vptr);
     }
-    hipLaunchKernelGGL(vptr_gaps_k, dim3((unsigned)cdiv(c->Vk + 1, 256)), dim3(256), 0, s, (const uint32_t*)lk[0], nr,
+    hipLaunchKernelGGL(vptr_gaps_k, dim3((unsigned)cdiv(c->Vk + 1, 4096)), dim3(256), 0, s, (const uint32_t*)lk[0], nr,
                        c->Vk, edges, vptr, rptr);
     return hipGetLastError();
 }
