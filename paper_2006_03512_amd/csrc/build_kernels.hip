@@ -1028,8 +1028,8 @@ __global__ __launch_bounds__(RS_T) void rs_hist_k(const uint32_t* __restrict__ k
     hist[(int64_t)blockIdx.x * 256 + threadIdx.x] = h[threadIdx.x];
 }
 
-// Digit offsets from the tile-major (tile, digit) counts, in three steps:
-// per-chunk column sums (coalesced rows), an exclusive scan of each digit's
+// Digit offsets from the tile-major (tile, digit) counts, of few tiles by the scatter's
+// blocks themselves, else in three steps: per-chunk column sums (coalesced rows), an exclusive scan of each digit's
 // chunk sums (one block per digit), and per-tile running sums inside each
 // chunk on top of the digit's base (the exclusive scan of the digit totals).
 __global__ __launch_bounds__(256) void rs_colsum_k(const int32_t* __restrict__ hist, int64_t nb,
@@ -1087,7 +1087,7 @@ __global__ __launch_bounds__(256) void rs_offsets_k(const int32_t* __restrict__ 
 // t's run of a digit ends where tile t+1's begins, so consecutive tiles run on
 // one XCD (block remap) and their shared lines merge in its L2.  hist
 // and offs hold the tile's digit counts and output offsets (tile-major rows
-// of 256).  MASK: items carry a second value of 16 bits.
+// of 256); offs null: every block adds up the counts of all tiles.  MASK: items carry a second value of 16 bits.
 template <bool MASK>
 __global__ __launch_bounds__(RS_T) void rs_scatter_k(const uint32_t* __restrict__ keys_in,
                                                      const uint32_t* __restrict__ vals_in, int64_t n,
@@ -1136,7 +1136,21 @@ __global__ __launch_bounds__(RS_T) void rs_scatter_k(const uint32_t* __restrict_
             for (int r = 0; r < RS_IPT; ++r) vr[r] = (uint32_t)(wstart + r * 64 + lane);
         }
     }
-    const int64_t o0 = offs[tile * 256 + tid];
+    int64_t o0;
+    if (offs) {
+        o0 = offs[tile * 256 + tid];
+    } else {
+        int before = 0, all = 0;   // the thread's digit in the tiles before this one, and in all
+        const int nb = (int)gridDim.x;
+#pragma unroll 16
+        for (int b = 0; b < nb; ++b) {
+            const int x = hist[(int64_t)b * 256 + tid];
+            before += b < tile ? x : 0;
+            all += x;
+        }
+        int64_t total;
+        o0 = block_excl_scan_i64(all, &total) + before;
+    }
     const int64_t cnt = hist[tile * 256 + tid];
     boff[tid] = o0;
 #pragma unroll
@@ -1205,6 +1219,12 @@ struct RadixTables {
     int64_t* tmp;
 };
 
+// Most tiles whose offsets the scatter's blocks add up themselves: the three kernels
+// between the counts and the scatter take 13 us whatever the size, a block's pass over the
+// counts grows with the tiles.  Build of a frame of 1.2e5 slots (31 tiles) 226 us, 251 with
+// the three kernels; of 4.8e5 (116 tiles) 266 and 285.
+constexpr int64_t kRsFewTiles = 128;
+
 template <bool MASK>
 static hipError_t radix_pass(const uint32_t* sk, const uint32_t* sv, const uint16_t* sm, uint32_t* dk, uint32_t* dv,
                              uint16_t* dm, int64_t n, int shift, const RadixTables& t, const SlotGroups& groups,
@@ -1216,13 +1236,16 @@ static hipError_t radix_pass(const uint32_t* sk, const uint32_t* sv, const uint1
     int64_t* csum = t.tmp;
     int64_t* coff = csum + 256 * nch;
     int64_t* dtot = coff + 256 * nch;
+    const bool few = nb <= kRsFewTiles;
     hipLaunchKernelGGL(rs_hist_k, dim3((unsigned)nb), dim3(RS_T), 0, s, sk, n, shift, t.hist, nb);
-    hipLaunchKernelGGL(rs_colsum_k, dim3((unsigned)nch), dim3(256), 0, s, (const int32_t*)t.hist, nb, csum);
-    hipLaunchKernelGGL(rs_colscan_k, dim3(256), dim3(256), 0, s, (const int64_t*)csum, nch, coff, dtot);
-    hipLaunchKernelGGL(rs_offsets_k, dim3((unsigned)nch), dim3(256), 0, s, (const int32_t*)t.hist, nb,
-                       (const int64_t*)coff, (const int64_t*)dtot, t.offs);
+    if (!few) {
+        hipLaunchKernelGGL(rs_colsum_k, dim3((unsigned)nch), dim3(256), 0, s, (const int32_t*)t.hist, nb, csum);
+        hipLaunchKernelGGL(rs_colscan_k, dim3(256), dim3(256), 0, s, (const int64_t*)csum, nch, coff, dtot);
+        hipLaunchKernelGGL(rs_offsets_k, dim3((unsigned)nch), dim3(256), 0, s, (const int32_t*)t.hist, nb,
+                           (const int64_t*)coff, (const int64_t*)dtot, t.offs);
+    }
     hipLaunchKernelGGL(rs_scatter_k<MASK>, dim3((unsigned)nb), dim3(RS_T), 0, s, sk, sv, n, shift,
-                       (const int32_t*)t.hist, (const int64_t*)t.offs, dk, dv, groups, sm, dm);
+                       (const int32_t*)t.hist, few ? nullptr : (const int64_t*)t.offs, dk, dv, groups, sm, dm);
     return hipGetLastError();
 }
 
