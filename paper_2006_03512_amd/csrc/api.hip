@@ -503,23 +503,26 @@ static int build_impl(mrf_ctx* c, const mrf_scene* scenes, int32_t n_scenes, con
         HCK(launch_brick_mask(c, s), "mrf_build: brick mask");
     }
     HCK(launch_trace_count(c, s), "mrf_build: trace count");
-    HCK(scan_exclusive_i32((const int32_t*)c->b_counts.p, (int64_t*)c->b_rowptr.p, R, c->b_misc.p, sbytes, s),
-        "mrf_build: scan");
-
     // tiles of 4x4 rays, slot bases = exclusive scan of 16 * longest ray
     const int64_t T = c->T;
+    const size_t nf = c->frames_h.size();
     HCK(ensure(c->b_tiles, sizeof(TileDev) * (size_t)Tcap), "mrf_build: alloc tiles");
     HCK(ensure(c->b_tbase, sizeof(int64_t) * (size_t)(Tcap + 1)), "mrf_build: alloc tile bases");
-    HCK(ensure(c->b_tmp64, sizeof(int32_t) * (size_t)(T + 1)), "mrf_build: alloc");
-    HCK(launch_tiles(c, (int32_t*)c->b_tmp64.p, s), "mrf_build: tiles");
-    HCK(scan_exclusive_i32((const int32_t*)c->b_tmp64.p, (int64_t*)c->b_tbase.p, T, c->b_misc.p, c->b_misc.cap, s),
-        "mrf_build: tile scan");
-    HCK(launch_tile_bases(c, s), "mrf_build: tile bases");
+    HCK(ensure(c->b_export, 2 * sizeof(int64_t) * nf), "mrf_build: alloc");
+    if (launch_count_finish(c, (int64_t*)c->b_export.p, s)) {
+        HCK(hipGetLastError(), "mrf_build: row pointers and tiles");
+    } else {
+        HCK(scan_exclusive_i32((const int32_t*)c->b_counts.p, (int64_t*)c->b_rowptr.p, R, c->b_misc.p, sbytes, s),
+            "mrf_build: scan");
+        HCK(ensure(c->b_tmp64, sizeof(int32_t) * (size_t)(T + 1)), "mrf_build: alloc");
+        HCK(launch_tiles(c, (int32_t*)c->b_tmp64.p, s), "mrf_build: tiles");
+        HCK(scan_exclusive_i32((const int32_t*)c->b_tmp64.p, (int64_t*)c->b_tbase.p, T, c->b_misc.p, c->b_misc.cap, s),
+            "mrf_build: tile scan");
+        HCK(launch_tile_bases(c, s), "mrf_build: tile bases");
+        HCK(launch_frame_counts(c, (int64_t*)c->b_export.p, s), "mrf_build: per-frame counts");
+    }
 
     // one readback: the slots and edges of every frame, which size everything below
-    const size_t nf = c->frames_h.size();
-    HCK(ensure(c->b_export, 2 * sizeof(int64_t) * nf), "mrf_build: alloc");
-    HCK(launch_frame_counts(c, (int64_t*)c->b_export.p, s), "mrf_build: per-frame counts");
     std::vector<int64_t> h(2 * nf);
     HCK(hipMemcpyAsync(h.data(), c->b_export.p, 2 * sizeof(int64_t) * nf, hipMemcpyDeviceToHost, s),
         "mrf_build: read counts");

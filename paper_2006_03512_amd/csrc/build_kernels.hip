@@ -675,16 +675,10 @@ __global__ __launch_bounds__(256) void trace_emit_k(const SceneDev* __restrict__
     }
 }
 
-// One thread per tile: its rays, extent inside the image and longest ray.
-__global__ void tile_init_k(const SceneDev* __restrict__ scenes, const FrameDev* __restrict__ frames, int f0,
-                            const int32_t* __restrict__ counts, TileDev* __restrict__ tiles,
-                            int32_t* __restrict__ slots16, int64_t t0)
+// tile lt of frame f: its rays, extent inside the image and longest ray
+__device__ __forceinline__ TileDev tile_of(const SceneDev& sd, const FrameDev& fr, int f, int lt,
+                                           const int32_t* __restrict__ counts)
 {
-    const FrameDev fr = frames[f0 + blockIdx.y];
-    const SceneDev& sd = scenes[fr.scene];
-    const int nty = (sd.H + kTileW - 1) / kTileW;
-    const int lt = blockIdx.x * blockDim.x + threadIdx.x;
-    if (lt >= fr.ntx * nty) return;
     const int ty = lt / fr.ntx, tx = lt - ty * fr.ntx;
     TileDev td;
     td.ray0 = (int32_t)(fr.ray_base + (int64_t)(ty * kTileW) * sd.W + tx * kTileW);
@@ -696,9 +690,23 @@ __global__ void tile_init_k(const SceneDev* __restrict__ scenes, const FrameDev*
         for (int b = 0; b < td.nu; ++b) len = max(len, counts[td.ray0 + a * sd.W + b]);
     td.len = len;
     td.base = 0;
-    td.frame = f0 + (int32_t)blockIdx.y;
+    td.frame = f;
+    return td;
+}
+
+// one thread per tile
+__global__ void tile_init_k(const SceneDev* __restrict__ scenes, const FrameDev* __restrict__ frames, int f0,
+                            const int32_t* __restrict__ counts, TileDev* __restrict__ tiles,
+                            int32_t* __restrict__ slots16, int64_t t0)
+{
+    const FrameDev fr = frames[f0 + blockIdx.y];
+    const SceneDev& sd = scenes[fr.scene];
+    const int nty = (sd.H + kTileW - 1) / kTileW;
+    const int lt = blockIdx.x * blockDim.x + threadIdx.x;
+    if (lt >= fr.ntx * nty) return;
+    const TileDev td = tile_of(sd, fr, f0 + (int)blockIdx.y, lt, counts);
     tiles[fr.tile_base + lt] = td;
-    slots16[fr.tile_base + lt - t0] = kTile * len;
+    slots16[fr.tile_base + lt - t0] = kTile * td.len;
 }
 
 __global__ void tile_base_k(TileDev* __restrict__ tiles, const int64_t* __restrict__ tbase, int64_t T)
@@ -2532,18 +2540,108 @@ hipError_t export_canonical_edges(const mrf_ctx* c, const void* in_slots, void* 
 
 // ============================================================== per-frame counts
 
+__device__ __forceinline__ void frame_count(const FrameDev& fr, const SceneDev* scenes, const int64_t* tbase,
+                                            const int64_t* rowptr, int64_t* out)
+{
+    const SceneDev& sd = scenes[fr.scene];
+    const int64_t nt = (int64_t)fr.ntx * ((sd.H + kTileW - 1) / kTileW);
+    const int64_t hw = (int64_t)sd.W * sd.H;
+    out[0] = tbase[fr.tile_base + nt] - tbase[fr.tile_base];
+    out[1] = rowptr[fr.ray_base + hw] - rowptr[fr.ray_base];
+}
+
 __global__ void frame_counts_k(const FrameDev* __restrict__ frames, const SceneDev* __restrict__ scenes, int nf,
                                const int64_t* __restrict__ tbase, const int64_t* __restrict__ rowptr,
                                int64_t* __restrict__ out)
 {
     const int f = blockIdx.x * blockDim.x + threadIdx.x;
-    if (f >= nf) return;
-    const FrameDev fr = frames[f];
-    const SceneDev& sd = scenes[fr.scene];
-    const int64_t nt = (int64_t)fr.ntx * ((sd.H + kTileW - 1) / kTileW);
-    const int64_t hw = (int64_t)sd.W * sd.H;
-    out[2 * f] = tbase[fr.tile_base + nt] - tbase[fr.tile_base];
-    out[2 * f + 1] = rowptr[fr.ray_base + hw] - rowptr[fr.ray_base];
+    if (f < nf) frame_count(frames[f], scenes, tbase, rowptr, out + 2 * f);
+}
+
+// What follows the count pass of a few rays, by one block: row pointers, tiles with their
+// first slots, and every frame's slots and edges; a thread takes consecutive rays and tiles.
+__device__ int64_t block1024_excl_scan(int64_t x, int64_t* wsum, int64_t* total)
+{
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    int64_t incl = x;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int64_t y = __shfl_up(incl, d, 64);
+        if (lane >= d) incl += y;
+    }
+    if (lane == 63) wsum[w] = incl;
+    __syncthreads();
+    int64_t off = 0, tot = 0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        if (i < w) off += wsum[i];
+        tot += wsum[i];
+    }
+    __syncthreads();
+    *total = tot;
+    return off + incl - x;
+}
+
+__global__ __launch_bounds__(1024) void count_finish_k(const SceneDev* __restrict__ scenes,
+                                                       const FrameDev* __restrict__ frames, int nf,
+                                                       const int32_t* __restrict__ counts, int R, int T,
+                                                       int64_t* rowptr, TileDev* tiles, int64_t* tbase,
+                                                       int64_t* __restrict__ out)
+{
+    __shared__ int64_t wsum[16];
+    const int rper = (R + 1023) / 1024, tper = (T + 1023) / 1024;
+    const int r0 = min((int)threadIdx.x * rper, R), r1 = min(r0 + rper, R);
+    int64_t sum = 0, total;
+    for (int r = r0; r < r1; ++r) sum += counts[r];
+    int64_t at = block1024_excl_scan(sum, wsum, &total);
+    for (int r = r0; r < r1; ++r) {
+        rowptr[r] = at;
+        at += counts[r];
+    }
+    if (threadIdx.x == 0) rowptr[R] = total;
+
+    const int t0 = min((int)threadIdx.x * tper, T), t1 = min(t0 + tper, T);
+    int f = 0;
+    if (t0 < t1) {
+        int hi = nf;   // tile_base of f <= t0 < that of hi
+        while (hi - f > 1) {
+            const int mid = (f + hi) >> 1;
+            if (frames[mid].tile_base <= t0)
+                f = mid;
+            else
+                hi = mid;
+        }
+    }
+    sum = 0;
+    for (int t = t0; t < t1; ++t) {
+        while (f + 1 < nf && frames[f + 1].tile_base <= t) ++f;
+        const TileDev td = tile_of(scenes[frames[f].scene], frames[f], f, t - (int)frames[f].tile_base, counts);
+        tiles[t] = td;
+        sum += (int64_t)kTile * td.len;
+    }
+    at = block1024_excl_scan(sum, wsum, &total);
+    for (int t = t0; t < t1; ++t) {
+        tiles[t].base = at;
+        tbase[t] = at;
+        at += (int64_t)kTile * tiles[t].len;
+    }
+    if (threadIdx.x == 0) tbase[T] = total;
+    __syncthreads();   // the block's writes of rowptr and tbase
+    for (int i = threadIdx.x; i < nf; i += 1024) frame_count(frames[i], scenes, tbase, rowptr, out + 2 * i);
+}
+
+// Most rays of a batch finished by one block: its time grows with them, that of the seven
+// launches it replaces hardly.  Build of 256 rays 172 us and 200, of 3072 (64x48) 226 and
+// 258, of 12288 266 and 282, of 16384 303 and 308.
+constexpr int64_t kFinishRays = int64_t(1) << 14;
+
+bool launch_count_finish(mrf_ctx* c, int64_t* out, hipStream_t s)
+{
+    if (c->R > kFinishRays || c->n_frames <= 0) return false;
+    hipLaunchKernelGGL(count_finish_k, dim3(1), dim3(1024), 0, s, (const SceneDev*)c->b_scenes.p,
+                       (const FrameDev*)c->b_frames.p, c->n_frames, (const int32_t*)c->b_counts.p, (int)c->R,
+                       (int)c->T, (int64_t*)c->b_rowptr.p, (TileDev*)c->b_tiles.p, (int64_t*)c->b_tbase.p, out);
+    return true;
 }
 
 hipError_t launch_frame_counts(const mrf_ctx* c, int64_t* out, hipStream_t s)

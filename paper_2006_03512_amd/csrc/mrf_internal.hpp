@@ -468,6 +468,9 @@ hipError_t export_canonical_edges(const mrf_ctx* c, const void* in_slots, void* 
 // tile descriptors of frames [f0, f0 + nf); slots16[t - first tile of f0] = 16 * longest ray
 hipError_t launch_tiles(mrf_ctx* c, int32_t* slots16, hipStream_t s, int f0 = 0, int nf = -1);
 hipError_t launch_tile_bases(mrf_ctx* c, hipStream_t s, int64_t t0 = 0);
+// row pointers, tiles, slot bases and per-frame counts (out: slots, edges of each frame) of a
+// batch of few rays in one launch; false: too many, nothing done
+bool launch_count_finish(mrf_ctx* c, int64_t* out, hipStream_t s);
 hipError_t launch_add_i64(int64_t* p, int64_t v, int64_t n, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t s);
 // out[slot[j]] = in[j] for j < n (list order to slot order)
