@@ -1945,16 +1945,15 @@ struct PairItems {
     }
 };
 
-template <class F, int R>
-__global__ __launch_bounds__(256) void part_count_k(const F f, int64_t nb, uint32_t* __restrict__ bcnt)
+template <int R, class F>
+__device__ __forceinline__ void part_count(const F& f, int64_t block, int64_t nb, uint32_t* __restrict__ bcnt,
+                                           PartLds& l, uint32_t (&wc)[4][kPartMaxClasses])
 {
-    __shared__ PartLds l;
-    __shared__ uint32_t wc[4][kPartMaxClasses];
     for (int i = threadIdx.x; i < (int)(sizeof(PartLds) / 4); i += 256) ((uint32_t*)&l)[i] = 0;
     __syncthreads();
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int64_t i0, i1;
-    f.range(blockIdx.x, part_items<R>(), i0, i1);
+    f.range(block, part_items<R>(), i0, i1);
     i0 += (int64_t)w * R * 64;
     int cl[R];
 #pragma unroll
@@ -1976,17 +1975,43 @@ __global__ __launch_bounds__(256) void part_count_k(const F f, int64_t nb, uint3
     if (threadIdx.x < F::NC) {
         uint32_t t = 0;
         for (int q = 0; q < 4; ++q) t += wc[q][threadIdx.x];
-        bcnt[(int64_t)threadIdx.x * nb + blockIdx.x] = t;
+        bcnt[(int64_t)threadIdx.x * nb + block] = t;
     }
     f.flush(l, threadIdx.x);
 }
 
+// the blocks of f's items, then those of g's
+template <class F, int R, class G, int Q>
+__global__ __launch_bounds__(256) void part_count_k(const F f, int64_t nf, uint32_t* __restrict__ fcnt, const G g,
+                                                    int64_t ng, uint32_t* __restrict__ gcnt)
+{
+    __shared__ PartLds l;
+    __shared__ uint32_t wc[4][kPartMaxClasses];
+    if (blockIdx.x < nf)
+        part_count<R>(f, blockIdx.x, nf, fcnt, l, wc);
+    else
+        part_count<Q>(g, (int64_t)blockIdx.x - nf, ng, gcnt, l, wc);
+}
+
 // exclusive scan over the blocks of each class (one wave per class, in place),
 // the class totals, and with fo the value at every bpf-th block (a frame's first)
-__global__ __launch_bounds__(64 * kPartMaxClasses) void part_scan_k(uint32_t* __restrict__ bcnt, int64_t nb, int nc,
-                                                                    unsigned long long* __restrict__ tot,
-                                                                    int64_t* __restrict__ fo, int bpf, int nf)
+struct PartScan {
+    uint32_t* bcnt;
+    int64_t nb;
+    int nc;
+    unsigned long long* tot;
+    int64_t* fo;
+    int bpf, nf;
+};
+
+__global__ __launch_bounds__(64 * kPartMaxClasses) void part_scan_k(const PartScan a, const PartScan b2)
 {
+    const PartScan& l = blockIdx.x == 0 ? a : b2;
+    uint32_t* bcnt = l.bcnt;
+    const int64_t nb = l.nb;
+    const int nc = l.nc, bpf = l.bpf, nf = l.nf;
+    unsigned long long* tot = l.tot;
+    int64_t* fo = l.fo;
     const int k = threadIdx.x >> 6, lane = threadIdx.x & 63;
     if (k >= nc) return;
     uint32_t* p = bcnt + (int64_t)k * nb;
@@ -2024,14 +2049,14 @@ __global__ __launch_bounds__(64 * kPartMaxClasses) void part_scan_k(uint32_t* __
     }
 }
 
-template <class F, int R>
-__global__ __launch_bounds__(256) void part_place_k(const F f, int64_t nb, const uint32_t* __restrict__ boff,
-                                                    const unsigned long long* __restrict__ tot)
+template <int R, class F>
+__device__ __forceinline__ void part_place(const F& f, int64_t block, int64_t nb, const uint32_t* __restrict__ boff,
+                                           const unsigned long long* __restrict__ tot,
+                                           uint32_t (&wc)[4][kPartMaxClasses])
 {
-    __shared__ uint32_t wc[4][kPartMaxClasses];
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     int64_t i0, i1;
-    f.range(blockIdx.x, part_items<R>(), i0, i1);
+    f.range(block, part_items<R>(), i0, i1);
     i0 += (int64_t)w * R * 64;
     int cl[R];
     uint32_t cnt[F::NC] = {0};
@@ -2056,7 +2081,7 @@ __global__ __launch_bounds__(256) void part_place_k(const F f, int64_t nb, const
     uint32_t base = 0;
 #pragma unroll
     for (int k = 0; k < F::NC; ++k) {
-        at[k] = base + boff[(int64_t)k * nb + blockIdx.x];
+        at[k] = base + boff[(int64_t)k * nb + block];
         for (int q = 0; q < w; ++q) at[k] += wc[q][k];
         base += (uint32_t)tot[k];
     }
@@ -2074,25 +2099,51 @@ __global__ __launch_bounds__(256) void part_place_k(const F f, int64_t nb, const
     }
 }
 
-template <class F, int R>
-static hipError_t partition_r(const F& f, int64_t nb, uint32_t* bcnt, unsigned long long* tot, int64_t* fo, int bpf,
-                              int nf, hipStream_t s)
+template <class F, int R, class G, int Q>
+__global__ __launch_bounds__(256) void part_place_k(const F f, int64_t nf, const uint32_t* __restrict__ foff,
+                                                    const unsigned long long* __restrict__ ftot, const G g,
+                                                    int64_t ng, const uint32_t* __restrict__ goff,
+                                                    const unsigned long long* __restrict__ gtot)
 {
-    if (nb > 0) hipLaunchKernelGGL((part_count_k<F, R>), dim3((unsigned)nb), dim3(256), 0, s, f, nb, bcnt);
-    hipLaunchKernelGGL(part_scan_k, dim3(1), dim3(64 * kPartMaxClasses), 0, s, bcnt, nb, F::NC, tot, fo, bpf, nf);
+    __shared__ uint32_t wc[4][kPartMaxClasses];
+    if (blockIdx.x < nf)
+        part_place<R>(f, blockIdx.x, nf, foff, ftot, wc);
+    else
+        part_place<Q>(g, (int64_t)blockIdx.x - nf, ng, goff, gtot, wc);
+}
+
+// Two lists partitioned in the same three launches (sf, sg: their scans)
+template <class F, int R, class G, int Q>
+static hipError_t partition_r(const F& f, const PartScan& sf, const G& g, const PartScan& sg, hipStream_t s)
+{
+    const unsigned nb = (unsigned)(sf.nb + sg.nb);
     if (nb > 0)
-        hipLaunchKernelGGL((part_place_k<F, R>), dim3((unsigned)nb), dim3(256), 0, s, f, nb, (const uint32_t*)bcnt,
-                           (const unsigned long long*)tot);
+        hipLaunchKernelGGL((part_count_k<F, R, G, Q>), dim3(nb), dim3(256), 0, s, f, sf.nb, sf.bcnt, g, sg.nb, sg.bcnt);
+    hipLaunchKernelGGL(part_scan_k, dim3(2), dim3(64 * kPartMaxClasses), 0, s, sf, sg);
+    if (nb > 0)
+        hipLaunchKernelGGL((part_place_k<F, R, G, Q>), dim3(nb), dim3(256), 0, s, f, sf.nb, (const uint32_t*)sf.bcnt,
+                           (const unsigned long long*)sf.tot, g, sg.nb, (const uint32_t*)sg.bcnt,
+                           (const unsigned long long*)sg.tot);
     return hipGetLastError();
 }
 
-template <class F>
-static hipError_t partition(const F& f, int rounds, int64_t nb, uint32_t* bcnt, unsigned long long* tot, int64_t* fo,
-                            int bpf, int nf, hipStream_t s)
+template <class F, class G>
+static hipError_t partition(const F& f, int fr, const PartScan& sf, const G& g, int gr, const PartScan& sg,
+                            hipStream_t s)
 {
-    return rounds == 2 ? partition_r<F, 2>(f, nb, bcnt, tot, fo, bpf, nf, s)
-                       : partition_r<F, 16>(f, nb, bcnt, tot, fo, bpf, nf, s);
+    if (fr == 2) return gr == 2 ? partition_r<F, 2, G, 2>(f, sf, g, sg, s) : partition_r<F, 2, G, 16>(f, sf, g, sg, s);
+    return gr == 2 ? partition_r<F, 16, G, 2>(f, sf, g, sg, s) : partition_r<F, 16, G, 16>(f, sf, g, sg, s);
 }
+
+// A list that is not there
+struct NoItems {
+    static constexpr int NC = 1;
+    __device__ void range(int64_t, int, int64_t& i0, int64_t& i1) const { i0 = i1 = 0; }
+    __device__ int cls(int64_t) const { return 255; }
+    __device__ void note(int64_t, int, PartLds&) const {}
+    __device__ void flush(const PartLds&, int) const {}
+    __device__ void put(int64_t, int64_t, int) const {}
+};
 
 // The hub segments hubs[0, n) cut into pieces of `piece` items (one block): the
 // pieces in order, then per hub its range of them (at[np + i]).
@@ -2159,10 +2210,11 @@ hipError_t build_classes(mrf_ctx* c, hipStream_t s)
     if ((e = launch_fill_u32((uint32_t*)st, 0u, (int64_t)(sizeof(ListStats) / 4), s)) != hipSuccess) return e;
     const TileItems ti{(const TileDev*)c->b_tiles.p, (const int32_t*)c->b_counts.p, (const FrameDev*)c->b_frames.p,
                        c->T, nf, bpf, (uint32_t*)c->b_ray_list.p, st};
-    if ((e = partition(ti, tr, tb, tcnt, st->tiles, fo, bpf, nf, s)) != hipSuccess) return e;
     const VoxItems vi{(const int64_t*)c->b_vptr.p, c->by_runs ? (const uint32_t*)c->b_rptr.p : nullptr, c->Vk, (const SceneDev*)c->b_scenes.p, c->n_scenes,
                       (VoxDev*)c->vox.desc.p, st};
-    if ((e = partition(vi, vr, vb, vcnt, st->voxels, nullptr, 1, 0, s)) != hipSuccess) return e;
+    e = partition(ti, tr, PartScan{tcnt, tb, TileItems::NC, st->tiles, fo, bpf, nf}, vi, vr,
+                  PartScan{vcnt, vb, VoxItems::NC, st->voxels, nullptr, 1, 0}, s);
+    if (e != hipSuccess) return e;
 
     // one readback: class sizes, statistics, and per-frame offsets of the tile lists (plain schedule)
     std::vector<char> hb(head);
@@ -2204,8 +2256,10 @@ static hipError_t partition_pairs(mrf_ctx* c, const uint32_t* pstart, int64_t P,
     if ((e = ensure(c->b_part, head + sizeof(uint32_t) * (size_t)(PairItems::NC * nb))) != hipSuccess) return e;
     unsigned long long* tot = (unsigned long long*)c->b_part.p;
     if ((e = launch_fill_u32((uint32_t*)tot, 0u, (int64_t)(head / 4), s)) != hipSuccess) return e;
-    e = partition(PairItems{pstart, P, c->by_runs, (VoxDev*)c->pair.desc.p, tot + kPartMaxClasses}, rounds, nb,
-                  (uint32_t*)((char*)c->b_part.p + head), tot, nullptr, 1, 0, s);
+    const PairItems f{pstart, P, c->by_runs, (VoxDev*)c->pair.desc.p, tot + kPartMaxClasses};
+    const PartScan sf{(uint32_t*)((char*)c->b_part.p + head), nb, PairItems::NC, tot, nullptr, 1, 0}, none{};
+    e = rounds == 2 ? partition_r<PairItems, 2, NoItems, 2>(f, sf, NoItems{}, none, s)
+                    : partition_r<PairItems, 16, NoItems, 2>(f, sf, NoItems{}, none, s);
     unsigned long long h[kPartMaxClasses + 1];
     if (e == hipSuccess) e = hipMemcpyAsync(h, tot, head, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
