@@ -1231,7 +1231,8 @@ struct RadixTables {
 // between the counts and the scatter take 13 us whatever the size, a block's pass over the
 // counts grows with the tiles.  Build of a frame of 1.2e5 slots (31 tiles) 226 us, 251 with
 // the three kernels; of 4.8e5 (116 tiles) 266 and 285.
-constexpr int64_t kRsFewTiles = 128;
+// 256 tiles hold the 2^20 slots that are sorted one by one.
+constexpr int64_t kRsFewTiles = 256;
 
 template <bool MASK>
 static hipError_t radix_pass(const uint32_t* sk, const uint32_t* sv, const uint16_t* sm, uint32_t* dk, uint32_t* dv,
@@ -1545,11 +1546,11 @@ __global__ __launch_bounds__(256) void vptr_gaps_k(const uint32_t* __restrict__ 
 }
 
 // Slots are sorted one by one where there are few of them: the runs cost six more
-// launches and a readback of their number.  Build + 3 sweeps + marginals of one frame
-// in us, slot by slot and by runs: 64x48 (2e5 slots) 623 and 672, 128x96 (1e6) 887 and
-// 871, 320x240 (7e6) 1206 and 1176, 640x480 (2.4e7) 2075 and 1922; 2 cm voxels (6e7)
-// 4427 and 3855.
-bool incidence_by_runs(int64_t n) { return n >= (int64_t(1) << 19); }
+// launches and a readback of their number.  Build of one frame in us, slot by slot and by
+// runs: 128x128 (5.6e5 slots) 269 and 292, 144x112 (6.1e5) 268 and 281, 160x120 (7.3e5) 280
+// and 292; the difference falls by 5 us per 1e5 slots.  A 640x480 frame (2.4e7) 2075 and
+// 1922 with its sweeps, at 2 cm (6e7) 4427 and 3855.
+bool incidence_by_runs(int64_t n) { return n >= (int64_t(1) << 20); }
 
 static int key_bits(int64_t maxval)
 {

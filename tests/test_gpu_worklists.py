@@ -22,7 +22,7 @@ CASES = {
     "one tile": [((4, 4), (16, 16, 16), 1)],
     "4096 tiles, 4096 keys": [((256, 256), (16, 16, 16), 1)],
     "4160 tiles, 4608 keys": [((260, 256), (24, 24, 8), 2)],
-    # enough edge slots for the incidence to be sorted by runs (2^19), ragged rows and two scenes
+    # enough edge slots for the incidence to be sorted by runs (2^20), ragged rows and two scenes
     "runs": [((260, 256), (64, 60, 50), 2)],
     "runs, two scenes": [((257, 131), (33, 47, 21), 2), ((63, 66), (64, 17, 9), 3)],
     "ragged, mixed images": [((259, 253), (17, 15, 9), 1), ((5, 3), (31, 16, 16), 3)],
@@ -95,7 +95,7 @@ RUNS = {
 
 @pytest.mark.parametrize("name", list(RUNS))
 def test_large_graphs_sum_runs(name):
-    """Lists kept as runs (2^19 slots and more): beliefs as the exported messages and chords give them, for
+    """Lists kept as runs (2^20 slots and more): beliefs as the exported messages and chords give them, for
     exact and per-keyframe averaged messages; frames added to such a graph as built with it."""
     import dataclasses
 
@@ -114,7 +114,7 @@ def test_large_graphs_sum_runs(name):
         st = m.build(part if added else scs, keep_chords=True, keyframe_average=kf, reserve_frames=int(added))
         if added:
             st = m.add_frames(sc.depth[-1:], sc.T_wc[-1:])
-        assert st.n_slots >= 1 << 19 and (st.n_slot_groups > 1) == (log2 > 0)
+        assert st.n_slots >= 1 << 20 and (st.n_slot_groups > 1) == (log2 > 0)
         rng = np.random.default_rng(3)
         theta = torch.from_numpy(rng.normal(-2, 0.5, st.n_voxels).astype(np.float32)).cuda()
         dL = torch.from_numpy(rng.normal(0, 1, st.n_voxels).astype(np.float32)).cuda()
