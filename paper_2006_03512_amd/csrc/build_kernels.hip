@@ -312,10 +312,16 @@ __device__ __forceinline__ WalkAxis walk_axis(const SceneDev& sd, const Ray& r, 
 // test of the linear id only keeps an index out of range from ever being used.
 // emit(k, i, j, kz, lin, t_in, t_out).  5e8 steps (8 VGA frames at 2 cm): the bare walk
 // 1.18 ms with walk() and 0.78 (VALU-bound), emit pass 1.89 and 1.82 (its stores of 4, 4
-// and 1 bytes a step); the metric's walk of 4 frames to the grid exit 1.15 and 0.70; the
-// emit pass of one 64x48 frame, a chain of steps, 65 us and 42.
-template <bool FAST, class Emit>
-__device__ __forceinline__ int walk_dense(const SceneDev& sd, const Ray& r, Emit&& emit)
+// and 1 bytes a step); the metric's walk of 4 frames to the grid
+// exit 1.15 and 0.70.
+struct WalkState {
+    WalkAxis X, Y, Z;
+    int i, j, kz, lin, k;   // voxel, its linear id, chords so far
+    double tin;
+};
+
+template <bool FAST>
+__device__ __forceinline__ WalkState walk_start(const SceneDev& sd, const Ray& r)
 {
     int idx[3];
 #pragma unroll
@@ -327,18 +333,31 @@ __device__ __forceinline__ int walk_dense(const SceneDev& sd, const Ray& r, Emit
         idx[a] = (int)q;
     }
     const int nx = sd.n[0], nxy = sd.n[0] * sd.n[1];
-    const uint32_t nvox = (uint32_t)nxy * (uint32_t)sd.n[2];
-    int i = idx[0], j = idx[1], kz = idx[2];
-    int lin = i + nx * j + nxy * kz;
-    WalkAxis X = walk_axis<FAST>(sd, r, 0, i, 1), Y = walk_axis<FAST>(sd, r, 1, j, nx),
-             Z = walk_axis<FAST>(sd, r, 2, kz, nxy);
+    WalkState w;
+    w.i = idx[0], w.j = idx[1], w.kz = idx[2];
+    w.lin = w.i + nx * w.j + nxy * w.kz;
+    w.X = walk_axis<FAST>(sd, r, 0, w.i, 1);
+    w.Y = walk_axis<FAST>(sd, r, 1, w.j, nx);
+    w.Z = walk_axis<FAST>(sd, r, 2, w.kz, nxy);
+    w.tin = r.ts;
+    w.k = 0;
+    return w;
+}
+
+// the chords from a state on (PART: that end by tend); returns their number with those before
+template <bool FAST, bool PART, class Emit>
+__device__ __forceinline__ int walk_from(const SceneDev& sd, const Ray& r, const WalkState& w, double tend, Emit&& emit)
+{
+    const uint32_t nvox = (uint32_t)(sd.n[0] * sd.n[1]) * (uint32_t)sd.n[2];
+    WalkAxis X = w.X, Y = w.Y, Z = w.Z;
+    int i = w.i, j = w.j, kz = w.kz, lin = w.lin, k = w.k;
     const double ox = sd.o[0], oy = sd.o[1], oz = sd.o[2], h = sd.h;
-    double tin = r.ts;
-    int k = 0;
+    double tin = w.tin;
     for (;;) {
         const bool ax = X.t <= Y.t && X.t <= Z.t;   // ties step the lowest axis
         const bool ay = !ax && Y.t <= Z.t;
         const double tm = ax ? X.t : ay ? Y.t : Z.t;
+        if (PART && tm > tend) break;
         const double tout = tm < r.te ? tm : r.te;
         if (tout > tin) {
             emit(k, i, j, kz, lin, tin, tout);
@@ -364,6 +383,12 @@ __device__ __forceinline__ int walk_dense(const SceneDev& sd, const Ray& r, Emit
         if ((uint32_t)lin >= nvox) break;
     }
     return k;
+}
+
+template <bool FAST, class Emit>
+__device__ __forceinline__ int walk_dense(const SceneDev& sd, const Ray& r, Emit&& emit)
+{
+    return walk_from<FAST, false>(sd, r, walk_start<FAST>(sd, r), 0.0, emit);
 }
 
 __device__ __forceinline__ bool times_by_quot(const SceneDev& sd, const Ray& r)
@@ -466,6 +491,51 @@ __device__ int count_dense(const SceneDev& sd, const Ray& r)
         shares_time(sd, r, 1, 2, n, t0, y, mh, rh))
         return -1;
     return n[0] + n[1] + n[2] + 1;
+}
+
+// one axis of a state moved past its faces up to time t
+__device__ __forceinline__ void walk_axis_to(const SceneDev& sd, const Ray& r, int a, double t, WalkAxis& x, int& idx,
+                                             WalkState& w)
+{
+    if (x.w == 0.0) return;
+    const double o = sd.o[a], h = sd.h, f0 = x.f;
+    auto time = [&](double f) { return quot((o + f * h) - x.c, x.w, x.y); };
+    // faces passed: as many as lie at or before the ray's position at t, settled by their times
+    const double e = floor((((x.c + t * x.w) - o) / h - f0) * x.s) + 1.0;
+    int m = (int)fmin(fmax(e, 0.0), (double)kMaxFaces);
+    if (m > 0 && time(f0 + x.s * (double)(m - 1)) > t)
+        --m;
+    else if (time(f0 + x.s * (double)m) <= t)
+        ++m;
+    if (m == 0) return;
+    w.k += x.t <= r.ts ? m - 1 : m;   // a face on the start ends no chord
+    w.tin = fmax(w.tin, time(f0 + x.s * (double)(m - 1)));
+    w.lin += x.dl * m;
+    idx += x.di * m;
+    x.f = f0 + x.s * (double)m;
+    x.t = time(x.f);
+}
+
+// Part `part` of a ray's chords, those that end in its quarter of (ts, te]; every part starts
+// from the faces before it.  Rays that count_dense does not count stay whole (part 0).
+constexpr int kEmitParts = 4;
+
+template <class Emit>
+__device__ __forceinline__ void walk_part(const SceneDev& sd, const Ray& r, int part, Emit&& emit)
+{
+    auto cut = [&](int p) { return r.ts + (r.te - r.ts) * ((double)p * (1.0 / kEmitParts)); };
+    if (!times_by_quot(sd, r) || !(cut(1) > r.ts && cut(kEmitParts - 1) < r.te) || count_dense(sd, r) < 0) {
+        if (part == 0) walk_dense(sd, r, emit);
+        return;
+    }
+    WalkState w = walk_start<true>(sd, r);
+    if (part > 0) {
+        const double t = cut(part);
+        walk_axis_to(sd, r, 0, t, w.X, w.i, w);
+        walk_axis_to(sd, r, 1, t, w.Y, w.j, w);
+        walk_axis_to(sd, r, 2, t, w.Z, w.kz, w);
+    }
+    walk_from<true, true>(sd, r, w, part < kEmitParts - 1 ? cut(part + 1) : __builtin_huge_val(), emit);
 }
 
 // Pixel (u, v) of thread t of block b: 16 x 16 pixels a block, 8 x 8 a wave, so that a
@@ -627,7 +697,7 @@ struct EdgeEmit {
 // padding (no voxel, no bin, sort key pad_key past every voxel); lanes of pixels
 // outside the image pad their whole column.  Sort keys are written where the
 // slots themselves are sorted (KEY).
-template <bool DENSE, bool KEY>
+template <bool DENSE, bool KEY, int PARTS>
 __global__ __launch_bounds__(256) void trace_emit_k(const SceneDev* __restrict__ scenes,
                                                     const FrameDev* __restrict__ frames, BuildDev bp,
                                                     const int32_t* __restrict__ counts,
@@ -639,10 +709,12 @@ __global__ __launch_bounds__(256) void trace_emit_k(const SceneDev* __restrict__
     const FrameDev fr = frames[blockIdx.y];
     const SceneDev& sd = scenes[fr.scene];
     const int nty = (sd.H + kTileW - 1) / kTileW;
-    const int lt = blockIdx.x * (256 / kTile) + (int)threadIdx.x / kTile;
+    // PARTS > 1: wave w of a block takes part w of the rays of its four tiles
+    const int th = PARTS > 1 ? threadIdx.x & 63 : threadIdx.x, part = PARTS > 1 ? threadIdx.x >> 6 : 0;
+    const int lt = blockIdx.x * (256 / PARTS / kTile) + th / kTile;
     if (lt >= fr.ntx * nty) return;
     const int ty = lt / fr.ntx, tx = lt - ty * fr.ntx;
-    const int q = (int)threadIdx.x % kTile;
+    const int q = th % kTile;
     const int v = ty * kTileW + q / kTileW, u = tx * kTileW + q % kTileW;
     const int64_t t = fr.tile_base + lt;
     const int64_t slot0 = tbase[t] + q;
@@ -660,13 +732,15 @@ __global__ __launch_bounds__(256) void trace_emit_k(const SceneDev* __restrict__
             const double dbin = bp.dmax / 64.0;
             EdgeEmit<KEY> em{col,   key,   delta, bin, tin, tout, wlen, &sd, slot0, (int32_t)sd.voxel_base, ray.Z,
                         dbin,  sqrt(wn), 1.0 / dbin};
-            if constexpr (DENSE)
+            if constexpr (PARTS > 1)
+                walk_part(sd, ray, part, em);
+            else if constexpr (DENSE)
                 walk_dense(sd, ray, em);
             else
                 walk(sd, ray, scene_bricks(bp, sd), em, bp.skip);
         }
     }
-    for (int k = m; k < len; ++k) {
+    for (int k = m + part; k < len; k += PARTS) {
         const int64_t e = slot0 + (int64_t)kTile * k;
         col[e] = -1;
         if constexpr (KEY) key[e] = pad_key;
@@ -793,11 +867,12 @@ hipError_t launch_scatter_by_slot(const uint32_t* slot, const float* in, int64_t
     return hipGetLastError();
 }
 
-template <bool DENSE, bool KEY>
+template <bool DENSE, bool KEY, int PARTS>
 static void launch_emit_t(mrf_ctx* c, hipStream_t s, int f0, int nf)
 {
-    const dim3 grid((unsigned)((c->max_tpf + 256 / kTile - 1) / (256 / kTile)), nf);
-    hipLaunchKernelGGL((trace_emit_k<DENSE, KEY>), grid, dim3(256), 0, s, (const SceneDev*)c->b_scenes.p,
+    constexpr int per = 256 / PARTS / kTile;   // tiles of a block
+    const dim3 grid((unsigned)((c->max_tpf + per - 1) / per), nf);
+    hipLaunchKernelGGL((trace_emit_k<DENSE, KEY, PARTS>), grid, dim3(256), 0, s, (const SceneDev*)c->b_scenes.p,
                        (const FrameDev*)c->b_frames.p + f0, c->bp, (const int32_t*)c->b_counts.p,
                        (const int64_t*)c->b_tbase.p, (const TileDev*)c->b_tiles.p, (uint32_t)c->Vk,
                        (int32_t*)c->b_col.p, (uint32_t*)c->b_g.p, (float*)c->b_delta.p, (uint8_t*)c->b_bin.p,
@@ -805,14 +880,25 @@ static void launch_emit_t(mrf_ctx* c, hipStream_t s, int f0, int nf)
                        c->keep_chords ? (double*)c->b_tout.p : nullptr, c->kf ? (float*)c->b_kflen.p : nullptr);
 }
 
+// Whether rays are walked in parts: where they are few, the pass lasts as long as its longest
+// chain of steps, and a part's is a quarter; many fill the chip by themselves, and the parts'
+// starts are added work.  Build in us, whole and in parts: 16 tiles 165 and 156, 192 (64x48)
+// 218 and 192, 1200 282 and 270, 4800 (320x240) 418 and 411; 14400 504 and 511, 19200 (VGA)
+// 510 and 535; the emit pass of 8 VGA frames at 2 cm 1.84 ms and 1.95 (in other scenes of
+// that size the build is 5% faster in parts).
+static bool emit_in_parts(int64_t tiles) { return tiles <= 8192; }
+
 hipError_t launch_trace_emit(mrf_ctx* c, bool keys, hipStream_t s, int f0, int nf)
 {
     if (nf < 0) nf = c->n_frames - f0;
     if (nf <= 0) return hipSuccess;
+    const bool split = emit_in_parts((int64_t)c->max_tpf * nf);
     if (c->bp.bricks)
-        keys ? launch_emit_t<false, true>(c, s, f0, nf) : launch_emit_t<false, false>(c, s, f0, nf);
+        keys ? launch_emit_t<false, true, 1>(c, s, f0, nf) : launch_emit_t<false, false, 1>(c, s, f0, nf);
+    else if (split)
+        keys ? launch_emit_t<true, true, kEmitParts>(c, s, f0, nf) : launch_emit_t<true, false, kEmitParts>(c, s, f0, nf);
     else
-        keys ? launch_emit_t<true, true>(c, s, f0, nf) : launch_emit_t<true, false>(c, s, f0, nf);
+        keys ? launch_emit_t<true, true, 1>(c, s, f0, nf) : launch_emit_t<true, false, 1>(c, s, f0, nf);
     return hipGetLastError();
 }
 

@@ -88,22 +88,71 @@ def _first(n, h, o, c, w, ts, a):
     return float(min(max(q, 0), n[a] - 1))
 
 
-def _walk(n, h, o, ray):
+def _start(n, h, o, ray):
+    """State before the first chord: face numbers and times of the axes, entry time, chords so far."""
     c, w, ts, te = ray
     f, t = [0.0] * 3, [float("inf")] * 3
     for a in range(3):
         f[a] = _first(n, h, o, c, w, ts, a) + (w[a] > 0)
         if w[a] != 0.0:
             t[a] = ((o[a] + f[a] * h) - c[a]) / w[a]
-    tin, k = ts, 0
+    return f, t, ts, 0
+
+
+def _chords(n, h, o, ray, state, tend=float("inf")):
+    """(number, last face of each axis, t_in, t_out) of the chords from a state on that end by tend."""
+    c, w, ts, te = ray
+    f, t, tin, k = list(state[0]), list(state[1]), state[2], state[3]
+    out = []
     while True:
         a = min(range(3), key=lambda i: t[i])   # the lowest axis of a tie
-        k += min(t[a], te) > tin
+        if t[a] > tend:
+            return out
+        if min(t[a], te) > tin:
+            out.append((k, tuple(f), tin, min(t[a], te)))
+            k += 1
         if t[a] >= te:
-            return k
+            return out
         tin = max(tin, t[a])
         f[a] += 1.0 if w[a] > 0 else -1.0
         t[a] = ((o[a] + f[a] * h) - c[a]) / w[a]
+
+
+def _walk(n, h, o, ray):
+    return len(_chords(n, h, o, ray, _start(n, h, o, ray)))
+
+
+def _parts(n, h, o, ray, parts=4):
+    """The chords by quarters of the ray, each from the faces before it (None: not split)."""
+    c, w, ts, te = ray
+
+    def cut(p):
+        return ts + (te - ts) * (p * (1.0 / parts))
+    if not (cut(1) > ts and cut(parts - 1) < te) or _faces(n, h, o, ray) < 0:
+        return None
+    out = []
+    for p in range(parts):
+        f, t, tin, k = _start(n, h, o, ray)
+        for a in range(3):
+            if p == 0 or w[a] == 0.0:
+                continue
+            s, f0, tau = (1.0 if w[a] > 0 else -1.0), f[a], cut(p)
+
+            def time(x):
+                return ((o[a] + x * h) - c[a]) / w[a]
+            m = int(min(max(math.floor((((c[a] + tau * w[a]) - o[a]) / h - f0) * s) + 1.0, 0.0), 1024.0))
+            if m > 0 and time(f0 + s * (m - 1)) > tau:
+                m -= 1
+            elif time(f0 + s * m) <= tau:
+                m += 1
+            if m == 0:
+                continue
+            k += m - 1 if t[a] <= ts else m
+            tin = max(tin, time(f0 + s * (m - 1)))
+            f[a] = f0 + s * m
+            t[a] = time(f[a])
+        out += _chords(n, h, o, ray, (f, t, tin, k), cut(p + 1) if p < parts - 1 else float("inf"))
+    return out
 
 
 def _faces(n, h, o, ray):
@@ -168,3 +217,22 @@ def test_voxels_counted_by_faces_are_those_walked(n, h, o):
             assert max(n) > 1024 or sum(g < 0 for g in got) <= 0.01 * len(got)
         if kind == 1 and min(n) > 1:   # shared times are found
             assert sum(g < 0 for g in got) > 0.2 * len(got)
+
+
+@pytest.mark.parametrize("n,h,o", [((25, 25, 15), 0.2, (-2.5, -2.5, -0.3)), ((250, 240, 150), 0.02, (-2.5, 1.1, 0.0)),
+                                   ((1, 7, 64), 0.25, (0.0, -0.875, 8.0))])
+def test_chords_by_parts_are_those_walked(n, h, o):
+    rng = random.Random(12)
+    for kind in range(5):
+        rays = [r for r in (_ray(rng, kind, n, h, o) for _ in range(500)) if r]
+        split = 0
+        for r in rays:
+            if rng.random() < 0.2:   # an end next to the start
+                r = (*r[:3], r[2] + (r[3] - r[2]) * 2.0 ** -rng.randrange(1, 52))
+                if r[3] <= r[2]:
+                    continue
+            got = _parts(n, h, o, r)
+            if got is not None:
+                split += 1
+                assert got == _chords(n, h, o, r, _start(n, h, o, r)), (kind, r)
+        assert split > 0.9 * len(rays) * 0.8 if kind == 0 else True
