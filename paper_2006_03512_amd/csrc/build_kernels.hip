@@ -311,9 +311,8 @@ __device__ __forceinline__ WalkAxis walk_axis(const SceneDev& sd, const Ray& r, 
 // the axes' last boundary times (the same expression), so it stops there first; the
 // test of the linear id only keeps an index out of range from ever being used.
 // emit(k, i, j, kz, lin, t_in, t_out).  5e8 steps (8 VGA frames at 2 cm): the bare walk
-// 1.18 ms with walk() and 0.78 (VALU-bound), emit pass 1.89 and 1.82 (its stores of 4, 4
-// and 1 bytes a step); the metric's walk of 4 frames to the grid
-// exit 1.15 and 0.70.
+// 1.18 ms with walk() and 0.78 (VALU-bound), emit pass 1.89 and 1.82 (with its stores of 4,
+// 4 and 1 bytes a step); the metric's walk of 4 frames to the grid exit 1.15 and 0.70.
 struct WalkState {
     WalkAxis X, Y, Z;
     int i, j, kz, lin, k;   // voxel, its linear id, chords so far
@@ -358,13 +357,13 @@ __device__ __forceinline__ int walk_from(const SceneDev& sd, const Ray& r, const
         const bool ay = !ax && Y.t <= Z.t;
         const double tm = ax ? X.t : ay ? Y.t : Z.t;
         if (PART && tm > tend) break;
-        const double tout = tm < r.te ? tm : r.te;
+        const double tout = fmin(tm, r.te);
         if (tout > tin) {
             emit(k, i, j, kz, lin, tin, tout);
             ++k;
         }
         if (tm >= r.te) break;
-        if (tm > tin) tin = tm;
+        tin = fmax(tin, tm);
         // one branch per axis: lanes that step different axes run them one after the
         // other, still fewer instructions than selecting every operand by axis
         if (ax) {
@@ -654,18 +653,22 @@ struct EdgeEmit {
     double Z, dbin;
     double wn;            // |w| of the ray: chord length = (t_out - t_in) |w|
     double rbin;          // 1 / dbin, correctly rounded
-    // The bin is floor(d / dbin) with the quotient rounded once, as in the
-    // oracle.  y = d * rbin is within about 2^-51 |d / dbin| of that quotient
-    // (under 4e-10 below 2^20), so wherever y is more than 1e-9 from an integer
-    // the two have the same floor; next to a bin boundary the division decides.
-    // Quotients of 2^20 and more clamp to the last bin either way.
-    __device__ double bin_of(double d) const
+    bool by_quot;         // quot() gives d / dbin
+    // The bin is floor(d / dbin) with the quotient rounded once, as in the oracle: by
+    // quot(), seven operations with the clamp below (a quotient of 128 and one of more are
+    // the last bin alike; chord midpoints are not negative).  Where that is not exact the
+    // division is behind a barrier that keeps the compiler from forming it on every step,
+    // which took 25.  Emit pass of 8 VGA frames at 2 cm 1.83 -> 1.72 ms, of one at 4 cm 92
+    // -> 87 us.
+    __device__ int bin_of(double d) const
     {
-        const double y = d * rbin;
-        double q = floor(y);
-        const double f = y - q;   // exact for y >= 0 (chord midpoints are)
-        if (f < 1e-9 || f > 1.0 - 1e-9) q = floor(d / dbin);
-        return q;
+        d = fmin(d, 128.0 * dbin);
+        double q = quot(d, dbin, rbin);
+        if (!by_quot) {
+            asm volatile("");
+            q = d / dbin;
+        }
+        return min(max((int)q, 0), 63);
     }
     __device__ void operator()(int k, int vi, int vj, int vk, double ti, double to) const
     {
@@ -675,13 +678,10 @@ struct EdgeEmit {
     {
         const int64_t e = base + (int64_t)kTile * k;   // step k of this ray's tile lane
         const double d = (ti + to) * 0.5;   // voxel depth: chord midpoint
-        double q = bin_of(d);
-        if (q < 0.0) q = 0.0;
-        if (q > 63.0) q = 63.0;
         col[e] = vbase + lin;
         if constexpr (KEY) key[e] = brick_key(*sd, vi, vj, vk);
         delta[e] = (float)(Z - d);
-        bin[e] = (uint8_t)q;
+        bin[e] = (uint8_t)bin_of(d);
         if (tin) {
             tin[e] = ti;
             tout[e] = to;
@@ -731,7 +731,7 @@ __global__ __launch_bounds__(256) void trace_emit_k(const SceneDev* __restrict__
             wn = wn + ray.w[2] * ray.w[2];
             const double dbin = bp.dmax / 64.0;
             EdgeEmit<KEY> em{col,   key,   delta, bin, tin, tout, wlen, &sd, slot0, (int32_t)sd.voxel_base, ray.Z,
-                        dbin,  sqrt(wn), 1.0 / dbin};
+                        dbin,  sqrt(wn), 1.0 / dbin, dbin > 0.0 && quot_exact(0.0, 0.0, 0.0, dbin)};
             if constexpr (PARTS > 1)
                 walk_part(sd, ray, part, em);
             else if constexpr (DENSE)
