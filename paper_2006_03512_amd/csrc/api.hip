@@ -195,16 +195,24 @@ static hipError_t enqueue_forward_kf(mrf_ctx* c, int K, int keep, bool plain, hi
 // The captured sweeps run on the caller's stream (an internal stream beside it costs an
 // event and a wait on each side: 116 us for 5 sweeps of a 64x48 frame, 66 without them and
 // with the inputs in one launch).  Launches of one context on
-// different streams stay in order, as they were on one internal stream.
+// different streams stay in order, as they were on one internal stream.  In a capture of
+// the caller's there is nothing to order: an event from outside it cannot be waited for
+// there, and one recorded in it not outside.
 static hipError_t after_last_graph(mrf_ctx* c, hipStream_t s)
 {
-    return c->launched ? hipStreamWaitEvent(s, c->ev_out, 0) : hipSuccess;
+    if (!c->launched) return hipSuccess;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    const hipError_t e = hipStreamIsCapturing(s, &st);
+    return e == hipSuccess && st == hipStreamCaptureStatusNone ? hipStreamWaitEvent(s, c->ev_out, 0) : e;
 }
 
 static hipError_t launch_graph(mrf_ctx* c, hipStream_t s)
 {
     hipError_t e = hipGraphLaunch(c->gexec, s);
-    if (e == hipSuccess) e = hipEventRecord(c->ev_out, s);
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (e == hipSuccess) e = hipStreamIsCapturing(s, &st);
+    if (e != hipSuccess || st != hipStreamCaptureStatusNone) return e;
+    e = hipEventRecord(c->ev_out, s);
     if (e == hipSuccess) c->launched = 1;
     return e;
 }
@@ -1196,7 +1204,7 @@ extern "C" {
 
 static std::string kid_name(const mrf_ctx* c, int k)
 {
-    if (k == KID_VOX) return c->by_runs ? "run_sum_k" : "seg_sum_k";
+    if (k == KID_VOX) return c->by_runs ? "run_sum_k<false>" : "seg_sum_k";
     auto ray_name = [](const char* direct, const char* lds, int q, RayShape sh, bool adj) {
         std::string n = std::string(ray_class_lds(q) ? lds : direct) + "<" + std::to_string(sh.g) + "," +
                         std::to_string(kRayCap[q] / sh.g);

@@ -539,9 +539,9 @@ __device__ __forceinline__ unsigned xcd_block(unsigned bid, unsigned nb)
 
 }  // namespace mrf
 
-// Work item of the ray kernels: a 4x4-pixel tile of rays.  A 256-thread block
-// holds 16 rays of 16 lanes (G == 16) or 4 rays of one wave (G == 64, four
-// consecutive blocks per tile, kept on one XCD by the block remap).
+// Work item of the ray kernels: a 4x4-pixel tile of rays.  A 256-thread block of the
+// direct kernels (tiles too long for LDS) holds 256 / G rays of G lanes; a tile's
+// consecutive blocks are kept on one XCD by the block remap.
 namespace mrf {
 
 template <int G>
