@@ -255,6 +255,7 @@ int mrf_create(mrf_ctx** out)
     if (e == hipSuccess) static_scratch_init(c->device);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->aux, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_out, hipEventDisableTiming);
+    if (e == hipSuccess) e = hipHostMalloc(&c->pinned, kPinnedBytes, hipHostMallocDefault);
     if (e != hipSuccess) {
         int rc = hip_fail(e, "mrf_create");
         mrf_destroy(c);
@@ -286,6 +287,7 @@ void mrf_destroy(mrf_ctx* c)
                      &c->b_kfxr, &c->b_kfy, &c->b_kfws};
     for (DevBuf* b : all) free_buf(*b);
     for (auto& b : c->b_host_in) free_buf(b);
+    if (c->pinned) hipHostFree(c->pinned);
     if (c->ev_out) hipEventDestroy(c->ev_out);
     if (c->aux) hipStreamDestroy(c->aux);
     delete c;
@@ -532,9 +534,7 @@ static int build_impl(mrf_ctx* c, const mrf_scene* scenes, int32_t n_scenes, con
 
     // one readback: the slots and edges of every frame, which size everything below
     std::vector<int64_t> h(2 * nf);
-    HCK(hipMemcpyAsync(h.data(), c->b_export.p, 2 * sizeof(int64_t) * nf, hipMemcpyDeviceToHost, s),
-        "mrf_build: read counts");
-    HCK(hipStreamSynchronize(s), "mrf_build: sync");
+    HCK(read_back(c, h.data(), c->b_export.p, 2 * sizeof(int64_t) * nf, s), "mrf_build: read counts");
     int64_t S = 0, E = 0;
     for (size_t f = 0; f < nf; ++f) {
         S += h[2 * f];
@@ -778,8 +778,7 @@ int mrf_add_frames(mrf_ctx* c, int32_t n_frames, const float* depth, const doubl
         "mrf_add_frames: scan");
     HCK(launch_add_i64((int64_t*)c->b_rowptr.p + R0, E0, R1 - R0 + 1, s), "mrf_add_frames: scan");
     int64_t E1 = 0;
-    HCK(hipMemcpyAsync(&E1, (int64_t*)c->b_rowptr.p + R1, sizeof(int64_t), hipMemcpyDeviceToHost, s), "read E");
-    HCK(hipStreamSynchronize(s), "mrf_add_frames: sync");
+    HCK(read_back(c, &E1, (int64_t*)c->b_rowptr.p + R1, sizeof(int64_t), s), "mrf_add_frames: read E");
     c->E = E1;
 
     // tiles of the new frames, slot bases after every existing slot
@@ -796,8 +795,7 @@ int mrf_add_frames(mrf_ctx* c, int32_t n_frames, const float* depth, const doubl
     HCK(launch_add_i64((int64_t*)c->b_tbase.p + T0, S0, T1 - T0 + 1, s), "mrf_add_frames: tile scan");
     HCK(launch_tile_bases(c, s, T0), "mrf_add_frames: tile bases");
     int64_t S1 = 0;
-    HCK(hipMemcpyAsync(&S1, (int64_t*)c->b_tbase.p + T1, sizeof(int64_t), hipMemcpyDeviceToHost, s), "read S");
-    HCK(hipStreamSynchronize(s), "mrf_add_frames: sync");
+    HCK(read_back(c, &S1, (int64_t*)c->b_tbase.p + T1, sizeof(int64_t), s), "mrf_add_frames: read S");
     const int64_t gb = c->sg.slot[c->sg.n - 1];   // the last scene's group
     if (S1 - gb >= (int64_t(1) << c->group_log2))
         return fail(MRF_ERANGE, "mrf_add_frames: the last scene's group would reach 2^" +

@@ -11,6 +11,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstring>
 #include <mutex>
 
 #include "dev_common.hpp"
@@ -1687,8 +1688,7 @@ hipError_t build_incidence(mrf_ctx* c, int64_t n, int64_t edges, uint32_t* keys,
                        (const SceneDev*)c->b_scenes.p, c->n_scenes, gkey, ginfo, bcnt);
     if ((e = scan_exclusive_i32(bcnt, boff, nb, c->b_misc.p, c->b_misc.cap, s)) != hipSuccess) return e;
     int64_t nr = 0;
-    if ((e = hipMemcpyAsync(&nr, boff + nb, sizeof(int64_t), hipMemcpyDeviceToHost, s)) != hipSuccess) return e;
-    if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
+    if ((e = read_back(c, &nr, boff + nb, sizeof(int64_t), s)) != hipSuccess) return e;
     if (keep_runs && nr >= (int64_t(1) << 32)) {   // more than rptr's 32 bits: lists of edges after all
         if ((e = ensure(c->b_vedge, sizeof(uint32_t) * (size_t)n + 16)) != hipSuccess) return e;
         vals = (uint32_t*)c->b_vedge.p;
@@ -2305,8 +2305,7 @@ hipError_t build_classes(mrf_ctx* c, hipStream_t s)
 
     // one readback: class sizes, statistics, and per-frame offsets of the tile lists (plain schedule)
     std::vector<char> hb(head);
-    if ((e = hipMemcpyAsync(hb.data(), st, head, hipMemcpyDeviceToHost, s)) != hipSuccess) return e;
-    if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
+    if ((e = read_back(c, hb.data(), st, head, s)) != hipSuccess) return e;
     const ListStats& h = *(const ListStats*)hb.data();
     if (h.tiles[kRayClasses] > 0) {
         set_error("a ray crosses more than 2048 voxels");
@@ -2348,8 +2347,7 @@ static hipError_t partition_pairs(mrf_ctx* c, const uint32_t* pstart, int64_t P,
     e = rounds == 2 ? partition_r<PairItems, 2, NoItems, 2>(f, sf, NoItems{}, none, s)
                     : partition_r<PairItems, 16, NoItems, 2>(f, sf, NoItems{}, none, s);
     unsigned long long h[kPartMaxClasses + 1];
-    if (e == hipSuccess) e = hipMemcpyAsync(h, tot, head, hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e == hipSuccess) e = read_back(c, h, tot, head, s);
     if (e != hipSuccess) return e;
     return finish_segments(c, c->pair, h, (int64_t)h[kPartMaxClasses], c->by_runs ? kRunPiece : kSegPiece, s);
 }
@@ -2370,6 +2368,15 @@ __global__ void add_i64_k(int64_t* __restrict__ p, int64_t v, int64_t n)
 {
     for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < n; k += (int64_t)gridDim.x * blockDim.x)
         p[k] += v;
+}
+
+hipError_t read_back(mrf_ctx* c, void* dst, const void* src, size_t bytes, hipStream_t s)
+{
+    const bool fits = bytes <= kPinnedBytes;
+    hipError_t e = hipMemcpyAsync(fits ? c->pinned : dst, src, bytes, hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e == hipSuccess && fits) std::memcpy(dst, c->pinned, bytes);
+    return e;
 }
 
 static unsigned grid_of(int64_t n)
@@ -2557,8 +2564,7 @@ hipError_t build_keyframe_pairs(mrf_ctx* c, hipStream_t s)
     if ((e = ensure(c->b_misc, sb > c->b_misc.cap ? sb : c->b_misc.cap)) != hipSuccess) return e;
     if ((e = scan_rec(ld, n, pos, (int64_t*)c->b_misc.p, s)) != hipSuccess) return e;
     uint32_t P32 = 0;
-    if ((e = hipMemcpyAsync(&P32, pos + n, sizeof(uint32_t), hipMemcpyDeviceToHost, s)) != hipSuccess) return e;
-    if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
+    if ((e = read_back(c, &P32, pos + n, sizeof(uint32_t), s)) != hipSuccess) return e;
     const int64_t P = P32;
     c->n_pairs = P;
     uint32_t* pstart = (uint32_t*)(runs ? c->b_ellbar.p : c->b_ell.p);   // P + 1 <= n + 1 entries

@@ -94,6 +94,7 @@ static_assert(kRayCap[kSmallClasses - 1] == 256, "classes of one launch");
 // share a 64-byte line.
 constexpr int kTileW = 4;
 constexpr int kTile = kTileW * kTileW;
+constexpr size_t kPinnedBytes = 16384;   // of a context's pinned memory
 
 // Work classes of the voxel phase by degree (seg_sum_k): capacities, and the
 // segments that a lane group (capacities 16 and 32) or a wave walks with every
@@ -311,6 +312,7 @@ struct Profiler {
 struct mrf_ctx {
     int device = 0;
     hipStream_t aux = nullptr;    // internal stream used for graph capture
+    void* pinned = nullptr;       // host memory for the sizes that a build reads back
     hipEvent_t ev_out = nullptr;  // recorded after every graph launch
     int launched = 0;
 
@@ -471,6 +473,11 @@ hipError_t launch_tile_bases(mrf_ctx* c, hipStream_t s, int64_t t0 = 0);
 // row pointers, tiles, slot bases and per-frame counts (out: slots, edges of each frame) of a
 // batch of few rays in one launch; false: too many, nothing done
 bool launch_count_finish(mrf_ctx* c, int64_t* out, hipStream_t s);
+// Bytes of device memory to dst, through the context's pinned memory where they fit; waits
+// for s.  Into pageable memory the runtime stages the copy, 14 to 18 us more each: build of a
+// 64x48 frame (two of them) 192 us and 163, of a 640x480 frame (three) 506 and 452.  The
+// build's two uploads through pinned memory gained nothing.
+hipError_t read_back(mrf_ctx* c, void* dst, const void* src, size_t bytes, hipStream_t s);
 hipError_t launch_add_i64(int64_t* p, int64_t v, int64_t n, hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t s);
 // out[slot[j]] = in[j] for j < n (list order to slot order)
