@@ -43,23 +43,32 @@ void drop_graph(mrf_ctx* c)
     c->g_key.clear();
 }
 
-// Everything a captured forward graph bakes in: launch shapes and addresses.
-std::vector<uint64_t> graph_key(const mrf_ctx* c, int K, int keep)
+// The context's device buffers (of the copies of host inputs only the traversal reads).
+std::vector<mrf::DevBuf*> context_buffers(mrf_ctx* c)
+{
+    return {&c->b_scenes, &c->b_frames, &c->b_counts, &c->b_rowptr, &c->b_col, &c->b_delta,
+            &c->b_bin, &c->b_tin, &c->b_tout, &c->b_g, &c->b_lam, &c->b_ell, &c->b_vedge,
+            &c->b_vptr, &c->b_theta, &c->b_theta2, &c->b_L, &c->b_thetabar, &c->b_sigma, &c->b_bias,
+            &c->b_ckpt, &c->b_tsum, &c->b_tbar, &c->b_metric, &c->b_bricks,
+            &c->b_ellbar, &c->b_lambar, &c->b_gsum, &c->b_tmp64, &c->b_part, &c->b_sigpart,
+            &c->b_misc, &c->b_ray_list, &c->vox.desc, &c->vox.hub, &c->pair.desc, &c->pair.hub, &c->b_hubsum,
+            &c->b_runrow, &c->b_runmask, &c->b_rptr, &c->b_tiles, &c->b_tbase, &c->b_export,
+            &c->b_kfw, &c->b_kflen, &c->b_pair_m, &c->b_pair_x, &c->b_kfx, &c->b_kfxb, &c->b_kf_vox,
+            &c->b_kfxr, &c->b_kfy, &c->b_kfws};
+}
+
+// Everything a captured forward graph bakes in: launch shapes and addresses.  Every buffer
+// of the context counts, whether the sweeps read it or not, so that none can be left out:
+// one that a build or a readout has moved costs a capture of the next inference.
+std::vector<uint64_t> graph_key(mrf_ctx* c, int K, int keep)
 {
     std::vector<uint64_t> k = {(uint64_t)K, (uint64_t)keep, (uint64_t)c->E, (uint64_t)c->R, (uint64_t)c->V,
                                (uint64_t)c->Vk, (uint64_t)c->S, (uint64_t)c->T};
     for (int i = 0; i < mrf::kRayClasses; ++i) k.push_back((uint64_t)c->ray_cnt[i]);
     for (int i = 0; i < mrf::kRayClasses; ++i) k.push_back((uint64_t)c->fwd_sel[i]);
-    const mrf::DevBuf* bufs[] = {&c->b_rowptr, &c->b_col,   &c->b_delta, &c->b_bin,  &c->b_g,    &c->b_lam,
-                                 &c->b_ell,    &c->b_vedge, &c->b_vptr,  &c->b_theta, &c->b_L,   &c->b_sigma, &c->b_bias,
-                                 &c->b_ckpt,   &c->b_tsum,  &c->b_tbar,  &c->b_tiles, &c->b_counts, &c->b_theta2,
-                                 &c->b_kfw,    &c->b_pair_m, &c->b_pair_x, &c->b_kfx, &c->b_kfxb, &c->b_kf_vox};
-    for (const mrf::DevBuf* b : bufs) k.push_back((uint64_t)(uintptr_t)b->p);
+    for (const mrf::DevBuf* b : context_buffers(c)) k.push_back((uint64_t)(uintptr_t)b->p);
     k.push_back((uint64_t)c->by_runs);
-    for (const mrf::DevBuf* b : {&c->b_ray_list, &c->b_hubsum, &c->b_runrow, &c->b_runmask}) k.push_back((uint64_t)(uintptr_t)b->p);
     for (const mrf::SegList* l : {&c->vox, &c->pair}) {
-        k.push_back((uint64_t)(uintptr_t)l->desc.p);
-        k.push_back((uint64_t)(uintptr_t)l->hub.p);
         k.push_back((uint64_t)l->n_pieces);
         for (int i = 0; i < mrf::kVoxClasses; ++i) k.push_back((uint64_t)l->cnt[i]);
     }
@@ -71,8 +80,6 @@ std::vector<uint64_t> graph_key(const mrf_ctx* c, int K, int keep)
         k.push_back((uint64_t)c->sg.slot[g]);
         k.push_back((uint64_t)c->sg.pos[g]);
     }
-    k.push_back((uint64_t)(uintptr_t)c->b_frames.p);
-    k.push_back((uint64_t)(uintptr_t)c->b_scenes.p);
     return k;
 }
 
@@ -276,16 +283,7 @@ void mrf_destroy(mrf_ctx* c)
 {
     if (!c) return;
     drop_graph(c);
-    DevBuf* all[] = {&c->b_scenes, &c->b_frames, &c->b_counts, &c->b_rowptr, &c->b_col, &c->b_delta,
-                     &c->b_bin, &c->b_tin, &c->b_tout, &c->b_g, &c->b_lam, &c->b_ell, &c->b_vedge,
-                     &c->b_vptr, &c->b_theta, &c->b_theta2, &c->b_L, &c->b_thetabar, &c->b_sigma, &c->b_bias,
-                     &c->b_ckpt, &c->b_tsum, &c->b_tbar, &c->b_metric, &c->b_bricks,
-                     &c->b_ellbar, &c->b_lambar, &c->b_gsum, &c->b_tmp64, &c->b_part, &c->b_sigpart,
-                     &c->b_misc, &c->b_ray_list, &c->vox.desc, &c->vox.hub, &c->pair.desc, &c->pair.hub, &c->b_hubsum, &c->b_runrow,
-                     &c->b_runmask, &c->b_rptr, &c->b_tiles, &c->b_tbase, &c->b_export,
-                     &c->b_kfw, &c->b_kflen, &c->b_pair_m, &c->b_pair_x, &c->b_kfx, &c->b_kfxb, &c->b_kf_vox,
-                     &c->b_kfxr, &c->b_kfy, &c->b_kfws};
-    for (DevBuf* b : all) free_buf(*b);
+    for (DevBuf* b : context_buffers(c)) free_buf(*b);
     for (auto& b : c->b_host_in) free_buf(b);
     if (c->pinned) hipHostFree(c->pinned);
     if (c->ev_out) hipEventDestroy(c->ev_out);
