@@ -1310,6 +1310,66 @@ namespace mrf {
 // visibility P_i summed in FP64, the mode is the first largest W_i,
 // q_i = 2^(W_i - max) / sum, and the mean depth sum_i q_i d_i, d_i = Z - delta_i.
 
+// Depth messages of one ray held by a group of G lanes, blocked as in ray_body (lane l
+// holds steps [i0, i0 + IPL), i0 = l IPL).  step(j, al, be, gg) gives the base-2 logs of step
+// i0 + j (load_step); ready() is called once all of them have been taken, then delta(j) gives
+// its Z - d_i.  Returns the probabilities of the lane's steps (0 past the ray), and in every
+// lane the most probable step and, with want_mean, the expected depth.
+template <int G, int IPL, class Step, class Ready, class Delta>
+__device__ __forceinline__ void depth_body(int m, int i0, bool want_mean, double Z, Step&& step, Ready&& ready,
+                                           Delta&& delta, float (&prob)[IPL], int& best, double& mean)
+{
+    double W[IPL];
+    double P = 0.0;
+#pragma unroll
+    for (int j = 0; j < IPL; ++j) {
+        float al, be, gg;
+        step(j, al, be, gg);
+        W[j] = ((double)be + (double)gg) + P;   // past the ray: log 0
+        P += (double)al;
+    }
+    ready();
+    const double before = dexcl_scan_d<G>(P);   // log2 visibility up to the lane's first step
+    double M = -__builtin_huge_val();
+    best = 0;
+#pragma unroll
+    for (int j = 0; j < IPL; ++j) {
+        W[j] += before;
+        if (i0 + j < m && W[j] > M) {
+            M = W[j];
+            best = i0 + j;
+        }
+    }
+#pragma unroll
+    for (int d = 1; d < G; d <<= 1) {
+        const double oM = __shfl_xor(M, d, G);
+        const int ob = __shfl_xor(best, d, G);
+        if (oM > M || (oM == M && ob < best)) {
+            M = oM;
+            best = ob;
+        }
+    }
+    double S = 0.0;
+#pragma unroll
+    for (int j = 0; j < IPL; ++j) {
+        prob[j] = i0 + j < m ? ex2((float)(W[j] - M)) : 0.0f;
+        S += (double)prob[j];
+    }
+#pragma unroll
+    for (int d = 1; d < G; d <<= 1) S += __shfl_xor(S, d, G);
+    const double inv = 1.0 / S;
+    mean = 0.0;
+    if (want_mean) {
+#pragma unroll
+        for (int j = 0; j < IPL; ++j)
+            if (i0 + j < m) mean += ((double)prob[j] * inv) * (Z - (double)delta(j));
+#pragma unroll
+        for (int d = 1; d < G; d <<= 1) mean += __shfl_xor(mean, d, G);
+    }
+#pragma unroll
+    for (int j = 0; j < IPL; ++j) prob[j] = (float)((double)prob[j] * inv);
+}
+
 // One group of G lanes per ray, one block per tile, staged through LDS like
 // ray_lds_k; lane l holds steps [l IPL, (l + 1) IPL).  The probabilities go back
 // through the ray's LDS column and leave as contiguous runs in canonical edge
@@ -1362,67 +1422,33 @@ __global__ __launch_bounds__(kTile * G) void depth_lds_k(const uint32_t* __restr
         tile_to_lds<NT, IPL, IPL>(sg, vg);
     }
     __syncthreads();
-    double W[IPL];
-    double P = 0.0;
-#pragma unroll
-    for (int j = 0; j < IPL; ++j) {   // column rows are inside the LDS tile even past the ray
-        float al, be, gg;
-        load_step(sl[cb + kTile * j], sg[cb + kTile * j], i0 + j < m, al, be, gg);
-        W[j] = ((double)be + (double)gg) + P;   // past the ray: log 0
-        P += (double)al;
-    }
-    __syncthreads();   // every group has its g: reuse sg for delta
-    tile_to_lds<NT, IPL, IPL>(sg, vd);
-    __syncthreads();
-    const double before = dexcl_scan_d<G>(P);   // log2 visibility up to the lane's first step
-    double M = -__builtin_huge_val();
-    int best = 0;
-#pragma unroll
-    for (int j = 0; j < IPL; ++j) {
-        W[j] += before;
-        if (i0 + j < m && W[j] > M) {
-            M = W[j];
-            best = i0 + j;
-        }
-    }
-#pragma unroll
-    for (int d = 1; d < G; d <<= 1) {
-        const double oM = __shfl_xor(M, d, G);
-        const int ob = __shfl_xor(best, d, G);
-        if (oM > M || (oM == M && ob < best)) {
-            M = oM;
-            best = ob;
-        }
-    }
-    float q[IPL];
-    double S = 0.0;
-#pragma unroll
-    for (int j = 0; j < IPL; ++j) {
-        q[j] = i0 + j < m ? ex2((float)(W[j] - M)) : 0.0f;
-        S += (double)q[j];
-    }
-#pragma unroll
-    for (int d = 1; d < G; d <<= 1) S += __shfl_xor(S, d, G);
-    const double inv = 1.0 / S;
     const int64_t r = td.ray0 + (int64_t)(i / kTileW) * td.W + (i & (kTileW - 1));
     const int64_t at = m > 0 ? row_ptr[r] : 0;
-    double mq = 0.0;
-    if (mean) {
+    double Z = 0.0, mq;
+    if (mean && m > 0) {
         const FrameDev fr = frames[td.frame];
-        const double Z = m > 0 ? (double)fr.depth[r - fr.ray_base] : 0.0;
-#pragma unroll
-        for (int j = 0; j < IPL; ++j)
-            if (i0 + j < m) mq += ((double)q[j] * inv) * (Z - (double)sg[cb + kTile * j]);
-#pragma unroll
-        for (int d = 1; d < G; d <<= 1) mq += __shfl_xor(mq, d, G);
+        Z = (double)fr.depth[r - fr.ray_base];
     }
+    float q[IPL];
+    int best;
+    depth_body<G, IPL>(
+        m, i0, mean != nullptr, Z,
+        [&](int j, float& al, float& be, float& gg) {   // column rows are inside the LDS tile even past the ray
+            load_step(sl[cb + kTile * j], sg[cb + kTile * j], i0 + j < m, al, be, gg);
+        },
+        [&] {
+            __syncthreads();   // every group has its g: reuse sg for delta
+            tile_to_lds<NT, IPL, IPL>(sg, vd);
+            __syncthreads();
+        },
+        [&](int j) { return sg[cb + kTile * j]; }, q, best, mq);
     if (m > 0 && gl == 0) {
         if (mode) mode[r] = best;
         if (mean) mean[r] = (float)mq;
     }
     if (!prob) return;
 #pragma unroll
-    for (int j = 0; j < IPL; ++j) sl[cb + kTile * j] = (float)((double)q[j] * inv);
+    for (int j = 0; j < IPL; ++j) sl[cb + kTile * j] = q[j];
     // the group reads back its own column: accesses of one wave complete in order
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -1434,62 +1460,89 @@ __global__ __launch_bounds__(kTile * G) void depth_lds_k(const uint32_t* __restr
     }
 }
 
-// Tiles longer than a block's LDS holds: one thread per ray, two walks of its steps.
-__global__ __launch_bounds__(256) void depth_dist_k(const uint32_t* __restrict__ list, int64_t ntiles,
+// Tiles longer than a block's LDS holds: one wave per ray, read in place as ray_k does.  The
+// probabilities go through the wave's LDS row (a word more every 32, for the blocked writes)
+// and leave as contiguous runs.  3.2e7 edges in rays of up to 1109 steps: 554 us; a thread per
+// ray took 9.84 ms when it stored its ray's run word by word, and 4.09 with a pass of its own
+// from slot to canonical order.
+template <int IPL, bool KF>
+__global__ __launch_bounds__(256) void depth_wave_k(const uint32_t* __restrict__ list, int64_t ntiles,
                                                     const TileDev* __restrict__ tiles,
                                                     const FrameDev* __restrict__ frames,
                                                     const int32_t* __restrict__ counts,
                                                     const int64_t* __restrict__ row_ptr,
                                                     const int32_t* __restrict__ col, ExclDev lam, KfSrc kf,
-                                                    int is_kf, const float* __restrict__ g,
-                                                    const float* __restrict__ delta, float* __restrict__ prob,
-                                                    int32_t* __restrict__ mode, float* __restrict__ mean)
+                                                    const float* __restrict__ g, const float* __restrict__ delta,
+                                                    float* __restrict__ prob, int32_t* __restrict__ mode,
+                                                    float* __restrict__ mean)
 {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t ti = t / kTile;
-    if (ti >= ntiles) return;
-    const int i = (int)(t % kTile);
+    constexpr int G = 64, BPT = tile_blocks<G>();
+    __shared__ float row[4][G * IPL + 2 * IPL];
+    const int64_t lb = xcd_block(blockIdx.x, gridDim.x);
+    const int64_t ti = lb / BPT;
+    if (ti >= ntiles) return;   // whole block
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l = threadIdx.x & 63;
+    const int i = (int)(lb % BPT) * 4 + w;   // this wave's ray: lane i of the tile
     const TileDev td = tiles[list[ti]];
     const int m = tile_ray_len(td, counts, i);
-    if (m == 0) return;
+    if (m == 0) return;   // whole wave
+    const int i0 = l * IPL;
+    const int64_t s = td.base + i;
+    int32_t cv[IPL];
+    float ov[IPL], gv[IPL], lv[IPL], dv[IPL];
+    float2 tv[IPL];
+#pragma unroll
+    for (int j = 0; j < IPL; ++j) {   // indices clamped to the ray: every load before the first wait
+        const int64_t at = s + kTile * (int64_t)min(i0 + j, m - 1);
+        cv[j] = col[at];
+        if constexpr (!KF) ov[j] = lam.own[at];
+        gv[j] = g[at];
+        dv[j] = delta[at];
+    }
+    if constexpr (KF) {
+        const float* xf = kf.x + kf.xb[td.frame];
+#pragma unroll
+        for (int j = 0; j < IPL; ++j) lv[j] = cv[j] >= 0 ? xf[cv[j]] : 0.0f;
+    } else {
+#pragma unroll
+        for (int j = 0; j < IPL; ++j) tv[j] = lam.tot[max(cv[j], 0)];
+#pragma unroll
+        for (int j = 0; j < IPL; ++j) lv[j] = excl_value(cv[j], tv[j], ov[j], lam.has_own);
+    }
     const int64_t r = td.ray0 + (int64_t)(i / kTileW) * td.W + (i & (kTileW - 1));
-    const int64_t s0 = td.base + i;
-    const float* xf = is_kf ? kf.x + kf.xb[td.frame] : nullptr;
-    auto weight = [&](int k, double& P) {   // W_k (log2), then P += log2 mu_k(0)
-        const int64_t at = s0 + (int64_t)kTile * k;
-        const int32_t v = col[at];
-        const float lm = is_kf ? xf[v] : excl_value(v, lam.tot[v], lam.own[at], lam.has_own);
-        float al, be, gg;
-        load_step(lm, g[at], true, al, be, gg);
-        const double W = ((double)be + (double)gg) + P;
-        P += (double)al;
-        return W;
-    };
-    double P = 0.0, M = -__builtin_huge_val(), S = 0.0;
-    int best = 0;
-    for (int k = 0; k < m; ++k) {
-        const double W = weight(k, P);
-        if (W > M) {
-            S = S * (double)ex2((float)(M - W)) + 1.0;
-            M = W;
-            best = k;
-        } else {
-            S += (double)ex2((float)(W - M));
-        }
+    double Z = 0.0, mq;
+    if (mean) {
+        const FrameDev fr = frames[td.frame];
+        Z = (double)fr.depth[r - fr.ray_base];
     }
-    if (mode) mode[r] = best;
-    const FrameDev fr = frames[td.frame];
-    const double Z = (double)fr.depth[r - fr.ray_base];
-    const int64_t d0 = row_ptr[r];
-    double mq = 0.0;
-    P = 0.0;
-    for (int k = 0; k < m; ++k) {
-        const double W = weight(k, P);
-        const double qk = (double)ex2((float)(W - M)) / S;
-        if (prob) prob[d0 + k] = (float)qk;
-        mq += qk * (Z - (double)delta[s0 + (int64_t)kTile * k]);
+    float q[IPL];
+    int best;
+    depth_body<G, IPL>(
+        m, i0, mean != nullptr, Z,
+        [&](int j, float& al, float& be, float& gg) { load_step(lv[j], gv[j], i0 + j < m, al, be, gg); }, [] {},
+        [&](int j) { return dv[j]; }, q, best, mq);
+    if (l == 0) {
+        if (mode) mode[r] = best;
+        if (mean) mean[r] = (float)mq;
     }
-    if (mean) mean[r] = (float)mq;
+    if (!prob) return;
+    float* o = row[w];
+#pragma unroll
+    for (int j = 0; j < IPL; ++j) {
+        const int k = i0 + j;
+        o[k + (k >> 5)] = q[j];
+    }
+    // LDS accesses of one wave complete in order: the fences keep the compiler from moving
+    // the reads above the writes
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const int64_t at = row_ptr[r];
+#pragma unroll
+    for (int j = 0; j < IPL; ++j) {
+        const int k = j * G + l;
+        if (k < m) prob[at + k] = o[k + (k >> 5)];
+    }
 }
 
 // rays without voxels
@@ -1503,7 +1556,7 @@ __global__ void depth_none_k(const int32_t* __restrict__ counts, int64_t R, int3
 }
 
 // The depth messages of one class's tiles; classes of LDS tiles take the class's
-// default forward shape.
+// default forward shape, longer ones a wave per ray.
 template <int Q, bool KF>
 static void launch_depth_class(const mrf_ctx* c, const ExclDev& lam, const KfSrc& kf, float* prob, int32_t* mode,
                                float* mean, hipStream_t s)
@@ -1522,8 +1575,8 @@ static void launch_depth_class(const mrf_ctx* c, const ExclDev& lam, const KfSrc
         hipLaunchKernelGGL((depth_lds_k<G, kRayCap[Q] / G, KF>), dim3((unsigned)n), dim3(kTile * G), 0, s, list, n,
                            tiles, frames, counts, rp, col, lam, kf, g, delta, prob, mode, mean);
     } else {
-        hipLaunchKernelGGL(depth_dist_k, dim3(nblk(n * kTile, 256)), dim3(256), 0, s, list, n, tiles, frames, counts,
-                           rp, col, lam, kf, KF ? 1 : 0, g, delta, prob, mode, mean);
+        hipLaunchKernelGGL((depth_wave_k<kRayCap[Q] / 64, KF>), dim3((unsigned)(n * tile_blocks<64>())), dim3(256), 0, s,
+                           list, n, tiles, frames, counts, rp, col, lam, kf, g, delta, prob, mode, mean);
     }
 }
 
