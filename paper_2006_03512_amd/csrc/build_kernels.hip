@@ -1381,11 +1381,26 @@ hipError_t radix_sort_pairs(const uint32_t* keys_in, uint32_t* keys_a, uint32_t*
 constexpr int kRunRows = 256;                   // rows per block of runs_find_k, 64 per wave
 constexpr int kRunSlots = kTile * kRunRows;
 
+// The scene whose voxels, or keys (BASE: its first), hold id x: the last with BASE <= x.  By
+// halves, since a batch may hold thousands of scenes (2500 of 16x12 pixels: build 1.02 ms, 11.5 with
+// a walk along them for every run).
+template <int64_t SceneDev::*BASE>
+__device__ __forceinline__ const SceneDev& scene_of(const SceneDev* __restrict__ scenes, int ns, int64_t x)
+{
+    int lo = 0, hi = ns;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (scenes[mid].*BASE <= x)
+            lo = mid;
+        else
+            hi = mid;
+    }
+    return scenes[lo];
+}
+
 __device__ __forceinline__ uint32_t voxel_key32(const SceneDev* __restrict__ scenes, int ns, uint32_t v)
 {
-    int sc = 0;
-    while (sc + 1 < ns && (int64_t)v >= scenes[sc + 1].voxel_base) ++sc;
-    const SceneDev& sd = scenes[sc];
+    const SceneDev& sd = scene_of<&SceneDev::voxel_base>(scenes, ns, v);
     const uint32_t local = v - (uint32_t)sd.voxel_base;
     const uint32_t nx = (uint32_t)sd.n[0], nxy = nx * (uint32_t)sd.n[1];
     const uint32_t k = local / nxy, rem = local - k * nxy;
@@ -1767,9 +1782,7 @@ hipError_t launch_vptr_from_sorted(const uint32_t* sorted_keys, int64_t n, int64
 // linear voxel id of a brick-major key (keys of padding voxels never appear)
 __device__ uint32_t key_to_voxel(const SceneDev* __restrict__ scenes, int ns, uint32_t key)
 {
-    int sc = 0;
-    while (sc + 1 < ns && (int64_t)key >= scenes[sc + 1].key_base) ++sc;
-    const SceneDev& sd = scenes[sc];
+    const SceneDev& sd = scene_of<&SceneDev::key_base>(scenes, ns, key);
     const int64_t local = (int64_t)key - sd.key_base;
     const int64_t brick = local >> 9;
     const int l = (int)(local & 511);
@@ -1783,9 +1796,7 @@ __device__ uint32_t key_to_voxel(const SceneDev* __restrict__ scenes, int ns, ui
 // brick-major key of a linear voxel id
 __device__ uint32_t voxel_to_key(const SceneDev* __restrict__ scenes, int ns, int64_t v)
 {
-    int sc = 0;
-    while (sc + 1 < ns && v >= scenes[sc + 1].voxel_base) ++sc;
-    const SceneDev& sd = scenes[sc];
+    const SceneDev& sd = scene_of<&SceneDev::voxel_base>(scenes, ns, v);
     const int64_t local = v - sd.voxel_base;
     const int64_t nxy = (int64_t)sd.n[0] * sd.n[1];
     const int k = (int)(local / nxy);
