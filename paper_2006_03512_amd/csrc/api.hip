@@ -661,11 +661,12 @@ static void update_stats(mrf_ctx* c)
     st.n_tiles = c->T;
     st.n_touched_voxels = 0;
     for (int k = 0; k < kVoxClasses; ++k) st.n_touched_voxels += c->vox.cnt[k];
-    // voxel phase: vedge 4 + gathered ell 4 per edge, descriptor 16 + theta 4 + total 4 per
-    // touched voxel; ray phase: col 4 + own ell 4 + g 4 + ell 4 per edge, total 4 per touched
-    // voxel, count 4 per kept ray, list 4 + descriptor 32 per tile
-    st.fwd_bytes_per_sweep =
-        24.0 * (double)E + 28.0 * (double)st.n_touched_voxels + 4.0 * (double)st.n_kept_rays + 36.0 * (double)c->T;
+    // voxel phase: vedge 4 + gathered ell 4 per edge (lists of runs: ell 4, and row 4 + mask 2
+    // per run), descriptor 16 + theta 4 + total 4 per touched voxel; ray phase: col 4 + own ell
+    // 4 + g 4 + ell 4 per edge, total 4 per touched voxel, count 4 per kept ray, list 4 +
+    // descriptor 32 per tile
+    st.fwd_bytes_per_sweep = (c->by_runs ? 20.0 : 24.0) * (double)E + (c->by_runs ? 6.0 * (double)c->n_runs : 0.0) +
+                             28.0 * (double)st.n_touched_voxels + 4.0 * (double)st.n_kept_rays + 36.0 * (double)c->T;
     st.sweeps_done = 0;
     st.have_checkpoints = 0;
     st.n_keyframe_pairs = c->n_pairs;
