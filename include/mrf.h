@@ -117,7 +117,8 @@ typedef struct {
                                   (mrf_add_frames), per-edge ones at 1.25 times the batch's mean
                                   edge slots per frame */
     int32_t group_slots_log2;  /* 0 (= 32) or 12..32: a group of scenes holds fewer than 2^this
-                                  edge slots (see below); smaller values only for testing */
+                                  edge slots (see below), and lists are kept as runs below 2^this
+                                  of them; smaller values only for testing */
 } mrf_build_params;
 
 typedef struct {

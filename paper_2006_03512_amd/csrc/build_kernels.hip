@@ -1704,7 +1704,9 @@ hipError_t build_incidence(mrf_ctx* c, int64_t n, int64_t edges, uint32_t* keys,
     if ((e = scan_exclusive_i32(bcnt, boff, nb, c->b_misc.p, c->b_misc.cap, s)) != hipSuccess) return e;
     int64_t nr = 0;
     if ((e = read_back(c, &nr, boff + nb, sizeof(int64_t), s)) != hipSuccess) return e;
-    if (keep_runs && nr >= (int64_t(1) << 32)) {   // more than rptr's 32 bits: lists of edges after all
+    // more runs than rptr's 32 bits number (a batch of several slot groups; fewer bits for
+    // tests, as the groups'): lists of edges after all
+    if (keep_runs && nr >= (int64_t(1) << c->group_log2)) {
         if ((e = ensure(c->b_vedge, sizeof(uint32_t) * (size_t)n + 16)) != hipSuccess) return e;
         vals = (uint32_t*)c->b_vedge.p;
         keep_runs = false;

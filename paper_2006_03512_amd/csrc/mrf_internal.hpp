@@ -335,7 +335,7 @@ struct mrf_ctx {
     int64_t n_cells = 1;
 
     mrf::SlotGroups sg{};     // edge-slot groups of the voxel -> ray lists
-    int32_t group_log2 = 32;  // a group holds fewer than 2^group_log2 slots
+    int32_t group_log2 = 32;  // a group holds fewer than 2^group_log2 slots, lists of runs fewer than as many runs
     std::vector<int> group_scene;   // first scene of each group
 
     // buffers (raw device pointers into `bufs`)
