@@ -915,11 +915,6 @@ struct LoadI64 {
     const int64_t* p;
     __device__ int64_t operator()(int64_t i) const { return p[i]; }
 };
-struct LoadEqU8 {
-    const uint8_t* p;
-    uint8_t c;
-    __device__ int64_t operator()(int64_t i) const { return p[i] == c ? 1 : 0; }
-};
 
 __device__ int64_t block_excl_scan_i64(int64_t x, int64_t* total)
 {

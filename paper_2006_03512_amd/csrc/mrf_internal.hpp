@@ -520,7 +520,7 @@ hipError_t launch_voxel_phase(mrf_ctx* c, const float* in, VoxOut out, hipStream
 // an inference's prior and tables into the context (theta, its pairs, the beliefs of
 // untouched voxels, sigma, bias); bias null: zero
 hipError_t launch_infer_inputs(mrf_ctx* c, const float* prior, const float* sigma, const float* bias, hipStream_t s);
-// thetabar = dlogit, seed = (dlogit, 0) when not null
+// thetabar = dlogit, seed = (dlogit, 0)
 hipError_t launch_reverse_seed(const float* dlogit, float* thetabar, float2* seed, int64_t n, hipStream_t s);
 hipError_t launch_ray_phase(mrf_ctx* c, ExclSrc lam, float* ell, bool plain, hipStream_t s);
 // the potentials and the first sweep's ray phase (lambda = theta, b_theta2)

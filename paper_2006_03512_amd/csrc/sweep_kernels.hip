@@ -96,7 +96,7 @@ __global__ void reverse_seed_k(const float* __restrict__ dlogit, float* __restri
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const float x = dlogit[i];
         thetabar[i] = x;
-        if (seed) seed[i] = make_float2(x, 0.0f);
+        seed[i] = make_float2(x, 0.0f);
     }
 }
 
@@ -475,9 +475,9 @@ struct SegWork {
 };
 
 template <bool WT, bool MG>
-__global__ __launch_bounds__(256, WT ? (MG ? 5 : 6) : 8) void seg_sum_k(const SegWork s, const uint32_t* __restrict__ vedge,
-                                                 const float* __restrict__ in, VoxOut out,
-                                                 const float* __restrict__ w, const SlotGroups sg)
+__global__ __launch_bounds__(256, WT ? 6 : 8) void seg_sum_k(const SegWork s, const uint32_t* __restrict__ vedge,
+                                                             const float* __restrict__ in, VoxOut out,
+                                                             const float* __restrict__ w, const SlotGroups sg)
 {
     __shared__ double red[4 * kSegRed];
     int k = kVoxClasses - 1;   // uniform: the class whose blocks hold this one
@@ -750,9 +750,7 @@ static hipError_t seg_sum(mrf_ctx* c, const SegList& l, const float* in, const V
     if (blocks == 0) return hipSuccess;
     const dim3 g((unsigned)blocks), b(256);
     const uint32_t* ve = (const uint32_t*)c->b_vedge.p;
-    if (w && c->sg.n > 1)
-        hipLaunchKernelGGL((seg_sum_k<true, true>), g, b, 0, s, k, ve, in, out, w, c->sg);
-    else if (w)
+    if (w)   // weights: keyframe pairs, whose builds have one slot group
         hipLaunchKernelGGL((seg_sum_k<true, false>), g, b, 0, s, k, ve, in, out, w, c->sg);
     else if (c->sg.n > 1)
         hipLaunchKernelGGL((seg_sum_k<false, true>), g, b, 0, s, k, ve, in, out, w, c->sg);
