@@ -213,6 +213,31 @@ static hipError_t after_last_graph(mrf_ctx* c, hipStream_t s)
     return e == hipSuccess && st == hipStreamCaptureStatusNone ? hipStreamWaitEvent(s, c->ev_out, 0) : e;
 }
 
+// The captured sweeps of these arguments, captured anew unless the last ones are theirs.
+static hipError_t capture_sweeps(mrf_ctx* c, int sweeps, int keep, bool kf)
+{
+    std::vector<uint64_t> key = graph_key(c, sweeps, keep);
+    if (kf) key.push_back(0x6b66);   // the keyframe-average schedule
+    if (c->gexec && key == c->g_key) return hipSuccess;
+    drop_graph(c);
+    hipError_t e = hipStreamBeginCapture(c->aux, hipStreamCaptureModeThreadLocal);
+    if (e != hipSuccess) return e;
+    hipGraph_t g = nullptr;
+    e = kf ? enqueue_forward_kf(c, sweeps, keep, false, c->aux) : enqueue_forward(c, sweeps, keep, false, c->aux);
+    const hipError_t e2 = hipStreamEndCapture(c->aux, &g);
+    if (e == hipSuccess) e = e2;
+    if (e == hipSuccess) e = hipGraphInstantiate(&c->gexec, g, nullptr, nullptr, 0);
+    if (g) hipGraphDestroy(g);
+    if (e != hipSuccess) {
+        c->gexec = nullptr;
+        return e;
+    }
+    c->g_K = sweeps;
+    c->g_ckpt = keep;
+    c->g_key = key;
+    return hipSuccess;
+}
+
 static hipError_t launch_graph(mrf_ctx* c, hipStream_t s)
 {
     hipError_t e = hipGraphLaunch(c->gexec, s);
@@ -870,31 +895,15 @@ int mrf_infer_sensor(mrf_ctx* c, const float* prior_logit, const float* sigma_ta
             HCK(ensure(c->b_tsum, need_tot), "mrf_infer: alloc voxel totals");
         }
     }
+    // before anything of the last inference is overwritten: a failed capture leaves it as it was
+    const bool graph = c->schedule != MRF_SCHED_PLAIN;
+    if (graph) HCK(capture_sweeps(c, sweeps, keep, false), "mrf_infer: graph capture");
     HCK(after_last_graph(c, s), "mrf_infer: wait");
     HCK(launch_infer_inputs(c, prior_logit, sigma_table, bias_table, s), "mrf_infer: inputs");
-    if (c->schedule == MRF_SCHED_PLAIN) {
-        HCK(enqueue_forward(c, sweeps, keep, true, s), "mrf_infer: sweeps");
-    } else {
-        std::vector<uint64_t> key = graph_key(c, sweeps, keep);
-        if (!c->gexec || key != c->g_key) {
-            drop_graph(c);
-            hipGraph_t g = nullptr;
-            HCK(hipStreamBeginCapture(c->aux, hipStreamCaptureModeThreadLocal), "mrf_infer: begin capture");
-            hipError_t e = enqueue_forward(c, sweeps, keep, false, c->aux);
-            hipError_t e2 = hipStreamEndCapture(c->aux, &g);
-            if (e == hipSuccess) e = e2;
-            if (e == hipSuccess) e = hipGraphInstantiate(&c->gexec, g, nullptr, nullptr, 0);
-            if (g) hipGraphDestroy(g);
-            if (e != hipSuccess) {
-                c->gexec = nullptr;
-                return hip_fail(e, "mrf_infer: graph capture");
-            }
-            c->g_K = sweeps;
-            c->g_ckpt = keep;
-            c->g_key = key;
-        }
+    if (graph)
         HCK(launch_graph(c, s), "mrf_infer: graph launch");
-    }
+    else
+        HCK(enqueue_forward(c, sweeps, keep, true, s), "mrf_infer: sweeps");
     c->inferred = 1;
     c->kf_inferred = 0;
     ++c->gen;
@@ -923,33 +932,15 @@ int mrf_infer_keyframe_avg(mrf_ctx* c, const float* prior_logit, const float* si
             HCK(ensure(c->b_ckpt, need), "mrf_infer_keyframe_avg: alloc checkpoints");
         }
     }
+    // before anything of the last inference is overwritten: a failed capture leaves it as it was
+    const bool graph = c->schedule != MRF_SCHED_PLAIN;
+    if (graph) HCK(capture_sweeps(c, sweeps, keep, true), "mrf_infer_keyframe_avg: graph capture");
     HCK(after_last_graph(c, s), "mrf_infer_keyframe_avg: wait");
     HCK(launch_infer_inputs(c, prior_logit, sigma_table, bias_table, s), "mrf_infer_keyframe_avg: inputs");
-    if (c->schedule == MRF_SCHED_PLAIN) {
-        HCK(enqueue_forward_kf(c, sweeps, keep, true, s), "mrf_infer_keyframe_avg: sweeps");
-    } else {
-        std::vector<uint64_t> key = graph_key(c, sweeps, keep);
-        key.push_back(0x6b66);   // the keyframe-average schedule
-        if (!c->gexec || key != c->g_key) {
-            drop_graph(c);
-            hipGraph_t g = nullptr;
-            HCK(hipStreamBeginCapture(c->aux, hipStreamCaptureModeThreadLocal),
-                "mrf_infer_keyframe_avg: begin capture");
-            hipError_t e = enqueue_forward_kf(c, sweeps, keep, false, c->aux);
-            hipError_t e2 = hipStreamEndCapture(c->aux, &g);
-            if (e == hipSuccess) e = e2;
-            if (e == hipSuccess) e = hipGraphInstantiate(&c->gexec, g, nullptr, nullptr, 0);
-            if (g) hipGraphDestroy(g);
-            if (e != hipSuccess) {
-                c->gexec = nullptr;
-                return hip_fail(e, "mrf_infer_keyframe_avg: graph capture");
-            }
-            c->g_K = sweeps;
-            c->g_ckpt = keep;
-            c->g_key = key;
-        }
+    if (graph)
         HCK(launch_graph(c, s), "mrf_infer_keyframe_avg: graph launch");
-    }
+    else
+        HCK(enqueue_forward_kf(c, sweeps, keep, true, s), "mrf_infer_keyframe_avg: sweeps");
     c->inferred = 1;
     c->kf_inferred = 1;
     ++c->gen;

@@ -76,3 +76,11 @@ def test_key_names_every_buffer_of_the_captured_sweeps(entry):
 def test_context_releases_every_buffer():
     funcs = _functions()
     assert _declared() <= _named(funcs, "mrf_destroy"), sorted(_declared() - _named(funcs, "mrf_destroy"))
+
+
+@pytest.mark.parametrize("entry", ["mrf_infer_sensor", "mrf_infer_keyframe_avg"])
+def test_a_failed_capture_overwrites_nothing(entry):
+    """The sweeps are captured before the new prior and tables are written, so that an inference whose capture fails
+    leaves the beliefs of the last one."""
+    (body,) = _functions()[entry]
+    assert body.index("capture_sweeps(") < body.index("launch_infer_inputs(") < body.index("launch_graph(")
