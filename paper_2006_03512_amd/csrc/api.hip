@@ -891,6 +891,8 @@ int mrf_infer_sensor(mrf_ctx* c, const float* prior_logit, const float* sigma_ta
         const size_t need_tot = sizeof(float2) * (size_t)(keep && sweeps > 2 ? sweeps - 1 : 1) * (size_t)c->V;
         if (c->b_ckpt.cap < need_ell || c->b_tsum.cap < need_tot) {
             drop_graph(c);   // the graph holds the old addresses
+            if (c->have_ckpt || c->b_tsum.cap < need_tot)   // and these the last inference's messages
+                c->inferred = c->have_ckpt = c->kf_inferred = 0;
             HCK(ensure(c->b_ckpt, need_ell), "mrf_infer: alloc checkpoints");
             HCK(ensure(c->b_tsum, need_tot), "mrf_infer: alloc voxel totals");
         }
@@ -929,6 +931,7 @@ int mrf_infer_keyframe_avg(mrf_ctx* c, const float* prior_logit, const float* si
         const size_t need = sizeof(double) * (size_t)(sweeps > 1 ? sweeps - 1 : 1) * (size_t)c->n_pairs;
         if (c->b_ckpt.cap < need) {
             drop_graph(c);   // the graph holds the old address
+            if (c->have_ckpt) c->inferred = c->have_ckpt = c->kf_inferred = 0;   // and this the last inference's
             HCK(ensure(c->b_ckpt, need), "mrf_infer_keyframe_avg: alloc checkpoints");
         }
     }
