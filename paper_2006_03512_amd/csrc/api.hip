@@ -199,6 +199,18 @@ static hipError_t enqueue_forward_kf(mrf_ctx* c, int K, int keep, bool plain, hi
     return launch_kf_voxel(c, Mlast, theta, nullptr, (float*)c->b_L.p, s);
 }
 
+// Whether s is in a capture of the caller's.  The sweeps are then enqueued one by one: a graph
+// launch is not recorded but runs at once, so that replays would miss the sweeps.
+static bool in_capture(hipStream_t s)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {   // the null stream beside another's capture
+        hipGetLastError();
+        return false;
+    }
+    return st != hipStreamCaptureStatusNone;
+}
+
 // The captured sweeps run on the caller's stream (an internal stream beside it costs an
 // event and a wait on each side: 116 us for 5 sweeps of a 64x48 frame, 66 without them and
 // with the inputs in one launch).  Launches of one context on
@@ -207,10 +219,7 @@ static hipError_t enqueue_forward_kf(mrf_ctx* c, int K, int keep, bool plain, hi
 // there, and one recorded in it not outside.
 static hipError_t after_last_graph(mrf_ctx* c, hipStream_t s)
 {
-    if (!c->launched) return hipSuccess;
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    const hipError_t e = hipStreamIsCapturing(s, &st);
-    return e == hipSuccess && st == hipStreamCaptureStatusNone ? hipStreamWaitEvent(s, c->ev_out, 0) : e;
+    return c->launched ? hipStreamWaitEvent(s, c->ev_out, 0) : hipSuccess;
 }
 
 // The captured sweeps of these arguments, captured anew unless the last ones are theirs.
@@ -241,10 +250,7 @@ static hipError_t capture_sweeps(mrf_ctx* c, int sweeps, int keep, bool kf)
 static hipError_t launch_graph(mrf_ctx* c, hipStream_t s)
 {
     hipError_t e = hipGraphLaunch(c->gexec, s);
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (e == hipSuccess) e = hipStreamIsCapturing(s, &st);
-    if (e != hipSuccess || st != hipStreamCaptureStatusNone) return e;
-    e = hipEventRecord(c->ev_out, s);
+    if (e == hipSuccess) e = hipEventRecord(c->ev_out, s);
     if (e == hipSuccess) c->launched = 1;
     return e;
 }
@@ -898,14 +904,14 @@ int mrf_infer_sensor(mrf_ctx* c, const float* prior_logit, const float* sigma_ta
         }
     }
     // before anything of the last inference is overwritten: a failed capture leaves it as it was
-    const bool graph = c->schedule != MRF_SCHED_PLAIN;
+    const bool plain = c->schedule == MRF_SCHED_PLAIN, captured = in_capture(s), graph = !plain && !captured;
     if (graph) HCK(capture_sweeps(c, sweeps, keep, false), "mrf_infer: graph capture");
-    HCK(after_last_graph(c, s), "mrf_infer: wait");
+    if (!captured) HCK(after_last_graph(c, s), "mrf_infer: wait");
     HCK(launch_infer_inputs(c, prior_logit, sigma_table, bias_table, s), "mrf_infer: inputs");
     if (graph)
         HCK(launch_graph(c, s), "mrf_infer: graph launch");
     else
-        HCK(enqueue_forward(c, sweeps, keep, true, s), "mrf_infer: sweeps");
+        HCK(enqueue_forward(c, sweeps, keep, plain, s), "mrf_infer: sweeps");
     c->inferred = 1;
     c->kf_inferred = 0;
     ++c->gen;
@@ -936,14 +942,14 @@ int mrf_infer_keyframe_avg(mrf_ctx* c, const float* prior_logit, const float* si
         }
     }
     // before anything of the last inference is overwritten: a failed capture leaves it as it was
-    const bool graph = c->schedule != MRF_SCHED_PLAIN;
+    const bool plain = c->schedule == MRF_SCHED_PLAIN, captured = in_capture(s), graph = !plain && !captured;
     if (graph) HCK(capture_sweeps(c, sweeps, keep, true), "mrf_infer_keyframe_avg: graph capture");
-    HCK(after_last_graph(c, s), "mrf_infer_keyframe_avg: wait");
+    if (!captured) HCK(after_last_graph(c, s), "mrf_infer_keyframe_avg: wait");
     HCK(launch_infer_inputs(c, prior_logit, sigma_table, bias_table, s), "mrf_infer_keyframe_avg: inputs");
     if (graph)
         HCK(launch_graph(c, s), "mrf_infer_keyframe_avg: graph launch");
     else
-        HCK(enqueue_forward_kf(c, sweeps, keep, true, s), "mrf_infer_keyframe_avg: sweeps");
+        HCK(enqueue_forward_kf(c, sweeps, keep, plain, s), "mrf_infer_keyframe_avg: sweeps");
     c->inferred = 1;
     c->kf_inferred = 1;
     ++c->gen;
