@@ -498,7 +498,10 @@ def main():
     dom_edges = dom.get("edges_per_launch", 0)
     ach_survey = survey_b * dom_edges / (dom["avg_ms"] / 1e3) / 1e9
     fwd_ms_step = kf_fwd_ms if kf_step else fwd_graph_ms
+    # (a kernel that moves fewer bytes an edge than the table's, as the voxel phase over runs
+    # does, has a frac_survey above its share of the peak, which is frac)
     survey = {"kernel_bytes_per_edge": survey_b, "kernel_GBs": round(ach_survey, 1),
+              "kernel_moves_bytes_per_edge": round(dom["bytes_per_launch"] / max(dom_edges, 1), 2),
               "forward_24B_GBs": round(24.0 * E * K / (fwd_ms_step / 1e3) / 1e9, 1)}
     survey["forward_frac"] = round(survey["forward_24B_GBs"] / HBM_PEAK_GBS, 4)
     if backward:

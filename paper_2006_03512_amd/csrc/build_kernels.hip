@@ -313,7 +313,8 @@ __device__ __forceinline__ WalkAxis walk_axis(const SceneDev& sd, const Ray& r, 
 // test of the linear id only keeps an index out of range from ever being used.
 // emit(k, i, j, kz, lin, t_in, t_out).  5e8 steps (8 VGA frames at 2 cm): the bare walk
 // 1.18 ms with walk() and 0.78 (VALU-bound), emit pass 1.89 and 1.82 (with its stores of 4,
-// 4 and 1 bytes a step); the metric's walk of 4 frames to the grid exit 1.15 and 0.70.
+// 4 and 1 bytes a step; 1.72 with its bins by quot() too); the metric's walk of 4 frames to
+// the grid exit 1.15 and 0.70.
 struct WalkState {
     WalkAxis X, Y, Z;
     int i, j, kz, lin, k;   // voxel, its linear id, chords so far
@@ -1312,7 +1313,7 @@ struct RadixTables {
 // Most tiles whose offsets the scatter's blocks add up themselves: the three kernels
 // between the counts and the scatter take 13 us whatever the size, a block's pass over the
 // counts grows with the tiles.  Build of a frame of 1.2e5 slots (31 tiles) 226 us, 251 with
-// the three kernels; of 4.8e5 (116 tiles) 266 and 285.
+// the three kernels; of 6.2e5 (152 tiles) 247 and 258; of 9.1e5 (222 tiles) 252 and 257.
 // 256 tiles hold the 2^20 slots that are sorted one by one.
 constexpr int64_t kRsFewTiles = 256;
 
@@ -1365,7 +1366,8 @@ hipError_t radix_sort_pairs(const uint32_t* keys_in, uint32_t* keys_a, uint32_t*
 // ------------------------------------------------------------ runs
 //
 // The 16 rays of a tile cross the same few voxels at a step: a row of 16 slots
-// holds about 3 different voxels.  Sorting one item per (row, voxel) -- a run:
+// holds few different voxels (1.4 on average for VGA at 5 cm, 1.7 at 2 cm, 5 for 64x48 at
+// 5 cm).  Sorting one item per (row, voxel) -- a run:
 // its key, row and the 16-bit mask of its lanes -- instead of one per slot, and
 // writing the runs out as list entries afterwards, gives the same lists: a
 // (row, voxel) pair is one run, so runs of a voxel in row order, lanes
@@ -1642,11 +1644,14 @@ __global__ __launch_bounds__(256) void vptr_gaps_k(const uint32_t* __restrict__ 
     }
 }
 
-// Slots are sorted one by one where there are few of them: the runs cost six more
-// launches and a readback of their number.  Build of one frame in us, slot by slot and by
-// runs: 128x128 (5.6e5 slots) 269 and 292, 144x112 (6.1e5) 268 and 281, 160x120 (7.3e5) 280
-// and 292; the difference falls by 5 us per 1e5 slots.  A 640x480 frame (2.4e7) 2075 and
-// 1922 with its sweeps, at 2 cm (6e7) 4427 and 3855.
+// Slots are sorted one by one, and lists kept per edge, where there are few of them: the runs
+// cost six more launches and a readback of their number, and sweeps gain from them.  The
+// line lies where a build with three sweeps takes as long either way.  One frame in 100x100x60
+// voxels in us, by slots and by runs: 6.2e5 slots, build 245 and 257, build with 3 sweeps and
+// marginals 327 and 336, 10 sweeps alone 170 and 155; 9.1e5, 254 and 258, 335 and 341, 184 and
+// 170; 1.08e6, 286 and 286, 378 and 370, 196 and 182; 2.9e6, 286 and 275, 398 and 382, 286 and
+// 282.  With keyframe pairs, 1.2e6: build 389 and 394, three sweeps and their reverse 229 and
+// 225.  A 640x480 frame (2.4e7) 2075 and 1922 with its sweeps, at 2 cm (6e7) 4427 and 3855.
 bool incidence_by_runs(int64_t n) { return n >= (int64_t(1) << 20); }
 
 static int key_bits(int64_t maxval)
