@@ -54,17 +54,17 @@ WORKLOADS = {
 TRAFFIC = {"workload": "c4",
            "sources": ['adjoint_kernels.hip', 'sweep_kernels.hip', 'dev_common.hpp', 'tile_lds.hpp',
                        'mrf_internal.hpp'],
-           "src_sha256": "39590eb9fd56f118d3f31fcba4ed3d632750ad7d146c998420b79952753bc1a1",
+           "src_sha256": "e38f3fee84d48c61cd0a9e7fe520e4b12293af8e31ad12eb5426b5ef6a941de2",
            "kernels": {
-                       "ray_adj_lds_k<32,10,1>": [1.2763e+10, 4.666e+09],
+                       "ray_adj_lds_k<32,10,1>": [1.2766e+10, 4.666e+09],
                        "ray_adj_lds_k<32,10,2>": [1.2795e+10, 4.666e+09],
-                       "ray_adj_lds_k<32,8,1>": [7.4017e+09, 2.7666e+09],
-                       "ray_adj_lds_k<32,8,2>": [7.4039e+09, 2.768e+09],
-                       "ray_adj_lds_k<64,4,1>": [7.3929e+09, 2.7666e+09],
-                       "ray_adj_lds_k<64,4,2>": [7.4074e+09, 2.7666e+09],
-                       "ray_adj_lds_k<64,5,1>": [1.2767e+10, 4.666e+09],
-                       "ray_adj_lds_k<64,5,2>": [1.2778e+10, 4.6661e+09],
-                       "run_sum_k<false>": [1.2904e+10, 1.2967e+08]}}
+                       "ray_adj_lds_k<32,8,1>": [7.4013e+09, 2.7666e+09],
+                       "ray_adj_lds_k<32,8,2>": [7.3994e+09, 2.7682e+09],
+                       "ray_adj_lds_k<64,4,1>": [7.3924e+09, 2.7666e+09],
+                       "ray_adj_lds_k<64,4,2>": [7.4058e+09, 2.7666e+09],
+                       "ray_adj_lds_k<64,5,1>": [1.2769e+10, 4.666e+09],
+                       "ray_adj_lds_k<64,5,2>": [1.2781e+10, 4.6661e+09],
+                       "run_sum_k<false>": [1.2904e+10, 1.2969e+08]}}
 
 
 def src_sha256(files):
