@@ -127,8 +127,8 @@ def lib(tmp_path_factory):
     assert not re.search(r"threadIdx|__shared__|asm", src)   # plain functions alone
     d = tmp_path_factory.mktemp("traversal")
     (d / "t.cpp").write_text(src)
-    r = subprocess.run(["g++", "-std=c++17", "-O2", "-ffp-contract=off", "-mfma", "-fPIC", "-shared", "-w", str(d / "t.cpp"),
-                        "-o", str(d / "t.so")], capture_output=True, text=True)
+    r = subprocess.run(["g++", "-std=c++17", "-O2", "-ffp-contract=off", "-fPIC", "-shared", "-w", str(d / "t.cpp"),
+                        "-o", str(d / "t.so"), "-lm"], capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-3000:]
     return C.CDLL(str(d / "t.so"))
 
