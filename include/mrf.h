@@ -372,7 +372,10 @@ int mrf_export_edges(const mrf_ctx* ctx, float* delta, uint8_t* bin, float* g,
  *                    with the fixed untuned shape of one 64-lane wave per
  *                    ray (16 lanes for rays of at most 16 voxels);
  *   MRF_SCHED_GRAPH  all sweeps captured once into a hipGraph and replayed
- *                    (default), with tuned launch shapes. */
+ *                    (default), with tuned launch shapes; on a stream that
+ *                    the caller is capturing, the same launches are recorded
+ *                    into the caller's graph instead (every buffer must have
+ *                    its size from an earlier inference). */
 enum { MRF_SCHED_PLAIN = 0, MRF_SCHED_GRAPH = 1 };
 int mrf_set_schedule(mrf_ctx* ctx, int32_t schedule);
 
